@@ -281,7 +281,9 @@ size_t thrift_attn_decode_workspace(int B, int Hq, int Hkv, int Nkv, int D, int 
  *   out [B,Hq,D] in out_dt
  *   idx_out (nullable) [B,Hq,kmax_out], cnt_out (nullable) [B,Hq]: the selection that was used
  *     (kmax_out >= thrift_select_kmax(1, Nkv/Bk, 1, Bk, 0, budget, fixed_k, 0))
- *   workspace: thrift_attn_decode_workspace(...) bytes
+ *   workspace: thrift_attn_decode_workspace(...) bytes (where short caches or few sequences leave the chip idle the
+ *     call works in two passes over finer pieces, which takes more of it; with a smaller workspace that still holds the
+ *     one-pass form, that form runs: the same selection and the same codes of P, sums in another order)
  */
 thrift_status thrift_attn_decode(const void* q, thrift_dtype dt, const void* k16, const void* v16,
                                  const uint8_t* k4, const uint8_t* ks, const uint8_t* v4, const uint8_t* vs,

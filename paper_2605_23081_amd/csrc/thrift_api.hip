@@ -78,6 +78,32 @@ struct DecodeLayout {
   int nsplit, nparts, words, order_items;
 };
 
+// Workspace of the two-pass form; it also fits wherever the one-pass form's does not exceed it.
+struct DecodeSplitLayout {
+  size_t keys, bitmap, scores, cmax, part_o, part_ml, total;
+  int nsplit, nparts, words, cw, nsub;
+};
+
+DecodeSplitLayout decode_split_layout(int B, int Hq, int Hkv, int Nkv, int Bk, int split_blocks) {
+  DecodeSplitLayout L;
+  const int Tk = Nkv / Bk, part = split_blocks < Tk ? split_blocks : Tk;
+  L.nsplit = (Tk + split_blocks - 1) / split_blocks;
+  L.words = (Tk + 63) / 64;
+  L.cw = decode_split_chunk(B, Hkv, Tk);
+  L.nsub = (part + 4 * L.cw - 1) / (4 * L.cw);
+  L.nparts = L.nsplit * L.nsub + 1;              // one partial per workgroup + one for a partly filled last block
+  const size_t rows = (size_t)B * Hq;
+  size_t off = 0;
+  L.keys = off; off += align256(rows * Tk * sizeof(uint64_t));
+  L.bitmap = off; off += align256(rows * L.words * sizeof(unsigned long long));
+  L.scores = off; off += align256(rows * Nkv * sizeof(float));
+  L.cmax = off; off += align256(rows * L.nsplit * L.nsub * 4 * sizeof(float));
+  L.part_o = off; off += align256(rows * L.nparts * kHeadDim * sizeof(float));
+  L.part_ml = off; off += align256(rows * L.nparts * 2 * sizeof(float));
+  L.total = off;
+  return L;
+}
+
 DecodeLayout decode_layout(int B, int Hq, int Hkv, int Nkv, int Bk, int split_blocks) {
   DecodeLayout L;
   const int Tk = Nkv / Bk;
@@ -315,11 +341,21 @@ thrift_status thrift_attn_prefill(const void* q, const void* k, const void* v, t
                                    softmax_scale, out, out_dt, lse, workspace, workspace_bytes, stream);
 }
 
-size_t thrift_attn_decode_workspace(int B, int Hq, int Hkv, int Nkv, int D, int Bk, int split_blocks) {
+// Bytes without which no form of the decode call can run; 0 for sizes that no form takes.
+static size_t decode_least_workspace(int B, int Hq, int Hkv, int Nkv, int D, int Bk, int split_blocks) {
   if (B <= 0 || Hq <= 0 || Hkv <= 0 || Nkv <= 0 || D != kHeadDim || Bk != kKeyBlock || split_blocks <= 0 || Nkv % Bk != 0 ||
       Nkv / Bk > kMaxKeyBlocks || !fits_int(B, Hq, 64))
     return 0;
   return decode_layout(B, Hq, Hkv, Nkv, Bk, split_blocks).total;
+}
+
+size_t thrift_attn_decode_workspace(int B, int Hq, int Hkv, int Nkv, int D, int Bk, int split_blocks) {
+  const size_t least = decode_least_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks);
+  if (least == 0 || Hq % Hkv != 0) return least;
+  const int nsplit = (Nkv / Bk + split_blocks - 1) / split_blocks;
+  if (!decode_split_wanted(B, Hq, Hkv, Nkv / Bk, nsplit, split_blocks)) return least;
+  const size_t split = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks).total;
+  return split > least ? split : least;
 }
 
 static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void* k16, const void* v16,
@@ -346,6 +382,29 @@ static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void
   if (thrift_status s = check_arch()) return s;
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
+  if (decode_split_wanted(B, Hq, Hkv, Tk, L.nsplit, split_blocks)) {
+    const DecodeSplitLayout S = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks);
+    if (workspace_bytes >= S.total) {              // a caller's (or the static) workspace may hold the one-pass form only
+      DecodeSplitArgs s;
+      DecodeArgs& a = s.a;
+      unsigned long long* bitmap = (unsigned long long*)(ws + S.bitmap);
+      const bool select = kneed > 0 || idx_out != nullptr;
+      if (select)
+        launch_decode_select((const uint16_t*)q, dt == THRIFT_BF16 ? 1 : 0, kmean, seqlens, (uint64_t*)(ws + S.keys), bitmap, S.words,
+                             idx_out, cnt_out, kmax_out, B, Hq, Hkv, Tk, fixed_k, fixed_k >= 0 ? 0 : budget_ppm(budget), shared, st);
+      a.q = (const uint16_t*)q; a.k16 = (const uint16_t*)k16; a.v16 = (const uint16_t*)v16;
+      a.k4 = k4; a.ks = ks; a.v4 = v4; a.vs = vs; a.seqlens = seqlens;
+      a.bitmap = kneed > 0 ? bitmap : nullptr; a.bitmap_words = S.words;
+      a.out = out; a.part_o = (float*)(ws + S.part_o); a.part_ml = (float*)(ws + S.part_ml); a.order = nullptr;
+      a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.Nkv = Nkv; a.split_blocks = split_blocks < Tk ? split_blocks : Tk; a.nsplit = S.nsplit; a.nparts = S.nparts; a.nmerge = S.nparts;
+      a.scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)D);
+      a.dt = dt; a.out_dt = out_dt;
+      s.scores = (float*)(ws + S.scores); s.cmax = (float*)(ws + S.cmax);
+      s.cw = S.cw; s.nsub = S.nsub; s.chunks = S.nsplit * S.nsub * 4; s.items = S.nsplit * S.nsub + (seqlens ? 1 : 0);
+      launch_decode_split(s, st);
+      return after_launch();
+    }
+  }
   unsigned long long* bitmap = (unsigned long long*)(ws + L.bitmap);
 
   // (i) the query token is its own block mean; score it against the cached key-block means and select
@@ -397,7 +456,7 @@ thrift_status thrift_attn_decode_static(const void* q, thrift_dtype dt, const vo
                                         void* out, thrift_dtype out_dt, int32_t* idx_out, int32_t* cnt_out, int kmax_out,
                                         void* stream) {
   // sizes first: a problem whose workspace does not fit the static array is refused before anything else happens
-  const size_t need = thrift_attn_decode_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks);
+  const size_t need = decode_least_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks);
   if (need == 0) return THRIFT_ERR_SHAPE;
   if (need > kStaticScratchBytes) return THRIFT_ERR_WORKSPACE;
   void* ws = nullptr;

@@ -69,6 +69,21 @@ struct DecodeArgs {
 void launch_decode(const DecodeArgs& a, hipStream_t st);
 // entries of DecodeArgs::order that launch_decode wants; 0 = so many workgroups that their order does not matter (pass nullptr)
 int decode_order_items(int B, int Hkv, int nsplit);
+// Two-pass decode for caches that leave the chip idle otherwise (thrift_decode_split.hip)
+struct DecodeSplitArgs {
+  DecodeArgs a;           // nparts: partial slots per head here: nsplit * nsub + 1; bitmap may be nullptr (no block promoted)
+  float* scores;          // [B,Hq,Nkv] raw scores
+  float* cmax;            // [B,Hq,chunks] largest raw score of every chunk
+  int cw;                 // key blocks per chunk (wavefront)
+  int nsub;               // workgroups (of four chunks) per partition
+  int chunks;             // nsplit * nsub * 4
+  int items;              // workgroups per (sequence, KV head): nsplit * nsub, + 1 where lengths can leave a block partly filled
+};
+constexpr int kSplitMaxItems = 320;   // partitions up to which the two passes are faster than one walk of a workgroup each
+constexpr int kSplitMaxChunk = 8;
+bool decode_split_wanted(int B, int Hq, int Hkv, int Tk, int nsplit, int split_blocks);
+int decode_split_chunk(int B, int Hkv, int Tk);
+void launch_decode_split(const DecodeSplitArgs& s, hipStream_t st);
 // decode-time selection: scores of the cached key-block means against the query heads, then per-row TopK
 // as a bitmap ([B*Hq][words], bit j%64 of word j/64) and optionally as ascending id lists
 void launch_decode_select(const uint16_t* q16, int q_is_bf16, const float* kmean, const int32_t* seqlens, uint64_t* keys,

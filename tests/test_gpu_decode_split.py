@@ -1,0 +1,73 @@
+"""The two-pass decode (short caches, few sequences) against the oracle and against the one-pass form.
+
+Both forms give every block the running maximum of its partition, hence the same codes of P and the same selection: their
+fp32 results differ by the order of the sums and of the rescaling factors alone, a few 2^-24 per addition over at most some
+hundred partials.  A workspace that is too small for the two-pass form selects the one-pass form.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_23081_amd import workloads as W
+from tests.test_gpu_parity import TOLMIX, _decode_case
+
+pytestmark = pytest.mark.gpu
+
+REL = 4e-6          # 2-norm: 64 x 2^-24, for sums of about 128 partials and blocks and the last bits of the exponentials
+
+
+@pytest.fixture(scope="module")
+def T():
+    from paper_2605_23081_amd import binding
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    binding.lib()
+    return binding
+
+
+def _cache(T, wl):
+    q, k, v = W.make_decode(wl, device="cuda")
+    k4, ks = T.thrift_quantize_mxfp4(k, 0)
+    v4, vs = T.thrift_quantize_mxfp4(v, 1)
+    return q, k, v, k4, ks, v4, vs, T.thrift_block_means(k, wl.Bk)
+
+
+@pytest.mark.parametrize("Hq,Hkv,B,N,split,lens,budget", [
+    (1, 1, 1, 64, 256, None, 0.05),                                          # one key block
+    (4, 2, 3, 1152, 256, [1152, 1, 0], 0.05),                                # a full cache, one token, none
+    (6, 2, 2, 2048, 23, [2047, 1024], 0.25),                                 # partitions that end inside a workgroup's blocks
+    (10, 2, 2, 1600, 17, [1537, 63], 1.0),                                   # five heads of eight columns, every block promoted
+    (16, 2, 2, 4096, 256, [4095, 2049], 0.0),                                # eight heads, no block promoted
+    (7, 1, 1, 4096, 40, None, 0.1),
+    (32, 8, 2, 16384, 100, [16384, 9000], 0.05),                             # 2 key blocks per wavefront
+    (8, 8, 2, 65536, 256, [65535, 40001], 0.05),                             # 4
+    (16, 8, 2, 131072, 250, [131072, 70000], 0.25),                          # 8
+])
+def test_two_pass_decode_equals_one_pass(T, Hq, Hkv, B, N, split, lens, budget):
+    print(f"decode split Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} lens={lens} budget={budget}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv)
+    args = _cache(T, wl)
+    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+    need = T.decode_workspace_bytes(B, Hq, Hkv, N, wl.D, 64, split)
+    big, small = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda"), torch.full((need - 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    kw = dict(split_blocks=split, seqlens=sl, out_dtype=torch.float32, return_selection=True)
+    two, idx2, cnt2 = T.thrift_attn_decode(*args, 64, budget, workspace=big, **kw)
+    one, idx1, cnt1 = T.thrift_attn_decode(*args, 64, budget, workspace=small, **kw)
+    assert torch.equal(idx1, idx2) and torch.equal(cnt1, cnt2)
+    assert bool(torch.isfinite(two).all())
+    err = float((two - one).norm() / one.norm().clamp_min(1e-30))
+    print(f"  rel {err:.2e}", flush=True)
+    assert err <= REL
+    again, _, _ = T.thrift_attn_decode(*args, 64, budget, workspace=big, **kw)
+    assert torch.equal(two, again)
+
+
+@pytest.mark.parametrize("Hq,Hkv,B,N,split,lens,budget", [
+    (8, 2, 2, 1536, 256, None, 0.1), (5, 1, 1, 1024, 256, [833], 0.25), (8, 1, 2, 2048, 24, [2048, 1300], 0.05), (3, 3, 1, 704, 256, None, 1.0),
+])
+def test_two_pass_decode_matches_the_oracle(T, Hq, Hkv, B, N, split, lens, budget):
+    from oracle import thrift_oracle as oracle
+    print(f"decode split vs oracle Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} lens={lens} budget={budget}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv)
+    lens = None if lens is None else [n // 64 * 64 for n in lens]            # the helper's selection takes whole blocks
+    got, want, swaps = _decode_case(T, oracle, wl, budget, split, lens)
+    assert swaps == 0 and np.abs(got - want).max() <= TOLMIX
