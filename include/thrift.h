@@ -345,6 +345,13 @@ thrift_status thrift_kv_cache_append(const void* k_new, const void* v_new, thrif
                                      void* k16, void* v16, uint8_t* k4, uint8_t* ks, uint8_t* v4, uint8_t* vs, float* kmean,
                                      int B, int Hkv, int Nkv, int D, int Bk, void* stream);
 
+/* thrift_kv_cache_append that also stores the lengths after the call: seqlens_out (nullable, device) [B] int32, another
+ * array than seqlens. */
+thrift_status thrift_kv_cache_append_advance(const void* k_new, const void* v_new, thrift_dtype dt, int n_new,
+                                             const int32_t* seqlens, const int32_t* new_lens, int32_t* seqlens_out,
+                                             void* k16, void* v16, uint8_t* k4, uint8_t* ks, uint8_t* v4, uint8_t* vs, float* kmean,
+                                             int B, int Hkv, int Nkv, int D, int Bk, void* stream);
+
 /*
  * Measurement helper (not a step of the method): one launch of a microbenchmark of a hardware rate that the
  * roofline figures of the attention kernels are priced against.  The caller times the launch (events on `stream`)

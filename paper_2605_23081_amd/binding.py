@@ -24,7 +24,7 @@ EXPORTS = (
     "thrift_select_kmax", "thrift_block_means", "thrift_select_topk", "thrift_select_topk_shared", "thrift_select_ablation", "thrift_quantize_mxfp4",
     "thrift_attn_prefill_workspace", "thrift_attn_prefill", "thrift_attn_prefill_chunk", "thrift_attn_prefill_ordered",
     "thrift_attn_decode_workspace", "thrift_attn_decode", "thrift_attn_decode_shared", "thrift_attn_decode_static",
-    "thrift_kv_cache_append",
+    "thrift_kv_cache_append", "thrift_kv_cache_append_advance",
     "thrift_attention_forward_workspace", "thrift_attention_forward", "thrift_peak_probe",
 )
 
@@ -70,9 +70,37 @@ def lib() -> C.CDLL:
         L.thrift_attention_forward_workspace.restype = sz
         L.thrift_attention_forward_workspace.argtypes = [i, i, i, i, i, i, i, i, d, i]
         L.thrift_attention_forward.argtypes = [p, p, p, i, i, i, i, i, i, i, i, i, d, i, i, f, p, i, p, p, sz, p]
+        L.thrift_kv_cache_append_advance.argtypes = [p, p, i, i, p, p, p, p, p, p, p, p, p, p, i, i, i, i, i, p]
         L.thrift_peak_probe.argtypes = [i, i, i, p, sz, C.POINTER(C.c_double), p]
         _lib = L
     return _lib
+
+
+_call = None
+
+
+def _native():
+    """The module that makes the calls of a serving loop without ctypes (csrc/thrift_call.cpp)."""
+    global _call
+    if _call is None:
+        lib()
+        try:
+            from . import _call as module
+        except ImportError as e:
+            raise RuntimeError("the module _call is missing: build it with `python -m paper_2605_23081_amd.build`") from e
+        _call = module
+    return _call
+
+
+def _raw_stream() -> int:
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _result(r, where: str):
+    """What a function of _native() returned: the result, or the status of the C call."""
+    if r.__class__ is int:
+        raise ThriftError(r, where)
+    return r
 
 
 def status_string(code: int) -> str:
@@ -261,6 +289,11 @@ def thrift_attn_decode(q, k16, v16, k4, ks, v4, vs, kmean, Bk: int, budget: floa
                        out: Optional[torch.Tensor] = None, out_dtype: Optional[torch.dtype] = None,
                        workspace: Optional[torch.Tensor] = None, return_selection: bool = False,
                        group_shared: bool = False):
+    if not return_selection and (out is not None or out_dtype is None):
+        r = (_call or _native()).decode(q, k16, v16, k4, ks, v4, vs, kmean, Bk, budget, fixed_k, split_blocks, softmax_scale,
+                                        seqlens, out, workspace, int(group_shared), _raw_stream())
+        if r is not None:
+            return _result(r, "thrift_attn_decode_shared" if group_shared else "thrift_attn_decode")
     for t in (q, k16, v16, k4, ks, v4, vs, kmean):
         _dev(t)
     _cache_shapes(k16, v16, k4, ks, v4, vs, kmean, Bk)
@@ -344,16 +377,20 @@ class KVCache:
         self.seqlens = torch.zeros(B, dtype=torch.int32, device=device)
 
     def append(self, k_new, v_new, new_lens: Optional[torch.Tensor] = None):
-        """Append k_new, v_new [B,Hkv,n,D] (all n tokens, or new_lens[b] of them) and advance seqlens."""
+        """Append k_new, v_new [B,Hkv,n,D] (all n tokens, or new_lens[b] of them) and advance seqlens (a new tensor)."""
+        r = (_call or _native()).append(k_new, v_new, self.seqlens, new_lens, self.k16, self.v16, self.k4, self.ks, self.v4, self.vs,
+                                        self.kmean, self.Bk, _raw_stream())
+        if r is not None:
+            self.seqlens = _result(r, "thrift_kv_cache_append")
+            return
+        after = torch.empty_like(self.seqlens)
         thrift_kv_cache_append(k_new, v_new, self.seqlens, self.k16, self.v16, self.k4, self.ks, self.v4, self.vs,
-                               self.kmean, self.Bk, new_lens)
-        n = k_new.shape[2]
-        step = torch.full_like(self.seqlens, n) if new_lens is None else new_lens.clamp(0, n).to(torch.int32)
-        self.seqlens = torch.minimum(self.seqlens + step, torch.full_like(self.seqlens, self.Nkv))
+                               self.kmean, self.Bk, new_lens, after)
+        self.seqlens = after
 
 
 def thrift_kv_cache_append(k_new, v_new, seqlens, k16, v16, k4, ks, v4, vs, kmean, Bk: int,
-                           new_lens: Optional[torch.Tensor] = None) -> None:
+                           new_lens: Optional[torch.Tensor] = None, seqlens_out: Optional[torch.Tensor] = None) -> None:
     for t in (k_new, v_new, k16, v16, k4, ks, v4, vs, kmean):
         _dev(t)
     _dev(seqlens, torch.int32)
@@ -365,8 +402,9 @@ def thrift_kv_cache_append(k_new, v_new, seqlens, k16, v16, k4, ks, v4, vs, kmea
     _, _, Nkv, _ = k16.shape
     assert tuple(k16.shape[:2]) == (B, Hkv) and k16.shape[3] == D and tuple(seqlens.shape) == (B,)
     assert new_lens is None or tuple(new_lens.shape) == (B,)
-    _check(lib().thrift_kv_cache_append(_ptr(k_new), _ptr(v_new), _DT[k_new.dtype], n_new, _ptr(seqlens), _ptr(new_lens),
-                                        _ptr(k16), _ptr(v16), _ptr(k4), _ptr(ks), _ptr(v4), _ptr(vs), _ptr(kmean),
+    assert seqlens_out is None or (tuple(_dev(seqlens_out, torch.int32).shape) == (B,))
+    _check(lib().thrift_kv_cache_append_advance(_ptr(k_new), _ptr(v_new), _DT[k_new.dtype], n_new, _ptr(seqlens), _ptr(new_lens),
+                                        _ptr(seqlens_out), _ptr(k16), _ptr(v16), _ptr(k4), _ptr(ks), _ptr(v4), _ptr(vs), _ptr(kmean),
                                         B, Hkv, Nkv, D, Bk, _stream()), "thrift_kv_cache_append")
 
 
@@ -434,6 +472,11 @@ def thrift_attention(q, k, v, causal: bool = True, Bq: int = 128, Bk: int = 64, 
                      workspace: Optional[torch.Tensor] = None, out: Optional[torch.Tensor] = None,
                      lse: Optional[torch.Tensor] = None, tile_order: int = 0) -> torch.Tensor:
     """Alg. 1: Q, K, V, block sizes and FP16 budget in, attention output out (thrift_attention_forward: one C call)."""
+    if out is not None or out_dtype is None:
+        r = (_call or _native()).attention(q, k, v, int(causal), Bq, Bk, budget, fixed_k, softmax_scale, workspace, out, lse, tile_order,
+                                           _raw_stream())
+        if r is not None:
+            return _result(r, "thrift_attention_forward")
     for t in (q, k, v):
         _dev(t)
     B, Hq, N, D = q.shape

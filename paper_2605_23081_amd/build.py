@@ -10,6 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libthrift_hip.so")
+CALL = os.path.join(HERE, "_call.so")          # the Python entry of the calls of a serving loop (host code only)
 SOURCES = ["thrift_api.hip", "thrift_prepass.hip", "thrift_prefill.hip", "thrift_decode.hip", "thrift_decode_split.hip", "thrift_cache.hip", "thrift_probe.hip"]
 DMA_SOURCES = ["thrift_prefill.hip", "thrift_decode.hip", "thrift_decode_split.hip"]      # kernels whose inline assembly sets M0 and keeps DMA in flight
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -81,6 +82,29 @@ def m0_outside_inline_asm(asm_text: str) -> int:
     return count
 
 
+def _start_call_module(obj):
+    """Compile csrc/thrift_call.cpp against the headers of the installed torch (host compiler)."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+
+    inc = [INCLUDE, sysconfig.get_paths()["include"], *include_paths()]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           *[f"-I{inc[0]}"], *[a for d in inc[1:] for a in ("-isystem", d)], "-c", os.path.join(CSRC, "thrift_call.cpp"), "-o", obj]
+    return cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+
+
+def _link_call_module(obj):
+    import torch
+
+    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    # the HIP library stands next to the module; torch's libraries are those of the process that imports it
+    cmd = ["g++", "-shared", "-o", CALL, obj, "-L" + HERE, "-lthrift_hip", "-Wl,-rpath,$ORIGIN", "-L" + tlib,
+           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    subprocess.run(cmd, check=True)
+
+
 def build(verbose: bool = False, extra=()):
     objs = []
     procs = []
@@ -89,6 +113,8 @@ def build(verbose: bool = False, extra=()):
         cmd = ["hipcc", *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
         procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    call_obj = os.path.join(CSRC, "thrift_call.o")
+    procs.append(_start_call_module(call_obj))
     # the device listings of the kernels that stage by LDS DMA, for the spill and M0 checks (run beside the object builds)
     listings = []
     for src in DMA_SOURCES:
@@ -100,7 +126,7 @@ def build(verbose: bool = False, extra=()):
         out = "\n".join(l for l in out.splitlines() if "not a recognized feature for this target" not in l)
         if p.returncode != 0:
             sys.stderr.write(out + "\n")
-            raise RuntimeError("hipcc failed: " + " ".join(cmd))
+            raise RuntimeError("compilation failed: " + " ".join(cmd))
         if verbose and out.strip():
             print(out)
     for src, listing, lcmd, lproc in listings:
@@ -118,6 +144,7 @@ def build(verbose: bool = False, extra=()):
             raise RuntimeError(f"{src}: the compiler uses M0: the LDS DMA statements would clobber it")
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
+    _link_call_module(call_obj)
     return LIB
 
 

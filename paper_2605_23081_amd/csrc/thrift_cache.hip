@@ -23,6 +23,7 @@ __global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
   constexpr int kRow = kD + 8;   // padded LDS row in 16-bit elements
   __shared__ __align__(16) uint16_t ktile[kBk * kRow];
   __shared__ __align__(16) uint16_t vtile[kBk * kRow];
+  __shared__ double upper[kD];   // channel sums of rows 32 .. 63
   const int tid = threadIdx.x;
   const int slot = blockIdx.x % a.blocks_per_unit;            // which of the blocks this append can touch
   const int unit = blockIdx.x / a.blocks_per_unit;            // (sequence, KV head)
@@ -31,6 +32,7 @@ __global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
   int n = a.new_lens ? min(a.n_new, max(0, a.new_lens[b])) : a.n_new;
   n = min(n, a.Nkv - len_old);                                // tokens past the capacity are dropped
   const int len_new = len_old + n;
+  if (a.seqlens_out != nullptr && slot == 0 && unit % a.Hkv == 0 && tid == 0) a.seqlens_out[b] = len_new;
   const int j = len_old / kBk + slot;                         // key block of this workgroup
   if (n <= 0 || j * kBk >= len_new) return;                   // uniform over the workgroup
   const int tok0 = j * kBk;
@@ -75,13 +77,14 @@ __global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
     }
   }
 
-  // ---- K mean of the block: fp64 sum of 16-bit values is exact, so the order of additions does not matter ----
+  // ---- K mean of the block: fp64 sum of 16-bit values is exact, so the order of additions does not matter, and the rows
+  // past the last token are zeros: two threads per channel take 32 rows each, all LDS reads in flight together (one thread
+  // walking `count` rows waited for each of them: 3 us of a one-token append) ----
   const size_t blk = (size_t)unit * (a.Nkv / kBk) + j;
-  if (tid < kD) {
-    double s = 0.0;
-    for (int r = 0; r < count; ++r) s += (double)T::to_float(ktile[r * kRow + tid]);
-    a.kmean[blk * kD + tid] = (float)(s / (double)count);
-  }
+  double sum = 0.0;
+#pragma unroll
+  for (int r = 0; r < 32; ++r) sum += (double)T::to_float(ktile[(32 * (tid >> 7) + r) * kRow + (tid & 127)]);
+  if (tid >= kD) upper[tid - kD] = sum;
 
   // ---- V: both 32-token groups of the block; thread = (group, channel) walks down a column ----
   {
@@ -96,6 +99,8 @@ __global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
     *reinterpret_cast<uint4*>(a.v4 + (blk * kD + c) * 32 + g * 16) = make_uint4(out[0], out[1], out[2], out[3]);
     a.vs[(blk * 2 + g) * kD + c] = (uint8_t)sb;
   }
+  __syncthreads();
+  if (tid < kD) a.kmean[blk * kD + tid] = (float)((sum + upper[tid]) / (double)count);
 }
 
 void launch_cache_append(const CacheAppendArgs& a, thrift_dtype dt, hipStream_t st) {

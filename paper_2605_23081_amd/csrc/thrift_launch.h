@@ -96,6 +96,7 @@ struct CacheAppendArgs {
   const uint16_t* v_new;
   const int32_t* seqlens;     // [B] tokens cached before the call
   const int32_t* new_lens;    // nullable [B]: tokens to take from k_new / v_new (<= n_new)
+  int32_t* seqlens_out;       // nullable [B]: tokens cached after the call (another array than seqlens)
   uint16_t* k16;              // [B,Hkv,Nkv,D]
   uint16_t* v16;
   uint8_t* k4;

@@ -1,0 +1,49 @@
+"""The native entry of the serving calls: what it does not serve goes to the general path, which names the fault."""
+import pytest
+import torch
+
+from paper_2605_23081_amd import binding as T
+
+
+def _args(device):
+    B, Hq, Hkv, N, D = 1, 4, 2, 128, 128
+    z = lambda *s, dt=torch.uint8: torch.zeros(*s, dtype=dt, device=device)
+    h = torch.float16
+    return [z(B, Hq, D, dt=h), z(B, Hkv, N, D, dt=h), z(B, Hkv, N, D, dt=h), z(B, Hkv, N, D // 2), z(B, Hkv, N, D // 32),
+            z(B, Hkv, N // 64, D, 32), z(B, Hkv, N // 32, D), z(B, Hkv, N // 64, D, dt=torch.float32)]
+
+
+def test_other_devices_and_kinds_of_arguments_are_left_to_the_general_path():
+    m = T._native()
+    a = _args("cpu")
+    rest = (64, 0.05, -1, 256, 0.0, None, None, None, 0, 0)
+    assert m.decode(*a, *rest) is None                       # host tensors
+    assert m.decode(*[None] * 8, *rest) is None and m.decode() is None
+    assert m.append(*a[:2], None, None, *a[1:], 64, 0) is None and m.attention(*a[:3], 1, 128, 64, 0.05, -1, 0.0, None, None, None, 0, 0) is None
+    with pytest.raises(AssertionError):
+        T.thrift_attn_decode(*a, 64, 0.05)
+
+
+@pytest.mark.gpu
+def test_device_tensors_of_wrong_shape_or_type_raise_as_before():
+    a = _args("cuda")
+    assert torch.equal(T.thrift_attn_decode(*a, 64, 0.05), torch.zeros(1, 4, 128, dtype=torch.float16, device="cuda"))
+    for i, bad in ((0, a[0].float()), (3, a[3][:, :, :64].contiguous()), (7, a[7].half()), (1, a[1].transpose(1, 2))):
+        b = list(a)
+        b[i] = bad
+        with pytest.raises(AssertionError):
+            T.thrift_attn_decode(*b, 64, 0.05)
+    with pytest.raises(T.ThriftError):
+        T.thrift_attn_decode(*a, 64, 1.5)                    # a status of the C call
+    with pytest.raises(AssertionError):
+        T.thrift_attn_decode(*a, 64, 0.05, seqlens=torch.zeros(2, dtype=torch.int32, device="cuda"))
+    cache = T.KVCache(1, 2, 128, 128, 64, torch.float16, "cuda", fill=0)
+    new = torch.zeros(1, 2, 100, 128, dtype=torch.float16, device="cuda")
+    before = cache.seqlens
+    cache.append(new, new)
+    cache.append(new, new, torch.tensor([20], dtype=torch.int32, device="cuda"))
+    assert before.tolist() == [0] and cache.seqlens.tolist() == [120]
+    cache.append(new, new)
+    assert cache.seqlens.tolist() == [128]                   # the capacity
+    with pytest.raises(AssertionError):
+        cache.append(new.float(), new.float())
