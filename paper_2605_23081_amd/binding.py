@@ -93,7 +93,10 @@ def _native():
 
 
 def _raw_stream() -> int:
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except RuntimeError:                                    # no device: no device tensors either, the general path says so
+        return 0
 
 
 def _result(r, where: str):
