@@ -621,11 +621,14 @@ __device__ __forceinline__ uint64_t order_key64(double s) {
   return (u >> 63) ? ~u : (u | 0x8000000000000000ULL);   // larger double <=> larger key
 }
 
-constexpr int kScoreChunksPerWg = 8;     // 64-block chunks one workgroup of decode_scores_kernel walks
+// 64-block chunks one workgroup of decode_scores_kernel walks, at most: the query rows are widened once for all of them and
+// the next chunk arrives behind the arithmetic of the present one.  Fewer where the grid would leave CUs without a workgroup
+// (one sequence of 32768 tokens: 64 workgroups instead of 8, 7 us instead of 20).
+constexpr int kScoreChunksPerWg = 8;
 
 __global__ void __launch_bounds__(256) decode_scores_kernel(const uint16_t* __restrict__ q16, int q_is_bf16, const float* __restrict__ kmean,
                                                             const int32_t* __restrict__ seqlens, uint64_t* __restrict__ keys,
-                                                            int Hq, int Hkv, int Tk, int shared) {
+                                                            int Hq, int Hkv, int Tk, int shared, int per_wg) {
   constexpr int kStride = kD + 4;
   __shared__ __align__(16) float kst[64 * kStride];
   __shared__ __align__(16) float qst[32 * kD];
@@ -633,12 +636,12 @@ __global__ void __launch_bounds__(256) decode_scores_kernel(const uint16_t* __re
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform: the loop over the heads stays scalar
   const int G = Hq / Hkv, chunks = (Tk + 63) / 64;
-  const int groups = (chunks + kScoreChunksPerWg - 1) / kScoreChunksPerWg;
-  const int chunk0 = (blockIdx.x % groups) * kScoreChunksPerWg, unit = blockIdx.x / groups;
+  const int groups = (chunks + per_wg - 1) / per_wg;
+  const int chunk0 = (blockIdx.x % groups) * per_wg, unit = blockIdx.x / groups;
   const int b = unit / Hkv, kvh = unit % Hkv;
   const int cap = seqlens ? min(Tk, (max(0, seqlens[b]) + kBk - 1) / kBk) : Tk;
   if (chunk0 * 64 >= cap) return;                           // uniform: nothing of these chunks is valid
-  const int chunk_end = min(chunk0 + kScoreChunksPerWg, (cap + 63) / 64);
+  const int chunk_end = min(chunk0 + per_wg, (cap + 63) / 64);
   const float* kunit = kmean + (size_t)unit * Tk * kD;
   // the chunk after the one being scored travels through registers, so its latency hides behind the arithmetic
   float4 pre[8];
@@ -824,8 +827,10 @@ void launch_decode_select(const uint16_t* q16, int q_is_bf16, const float* kmean
                           unsigned long long* bitmap, int words, int32_t* idx_out, int32_t* cnt_out, int kmax_out,
                           int B, int Hq, int Hkv, int Tk, int fixed_k, long long ppm, int shared, hipStream_t st) {
   const int chunks = (Tk + 63) / 64;
-  const int score_groups = (chunks + kScoreChunksPerWg - 1) / kScoreChunksPerWg;
-  decode_scores_kernel<<<dim3((unsigned)((long)B * Hkv * score_groups)), dim3(256), 0, st>>>(q16, q_is_bf16, kmean, seqlens, keys, Hq, Hkv, Tk, shared);
+  int per_wg = kScoreChunksPerWg;
+  while (per_wg > 1 && (long)B * Hkv * ((chunks + per_wg - 1) / per_wg) < 512) per_wg /= 2;
+  const int score_groups = (chunks + per_wg - 1) / per_wg;
+  decode_scores_kernel<<<dim3((unsigned)((long)B * Hkv * score_groups)), dim3(256), 0, st>>>(q16, q_is_bf16, kmean, seqlens, keys, Hq, Hkv, Tk, shared, per_wg);
   DecodeSelectArgs p;
   p.keys = keys; p.seqlens = seqlens; p.bitmap = bitmap; p.idx_out = idx_out; p.cnt_out = cnt_out;
   p.Hq = Hq; p.Tk = Tk; p.words = words; p.kmax_out = kmax_out; p.fixed_k = fixed_k; p.ppm = ppm;

@@ -6,8 +6,8 @@
 //   decode_split_values_kernel  softmax, P quantiser and P.V of a chunk, started from the largest score of the chunks in
 //                               front of it in the partition: the running maximum of every block, hence every code of P, is
 //                               the one of the serial walk.
-// A chunk is `cw` key blocks and belongs to ONE wavefront, which takes all heads of the KV group at once (head u in rows u
-// and u + 4 of the score tiles, column u of the P.V tiles: up to 8 heads cost the matrix instructions of one), operands
+// A chunk is `cw` key blocks and belongs to ONE wavefront, which takes all heads of the KV group at once (a row or
+// column of the matrix tiles each: up to 8 heads cost the matrix instructions of one), operands
 // straight from global memory: no barrier and no LDS on the 4-bit path.  Four chunks that follow each other make a workgroup,
 // whose partials are added up in LDS before they are written.
 // Measured against the walk (attention kernels alone): 14 + 15 us against 250 us for one sequence of 32768 tokens and 32/8
@@ -76,13 +76,50 @@ __device__ __forceinline__ int promoted_mask(unsigned long long bits, int i) {
   return (int)__builtin_amdgcn_ballot_w64(((bits >> i) & 1ULL) != 0ULL);
 }
 
+template <typename T>
+__device__ __forceinline__ v4f mfma16(v8s x, v8s y, v4f acc) {
+  if constexpr (std::is_same_v<T, F16>)
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, x), __builtin_bit_cast(v8h, y), acc, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, x), __builtin_bit_cast(v8bf, y), acc, 0, 0, 0);
+}
+
 }  // namespace
+
+// Matrix tiles: 16 x 16, one operand row or column per head (up to 8 of 16 used) and 16 keys or channels.  Lane = 16 g + r:
+//   A operand  row r,    contraction slots of group g (32 codes of MXFP4 with a scale each, or 8 elements of 16 bits)
+//   B operand  column r, the same slots
+//   C / D      column r, rows 4 g + i in register i
+// All 128 channels of a 4-bit score are one instruction, and a wavefront's load of 16 keys x 64 bytes is 1 KiB in a row.
+
+// largest value over the lanes that hold the same head (lane % NH), in every one of them: first of each 32 lanes
+template <int NH>
+__device__ __forceinline__ float head_max32(float v) {
+  if constexpr (NH <= 1) v = fmaxf(v, dpp_f<0x121>(v));        // row_ror: lane i of 16 reads lane i - n
+  if constexpr (NH <= 2) v = fmaxf(v, dpp_f<0x122>(v));
+  if constexpr (NH <= 4) v = fmaxf(v, dpp_f<0x124>(v));
+  v = fmaxf(v, dpp_f<0x128>(v));
+  const uint32_t b = __float_as_uint(v);
+  const auto s = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+  return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+template <int NH>
+__device__ __forceinline__ float head_sum(float v) {
+  if constexpr (NH <= 1) v += dpp_f<0x121>(v);
+  if constexpr (NH <= 2) v += dpp_f<0x122>(v);
+  if constexpr (NH <= 4) v += dpp_f<0x124>(v);
+  v += dpp_f<0x128>(v);
+  const uint32_t b = __float_as_uint(v);
+  const auto s = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+  v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  return v + other_half(v);
+}
 
 // NH: heads per KV group, rounded up to 1, 2, 4 or 8
 template <typename T, int NH>
-__global__ void __launch_bounds__(256) decode_split_scores_kernel(DecodeSplitArgs s) {
+__global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplitArgs s) {
   const DecodeArgs& a = s.a;
-  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, r = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SplitWork w = split_work(s, wave);
   if (w.j0 >= w.j1) return;
@@ -90,248 +127,319 @@ __global__ void __launch_bounds__(256) decode_split_scores_kernel(DecodeSplitArg
   const size_t group0 = (size_t)w.b * a.Hq + (size_t)w.kvh * G, kh = (size_t)w.b * a.Hkv + w.kvh;
   const uint8_t* k4base = a.k4 + kh * a.Nkv * 64;
   const uint8_t* ksbase = a.ks + kh * a.Nkv * 4;
-  const uint16_t* k16base = a.k16 + kh * a.Nkv * kD;
+  const uint8_t* k16base = reinterpret_cast<const uint8_t*>(a.k16 + kh * a.Nkv * kD);
+  const uint32_t k4off = (uint32_t)(64 * r + 16 * g), ksoff = (uint32_t)(4 * r + g);   // key 16t + r, channels 32g .. 32g + 31
+  const uint32_t k16off = (uint32_t)(256 * r + 16 * g);
 
   const unsigned long long bits = promoted_bits(a, group0, G, w.j0, lane);
   const int all = (1 << G) - 1;
 
-  // fragment (t, kk): key 32t + r, d-group 2*half + kk
-  auto load4 = [&](int j) {
-    K4Tile k;
-    const uint8_t* kt = k4base + (size_t)j * 4096 + r * 64 + half * 32;
-    const uint8_t* st = ksbase + (size_t)j * 256 + r * 4 + half * 2;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      k.a[2 * t] = *reinterpret_cast<const v4i*>(kt + 2048 * t);
-      k.a[2 * t + 1] = *reinterpret_cast<const v4i*>(kt + 2048 * t + 16);
-      k.ks[t] = *reinterpret_cast<const uint16_t*>(st + 128 * t);
-    }
-    return k;
+  struct Keys {
+    v4i k[4];            // key 16t + r, channels 32g .. 32g + 31
+    uint32_t ks[4];      // their scale
   };
-  K4Tile next = load4(w.j0);
-
-  // the query rows as A operand: head u in rows u, u + 4 (u < 4) or u + 4, u + 8, so that accumulator register u of both
-  // halves is head u; the lane quantises the two MXFP4 groups it carries
-  const int hu = (r & 3) + 4 * (r >> 3);
-  const bool qlane = r < (NH > 4 ? 16 : 8) && hu < G;
-  const uint16_t* qrow = a.q + (group0 + (qlane ? hu : 0)) * kD;
-  v4i qf4[2] = {(v4i){0, 0, 0, 0}, (v4i){0, 0, 0, 0}};
-  uint32_t qsc = 0x7f7f7f7fu;
-  if (qlane) {
-    uint32_t sb[2];
+  auto load4 = [&](int j) {
+    Keys x;
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const uint4* src = reinterpret_cast<const uint4*>(qrow + 64 * half + 32 * kk);
-      uint32_t pair[16], codes[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint4 x = src[t];
-        pair[4 * t] = x.x; pair[4 * t + 1] = x.y; pair[4 * t + 2] = x.z; pair[4 * t + 3] = x.w;
-      }
-      sb[kk] = quantize_group32<T>(pair, codes);
-      qf4[kk] = (v4i){(int)codes[0], (int)codes[1], (int)codes[2], (int)codes[3]};
+    for (int t = 0; t < 4; ++t) {
+      x.k[t] = *reinterpret_cast<const v4i*>(k4base + (size_t)j * 4096 + k4off + 1024 * t);
+      x.ks[t] = (ksbase + (size_t)j * 256)[ksoff + 64 * t];
     }
-    qsc = sb[0] | (sb[1] << 8);
+    return x;
+  };
+  // a block that every head takes in 16 bits is not read in 4
+  Keys next;
+  int Mnext = promoted_mask(bits, 0);
+  if (Mnext != all) next = load4(w.j0);
+
+  // the query rows as A operand: head r % NR in row r, so that every lane's accumulator registers i are heads
+  // (4 g + i) % NR; the lane quantises the MXFP4 group it carries
+  constexpr int NR = NH > 4 ? 8 : 4;
+  const int hq = r & (NR - 1);
+  const bool qlane = hq < G;
+  const uint16_t* qrow = a.q + (group0 + (qlane ? hq : 0)) * kD;
+  v4i qf4 = {0, 0, 0, 0};
+  uint32_t qsc = 127u;
+  if (qlane) {
+    const uint4* src = reinterpret_cast<const uint4*>(qrow + 32 * g);
+    uint32_t pair[16], codes[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint4 x = src[t];
+      pair[4 * t] = x.x; pair[4 * t + 1] = x.y; pair[4 * t + 2] = x.z; pair[4 * t + 3] = x.w;
+    }
+    qsc = quantize_group32<T>(pair, codes);
+    qf4 = (v4i){(int)codes[0], (int)codes[1], (int)codes[2], (int)codes[3]};
   }
 
-  float top[NH];
+  // The lane keeps NS scores of NV heads: with four rows of heads, key `lane` (tile g of the four); with eight, heads
+  // 4 (g & 1) + i of the keys 16 (g >> 1) + r and 32 more.
+  constexpr int NS = NH > 4 ? 2 : 1, NV = NH > 4 ? 4 : NH;
+  const int h0 = NH > 4 ? 4 * (g & 1) : 0, key0 = NH > 4 ? 16 * (g >> 1) + r : lane;
+  auto mine = [&](const v4f (&acc)[4], float (&v)[NS][NV]) {
 #pragma unroll
-  for (int u = 0; u < NH; ++u) top[u] = kEmptyMax;
-  for (int j = w.j0; j < w.j1; ++j) {
-    const int M = promoted_mask(bits, j - w.j0);
-    const K4Tile k = next;
-    if (j + 1 < w.j1) next = load4(j + 1);
-    float s4[NH], s16[NH];
-    if (M != all) scores4_row<NH>(k, lane, qf4, qsc, s4);
-    if (M != 0) {
-      // keys past the cached tokens are not read: the last valid row stands in, its scores are masked below
-      const uint16_t* kt = k16base + (size_t)j * kBk * kD + 8 * half;
-      v16f acc[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const uint16_t* krow = kt + min(32 * t + r, w.n_valid - 1) * kD;
-        acc[t] = (v16f){0.f};
-#pragma unroll
-        for (int s8 = 0; s8 < 8; ++s8) {
-          const v8s qf = qlane ? *reinterpret_cast<const v8s*>(qrow + 16 * s8 + 8 * half) : (v8s){0, 0, 0, 0, 0, 0, 0, 0};
-          acc[t] = T::mfma(qf, *reinterpret_cast<const v8s*>(krow + 16 * s8), acc[t]);
-        }
+    for (int i = 0; i < NV; ++i) {
+      if constexpr (NH > 4) {
+        v[0][i] = g >= 2 ? acc[1][i] : acc[0][i];
+        v[1][i] = g >= 2 ? acc[3][i] : acc[2][i];
+      } else {
+        const float lo = g & 1 ? acc[1][i] : acc[0][i], hi = g & 1 ? acc[3][i] : acc[2][i];
+        v[0][i] = g >= 2 ? hi : lo;
       }
+    }
+  };
+  float top[NV];
 #pragma unroll
-      for (int u = 0; u < NH; ++u) s16[u] = half ? acc[1][u] : acc[0][u];
+  for (int i = 0; i < NV; ++i) top[i] = kEmptyMax;
+  float* out = s.scores + (group0 + h0) * a.Nkv + key0;
+  for (int j = w.j0; j < w.j1; ++j) {
+    const int M = Mnext;
+    const Keys k = next;
+    Mnext = j + 1 < w.j1 ? promoted_mask(bits, j + 1 - w.j0) : all;
+    if (Mnext != all) next = load4(j + 1);
+    float v4[NS][NV], v16[NS][NV];
+    if (M != all) {
+      v4f acc[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        acc[t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(widen(qf4), widen(k.k[t]), (v4f){0.f, 0.f, 0.f, 0.f}, 4, 4, 0, qsc, 0, k.ks[t]);
+      mine(acc, v4);
+    }
+    if (M != 0) {
+      // rows past the cached tokens reach only their own keys' scores, which are masked below
+      const uint8_t* tile = k16base + (size_t)j * kTile16;
+      v4f acc[4];
+      v8s qf[4];
+#pragma unroll
+      for (int s4 = 0; s4 < 4; ++s4)
+        qf[s4] = qlane ? *reinterpret_cast<const v8s*>(qrow + 32 * s4 + 8 * g) : (v8s){0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        acc[t] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) acc[t] = mfma16<T>(qf[s4], *reinterpret_cast<const v8s*>(tile + k16off + 4096 * t + 64 * s4), acc[t]);
+      }
+      mine(acc, v16);
     }
 #pragma unroll
-    for (int u = 0; u < NH; ++u)
-      if (u < G) {
-        float v = ((M >> u) & 1) ? s16[u] : s4[u];
-        if (lane >= w.n_valid) v = -INFINITY;
-        s.scores[(group0 + u) * a.Nkv + (size_t)j * kBk + lane] = v;
-        top[u] = fmaxf(top[u], v);
-      }
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        if (h0 + i < G) {
+          float v = ((M >> (h0 + i)) & 1) ? v16[q][i] : v4[q][i];
+          if (key0 + 32 * q >= w.n_valid) v = -INFINITY;
+          out[(size_t)i * a.Nkv + (size_t)j * kBk + 32 * q] = v;
+          top[i] = fmaxf(top[i], v);
+        }
   }
   if (w.tail) return;                                          // a partition of its own: no chunk follows it
 #pragma unroll
-  for (int u = 0; u < NH; ++u)
-    if (u < G) {
-      const float m = wave_max(top[u]);
-      if (lane == 0) s.cmax[(group0 + u) * s.chunks + w.chunk] = m;
+  for (int i = 0; i < NV; ++i) {
+    float m = top[i];                                          // over the 16 keys of the lane's row of lanes, then over the rows with the same heads
+    m = fmaxf(m, dpp_f<0x121>(m));
+    m = fmaxf(m, dpp_f<0x122>(m));
+    m = fmaxf(m, dpp_f<0x124>(m));
+    m = fmaxf(m, dpp_f<0x128>(m));
+    if constexpr (NH <= 4) {
+      const uint32_t b = __float_as_uint(m);
+      const auto sw = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+      m = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     }
+    m = fmaxf(m, other_half(m));
+    if (r == 0 && g < (NH > 4 ? 2 : 1) && h0 + i < G) s.cmax[(group0 + h0 + i) * s.chunks + w.chunk] = m;
+  }
 }
 
+// Softmax layout: lane = NH kg + h holds the NH keys NH kg .. of head h, so that every step of the recurrence that is not
+// an exponential costs the heads of a group one instruction together, and each 32 lanes hold one MXFP4 group of P per head.
+// The operands of P.V (column = head) are formed through a few hundred bytes of the wavefront's own LDS.
+// The accumulators hold channel 8 (4 g + i) + e of head r in o[e][i]: row r of tile e is channel 8 r + e, because a lane's
+// 16 bytes of a 16-bit V row are 8 neighbouring channels, which are transposed against 8 rows inside the lane.
 template <typename T, int NH>
-__global__ void __launch_bounds__(256, 2) decode_split_values_kernel(DecodeSplitArgs s) {
+__global__ void __launch_bounds__(256, 3) decode_split_values_kernel(DecodeSplitArgs s) {
   const DecodeArgs& a = s.a;
-  __shared__ __align__(1024) unsigned char tiles[4 * kTile16];              // a 16-bit V tile per wavefront; the partials at the end
-  __shared__ __align__(16) uint16_t prow[4 * NH * 64];                      // rounded probabilities of the heads, per wavefront
+  __shared__ __align__(16) float red[4][NH][kD];
+  __shared__ __align__(16) uint16_t prow[4][NH * 64];          // probabilities rounded to 16 bits: [head][key]
+  __shared__ __align__(16) uint8_t pcode[4][NH * 32];          // codes of P: [head][key / 2]
+  __shared__ uint8_t pscale[4][NH * 2];                        // their E8M0 bytes: [head][group]
   __shared__ float ml[4][NH][2];
-  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, r = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SplitWork w = split_work(s, wave);
   if (!w.any) return;                                          // uniform over the workgroup
   const int G = a.Hq / a.Hkv;
   const size_t group0 = (size_t)w.b * a.Hq + (size_t)w.kvh * G, kh = (size_t)w.b * a.Hkv + w.kvh;
-  const uint8_t* v4base = a.v4 + kh * (size_t)(a.Nkv / 64) * 4096;
-  const uint8_t* vsbase = a.vs + kh * (size_t)(a.Nkv / 32) * kD;
-  const uint8_t* v16base = reinterpret_cast<const uint8_t*>(a.v16 + kh * a.Nkv * kD);
-  unsigned char* tile = tiles + wave * kTile16;
-  uint16_t* myp = prow + wave * NH * 64;
   const float c = a.scale * 1.4426950408889634f;
 
-  RowState st[NH];
+  const int h = lane & (NH - 1), kg = lane / NH;               // softmax layout
+  const size_t qh = group0 + min(h, G - 1);                    // lanes of a padding head follow the last one and are never read
+  RowState st = {kEmptyMax, 0.f};
+  v4f o[8];
 #pragma unroll
-  for (int u = 0; u < NH; ++u) st[u] = {kEmptyMax, 0.f};
-  v16f o[4];
-#pragma unroll
-  for (int n = 0; n < 4; ++n) o[n] = (v16f){0.f};
+  for (int e = 0; e < 8; ++e) o[e] = (v4f){0.f, 0.f, 0.f, 0.f};
 
   if (w.j0 < w.j1) {
+    // scalar bases and 32-bit lane offsets
+    const uint8_t* v4base = a.v4 + kh * (size_t)(a.Nkv / 64) * 4096;
+    const uint8_t* vsbase = a.vs + kh * (size_t)(a.Nkv / 32) * kD;
+    const uint8_t* v16base = reinterpret_cast<const uint8_t*>(a.v16 + kh * a.Nkv * kD);
+    const uint32_t v4off = (uint32_t)(r * 256 + (g & 1) * 16), vsoff = (uint32_t)((g & 1) * kD + 8 * r);   // channel 8 r, token group g
+    const uint32_t v16off = (uint32_t)(2048 * g + 16 * r);
+    const float* srow = s.scores + qh * a.Nkv + NH * kg;
+    uint16_t* prow_w = prow[wave];
+    uint8_t* pcode_w = pcode[wave];
+    uint8_t* pscale_w = pscale[wave];
     const unsigned long long bits = promoted_bits(a, group0, G, w.j0, lane);
     const int all = (1 << G) - 1, n_blocks = w.j1 - w.j0;
-    struct Block {
-      v4i v[4];
-      uint32_t vs[4];
-      float sv[NH];
-    };
-    auto load = [&](int j) {
-      Block x;
-      const uint8_t* vt = v4base + (size_t)j * 4096 + r * 32 + half * 16;   // channel 32n + r, token half
-      const uint8_t* vsr = vsbase + ((size_t)j * 2 + half) * kD + r;
+    struct Scores { float v[NH]; };
+    auto load_scores = [&](int j) {
+      Scores x;
+      if constexpr (NH >= 4) {
 #pragma unroll
-      for (int u = 0; u < NH; ++u) x.sv[u] = u < G ? s.scores[(group0 + u) * a.Nkv + (size_t)j * kBk + lane] : 0.f;
+        for (int u = 0; u < NH; u += 4) {
+          const float4 y = *reinterpret_cast<const float4*>(srow + (size_t)j * kBk + u);
+          x.v[u] = y.x; x.v[u + 1] = y.y; x.v[u + 2] = y.z; x.v[u + 3] = y.w;
+        }
+      } else {
 #pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        x.v[n] = *reinterpret_cast<const v4i*>(vt + 1024 * n);
-        x.vs[n] = vsr[32 * n];
+        for (int u = 0; u < NH; ++u) x.v[u] = srow[(size_t)j * kBk + u];
       }
       return x;
     };
-    // 16-bit V tile of block j into the wavefront's own buffer: instruction q covers rows 4q .. 4q+3; rows past the cached
-    // tokens are never written by anyone: the last valid row in their place
-    const uint32_t lds0 = lds_address(tile);
-    auto issue16 = [&](int j) {
-      const uint8_t* base = v16base + (size_t)__builtin_amdgcn_readfirstlane(j) * kTile16;
-      const uint32_t chunk = (uint32_t)((lane & 15) ^ v16_swizzle(lane >> 4)) * 16;
+    // keys 32 q + 8 g .. + 7 of block j, channels 8 r ..
+    auto load16 = [&](int j, int q, v4i (&row)[8]) {
+      const uint8_t* tile = v16base + (size_t)j * kTile16 + 8192 * q;
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const uint32_t row = (uint32_t)min(4 * q + (lane >> 4), w.n_valid - 1);
-        dma_b128(base, row * 256 + chunk, lds0 + q * 1024);
-      }
+      for (int u = 0; u < 8; ++u) row[u] = *reinterpret_cast<const v4i*>(tile + v16off + 256 * u);
     };
-    Block next = load(w.j0);
-    // the next promoted block of the chunk is fetched as soon as the buffer is free
-    int j16 = w.j0;
-    auto advance16 = [&]() {
-      while (j16 < w.j1 && promoted_mask(bits, j16 - w.j0) == 0) ++j16;
-      if (j16 < w.j1) issue16(j16);
+    // rows past the cached tokens hold whatever lies there, and zero times that need not be zero
+    auto clear16 = [&](int q, v4i (&row)[8]) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (32 * q + 8 * g + u >= w.n_valid) row[u] = (v4i){0, 0, 0, 0};
     };
-    advance16();
+    Scores next = load_scores(w.j0);
     // running maximum in front of the chunk
     const int ahead = w.chunk - w.first_chunk;
     if (ahead > 0) {
-#pragma unroll
-      for (int u = 0; u < NH; ++u)
-        if (u < G) {
-          const float* cm = s.cmax + (group0 + u) * s.chunks + w.first_chunk;
-          float m = kEmptyMax;
-          for (int e = lane; e < ahead; e += 64) m = fmaxf(m, cm[e]);
-          st[u].m = m;
-        }
-#pragma unroll
-      for (int u = 0; u < NH; ++u) st[u].m = wave_max(st[u].m);
+      const float* cm = s.cmax + qh * s.chunks + w.first_chunk;
+      float m = kEmptyMax;
+      for (int e = kg; e < ahead; e += 64 / NH) m = fmaxf(m, cm[e]);
+      m = head_max32<NH>(m);
+      st.m = fmaxf(m, other_half(m));
     }
     for (int i = 0; i < n_blocks; ++i) {
       const int j = w.j0 + i;
       const int M = promoted_mask(bits, i);
-      const Block x = next;
-      if (i + 1 < n_blocks) next = load(j + 1);
-      float p[NH], alpha_lane = 1.f;
-      uint32_t pb[NH];
-      bool grew = false;
-#pragma unroll
-      for (int u = 0; u < NH; ++u)
-        if (u < G) {
-          float alpha;
-          const bool g = softmax_row(x.sv[u], c, st[u], alpha, pb[u], p[u]);
-          if (g) alpha_lane = r == u ? alpha : alpha_lane;
-          grew |= g;
-        }
-      rescale(o, grew, alpha_lane);
+      const Scores x = next;
+      if (i + 1 < n_blocks) next = load_scores(j + 1);
+      v4i v[8];                                                // asked for here, needed after the softmax: 4-bit tile or half a 16-bit one
+      uint2 vs = make_uint2(0u, 0u);
       if (M != all) {
-        // head u's codes in column u; zeros for the heads that take the block in 16 bits
-        v4i pq = {0, 0, 0, 0};
-        uint32_t pb_lane = 127u;
-        auto place = [&](auto uc) {
-          constexpr int u = decltype(uc)::value;
-          if (u < G && ((M >> u) & 1) == 0) {
-            const v4i mine = gather_p4<u>(p[u], pb[u]);
-            if (r == u) { pq = mine; pb_lane = pb[u]; }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = *reinterpret_cast<const v4i*>(v4base + (size_t)j * 4096 + v4off + 32 * e);
+        vs = *reinterpret_cast<const uint2*>(vsbase + (size_t)j * 256 + vsoff);
+      } else {
+        load16(j, 0, v);
+      }
+      // ---- online softmax (Alg. 1 steps 10-12 / 16-17) of all heads ----
+      float gmax = x.v[0];
+#pragma unroll
+      for (int u = 1; u < NH; ++u) gmax = fmaxf(gmax, x.v[u]);
+      gmax = head_max32<NH>(gmax);                             // the lane's 32-key group
+      const uint32_t gb = __float_as_uint(gmax);
+      const auto s32 = __builtin_amdgcn_permlane32_swap(gb, gb, false, false);
+      const float m_new = max3(st.m, __uint_as_float(s32[0]), __uint_as_float(s32[1]));
+      if (__builtin_amdgcn_ballot_w64(m_new != st.m) != 0ULL) {
+        const float alpha = fast_exp2((st.m - m_new) * c);     // lane 16 g + r, r < NH: head r, which is also its column of o
+        st.l *= alpha;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] *= alpha;
+        st.m = m_new;
+      }
+      int ex;
+      {
+        const float d = (gmax - m_new) * c;                    // the group maximum maps to exactly 2^floor(d) or above
+        asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(ex) : "v"(d));
+      }
+      const uint32_t pb = (uint32_t)max(ex + 125, 1);
+      const float pscale_f = __uint_as_float(pb << 23), mc = m_new * c;
+      float p[NH];
+#pragma unroll
+      for (int u = 0; u < NH; ++u) {
+        p[u] = fast_exp2(__builtin_fmaf(x.v[u], c, -mc));
+        st.l += p[u];
+      }
+      if (M != all) {
+        if constexpr (NH == 1) {
+          const float nb = dpp_f<kDppSwap1>(p[0]);
+          const uint32_t code = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, p[0], nb, pscale_f, 0);
+          if ((lane & 1) == 0) pcode_w[lane >> 1] = (uint8_t)code;
+        } else {
+          uint32_t code = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, p[0], p[1], pscale_f, 0);
+          if constexpr (NH >= 4) code = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(code, p[2], p[3], pscale_f, 1);
+          if constexpr (NH == 8) {
+            code = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(code, p[4], p[5], pscale_f, 2);
+            code = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(code, p[6], p[7], pscale_f, 3);
           }
-        };
-        place(std::integral_constant<int, 0>{});
-        if constexpr (NH > 1) place(std::integral_constant<int, 1>{});
-        if constexpr (NH > 2) { place(std::integral_constant<int, 2>{}); place(std::integral_constant<int, 3>{}); }
-        if constexpr (NH > 4) {
-          place(std::integral_constant<int, 4>{}); place(std::integral_constant<int, 5>{});
-          place(std::integral_constant<int, 6>{}); place(std::integral_constant<int, 7>{});
+          uint8_t* to = pcode_w + h * 32 + kg * (NH / 2);
+          if constexpr (NH == 8) *reinterpret_cast<uint32_t*>(to) = code;
+          else if constexpr (NH == 4) *reinterpret_cast<uint16_t*>(to) = (uint16_t)code;
+          else *to = (uint8_t)code;
         }
-        pv_fp4_codes_regs<false>(pq, pb_lane, x.vs[0], x.vs[1], x.vs[2], x.vs[3], x.v[0], x.v[1], x.v[2], x.v[3], o);
+        if ((lane & 31) < NH) pscale_w[h * 2 + (lane >> 5)] = (uint8_t)pb;
+        // column r = head r, slots 32 g ..: zeros for padding columns, for the slots past the block's 64 keys and for the
+        // heads that take the block in 16 bits
+        v4i pq = {0, 0, 0, 0};
+        uint32_t pbl = 127u;
+        if (r < G && g < 2 && ((M >> r) & 1) == 0) {
+          pq = *reinterpret_cast<const v4i*>(pcode_w + r * 32 + g * 16);
+          pbl = pscale_w[r * 2 + g];
+        }
+        const v8i pq8 = widen(pq);
+#define THRIFT_PV4(E) o[E] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(widen(v[E]), pq8, o[E], 4, 4, (E) & 3, (E) < 4 ? vs.x : vs.y, 0, pbl);
+        THRIFT_PV4(0) THRIFT_PV4(1) THRIFT_PV4(2) THRIFT_PV4(3) THRIFT_PV4(4) THRIFT_PV4(5) THRIFT_PV4(6) THRIFT_PV4(7)
+#undef THRIFT_PV4
       }
       if (M != 0) {
 #pragma unroll
-        for (int u = 0; u < NH; ++u)
-          if (u < G) myp[u * 64 + lane] = T::from_float(p[u]);
+        for (int u = 0; u < NH; ++u) prow_w[h * 64 + NH * kg + u] = T::from_float(p[u]);
         const bool mine = r < G && ((M >> r) & 1) != 0;
-        v8s pf[4];
+        if (M != all) load16(j, 0, v);
+        v4i vb[8];
+        load16(j, 1, vb);
+        if (w.n_valid != kBk) { clear16(0, v); clear16(1, vb); }
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          pf[q] = mine ? *reinterpret_cast<const v8s*>(myp + (r & (NH - 1)) * 64 + 32 * half + 8 * q) : (v8s){0, 0, 0, 0, 0, 0, 0, 0};
-        vm_wait<0>();                                          // the tile has arrived (only this wavefront reads it)
-        pv_16_rounded<T, true>(tile, lane, pf, o);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // its reads are over before the next tile may land
-        ++j16;
-        advance16();
+        for (int q = 0; q < 2; ++q) {                          // keys 32 q + 8 g .. + 7
+          const v8s pf = mine ? *reinterpret_cast<const v8s*>(prow_w + r * 64 + 32 * q + 8 * g) : (v8s){0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+            v4i col;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) col[u] = (int)__builtin_amdgcn_perm((uint32_t)(q ? vb : v)[2 * u + 1][e >> 1], (uint32_t)(q ? vb : v)[2 * u][e >> 1], sel);
+            o[e] = mfma16<T>(__builtin_bit_cast(v8s, col), pf, o[e]);
+            if (e & 1) __builtin_amdgcn_sched_barrier(0);      // the transposed pieces are formed as they are used, not all ahead
+          }
+        }
       }
     }
-    // column u of the accumulators: head u
     if (r < G) {
-      float* red = reinterpret_cast<float*>(tile) + r * kD;
 #pragma unroll
-      for (int n = 0; n < 4; ++n)
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4)
-          *reinterpret_cast<float4*>(red + 32 * n + 8 * g4 + 4 * half) =
-              make_float4(o[n][4 * g4], o[n][4 * g4 + 1], o[n][4 * g4 + 2], o[n][4 * g4 + 3]);
+      for (int i = 0; i < 4; ++i) {
+        float* to = &red[wave][r][8 * (4 * g + i)];
+        *reinterpret_cast<float4*>(to) = make_float4(o[0][i], o[1][i], o[2][i], o[3][i]);
+        *reinterpret_cast<float4*>(to + 4) = make_float4(o[4][i], o[5][i], o[6][i], o[7][i]);
+      }
     }
   }
-#pragma unroll
-  for (int u = 0; u < NH; ++u) {
-    const float l = wave_sum(st[u].l);
-    if (lane == 0) { ml[wave][u][0] = st[u].m; ml[wave][u][1] = l; }
+  {
+    const float l = head_sum<NH>(st.l);
+    if (lane < NH) { ml[wave][lane][0] = st.m; ml[wave][lane][1] = l; }
   }
   __syncthreads();
-  // the workgroup's partial: chunks of one partition share nothing but the maximum they are scaled to.  A wavefront
-  // without blocks has left its tile unwritten; it is skipped by its row sum of zero (with a key it is positive, or the
-  // whole partial weighs nothing).
+  // the workgroup's partial.  A wavefront without blocks has left its sums unwritten; it is skipped by its row sum of zero
+  // (with a key it is positive, or the whole chunk weighs nothing).
   for (int e = tid; e < G * kD; e += 256) {
     const int u = e >> 7, ch = e & (kD - 1);
     float m = ml[0][u][0];
@@ -344,7 +452,7 @@ __global__ void __launch_bounds__(256, 2) decode_split_values_kernel(DecodeSplit
       if (lv > 0.f) {
         const float f = fast_exp2((ml[v][u][0] - m) * c);
         l += f * lv;
-        sum += f * reinterpret_cast<const float*>(tiles + v * kTile16)[u * kD + ch];
+        sum += f * red[v][u][ch];
       }
     }
     const size_t slot = (group0 + u) * a.nparts + w.item;

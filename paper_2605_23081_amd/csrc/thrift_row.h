@@ -40,8 +40,8 @@ __device__ __forceinline__ K4Tile load_k4_rows(const unsigned char* slot, int la
   return k;
 }
 // Scores of key `lane` of the block for the wavefront's NH heads (Alg. 1 step 15 for the one-token query block).
-// qf / qsc: the fragments and scale bytes of head u in lanes r = u and r = u + 4 (heads 4-7: r = u + 4 and u + 8), zeros
-// elsewhere: accumulator register u is then row u + 4*half (u + 4 + 4*half), head u against key r.
+// qf / qsc: the fragments and scale bytes of head u in lanes r = u and r = u + 4 (u < 4), zeros elsewhere: accumulator
+// register u is then row u + 4*half, head u against key r.
 template <int NH>
 __device__ __forceinline__ void scores4_row(const K4Tile& k, int lane, const v4i (&qf)[2], uint32_t qsc, float (&sv)[NH]) {
   v16f acc[2];
@@ -116,7 +116,7 @@ __device__ __forceinline__ bool softmax_row(float sv, float c, RowState& st, flo
 // 32-63), the B-operand column of head U; what the other lanes receive belongs to no query.
 template <int U>
 __device__ __forceinline__ v4i gather_p4(float p, uint32_t pb) {
-  static_assert(U >= 0 && U < 8, "the head's column must lie in the first eight lanes");
+  static_assert(U >= 0 && U < 4, "the head's column must lie in the first four lanes");
   const float pscale = __uint_as_float(pb << 23);
   const float nb = dpp_f<kDppSwap1>(p);
   // even lanes: one byte = the codes of keys (lane, lane + 1)
