@@ -119,6 +119,7 @@ __device__ __forceinline__ float head_sum(float v) {
 template <typename T, int NH>
 __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplitArgs s) {
   const DecodeArgs& a = s.a;
+  __shared__ __align__(1024) unsigned char half_tiles[4][kTile16 / 2];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SplitWork w = split_work(s, wave);
@@ -129,7 +130,6 @@ __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplit
   const uint8_t* ksbase = a.ks + kh * a.Nkv * 4;
   const uint8_t* k16base = reinterpret_cast<const uint8_t*>(a.k16 + kh * a.Nkv * kD);
   const uint32_t k4off = (uint32_t)(64 * r + 16 * g), ksoff = (uint32_t)(4 * r + g);   // key 16t + r, channels 32g .. 32g + 31
-  const uint32_t k16off = (uint32_t)(256 * r + 16 * g);
 
   const unsigned long long bits = promoted_bits(a, group0, G, w.j0, lane);
   const int all = (1 << G) - 1;
@@ -188,36 +188,49 @@ __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplit
       }
     }
   };
+  const unsigned char* half_tile = half_tiles[wave];
+  const uint32_t lds0 = lds_address(half_tile);
   float top[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) top[i] = kEmptyMax;
   float* out = s.scores + (group0 + h0) * a.Nkv + key0;
   for (int j = w.j0; j < w.j1; ++j) {
     const int M = Mnext;
-    const Keys k = next;
-    Mnext = j + 1 < w.j1 ? promoted_mask(bits, j + 1 - w.j0) : all;
-    if (Mnext != all) next = load4(j + 1);
     float v4[NS][NV], v16[NS][NV];
     if (M != all) {
       v4f acc[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t)
-        acc[t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(widen(qf4), widen(k.k[t]), (v4f){0.f, 0.f, 0.f, 0.f}, 4, 4, 0, qsc, 0, k.ks[t]);
+        acc[t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(widen(qf4), widen(next.k[t]), (v4f){0.f, 0.f, 0.f, 0.f}, 4, 4, 0, qsc, 0, next.ks[t]);
       mine(acc, v4);
     }
+    Mnext = j + 1 < w.j1 ? promoted_mask(bits, j + 1 - w.j0) : all;
+    if (Mnext != all) next = load4(j + 1);
     if (M != 0) {
-      // rows past the cached tokens reach only their own keys' scores, which are masked below
-      const uint8_t* tile = k16base + (size_t)j * kTile16;
+      // Half a tile of 32 keys at a time through the wavefront's own LDS: a DMA instruction reads four whole rows, and only
+      // reads of whole lines may carry the streaming hint (fragments read from memory directly are 64 bytes of a line each).
+      // Rows past the cached tokens reach only their own keys' scores, which are masked below.
+      const uint8_t* tile = k16base + (size_t)__builtin_amdgcn_readfirstlane(j) * kTile16;
       v4f acc[4];
       v8s qf[4];
 #pragma unroll
       for (int s4 = 0; s4 < 4; ++s4)
         qf[s4] = qlane ? *reinterpret_cast<const v8s*>(qrow + 32 * s4 + 8 * g) : (v8s){0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        acc[t] = (v4f){0.f, 0.f, 0.f, 0.f};
+      for (int hf = 0; hf < 2; ++hf) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the reads of the half before are over
+        // row 4 q + g of the half; its chunk c stands at position c ^ (row & 7)
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) acc[t] = mfma16<T>(qf[s4], *reinterpret_cast<const v8s*>(tile + k16off + 4096 * t + 64 * s4), acc[t]);
+        for (int q = 0; q < 8; ++q)
+          dma_b128<true>(tile + 8192 * hf + 1024 * q, (uint32_t)(256 * g + 16 * (r ^ (4 * (q & 1) + g))), lds0 + 1024 * q);
+        vm_wait<0>();
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          acc[2 * hf + t] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int s4 = 0; s4 < 4; ++s4)
+            acc[2 * hf + t] = mfma16<T>(qf[s4], *reinterpret_cast<const v8s*>(half_tile + 4096 * t + 256 * r + 16 * ((4 * s4 + g) ^ (r & 7))), acc[2 * hf + t]);
+        }
       }
       mine(acc, v16);
     }
@@ -310,7 +323,7 @@ __global__ void __launch_bounds__(256, 3) decode_split_values_kernel(DecodeSplit
     auto load16 = [&](int j, int q, v4i (&row)[8]) {
       const uint8_t* tile = v16base + (size_t)j * kTile16 + 8192 * q;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) row[u] = *reinterpret_cast<const v4i*>(tile + v16off + 256 * u);
+      for (int u = 0; u < 8; ++u) row[u] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(tile + v16off + 256 * u));
     };
     // rows past the cached tokens hold whatever lies there, and zero times that need not be zero
     auto clear16 = [&](int q, v4i (&row)[8]) {
