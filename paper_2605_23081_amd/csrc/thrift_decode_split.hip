@@ -61,19 +61,20 @@ __device__ __forceinline__ SplitWork split_work(const DecodeSplitArgs& s, int wa
   return w;
 }
 
-// Which heads of the group have promoted which of the (at most 64) blocks j0 .. : lane u < G holds head u's bits, bit 0 =
+// Which heads of the group have promoted which of the (at most 32) blocks j0 .. : lane u < G holds head u's bits, bit 0 =
 // block j0.
-__device__ __forceinline__ unsigned long long promoted_bits(const DecodeArgs& a, size_t group0, int G, int j0, int lane) {
-  if (a.bitmap == nullptr || lane >= G) return 0ULL;
+static_assert(kSplitMaxChunk <= 32, "one word of bits per chunk");
+__device__ __forceinline__ uint32_t promoted_bits(const DecodeArgs& a, size_t group0, int G, int j0, int lane) {
+  if (a.bitmap == nullptr || lane >= G) return 0u;
   const unsigned long long* bm = a.bitmap + (group0 + lane) * a.bitmap_words;
   const int w = j0 >> 6, sh = j0 & 63;
   unsigned long long bits = bm[w] >> sh;
   if (sh != 0 && w + 1 < a.bitmap_words) bits |= bm[w + 1] << (64 - sh);
-  return bits;
+  return (uint32_t)bits;
 }
 // mask over the heads for block j0 + i
-__device__ __forceinline__ int promoted_mask(unsigned long long bits, int i) {
-  return (int)__builtin_amdgcn_ballot_w64(((bits >> i) & 1ULL) != 0ULL);
+__device__ __forceinline__ int promoted_mask(uint32_t bits, int i) {
+  return (int)__builtin_amdgcn_ballot_w64(((bits >> i) & 1u) != 0u);
 }
 
 template <typename T>
@@ -131,7 +132,7 @@ __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplit
   const uint8_t* k16base = reinterpret_cast<const uint8_t*>(a.k16 + kh * a.Nkv * kD);
   const uint32_t k4off = (uint32_t)(64 * r + 16 * g), ksoff = (uint32_t)(4 * r + g);   // key 16t + r, channels 32g .. 32g + 31
 
-  const unsigned long long bits = promoted_bits(a, group0, G, w.j0, lane);
+  const uint32_t bits = promoted_bits(a, group0, G, w.j0, lane);
   const int all = (1 << G) - 1;
 
   struct Keys {
@@ -241,7 +242,7 @@ __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplit
         if (h0 + i < G) {
           float v = ((M >> (h0 + i)) & 1) ? v16[q][i] : v4[q][i];
           if (key0 + 32 * q >= w.n_valid) v = -INFINITY;
-          out[(size_t)i * a.Nkv + (size_t)j * kBk + 32 * q] = v;
+          __builtin_nontemporal_store(v, out + (size_t)i * a.Nkv + (size_t)j * kBk + 32 * q);
           top[i] = fmaxf(top[i], v);
         }
   }
@@ -269,9 +270,10 @@ __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplit
 // The accumulators hold channel 8 (4 g + i) + e of head r in o[e][i]: row r of tile e is channel 8 r + e, because a lane's
 // 16 bytes of a 16-bit V row are 8 neighbouring channels, which are transposed against 8 rows inside the lane.
 template <typename T, int NH>
-__global__ void __launch_bounds__(256, 3) decode_split_values_kernel(DecodeSplitArgs s) {
+__global__ void __launch_bounds__(256, 4) decode_split_values_kernel(DecodeSplitArgs s) {
   const DecodeArgs& a = s.a;
-  __shared__ __align__(16) float red[4][NH][kD];
+  constexpr int kSlot = 4096 + 256;                            // codes and scales of a V block
+  __shared__ __align__(1024) unsigned char slots[4][2][kSlot]; // per wavefront; its partial sums at the end
   __shared__ __align__(16) uint16_t prow[4][NH * 64];          // probabilities rounded to 16 bits: [head][key]
   __shared__ __align__(16) uint8_t pcode[4][NH * 32];          // codes of P: [head][key / 2]
   __shared__ uint8_t pscale[4][NH * 2];                        // their E8M0 bytes: [head][group]
@@ -292,17 +294,30 @@ __global__ void __launch_bounds__(256, 3) decode_split_values_kernel(DecodeSplit
   for (int e = 0; e < 8; ++e) o[e] = (v4f){0.f, 0.f, 0.f, 0.f};
 
   if (w.j0 < w.j1) {
-    // scalar bases and 32-bit lane offsets
     const uint8_t* v4base = a.v4 + kh * (size_t)(a.Nkv / 64) * 4096;
     const uint8_t* vsbase = a.vs + kh * (size_t)(a.Nkv / 32) * kD;
     const uint8_t* v16base = reinterpret_cast<const uint8_t*>(a.v16 + kh * a.Nkv * kD);
-    const uint32_t v4off = (uint32_t)(r * 256 + (g & 1) * 16), vsoff = (uint32_t)((g & 1) * kD + 8 * r);   // channel 8 r, token group g
     const uint32_t v16off = (uint32_t)(2048 * g + 16 * r);
-    const float* srow = s.scores + qh * a.Nkv + NH * kg;
+    // The 4-bit tile of a block travels one block ahead of the arithmetic by LDS DMA, whole lines per instruction.  Its 256
+    // bytes of channels 8 R .. 8 R + 7 hold chunk c (channel 8 R + c / 2, token group c & 1) at position c ^ R, so that the
+    // 16 rows of a fragment lie in different banks.
+    const uint32_t lds0 = lds_address(&slots[wave][0][0]);
+    const uint32_t dma_off = (uint32_t)(256 * g + 16 * (r ^ g));              // R = 4 m + g in instruction m
+    auto issue4 = [&](int j, int slot) {
+      const int j_ = __builtin_amdgcn_readfirstlane(j);
+      const uint32_t to = lds0 + (uint32_t)(__builtin_amdgcn_readfirstlane(slot) * kSlot);
+      uint32_t off = dma_off;
+      asm volatile("" : "+v"(off));                            // one offset kept, not four
+#pragma unroll
+      for (int m = 0; m < 4; ++m) dma_b128<true>(v4base + (size_t)j_ * 4096 + 1024 * m, off ^ (64u * m), to + 1024 * m);
+      dma_b32<true>(vsbase + (size_t)j_ * 256, (uint32_t)(4 * lane), to + 4096);
+    };
+    const float* sbase = s.scores + group0 * a.Nkv;                          // scalar; the lane's head and keys in 32 bits
+    const uint32_t soff = (uint32_t)(min(h, G - 1) * a.Nkv + NH * kg);
     uint16_t* prow_w = prow[wave];
     uint8_t* pcode_w = pcode[wave];
     uint8_t* pscale_w = pscale[wave];
-    const unsigned long long bits = promoted_bits(a, group0, G, w.j0, lane);
+    const uint32_t bits = promoted_bits(a, group0, G, w.j0, lane);
     const int all = (1 << G) - 1, n_blocks = w.j1 - w.j0;
     struct Scores { float v[NH]; };
     auto load_scores = [&](int j) {
@@ -310,12 +325,12 @@ __global__ void __launch_bounds__(256, 3) decode_split_values_kernel(DecodeSplit
       if constexpr (NH >= 4) {
 #pragma unroll
         for (int u = 0; u < NH; u += 4) {
-          const float4 y = *reinterpret_cast<const float4*>(srow + (size_t)j * kBk + u);
+          const float4 y = *reinterpret_cast<const float4*>(sbase + (size_t)j * kBk + soff + u);
           x.v[u] = y.x; x.v[u + 1] = y.y; x.v[u + 2] = y.z; x.v[u + 3] = y.w;
         }
       } else {
 #pragma unroll
-        for (int u = 0; u < NH; ++u) x.v[u] = srow[(size_t)j * kBk + u];
+        for (int u = 0; u < NH; ++u) x.v[u] = (sbase + (size_t)j * kBk)[soff + u];
       }
       return x;
     };
@@ -331,6 +346,8 @@ __global__ void __launch_bounds__(256, 3) decode_split_values_kernel(DecodeSplit
       for (int u = 0; u < 8; ++u)
         if (32 * q + 8 * g + u >= w.n_valid) row[u] = (v4i){0, 0, 0, 0};
     };
+    int Mnext = promoted_mask(bits, 0);
+    if (Mnext != all) issue4(w.j0, 0);
     Scores next = load_scores(w.j0);
     // running maximum in front of the chunk
     const int ahead = w.chunk - w.first_chunk;
@@ -343,18 +360,21 @@ __global__ void __launch_bounds__(256, 3) decode_split_values_kernel(DecodeSplit
     }
     for (int i = 0; i < n_blocks; ++i) {
       const int j = w.j0 + i;
-      const int M = promoted_mask(bits, i);
-      const Scores x = next;
-      if (i + 1 < n_blocks) next = load_scores(j + 1);
-      v4i v[8];                                                // asked for here, needed after the softmax: 4-bit tile or half a 16-bit one
-      uint2 vs = make_uint2(0u, 0u);
-      if (M != all) {
+      const int M = Mnext;
+      // everything in flight was asked for a block ago: the scores of this one and its 4-bit tile.  The statements on the
+      // registers keep the compiler from waiting for the scores again behind the loads issued next.
+      vm_wait<0>();
+      Scores x = next;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = *reinterpret_cast<const v4i*>(v4base + (size_t)j * 4096 + v4off + 32 * e);
-        vs = *reinterpret_cast<const uint2*>(vsbase + (size_t)j * 256 + vsoff);
-      } else {
-        load16(j, 0, v);
+      for (int u = 0; u < NH; ++u) asm volatile("" : "+v"(x.v[u]));
+      v4i v[8];
+      if (M != 0) load16(j, 0, v);                             // needed after the softmax
+      Mnext = i + 1 < n_blocks ? promoted_mask(bits, i + 1) : all;
+      if (Mnext != all) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the reads of the slot's last block are over
+        issue4(j + 1, (i + 1) & 1);
       }
+      if (i + 1 < n_blocks) next = load_scores(j + 1);
       // ---- online softmax (Alg. 1 steps 10-12 / 16-17) of all heads ----
       float gmax = x.v[0];
 #pragma unroll
@@ -410,37 +430,46 @@ __global__ void __launch_bounds__(256, 3) decode_split_values_kernel(DecodeSplit
           pbl = pscale_w[r * 2 + g];
         }
         const v8i pq8 = widen(pq);
-#define THRIFT_PV4(E) o[E] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(widen(v[E]), pq8, o[E], 4, 4, (E) & 3, (E) < 4 ? vs.x : vs.y, 0, pbl);
+        const unsigned char* slot = slots[wave][i & 1];
+        const uint2 vs = *reinterpret_cast<const uint2*>(slot + 4096 + (g & 1) * kD + 8 * r);
+        const uint32_t frag = (uint32_t)(256 * r + 16 * (r ^ (g & 1)));     // groups 2 and 3 meet zeros of P: anything finite
+#define THRIFT_PV4(E) o[E] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(widen(*reinterpret_cast<const v4i*>(slot + (frag ^ (32u * (E))))), pq8, o[E], 4, 4, (E) & 3, (E) < 4 ? vs.x : vs.y, 0, pbl);
         THRIFT_PV4(0) THRIFT_PV4(1) THRIFT_PV4(2) THRIFT_PV4(3) THRIFT_PV4(4) THRIFT_PV4(5) THRIFT_PV4(6) THRIFT_PV4(7)
 #undef THRIFT_PV4
       }
       if (M != 0) {
+        int lane_ = lane;                                      // addresses formed here, not kept through the 4-bit blocks
+        asm volatile("" : "+v"(lane_));
+        const int r_ = lane_ & 15, g_ = lane_ >> 4;
 #pragma unroll
-        for (int u = 0; u < NH; ++u) prow_w[h * 64 + NH * kg + u] = T::from_float(p[u]);
-        const bool mine = r < G && ((M >> r) & 1) != 0;
-        if (M != all) load16(j, 0, v);
-        v4i vb[8];
-        load16(j, 1, vb);
-        if (w.n_valid != kBk) { clear16(0, v); clear16(1, vb); }
+        for (int u = 0; u < NH; ++u) prow_w[(lane_ & (NH - 1)) * 64 + NH * (lane_ / NH) + u] = T::from_float(p[u]);
+        const bool mine = r_ < G && ((M >> r_) & 1) != 0;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {                          // keys 32 q + 8 g .. + 7
-          const v8s pf = mine ? *reinterpret_cast<const v8s*>(prow_w + r * 64 + 32 * q + 8 * g) : (v8s){0, 0, 0, 0, 0, 0, 0, 0};
+          if (q == 1) {
+            __builtin_amdgcn_sched_barrier(0);                 // into the registers of the first half
+            load16(j, 1, v);
+          }
+          if (w.n_valid != kBk) clear16(q, v);
+          const v8s pf = mine ? *reinterpret_cast<const v8s*>(prow_w + r_ * 64 + 32 * q + 8 * g_) : (v8s){0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
             v4i col;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) col[u] = (int)__builtin_amdgcn_perm((uint32_t)(q ? vb : v)[2 * u + 1][e >> 1], (uint32_t)(q ? vb : v)[2 * u][e >> 1], sel);
+            for (int u = 0; u < 4; ++u) col[u] = (int)__builtin_amdgcn_perm((uint32_t)v[2 * u + 1][e >> 1], (uint32_t)v[2 * u][e >> 1], sel);
             o[e] = mfma16<T>(__builtin_bit_cast(v8s, col), pf, o[e]);
             if (e & 1) __builtin_amdgcn_sched_barrier(0);      // the transposed pieces are formed as they are used, not all ahead
           }
         }
       }
     }
+    static_assert(NH * kD * 4 <= 2 * kSlot, "the sums of a wavefront take the place of its tiles");
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (r < G) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        float* to = &red[wave][r][8 * (4 * g + i)];
+        float* to = reinterpret_cast<float*>(slots[wave][0]) + r * kD + 8 * (4 * g + i);
         *reinterpret_cast<float4*>(to) = make_float4(o[0][i], o[1][i], o[2][i], o[3][i]);
         *reinterpret_cast<float4*>(to + 4) = make_float4(o[4][i], o[5][i], o[6][i], o[7][i]);
       }
@@ -465,7 +494,7 @@ __global__ void __launch_bounds__(256, 3) decode_split_values_kernel(DecodeSplit
       if (lv > 0.f) {
         const float f = fast_exp2((ml[v][u][0] - m) * c);
         l += f * lv;
-        sum += f * red[v][u][ch];
+        sum += f * reinterpret_cast<const float*>(slots[v][0])[u * kD + ch];
       }
     }
     const size_t slot = (group0 + u) * a.nparts + w.item;
