@@ -158,6 +158,15 @@ thrift_status thrift_select_ablation(int selector, uint64_t seed, int B, int Hq,
 thrift_status thrift_quantize_mxfp4(const void* x, thrift_dtype dt, int B, int H, int N, int D, int axis,
                                     uint8_t* codes, uint8_t* scales, void* stream);
 
+/*
+ * Steps 2 and 3 of Alg. 1 for a whole prompt in one launch: thrift_block_means of q (block Bq) and k (block Bk),
+ * thrift_quantize_mxfp4 of q and k (axis 0) and v (axis 1), bit for bit, reading q and k once.
+ *   q [B,Hq,N,D], k, v [B,Hkv,N,D] 16-bit (dt); the outputs as those calls describe them.  Bq 64 or 128, Bk == 64, D == 128.
+ */
+thrift_status thrift_prefill_prepass(const void* q, const void* k, const void* v, thrift_dtype dt, int B, int Hq, int Hkv, int N, int D,
+                                     int Bq, int Bk, float* qmean, float* kmean, uint8_t* q4, uint8_t* qs, uint8_t* k4, uint8_t* ks,
+                                     uint8_t* v4, uint8_t* vs, void* stream);
+
 /* Host: bytes of workspace thrift_attn_prefill needs (may be 0; then workspace may be NULL). */
 size_t thrift_attn_prefill_workspace(int B, int Hq, int Hkv, int N, int D, int Bq, int Bk, int kmax);
 
@@ -241,7 +250,7 @@ thrift_status thrift_attn_prefill_ordered(const void* q, const void* k, const vo
 /*
  * Alg. 1 in one call, the user-level form of the paper's signature (Q, K, V, block sizes, FP16 budget in; attention
  * output out): block means of Q and K, scores and per-row TopK, MXFP4 quantisation of Q, K, V, fused attention,
- * seven launches on `stream` in that order.  The intermediate tensors live in `workspace`
+ * three launches on `stream` in that order (means and quantisation share one).  The intermediate tensors live in `workspace`
  * (thrift_attention_forward_workspace(...) bytes, 256-byte aligned, device), which may be reused by the next call
  * on the same stream.  q [B,Hq,N,D], k, v [B,Hkv,N,D] 16-bit (dt); out [B,Hq,N,D] in out_dt; lse nullable [B,Hq,N].
  * budget / fixed_k as in thrift_select_topk; tile_order as in thrift_attn_prefill_ordered (0: Alg. 1's order, 1: the

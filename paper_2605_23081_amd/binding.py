@@ -21,7 +21,7 @@ _DT = {torch.float16: F16, torch.bfloat16: BF16, torch.float32: F32}
 
 EXPORTS = (
     "thrift_status_string", "thrift_row_budget", "thrift_visible_blocks", "thrift_budget_to_global_k",
-    "thrift_select_kmax", "thrift_block_means", "thrift_select_topk", "thrift_select_topk_shared", "thrift_select_ablation", "thrift_quantize_mxfp4",
+    "thrift_select_kmax", "thrift_block_means", "thrift_select_topk", "thrift_select_topk_shared", "thrift_select_ablation", "thrift_quantize_mxfp4", "thrift_prefill_prepass",
     "thrift_attn_prefill_workspace", "thrift_attn_prefill", "thrift_attn_prefill_chunk", "thrift_attn_prefill_ordered",
     "thrift_attn_decode_workspace", "thrift_attn_decode", "thrift_attn_decode_shared", "thrift_attn_decode_static",
     "thrift_kv_cache_append", "thrift_kv_cache_append_advance",
@@ -56,6 +56,7 @@ def lib() -> C.CDLL:
         L.thrift_select_topk_shared.argtypes = L.thrift_select_topk.argtypes
         L.thrift_select_ablation.argtypes = [i, C.c_uint64, i, i, i, i, i, i, i, d, i, i, p, p, i, p]
         L.thrift_quantize_mxfp4.argtypes = [p, i, i, i, i, i, i, p, p, p]
+        L.thrift_prefill_prepass.argtypes = [p, p, p, i, i, i, i, i, i, i, i, p, p, p, p, p, p, p, p, p]
         L.thrift_attn_prefill_workspace.restype = sz
         L.thrift_attn_prefill_workspace.argtypes = [i] * 8
         L.thrift_attn_prefill.argtypes = [p, p, p, i, p, p, p, p, p, p, p, p, i, i, i, i, i, i, i, i, i, f, p, i, p, p, sz, p]
@@ -238,6 +239,24 @@ def thrift_quantize_mxfp4(x: torch.Tensor, axis: int, codes: Optional[torch.Tens
     _check(lib().thrift_quantize_mxfp4(_ptr(x), _DT[x.dtype], B, H, N, D, int(axis), _ptr(codes), _ptr(scales), _stream()),
            "thrift_quantize_mxfp4")
     return codes, scales
+
+
+def thrift_prefill_prepass(q, k, v, Bq: int, Bk: int, qmean, kmean, q4, qs, k4, ks, v4, vs) -> None:
+    """Block means of q and k and the MXFP4 codes of q, k (axis 0) and v (axis 1) in one launch, into the given tensors."""
+    for t in (q, k, v, qmean, kmean, q4, qs, k4, ks, v4, vs):
+        _dev(t)
+    B, Hq, N, D = q.shape
+    Hkv = k.shape[1]
+    Tq, Tk, Tv = -(-N // max(Bq, 1)), -(-N // max(Bk, 1)), -(-N // 64)
+    u8, f32 = torch.uint8, torch.float32
+    assert q.dtype == k.dtype == v.dtype and k.shape == v.shape == (B, Hkv, N, D), (q.dtype, k.dtype, v.dtype, k.shape, v.shape)
+    for name, t, shape, dt in (("qmean", qmean, (B, Hq, Tq, D), f32), ("kmean", kmean, (B, Hkv, Tk, D), f32),
+                               ("q4", q4, (B, Hq, N, D // 2), u8), ("qs", qs, (B, Hq, N, D // 32), u8),
+                               ("k4", k4, (B, Hkv, N, D // 2), u8), ("ks", ks, (B, Hkv, N, D // 32), u8),
+                               ("v4", v4, (B, Hkv, Tv, D, 32), u8), ("vs", vs, (B, Hkv, 2 * Tv, D), u8)):
+        assert tuple(t.shape) == shape and t.dtype == dt, (name, tuple(t.shape), shape, t.dtype)
+    _check(lib().thrift_prefill_prepass(_ptr(q), _ptr(k), _ptr(v), _DT[q.dtype], B, Hq, Hkv, N, D, Bq, Bk, _ptr(qmean), _ptr(kmean),
+                                        _ptr(q4), _ptr(qs), _ptr(k4), _ptr(ks), _ptr(v4), _ptr(vs), _stream()), "thrift_prefill_prepass")
 
 
 def thrift_attn_prefill(q, k, v, q4, qs, k4, ks, v4, vs, idx, cnt, Bq: int, Bk: int, causal: bool,
@@ -454,16 +473,19 @@ class PrefillPlan:
     def run(self, q, k, v, softmax_scale: float = 0.0, prepass: bool = True, attention: bool = True) -> torch.Tensor:
         B, Hq, Hkv, N, D, Bq, Bk, causal, budget, fixed_k = self.args
         if prepass:
-            thrift_block_means(q, Bq, out=self.qmean)
-            thrift_block_means(k, Bk, out=self.kmean)
+            if Bk == 64 and Bq in (64, 128):
+                thrift_prefill_prepass(q, k, v, Bq, Bk, self.qmean, self.kmean, self.q4, self.qs, self.k4, self.ks, self.v4, self.vs)
+            else:                                           # blocks that only the single calls take
+                thrift_block_means(q, Bq, out=self.qmean)
+                thrift_block_means(k, Bk, out=self.kmean)
+                thrift_quantize_mxfp4(q, 0, self.q4, self.qs)
+                thrift_quantize_mxfp4(k, 0, self.k4, self.ks)
+                thrift_quantize_mxfp4(v, 1, self.v4, self.vs)
             if self.selector == 0:
                 thrift_select_topk(self.qmean, self.kmean, Bq, Bk, causal, budget, fixed_k, kmax=self.kmax, idx=self.idx, cnt=self.cnt)
             else:
                 thrift_select_ablation(self.selector, self.seed, B, Hq, self.Tq, self.Tk, Bq, Bk, causal, budget, fixed_k,
                                        kmax=self.kmax, idx=self.idx, cnt=self.cnt)
-            thrift_quantize_mxfp4(q, 0, self.q4, self.qs)
-            thrift_quantize_mxfp4(k, 0, self.k4, self.ks)
-            thrift_quantize_mxfp4(v, 1, self.v4, self.vs)
         if attention:
             thrift_attn_prefill_chunk(q, k, v, self.q4, self.qs, self.k4, self.ks, self.v4, self.vs, self.idx, self.cnt, Bq, Bk,
                                       causal, 0, softmax_scale, out=self.out, tile_order=self.tile_order)

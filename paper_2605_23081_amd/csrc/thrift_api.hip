@@ -286,6 +286,20 @@ thrift_status thrift_quantize_mxfp4(const void* x, thrift_dtype dt, int B, int H
   return after_launch();
 }
 
+thrift_status thrift_prefill_prepass(const void* q, const void* k, const void* v, thrift_dtype dt, int B, int Hq, int Hkv, int N, int D,
+                                     int Bq, int Bk, float* qmean, float* kmean, uint8_t* q4, uint8_t* qs, uint8_t* k4, uint8_t* ks,
+                                     uint8_t* v4, uint8_t* vs, void* stream) {
+  if (!q || !k || !v || !qmean || !kmean || !q4 || !qs || !k4 || !ks || !v4 || !vs) return THRIFT_ERR_NULL;
+  if (!is16(dt)) return THRIFT_ERR_DTYPE;
+  if (B <= 0 || Hq <= 0 || Hkv <= 0 || N <= 0 || D != kHeadDim || Bk != kKeyBlock || (Bq != 64 && Bq != 128)) return THRIFT_ERR_SHAPE;
+  // one grid for all blocks: below 2^31 together
+  const long tq = ((long)N + Bq - 1) / Bq, tk = ((long)N + Bk - 1) / Bk;
+  if (!fits_int(B, Hq, tq) || !fits_int(B, Hkv, 2 * tk) || (long)B * Hq * tq + 2L * B * Hkv * tk > 0x7fffffffL) return THRIFT_ERR_SHAPE;
+  if (thrift_status s = check_arch()) return s;
+  launch_prepass(q, k, v, dt, (long)B * Hq, (long)B * Hkv, N, Bq, qmean, kmean, q4, qs, k4, ks, v4, vs, (hipStream_t)stream);
+  return after_launch();
+}
+
 size_t thrift_attn_prefill_workspace(int, int, int, int, int, int, int, int) { return 0; }
 
 thrift_status thrift_attn_prefill_ordered(const void* q, const void* k, const void* v, thrift_dtype dt,
@@ -502,13 +516,10 @@ thrift_status thrift_attention_forward(const void* q, const void* k, const void*
           *v4 = (uint8_t*)(ws + L.v4), *vs = (uint8_t*)(ws + L.vs);
   // every stage validates its own arguments again before it launches (the checks above cover all of them)
   thrift_status s;
-  if ((s = thrift_block_means(q, dt, B, Hq, N, D, Bq, qmean, stream)) != THRIFT_OK) return s;                 // Alg. 1 step 3
-  if ((s = thrift_block_means(k, dt, B, Hkv, N, D, Bk, kmean, stream)) != THRIFT_OK) return s;
+  if ((s = thrift_prefill_prepass(q, k, v, dt, B, Hq, Hkv, N, D, Bq, Bk, qmean, kmean, q4, qs, k4, ks, v4, vs, stream)) != THRIFT_OK)
+    return s;                                                                                                 // Alg. 1 steps 2 and 3
   if ((s = thrift_select_topk(qmean, kmean, B, Hq, Hkv, L.Tq, L.Tk, D, Bq, Bk, causal, budget, fixed_k, 0, idx, cnt, L.kmax,
                               stream)) != THRIFT_OK) return s;                                                // step 5
-  if ((s = thrift_quantize_mxfp4(q, dt, B, Hq, N, D, 0, q4, qs, stream)) != THRIFT_OK) return s;              // step 2
-  if ((s = thrift_quantize_mxfp4(k, dt, B, Hkv, N, D, 0, k4, ks, stream)) != THRIFT_OK) return s;
-  if ((s = thrift_quantize_mxfp4(v, dt, B, Hkv, N, D, 1, v4, vs, stream)) != THRIFT_OK) return s;
   return thrift_attn_prefill_ordered(q, k, v, dt, q4, qs, k4, ks, v4, vs, idx, cnt, L.kmax, B, Hq, Hkv, N, 0, N, D, Bq, Bk,   // steps 4-23
                                      causal, tile_order, softmax_scale, out, out_dt, lse, nullptr, 0, stream);
 }

@@ -123,6 +123,35 @@ __device__ __forceinline__ uint32_t quantize_group32(const uint32_t (&pair)[16],
   return sb;
 }
 
+// The same for a group spread over the four lanes of a quad, eight elements each: this lane's four code bytes; sb: the
+// group's E8M0 byte.  The quad's largest magnitude comes from two lane permutes.
+template <typename T>
+__device__ __forceinline__ uint32_t quantize_quad8(const uint32_t (&pair)[4], uint32_t& sb) {
+  uint32_t amax16 = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) amax16 = max(amax16, max(pair[u] & 0x7fffu, (pair[u] >> 16) & 0x7fffu));
+  amax16 = max(amax16, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)amax16, 0xb1, 0xf, 0xf, true));   // lane ^ 1
+  amax16 = max(amax16, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)amax16, 0x4e, 0xf, 0xf, true));   // lane ^ 2
+  const uint32_t abits = __float_as_uint(T::to_float((uint16_t)amax16));
+  sb = e8m0_from_amax_bits(abits);
+  uint32_t o = 0;
+  if (sb >= 1u || abits == 0u) {
+    const float scale = __uint_as_float(sb << 23);
+    o = T::template cvt_pk_fp4<0>(o, pair[0], scale);
+    o = T::template cvt_pk_fp4<1>(o, pair[1], scale);
+    o = T::template cvt_pk_fp4<2>(o, pair[2], scale);
+    o = T::template cvt_pk_fp4<3>(o, pair[3], scale);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float lo = T::to_float((uint16_t)(pair[u] & 0xffffu)) * 0x1p64f * 0x1p63f;
+      const float hi = T::to_float((uint16_t)(pair[u] >> 16)) * 0x1p64f * 0x1p63f;
+      o |= (e2m1_encode_sw(lo) | (e2m1_encode_sw(hi) << 4)) << (8 * u);
+    }
+  }
+  return o;
+}
+
 // ---- cross-lane ----
 
 // Value held by the lane 32 positions away (lane l <-> lane l^32).

@@ -9,6 +9,9 @@
 namespace thrift {
 
 void launch_block_means(const void* x, thrift_dtype dt, long heads, int N, int block, float* means, hipStream_t st);
+// block means of q and k, axis-0 codes of both and axis-1 codes of v [B*H, N, D] in one launch (key blocks of 64)
+void launch_prepass(const void* q, const void* k, const void* v, thrift_dtype dt, long heads_q, long heads_kv, int N, int Bq, float* qmean,
+                    float* kmean, uint8_t* q4, uint8_t* qs, uint8_t* k4, uint8_t* ks, uint8_t* v4, uint8_t* vs, hipStream_t st);
 void launch_quantize(const void* x, thrift_dtype dt, long bh, int N, int axis, uint8_t* codes, uint8_t* scales, hipStream_t st);
 
 struct SelectArgs {

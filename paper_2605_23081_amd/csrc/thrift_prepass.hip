@@ -1,6 +1,8 @@
 // Pre-pass kernels of Algorithm 1: block token means (step 3), MXFP4 quantisation (step 2) and
 // block-pair scoring + per-row TopK (step 5).  All three are streaming / latency kernels: coalesced
 // 16-byte loads, wavefront shuffles and ballots for the reductions, no matrix units.
+#include <type_traits>
+
 #include "thrift_device.h"
 #include "thrift_launch.h"
 
@@ -88,13 +90,15 @@ __global__ void __launch_bounds__(256) quantize_axis0_kernel(const uint16_t* __r
 // N need not be a multiple of 64: a head has ceil(N/64) blocks; tokens past the end count as +0 (they
 // do not change a group's largest magnitude and encode as code 0), so a short last group is quantised
 // from the tokens it has and the padded codes are zeros.
+constexpr int kAxis1Row = kD + 8;  // padded row (in 16-bit elements): keeps 16-byte alignment, spreads banks
+
 template <typename T>
-__global__ void __launch_bounds__(256) quantize_axis1_kernel(const uint16_t* __restrict__ x, uint8_t* __restrict__ codes,
-                                                             uint8_t* __restrict__ scales, int N, int blocks_per_head) {
-  constexpr int kRow = kD + 8;  // padded row (in 16-bit elements): keeps 16-byte alignment, spreads banks
-  __shared__ __align__(16) uint16_t tile[64 * kRow];
+__device__ __forceinline__ void quantize_axis1_block(const uint16_t* __restrict__ x, uint8_t* __restrict__ codes,
+                                                     uint8_t* __restrict__ scales, int N, int blocks_per_head, unsigned block,
+                                                     uint16_t* tile) {
+  constexpr int kRow = kAxis1Row;
   const int tid = threadIdx.x;
-  const int head = blockIdx.x / blocks_per_head, t = blockIdx.x % blocks_per_head;
+  const int head = block / blocks_per_head, t = block % blocks_per_head;
   const int count = min(64, N - t * 64);
   const uint16_t* src = x + ((size_t)head * N + (size_t)t * 64) * kD;
 #pragma unroll
@@ -114,8 +118,15 @@ __global__ void __launch_bounds__(256) quantize_axis1_kernel(const uint16_t* __r
   }
   uint32_t out[4];
   const uint32_t sb = quantize_group32<T>(pair, out);
-  *reinterpret_cast<uint4*>(codes + ((size_t)blockIdx.x * kD + c) * 32 + g * 16) = make_uint4(out[0], out[1], out[2], out[3]);
-  scales[((size_t)blockIdx.x * 2 + g) * kD + c] = (uint8_t)sb;
+  *reinterpret_cast<uint4*>(codes + ((size_t)block * kD + c) * 32 + g * 16) = make_uint4(out[0], out[1], out[2], out[3]);
+  scales[((size_t)block * 2 + g) * kD + c] = (uint8_t)sb;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) quantize_axis1_kernel(const uint16_t* __restrict__ x, uint8_t* __restrict__ codes,
+                                                             uint8_t* __restrict__ scales, int N, int blocks_per_head) {
+  __shared__ __align__(16) uint16_t tile[64 * kAxis1Row];
+  quantize_axis1_block<T>(x, codes, scales, N, blocks_per_head, blockIdx.x, tile);
 }
 
 void launch_quantize(const void* x, thrift_dtype dt, long bh, int N, int axis, uint8_t* codes, uint8_t* scales, hipStream_t st) {
@@ -131,6 +142,97 @@ void launch_quantize(const void* x, thrift_dtype dt, long bh, int N, int axis, u
     if (dt == THRIFT_F16) quantize_axis1_kernel<F16><<<dim3(grid), dim3(256), 0, st>>>(xs, codes, scales, N, per_head);
     else quantize_axis1_kernel<BF16><<<dim3(grid), dim3(256), 0, st>>>(xs, codes, scales, N, per_head);
   }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Steps 2 and 3 of Alg. 1 for a whole prompt in one launch: block means and axis-0 codes of Q and K from ONE read of each,
+// axis-1 codes of V.  One workgroup per query block, key block and value block.  A thread owns 8 channels of every 16th row,
+// as in block_means_kernel; the four lanes of a quad hold one 32-channel group, so a row is quantised where it was loaded
+// and 16 lanes store its 64 code bytes together.  Bound by HBM for long prompts (before: five launches, Q and K read twice),
+// by the launch for short ones.
+// ------------------------------------------------------------------------------------------------
+struct PrepassArgs {
+  const uint16_t *q, *k, *v;
+  float *qmean, *kmean;
+  uint8_t *q4, *qs, *k4, *ks, *v4, *vs;
+  int N, Bq, Tq, Tk;
+  unsigned q_blocks, k_blocks;      // B Hq Tq, B Hkv Tk (as many value blocks as key blocks)
+};
+
+template <typename T>
+__device__ __forceinline__ void means_and_codes_block(const uint16_t* __restrict__ x, float* __restrict__ means, uint8_t* __restrict__ codes,
+                                                      uint8_t* __restrict__ scales, int block, int N, int blocks_per_head, unsigned item,
+                                                      double (*part)[16][8]) {
+  const int tid = threadIdx.x;
+  const int cg = tid & 15, rs = tid >> 4;
+  const int head = item / blocks_per_head, t = item % blocks_per_head;
+  const int count = min(block, N - t * block);            // tokens of this block
+  const size_t row0 = (size_t)head * N + (size_t)t * block;
+  const uint16_t* base = x + row0 * kD + cg * 8;
+  double acc[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) acc[c] = 0.0;
+#pragma unroll 4
+  for (int r = rs; r < count; r += 16) {
+    const uint4 w = *reinterpret_cast<const uint4*>(base + (size_t)r * kD);
+    const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      acc[2 * c] += (double)T::to_float((uint16_t)(ww[c] & 0xffffu));
+      acc[2 * c + 1] += (double)T::to_float((uint16_t)(ww[c] >> 16));
+    }
+    uint32_t sb;                                          // the lanes of a quad share the row: all of them are here
+    const uint32_t code = quantize_quad8<T>(ww, sb);
+    *reinterpret_cast<uint32_t*>(codes + (row0 + r) * (kD / 2) + cg * 4) = code;
+    if ((cg & 3) == 0) scales[(row0 + r) * (kD / 32) + (cg >> 2)] = (uint8_t)sb;
+  }
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    acc[c] += __shfl_xor(acc[c], 16);
+    acc[c] += __shfl_xor(acc[c], 32);
+  }
+  const int wave = tid >> 6;
+  if ((tid & 63) < 16) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) part[wave][cg][c] = acc[c];
+  }
+  __syncthreads();
+  if (tid < kD) {
+    const int g = tid >> 3, c = tid & 7;
+    const double s = part[0][g][c] + part[1][g][c] + part[2][g][c] + part[3][g][c];
+    means[(size_t)item * kD + tid] = (float)(s / (double)count);
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) prepass_kernel(PrepassArgs p) {
+  __shared__ __align__(16) union {
+    uint16_t tile[64 * kAxis1Row];
+    double part[4][16][8];
+  } lds;
+  unsigned item = blockIdx.x;
+  if (item < p.q_blocks) {
+    means_and_codes_block<T>(p.q, p.qmean, p.q4, p.qs, p.Bq, p.N, p.Tq, item, lds.part);
+    return;
+  }
+  item -= p.q_blocks;
+  if (item < p.k_blocks) {
+    means_and_codes_block<T>(p.k, p.kmean, p.k4, p.ks, kBk, p.N, p.Tk, item, lds.part);
+    return;
+  }
+  quantize_axis1_block<T>(p.v, p.v4, p.vs, p.N, p.Tk, item - p.k_blocks, lds.tile);
+}
+
+void launch_prepass(const void* q, const void* k, const void* v, thrift_dtype dt, long heads_q, long heads_kv, int N, int Bq, float* qmean,
+                    float* kmean, uint8_t* q4, uint8_t* qs, uint8_t* k4, uint8_t* ks, uint8_t* v4, uint8_t* vs, hipStream_t st) {
+  PrepassArgs p;
+  p.q = (const uint16_t*)q; p.k = (const uint16_t*)k; p.v = (const uint16_t*)v;
+  p.qmean = qmean; p.kmean = kmean; p.q4 = q4; p.qs = qs; p.k4 = k4; p.ks = ks; p.v4 = v4; p.vs = vs;
+  p.N = N; p.Bq = Bq; p.Tq = (N + Bq - 1) / Bq; p.Tk = (N + kBk - 1) / kBk;
+  p.q_blocks = (unsigned)(heads_q * p.Tq); p.k_blocks = (unsigned)(heads_kv * p.Tk);
+  const dim3 grid(p.q_blocks + 2 * p.k_blocks);
+  if (dt == THRIFT_F16) prepass_kernel<F16><<<grid, dim3(256), 0, st>>>(p);
+  else prepass_kernel<BF16><<<grid, dim3(256), 0, st>>>(p);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -262,13 +364,13 @@ __global__ void __launch_bounds__(NW * 64) select_topk_kernel(SelectArgs p) {
           const int t1 = cg * 4 + h + 1;
           if (t1 < MAXC && (t1 >> 2) * 256 < vis_max) fetch(t1);              // uniform over the workgroup
           __syncthreads();
-          if (cg * 256 < vis) {                          // uniform over the wavefront; keys past `vis` are scored and dropped
+          auto chains = [&](auto nc) {
 #pragma unroll
             for (int d = 0; d < kQuarter; d += 4) {
               const double2 qa = *reinterpret_cast<const double2*>(&qsd[wave][h * kQuarter + d]);
               const double2 qb = *reinterpret_cast<const double2*>(&qsd[wave][h * kQuarter + d + 2]);
 #pragma unroll
-              for (int cc = 0; cc < 4; ++cc) {
+              for (int cc = 0; cc < decltype(nc)::value; ++cc) {
                 const float4 kv = *reinterpret_cast<const float4*>(&kst[(cc * 64 + lane) * kStride + d]);
                 sc[cc] = fma(qa.x, (double)kv.x, sc[cc]);
                 sc[cc] = fma(qa.y, (double)kv.y, sc[cc]);
@@ -276,7 +378,11 @@ __global__ void __launch_bounds__(NW * 64) select_topk_kernel(SelectArgs p) {
                 sc[cc] = fma(qb.y, (double)kv.w, sc[cc]);
               }
             }
-          }
+          };
+          // uniform over the wavefront; keys past `vis` are scored and dropped, chunks past it left out by pairs
+          if (cg * 256 + 128 < vis) chains(std::integral_constant<int, 4>{});
+          else if (cg * 256 + 64 < vis) chains(std::integral_constant<int, 2>{});
+          else if (cg * 256 < vis) chains(std::integral_constant<int, 1>{});
         }
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc)
@@ -333,8 +439,10 @@ __global__ void __launch_bounds__(NW * 64) select_topk_kernel(SelectArgs p) {
 void launch_select_topk(const SelectArgs& p, hipStream_t st) {
   const int G = p.shared ? 1 : p.Hq / p.Hkv;
   const int chunks = (p.Tk + 63) / 64;
-  // 16 rows per workgroup where a (b, kv head) has that many and the keys of a row fit 128 registers per lane
-  const int nw = (p.Tq * G >= 16 && chunks <= 32) ? 16 : 4;
+  // 16 rows per workgroup where the keys of a row fit 128 registers per lane and that many rows leave no CU without a
+  // workgroup: a CU works through the chains of its rows one SIMD each, so few rows are better spread (2048 tokens, one
+  // head: 18 us with 2 workgroups of 16 rows)
+  const int nw = (chunks <= 32 && (long)p.B * p.Hkv * ((p.Tq * G + 15) / 16) >= 256) ? 16 : 4;
   const int wgs_per_unit = (p.Tq * G + nw - 1) / nw;
   const dim3 grid((unsigned)((long)p.B * p.Hkv * wgs_per_unit));
   if (nw == 16) {

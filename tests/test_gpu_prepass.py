@@ -1,0 +1,46 @@
+"""The one-launch pre-pass against the single calls it stands for (which are checked against the oracle): the same bits."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,N,Bq,dtype", [
+    (1, 1, 1, 1, 64, torch.float16), (1, 2, 1, 63, 128, torch.bfloat16), (2, 3, 3, 65, 64, torch.float16),
+    (1, 4, 2, 129, 128, torch.bfloat16), (2, 2, 1, 1000, 128, torch.float16), (1, 8, 2, 2048, 64, torch.bfloat16),
+])
+def test_prepass_equals_the_single_calls(B, Hq, Hkv, N, Bq, dtype):
+    from paper_2605_23081_amd import binding as T
+    print(f"prepass B={B} Hq={Hq} Hkv={Hkv} N={N} Bq={Bq} {dtype}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    mk = lambda H: torch.randn(B, H, N, 128, generator=g, device="cuda") * torch.exp2(torch.randint(-20, 5, (B, H, N, 1), generator=g, device="cuda").float())
+    q, k, v = mk(Hq).to(dtype), mk(Hkv).to(dtype), mk(Hkv).to(dtype)
+    k[0, 0, 0] = 0.0                                         # an all-zero group
+    if dtype == torch.bfloat16:
+        q[0, 0, 0, :32] = 2.0 ** -130                        # groups below the converter's range
+    qm, km = T.thrift_block_means(q, Bq), T.thrift_block_means(k, 64)
+    want = [qm, km, *T.thrift_quantize_mxfp4(q, 0), *T.thrift_quantize_mxfp4(k, 0), *T.thrift_quantize_mxfp4(v, 1)]
+    got = [torch.full_like(t, 77) for t in want]
+    T.thrift_prefill_prepass(q, k, v, Bq, 64, *got)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("rows,Tk", [(1, 1), (5, 64), (17, 65), (16, 128), (33, 129), (15, 300)])
+def test_selection_chunks_and_row_counts(rows, Tk):
+    """Rows per workgroup and 64-key chunks per lane at the edges of the dispatch."""
+    import numpy as np
+    from oracle import thrift_oracle as oracle
+    from paper_2605_23081_amd import binding as T
+    from tests.gpu_util import check_selection, to_np
+    print(f"select rows={rows} Tk={Tk}", flush=True)
+    rng = np.random.default_rng(rows * 1000 + Tk)
+    qm = rng.standard_normal((1, 2, rows, 128), dtype=np.float32)
+    km = rng.standard_normal((1, 1, Tk, 128), dtype=np.float32)
+    for causal in (False, True):
+        if causal and rows > Tk:
+            continue
+        idx_o, cnt_o = oracle.select_topk(qm, km, 64, 64, causal, 0.3)
+        idx, cnt = T.thrift_select_topk(torch.from_numpy(qm).cuda(), torch.from_numpy(km).cuda(), 64, 64, causal, 0.3)
+        assert check_selection(to_np(idx), to_np(cnt), idx_o, cnt_o, oracle.block_scores(qm, km)) == 0
