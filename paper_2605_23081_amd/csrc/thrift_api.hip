@@ -402,8 +402,14 @@ static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void
       DecodeSplitArgs s;
       DecodeArgs& a = s.a;
       unsigned long long* bitmap = (unsigned long long*)(ws + S.bitmap);
-      const bool select = kneed > 0 || idx_out != nullptr;
-      if (select)
+      const bool select = kneed > 0 || idx_out != nullptr || cnt_out != nullptr;
+      // nobody asks for the lists and a row fits a wavefront: the scores pass selects
+      const bool in_pass = kneed > 0 && idx_out == nullptr && cnt_out == nullptr && decode_split_selects(Hq, Hkv, Tk);
+      s.keys = in_pass ? (const uint64_t*)(ws + S.keys) : nullptr;
+      s.select_out = bitmap; s.fixed_k = fixed_k; s.ppm = fixed_k >= 0 ? 0 : budget_ppm(budget);
+      if (in_pass)
+        launch_decode_block_scores((const uint16_t*)q, dt == THRIFT_BF16 ? 1 : 0, kmean, seqlens, (uint64_t*)(ws + S.keys), B, Hq, Hkv, Tk, shared, st);
+      else if (select)
         launch_decode_select((const uint16_t*)q, dt == THRIFT_BF16 ? 1 : 0, kmean, seqlens, (uint64_t*)(ws + S.keys), bitmap, S.words,
                              idx_out, cnt_out, kmax_out, B, Hq, Hkv, Tk, fixed_k, fixed_k >= 0 ? 0 : budget_ppm(budget), shared, st);
       a.q = (const uint16_t*)q; a.k16 = (const uint16_t*)k16; a.v16 = (const uint16_t*)v16;

@@ -733,13 +733,7 @@ __global__ void __launch_bounds__(256) decode_select_kernel(DecodeSelectArgs p, 
   const long row = blockIdx.x;
   const int b = (int)(row / p.Hq);
   const int vis = p.seqlens ? min(p.Tk, (max(0, p.seqlens[b]) + kBk - 1) / kBk) : p.Tk;
-  int k;
-  if (p.fixed_k >= 0) k = min(p.fixed_k, vis);
-  else if (p.ppm <= 0 || vis == 0) k = 0;
-  else {
-    long long kk = (p.ppm * (long long)vis + 999999LL) / 1000000LL;
-    k = (int)max(1LL, min(kk, (long long)vis));
-  }
+  const int k = decode_row_budget(vis, p.fixed_k, p.ppm);
   uint64_t key[MAXC];
 #pragma unroll
   for (int c = 0; c < MAXC; ++c) {
@@ -823,14 +817,20 @@ __global__ void __launch_bounds__(256) decode_select_kernel(DecodeSelectArgs p, 
   if (out) for (int t = k + tid; t < p.kmax_out; t += 256) out[t] = -1;
 }
 
-void launch_decode_select(const uint16_t* q16, int q_is_bf16, const float* kmean, const int32_t* seqlens, uint64_t* keys,
-                          unsigned long long* bitmap, int words, int32_t* idx_out, int32_t* cnt_out, int kmax_out,
-                          int B, int Hq, int Hkv, int Tk, int fixed_k, long long ppm, int shared, hipStream_t st) {
+void launch_decode_block_scores(const uint16_t* q16, int q_is_bf16, const float* kmean, const int32_t* seqlens, uint64_t* keys,
+                                int B, int Hq, int Hkv, int Tk, int shared, hipStream_t st) {
   const int chunks = (Tk + 63) / 64;
   int per_wg = kScoreChunksPerWg;
   while (per_wg > 1 && (long)B * Hkv * ((chunks + per_wg - 1) / per_wg) < 512) per_wg /= 2;
   const int score_groups = (chunks + per_wg - 1) / per_wg;
   decode_scores_kernel<<<dim3((unsigned)((long)B * Hkv * score_groups)), dim3(256), 0, st>>>(q16, q_is_bf16, kmean, seqlens, keys, Hq, Hkv, Tk, shared, per_wg);
+}
+
+void launch_decode_select(const uint16_t* q16, int q_is_bf16, const float* kmean, const int32_t* seqlens, uint64_t* keys,
+                          unsigned long long* bitmap, int words, int32_t* idx_out, int32_t* cnt_out, int kmax_out,
+                          int B, int Hq, int Hkv, int Tk, int fixed_k, long long ppm, int shared, hipStream_t st) {
+  launch_decode_block_scores(q16, q_is_bf16, kmean, seqlens, keys, B, Hq, Hkv, Tk, shared, st);
+  const int chunks = (Tk + 63) / 64;
   DecodeSelectArgs p;
   p.keys = keys; p.seqlens = seqlens; p.bitmap = bitmap; p.idx_out = idx_out; p.cnt_out = cnt_out;
   p.Hq = Hq; p.Tk = Tk; p.words = words; p.kmax_out = kmax_out; p.fixed_k = fixed_k; p.ppm = ppm;

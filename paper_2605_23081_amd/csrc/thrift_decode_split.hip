@@ -116,15 +116,79 @@ __device__ __forceinline__ float head_sum(float v) {
   return v + other_half(v);
 }
 
-// NH: heads per KV group, rounded up to 1, 2, 4 or 8
-template <typename T, int NH>
+// TopK of one row of at most 64 MAXC order keys by one wavefront: word c of the bitmap to out[c].  The k-th largest key is
+// searched bit by bit from the top, a step being a comparison and a scalar count per 64 keys: no barrier and no LDS, which
+// is what a step of the kernel of its own (decode_select_kernel) waits for.  Ties go to the smaller block id.
+template <int MAXC>
+__device__ __forceinline__ void wave_select(const uint64_t* keys, int vis, int k, int lane, unsigned long long* out) {
+  uint64_t key[MAXC];
+#pragma unroll
+  for (int c = 0; c < MAXC; ++c) key[c] = c * 64 + lane < vis ? keys[c * 64 + lane] : 0ULL;   // a key is never 0
+  uint64_t T = 0;
+  if (k < vis) {
+    // the upper words alone separate the keys but for a step or two: 32-bit comparisons, none above the largest key
+    uint32_t hi[MAXC], top = 0;
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c) {
+      hi[c] = (uint32_t)(key[c] >> 32);
+      top = max(top, hi[c]);
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) top = max(top, (uint32_t)__shfl_xor((int)top, d));
+    top = __builtin_amdgcn_readfirstlane(top);
+    uint32_t t = 0;
+    int n = 0;
+    for (int bit = 31; bit >= 0; --bit) {
+      const uint32_t cand = t | (1u << bit);
+      if (cand > top) continue;                            // no key
+      n = 0;
+#pragma unroll
+      for (int c = 0; c < MAXC; ++c)
+        if (c * 64 < vis) n += __popcll(__ballot(hi[c] >= cand));
+      if (n >= k) t = cand;
+      if (n == k) break;                                   // exactly the k largest lie at or above cand
+    }
+    T = (uint64_t)t << 32;
+    if (n != k)
+      for (int bit = 31; bit >= 0; --bit) {
+        const uint64_t cand = T | (1ULL << bit);
+        n = 0;
+#pragma unroll
+        for (int c = 0; c < MAXC; ++c)
+          if (c * 64 < vis) n += __popcll(__ballot(key[c] >= cand));
+        if (n >= k) T = cand;
+        if (n == k) break;
+      }
+  }
+  int n_gt = 0;
+#pragma unroll
+  for (int c = 0; c < MAXC; ++c)
+    if (c * 64 < vis) n_gt += __popcll(__ballot(key[c] > T));
+  const int need = k - n_gt;                               // keys equal to T that are taken
+  int seen = 0;
+  const uint64_t below = (1ULL << lane) - 1ULL;
+#pragma unroll
+  for (int c = 0; c < MAXC; ++c) {
+    const bool tie = c * 64 + lane < vis && key[c] == T;
+    const uint64_t ties = __ballot(tie);
+    const uint64_t sel = __ballot(key[c] > T || (tie && seen + __popcll(ties & below) < need));
+    seen += __popcll(ties);
+    if (lane == 0) out[c] = sel;
+  }
+}
+
+// NH: heads per KV group, rounded up to 1, 2, 4 or 8.  SELECT: the promoted blocks come from the order keys, selected by every
+// workgroup for itself (one row per wavefront) while its first tile is on its way; the first workgroup of a (sequence, KV head)
+// leaves the bitmap for the pass behind.  A step of a serving loop, with and without a launch for the selection: 26.2 / 28.8 us
+// (1 x 4096 tokens, 32/8 heads), 40.4 / 41.9 us (1 x 32768), 52.8 / 56.1 us (16 x 8192), 176.4 / 178.1 us (16 x 32768).
+template <typename T, int NH, bool SELECT>
 __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplitArgs s) {
   const DecodeArgs& a = s.a;
   __shared__ __align__(1024) unsigned char half_tiles[4][kTile16 / 2];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SplitWork w = split_work(s, wave);
-  if (w.j0 >= w.j1) return;
+  if (SELECT ? !w.any && w.item != 0 : w.j0 >= w.j1) return;       // uniform over the workgroup where there is a barrier below
   const int G = a.Hq / a.Hkv;
   const size_t group0 = (size_t)w.b * a.Hq + (size_t)w.kvh * G, kh = (size_t)w.b * a.Hkv + w.kvh;
   const uint8_t* k4base = a.k4 + kh * a.Nkv * 64;
@@ -132,7 +196,6 @@ __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplit
   const uint8_t* k16base = reinterpret_cast<const uint8_t*>(a.k16 + kh * a.Nkv * kD);
   const uint32_t k4off = (uint32_t)(64 * r + 16 * g), ksoff = (uint32_t)(4 * r + g);   // key 16t + r, channels 32g .. 32g + 31
 
-  const uint32_t bits = promoted_bits(a, group0, G, w.j0, lane);
   const int all = (1 << G) - 1;
 
   struct Keys {
@@ -150,8 +213,34 @@ __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplit
   };
   // a block that every head takes in 16 bits is not read in 4
   Keys next;
-  int Mnext = promoted_mask(bits, 0);
-  if (Mnext != all) next = load4(w.j0);
+  uint32_t bits;
+  int Mnext;
+  if constexpr (SELECT) {
+    static_assert(NH <= 4, "a row per wavefront");
+    __shared__ unsigned long long sel[NH][kSplitSelectBlocks / 64];
+    const int vis = a.seqlens ? (min(a.Nkv, max(0, a.seqlens[w.b])) + kBk - 1) / kBk : a.Nkv / kBk;
+    const int k = decode_row_budget(vis, s.fixed_k, s.ppm);
+    if (w.j0 < w.j1 && k < vis) next = load4(w.j0);
+    if (wave < G) wave_select<kSplitSelectBlocks / 64>(s.keys + (group0 + wave) * (a.Nkv / kBk), vis, k, lane, sel[wave]);
+    __syncthreads();
+    if (w.item == 0 && tid < NH * (kSplitSelectBlocks / 64)) {
+      const int u = tid / (kSplitSelectBlocks / 64), word = tid % (kSplitSelectBlocks / 64);
+      if (u < G && word < a.bitmap_words) s.select_out[(group0 + u) * a.bitmap_words + word] = sel[u][word];
+    }
+    if (w.j0 >= w.j1) return;
+    bits = 0u;
+    if (lane < G) {
+      const int word = w.j0 >> 6, sh = w.j0 & 63;
+      unsigned long long x = sel[lane][word] >> sh;
+      if (sh != 0 && word + 1 < kSplitSelectBlocks / 64) x |= sel[lane][word + 1] << (64 - sh);
+      bits = (uint32_t)x;
+    }
+    Mnext = promoted_mask(bits, 0);
+  } else {
+    bits = promoted_bits(a, group0, G, w.j0, lane);
+    Mnext = promoted_mask(bits, 0);
+    if (Mnext != all) next = load4(w.j0);
+  }
 
   // the query rows as A operand: head r % NR in row r, so that every lane's accumulator registers i are heads
   // (4 g + i) % NR; the lane quantises the MXFP4 group it carries
@@ -560,6 +649,9 @@ bool decode_split_wanted(int B, int Hq, int Hkv, int Tk, int nsplit, int split_b
   return (long)B * Hkv * nsplit <= kSplitMaxItems;
 }
 
+// With more heads a wavefront would select two rows one after the other: 58.6 us against 57.5 us for 2 x 20480 tokens, 64/8 heads.
+bool decode_split_selects(int Hq, int Hkv, int Tk) { return Hq / Hkv <= 4 && Tk <= kSplitSelectBlocks; }
+
 // key blocks per wavefront: as few as leave about eight wavefronts per CU
 int decode_split_chunk(int B, int Hkv, int Tk) {
   const long blocks = (long)B * Hkv * Tk;
@@ -574,7 +666,8 @@ void launch_decode_split(const DecodeSplitArgs& s, hipStream_t st) {
   const int G = a.Hq / a.Hkv;
 #define THRIFT_SPLIT(T, NH)                                            \
   do {                                                                 \
-    decode_split_scores_kernel<T, NH><<<grid, block, 0, st>>>(s);      \
+    if (s.keys != nullptr) decode_split_scores_kernel<T, NH, (NH <= 4)><<<grid, block, 0, st>>>(s);  \
+    else decode_split_scores_kernel<T, NH, false><<<grid, block, 0, st>>>(s);                        \
     decode_split_values_kernel<T, NH><<<grid, block, 0, st>>>(s);      \
   } while (0)
 #define THRIFT_SPLIT_T(T)                  \

@@ -81,7 +81,15 @@ struct DecodeSplitArgs {
   int nsub;               // workgroups (of four chunks) per partition
   int chunks;             // nsplit * nsub * 4
   int items;              // workgroups per (sequence, KV head): nsplit * nsub, + 1 where lengths can leave a block partly filled
+  const uint64_t* keys;   // nullable [B,Hq,Nkv/64]: order keys of the block scores; the scores pass then selects and writes `select_out`
+  unsigned long long* select_out;     // = a.bitmap
+  int fixed_k;            // the budget of that selection, as in SelectArgs
+  long long ppm;
 };
+// Key blocks up to which the scores pass selects for itself: a row is eight keys per lane of one wavefront.  Every workgroup
+// repeats the selection of its KV group, 1-2 us next to the 4-6 us of a launch of its own.
+constexpr int kSplitSelectBlocks = 512;
+bool decode_split_selects(int Hq, int Hkv, int Tk);
 constexpr int kSplitMaxItems = 320;   // partitions up to which the two passes are faster than one walk of a workgroup each
 constexpr int kSplitMaxChunk = 8;
 bool decode_split_wanted(int B, int Hq, int Hkv, int Tk, int nsplit, int split_blocks);
@@ -89,6 +97,8 @@ int decode_split_chunk(int B, int Hkv, int Tk);
 void launch_decode_split(const DecodeSplitArgs& s, hipStream_t st);
 // decode-time selection: scores of the cached key-block means against the query heads, then per-row TopK
 // as a bitmap ([B*Hq][words], bit j%64 of word j/64) and optionally as ascending id lists
+void launch_decode_block_scores(const uint16_t* q16, int q_is_bf16, const float* kmean, const int32_t* seqlens, uint64_t* keys,
+                                int B, int Hq, int Hkv, int Tk, int shared, hipStream_t st);
 void launch_decode_select(const uint16_t* q16, int q_is_bf16, const float* kmean, const int32_t* seqlens, uint64_t* keys,
                           unsigned long long* bitmap, int words, int32_t* idx_out, int32_t* cnt_out, int kmax_out,
                           int B, int Hq, int Hkv, int Tk, int fixed_k, long long ppm, int shared, hipStream_t st);

@@ -161,4 +161,12 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x + other_half(x);
 }
 
+// Blocks that a decode row of `vis` key blocks promotes.
+__device__ __forceinline__ int decode_row_budget(int vis, int fixed_k, long long ppm) {
+  if (fixed_k >= 0) return min(fixed_k, vis);
+  if (ppm <= 0 || vis == 0) return 0;
+  const long long k = (ppm * (long long)vis + 999999LL) / 1000000LL;
+  return (int)max(1LL, min(k, (long long)vis));
+}
+
 }  // namespace thrift

@@ -71,3 +71,32 @@ def test_two_pass_decode_matches_the_oracle(T, Hq, Hkv, B, N, split, lens, budge
     lens = None if lens is None else [n // 64 * 64 for n in lens]            # the helper's selection takes whole blocks
     got, want, swaps = _decode_case(T, oracle, wl, budget, split, lens)
     assert swaps == 0 and np.abs(got - want).max() <= TOLMIX
+
+
+@pytest.mark.parametrize("Hq,Hkv,B,N,lens,budget,fixed_k,shared,ties", [
+    (4, 1, 1, 64, None, 0.05, -1, False, False),                              # one key block
+    (8, 2, 3, 4096, [4096, 1, 0], 0.05, -1, False, False),                    # a full row, one token, none
+    (6, 2, 2, 4160, [4159, 4097], 0.25, -1, False, False),                    # three rows; one block past the first word
+    (2, 2, 2, 32768, [32768, 32705], 0.1, -1, False, False),                  # all eight words; a partly filled last block
+    (8, 2, 1, 8192, [8191], 1.0, -1, False, False),                           # every block
+    (8, 2, 2, 8192, [8000, 130], 0.0, 7, False, False),                       # a fixed count, more than the second row has
+    (8, 2, 2, 16384, [16384, 9001], 0.05, -1, True, False),                   # one set per KV head
+    (4, 1, 1, 8192, None, 0.1, -1, False, True),                              # equal keys: the smaller ids
+])
+def test_selection_inside_the_scores_pass(T, Hq, Hkv, B, N, lens, budget, fixed_k, shared, ties):
+    """Without lists to write, the scores pass selects for itself; the kernel that writes the lists selects the same blocks:
+    equal bits of the results."""
+    print(f"decode selection in the pass Hq={Hq} Hkv={Hkv} B={B} N={N} lens={lens} f={budget} k={fixed_k} {shared} {ties}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv)
+    args = list(_cache(T, wl))
+    if ties:
+        args[7] = args[7][:, :, :1].expand_as(args[7]).contiguous()
+    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+    ws = torch.full((T.decode_workspace_bytes(B, Hq, Hkv, N, wl.D, 64, 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    kw = dict(fixed_k=fixed_k, seqlens=sl, workspace=ws, group_shared=shared)
+    want, _, _ = T.thrift_attn_decode(*args, 64, budget, out_dtype=torch.float32, return_selection=True, **kw)
+    for _ in range(2):
+        ws.fill_(0xFF)
+        out = torch.empty_like(want)
+        T.thrift_attn_decode(*args, 64, budget, out=out, **kw)
+        assert torch.equal(out, want)
