@@ -69,6 +69,12 @@ PyObject* answer(thrift_status s, const Tensor& out) {
   if (s != THRIFT_OK) return PyLong_FromLong((long)s);
   return THPVariable_Wrap(out);
 }
+// The interpreter lock, given up while this lives; also taken back when an exception passes (a tensor without storage has no
+// data pointer).
+struct Unlocked {
+  PyThreadState* state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
 Tensor bytes_like(const Tensor& t, size_t n) { return at::empty({(int64_t)std::max<size_t>(n, 256)}, t.options().dtype(at::kByte)); }
 
 // the tensors of a cache: k16 v16 k4 ks v4 vs kmean
@@ -105,22 +111,19 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (!is(*q, c.k16->scalar_type(), {c.B, Hq, c.D}) || (seqlens && !is(*seqlens, at::kInt, {c.B})) ||
       (out_given && !is(*out_given, out_given->scalar_type(), {c.B, Hq, c.D})))
     Py_RETURN_NONE;
-  try {
-    const Tensor out = out_given ? *out_given : at::empty({c.B, Hq, c.D}, q->options());
-    if (!dtype_out(out, &odt)) Py_RETURN_NONE;
-    const Tensor ws = ws_given ? *ws_given : bytes_like(*q, thrift_attn_decode_workspace(c.B, Hq, c.Hkv, c.N, c.D, Bk, split));
-    const size_t ws_bytes = (size_t)ws.numel();
-    thrift_status s;
-    Py_BEGIN_ALLOW_THREADS
+  const Tensor out = out_given ? *out_given : at::empty({c.B, Hq, c.D}, q->options());
+  if (!dtype_out(out, &odt)) Py_RETURN_NONE;
+  const Tensor ws = ws_given ? *ws_given : bytes_like(*q, thrift_attn_decode_workspace(c.B, Hq, c.Hkv, c.N, c.D, Bk, split));
+  const size_t ws_bytes = (size_t)ws.numel();
+  thrift_status s;
+  {
+    const Unlocked unlocked;
     s = (shared ? thrift_attn_decode_shared : thrift_attn_decode)(
         ptr(q), c.dt, ptr(c.k16), ptr(c.v16), ptr_as<uint8_t>(c.k4), ptr_as<uint8_t>(c.ks), ptr_as<uint8_t>(c.v4), ptr_as<uint8_t>(c.vs),
         ptr_as<float>(c.kmean), ptr_as<int32_t>(seqlens), c.B, Hq, c.Hkv, c.N, c.D, Bk, budget, fixed_k, split, (float)scale,
         out.data_ptr(), odt, nullptr, nullptr, 0, ws.data_ptr(), ws_bytes, stream);
-    Py_END_ALLOW_THREADS
-    return answer(s, out);
-  } catch (const std::exception&) {
-    Py_RETURN_NONE;
   }
+  return answer(s, out);
 }
 
 // append(k_new, v_new, seqlens, new_lens, k16, v16, k4, ks, v4, vs, kmean, Bk, stream): the lengths after the call
@@ -137,18 +140,15 @@ PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (!is(*k_new, st, {c.B, c.Hkv, n_new, c.D}) || !is(*v_new, st, {c.B, c.Hkv, n_new, c.D}) || !is(*seqlens, at::kInt, {c.B}) ||
       (new_lens && !is(*new_lens, at::kInt, {c.B})))
     Py_RETURN_NONE;
-  try {
-    const Tensor after = at::empty({c.B}, seqlens->options());
-    thrift_status s;
-    Py_BEGIN_ALLOW_THREADS
+  const Tensor after = at::empty({c.B}, seqlens->options());
+  thrift_status s;
+  {
+    const Unlocked unlocked;
     s = thrift_kv_cache_append_advance(ptr(k_new), ptr(v_new), c.dt, n_new, ptr_as<int32_t>(seqlens), ptr_as<int32_t>(new_lens),
                                        after.data_ptr<int32_t>(), ptr(c.k16), ptr(c.v16), ptr_as<uint8_t>(c.k4), ptr_as<uint8_t>(c.ks),
                                        ptr_as<uint8_t>(c.v4), ptr_as<uint8_t>(c.vs), ptr_as<float>(c.kmean), c.B, c.Hkv, c.N, c.D, Bk, stream);
-    Py_END_ALLOW_THREADS
-    return answer(s, after);
-  } catch (const std::exception&) {
-    Py_RETURN_NONE;
   }
+  return answer(s, after);
 }
 
 // attention(q, k, v, causal, Bq, Bk, budget, fixed_k, scale, workspace, out, lse, tile_order, stream)
@@ -171,28 +171,36 @@ PyObject* attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if ((out_given && !is(*out_given, out_given->scalar_type(), {s[0], s[1], s[2], s[3]})) || (lse && !is(*lse, at::kFloat, {s[0], s[1], s[2]})) ||
       (ws_given && ws_given->scalar_type() != at::kByte))
     Py_RETURN_NONE;
-  try {
-    const Tensor out = out_given ? *out_given : at::empty(s, q->options());
-    if (!dtype_out(out, &odt)) Py_RETURN_NONE;
-    const int B = (int)s[0], Hq = (int)s[1], N = (int)s[2], D = (int)s[3];
-    const Tensor ws = ws_given ? *ws_given
-                               : bytes_like(*q, thrift_attention_forward_workspace(B, Hq, (int)Hkv, N, D, Bq, Bk, causal, budget, fixed_k));
-    const size_t ws_bytes = (size_t)ws.numel();
-    thrift_status st;
-    Py_BEGIN_ALLOW_THREADS
+  const Tensor out = out_given ? *out_given : at::empty(s, q->options());
+  if (!dtype_out(out, &odt)) Py_RETURN_NONE;
+  const int B = (int)s[0], Hq = (int)s[1], N = (int)s[2], D = (int)s[3];
+  const Tensor ws = ws_given ? *ws_given
+                             : bytes_like(*q, thrift_attention_forward_workspace(B, Hq, (int)Hkv, N, D, Bq, Bk, causal, budget, fixed_k));
+  const size_t ws_bytes = (size_t)ws.numel();
+  thrift_status st;
+  {
+    const Unlocked unlocked;
     st = thrift_attention_forward(ptr(q), ptr(k), ptr(v), dt, B, Hq, (int)Hkv, N, D, Bq, Bk, causal, budget, fixed_k, order, (float)scale,
                                   out.data_ptr(), odt, ptr_as<float>(lse), ws.data_ptr(), ws_bytes, stream);
-    Py_END_ALLOW_THREADS
-    return answer(st, out);
+  }
+  return answer(st, out);
+}
+
+// A tensor whose sizes or storage cannot be asked for (a fake one, one under a transform) throws: not a plain argument.
+template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n) {
+  try {
+    return F(self, a, n);
   } catch (const std::exception&) {
+    PyErr_Clear();
     Py_RETURN_NONE;
   }
 }
 
 PyMethodDef methods[] = {
-    {"decode", (PyCFunction)(void (*)(void))decode, METH_FASTCALL, nullptr},
-    {"append", (PyCFunction)(void (*)(void))append, METH_FASTCALL, nullptr},
-    {"attention", (PyCFunction)(void (*)(void))attention, METH_FASTCALL, nullptr},
+    {"decode", (PyCFunction)(void (*)(void))guarded<decode>, METH_FASTCALL, nullptr},
+    {"append", (PyCFunction)(void (*)(void))guarded<append>, METH_FASTCALL, nullptr},
+    {"attention", (PyCFunction)(void (*)(void))guarded<attention>, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -24,6 +24,26 @@ def test_other_devices_and_kinds_of_arguments_are_left_to_the_general_path():
         T.thrift_attn_decode(*a, 64, 0.05)
 
 
+def test_tensors_without_storage_are_left_to_the_general_path():
+    """Under a transform a tensor has sizes but no data pointer; refusing it must not end the process."""
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    m = T._native()
+    with FakeTensorMode():
+        a = _args("cuda")                                    # device tensors in a process without a device
+        lens = torch.zeros(1, dtype=torch.int32, device="cuda")
+        ws = torch.zeros(1 << 20, dtype=torch.uint8, device="cuda")
+    seen = []
+
+    def served(q, k):
+        seen.append(m.decode(q, *a[1:], 64, 0.05, -1, 256, 0.0, lens, a[0], ws, 0, 0))
+        seen.append(m.append(k, a[1], lens, None, *a[1:], 64, 0))
+        seen.append(m.attention(k, a[1], a[1], 1, 128, 64, 0.05, -1, 0.0, ws, a[1], None, 0, 0))
+        return q
+
+    torch.vmap(served)(a[0].unsqueeze(0), a[1].unsqueeze(0))
+    assert seen == [None] * 3
+
+
 @pytest.mark.gpu
 def test_device_tensors_of_wrong_shape_or_type_raise_as_before():
     a = _args("cuda")
