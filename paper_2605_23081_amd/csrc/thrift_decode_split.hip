@@ -570,7 +570,8 @@ __global__ void __launch_bounds__(256, 4) decode_split_values_kernel(DecodeSplit
   }
   __syncthreads();
   // the workgroup's partial.  A wavefront without blocks has left its sums unwritten; it is skipped by its row sum of zero
-  // (with a key it is positive, or the whole chunk weighs nothing).
+  // (with a key it is positive, or the whole chunk weighs nothing, or it is NaN and has to reach the result: bits are
+  // compared, because comparisons of numbers are compiled as if there were no NaN).
   for (int e = tid; e < G * kD; e += 256) {
     const int u = e >> 7, ch = e & (kD - 1);
     float m = ml[0][u][0];
@@ -580,7 +581,7 @@ __global__ void __launch_bounds__(256, 4) decode_split_values_kernel(DecodeSplit
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const float lv = ml[v][u][1];
-      if (lv > 0.f) {
+      if (__float_as_uint(lv) != 0u) {
         const float f = fast_exp2((ml[v][u][0] - m) * c);
         l += f * lv;
         sum += f * reinterpret_cast<const float*>(slots[v][0])[u * kD + ch];

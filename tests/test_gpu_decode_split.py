@@ -100,3 +100,21 @@ def test_selection_inside_the_scores_pass(T, Hq, Hkv, B, N, lens, budget, fixed_
         out = torch.empty_like(want)
         T.thrift_attn_decode(*args, 64, budget, out=out, **kw)
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (2, 2)])
+def test_a_key_of_nan_reaches_the_results_it_reaches_in_one_pass(T, Hq, Hkv):
+    """Its row sums are NaN, in whichever chunk it lies, and what they divide is not a result of the other chunks alone."""
+    print(f"decode split NaN Hq={Hq} Hkv={Hkv}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=2, N=4096, Hq=Hq, Hkv=Hkv)
+    q, k, v = W.make_decode(wl, device="cuda")
+    k[0, 1, 1000] = float("nan")
+    k4, ks = T.thrift_quantize_mxfp4(k, 0)
+    v4, vs = T.thrift_quantize_mxfp4(v, 1)
+    args = (q, k, v, k4, ks, v4, vs, T.thrift_block_means(k, 64))
+    need = T.decode_workspace_bytes(2, Hq, Hkv, 4096, wl.D, 64, 256)
+    for budget in (0.0, 0.25, 1.0):
+        two, one = (T.thrift_attn_decode(*args, 64, budget, out_dtype=torch.float32, return_selection=True,
+                                         workspace=torch.zeros(n, dtype=torch.uint8, device="cuda"))[0] for n in (need, need - 256))
+        assert torch.equal(torch.isnan(two), torch.isnan(one))
+        assert float(torch.nan_to_num(two - one).norm() / torch.nan_to_num(one).norm()) <= REL
