@@ -644,10 +644,15 @@ __global__ void __launch_bounds__(256) decode_split_merge_kernel(DecodeSplitArgs
 // The split is used where the walk over whole partitions leaves the chip idle.  A walk takes its 256 key blocks one after
 // the other whatever else runs, so with fewer workgroups than the CUs take at once (two each) its time does not shrink.
 // Groups of more than 8 heads do not fit the row layout.  Partitions of at most 16 blocks are short walks already.
-bool decode_split_wanted(int B, int Hq, int Hkv, int Tk, int nsplit, int split_blocks) {
+// Above kSplitMaxItems the walk is the faster one (32/8 heads at 5 %, walk / two passes: 315 / 322 us for 6 x 131072 tokens,
+// 353 / 418 us for 8, 681 / 804 us for 16; 16/8 heads, 16 x 65536: 282 / 321 us), but for one query head per KV head in a
+// cache of one or two partitions that has lengths: three of a walk's four wavefronts have no head there, its partitions are
+// seldom full, and the scores cost 8 bytes a token.  A serving step with 16/16 heads: 242 / 220 us (16 x 32768 tokens, 5 %),
+// 344 / 300 us (25 %), 727 / 586 us (100 %), 255 / 167 us (14 x 24576, 10 %); without lengths 249 / 266 us (8 x 65536, 5 %).
+bool decode_split_wanted(int B, int Hq, int Hkv, int Tk, int nsplit, int split_blocks, bool lengths) {
   if (Hq / Hkv > 8) return false;
   if (nsplit > 1 && split_blocks <= 16) return false;
-  return (long)B * Hkv * nsplit <= kSplitMaxItems;
+  return (long)B * Hkv * nsplit <= (lengths && Hq == Hkv && nsplit <= 2 ? kSplitMaxItemsOneHead : kSplitMaxItems);
 }
 
 // With more heads a wavefront would select two rows one after the other: 58.6 us against 57.5 us for 2 x 20480 tokens, 64/8 heads.

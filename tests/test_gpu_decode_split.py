@@ -41,6 +41,8 @@ def _cache(T, wl):
     (32, 8, 2, 16384, 100, [16384, 9000], 0.05),                             # 2 key blocks per wavefront
     (8, 8, 2, 65536, 256, [65535, 40001], 0.05),                             # 4
     (16, 8, 2, 131072, 250, [131072, 70000], 0.25),                          # 8
+    (16, 16, 11, 2176, 17, [2176 - 197 * b for b in range(11)], 0.25),       # one head per KV head: 352 partitions
+    (16, 16, 16, 2176, 17, [2175] * 16, 0.05),                               # 512, the most
 ])
 def test_two_pass_decode_equals_one_pass(T, Hq, Hkv, B, N, split, lens, budget):
     print(f"decode split Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} lens={lens} budget={budget}", flush=True)
