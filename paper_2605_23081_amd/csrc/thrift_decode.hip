@@ -609,10 +609,10 @@ __global__ void __launch_bounds__(64) decode_tail_kernel(DecodeArgs a) {
 // ------------------------------------------------------------------------------------------------
 // Decode-time block selection (Alg. 1 step 5 for one-token query blocks).  Two kernels, so that the
 // whole chip works on the B*Hq short rows:
-//   decode_scores_kernel  one workgroup per (sequence, KV head, 256 key blocks): stages the cached
+//   decode_scores_kernel  one workgroup per (sequence, KV head, 64 to 512 key blocks): stages the cached
 //                         key-block means 64 at a time and scores them against the G query heads of the group
 //                         (fp64, channels in ascending order), storing order-preserving 64-bit keys;
-//   decode_select_kernel  one wavefront per (sequence, query head): finds the k-th largest key by a
+//   decode_select_kernel  one workgroup per (sequence, query head): finds the k-th largest key by a
 //                         bitwise search with ballot counting and writes the selection as a bitmap
 //                         (and, on request, as an ascending id list).
 // ------------------------------------------------------------------------------------------------

@@ -7,12 +7,12 @@
 //                               front of it in the partition: the running maximum of every block, hence every code of P, is
 //                               the one of the serial walk.
 // A chunk is `cw` key blocks and belongs to ONE wavefront, which takes all heads of the KV group at once (a row or
-// column of the matrix tiles each: up to 8 heads cost the matrix instructions of one), operands
-// straight from global memory: no barrier and no LDS on the 4-bit path.  Four chunks that follow each other make a workgroup,
+// column of the matrix tiles each: up to 8 heads cost the matrix instructions of one), with tiles in its own LDS and no
+// barrier between its blocks.  Four chunks that follow each other make a workgroup,
 // whose partials are added up in LDS before they are written.
-// Measured against the walk (attention kernels alone): 14 + 15 us against 250 us for one sequence of 32768 tokens and 32/8
-// heads, 39 + 28 us against 259 us at 131072 tokens, 147 + 94 us against 472 us for eight sequences of 16384-32768 tokens
-// and 64/8 heads at a 10 % budget.
+// Measured against the walk, whole calls or serving steps: 296 -> 74 us for one sequence of 131072 tokens and 32/8 heads,
+// 303 -> 43 us for one of 32768, 552 -> 191 us for eight of 16384-32768 tokens and 64/8 heads at a 10 % budget (scores pass
+// 70 us, values pass 76 us).
 // What bounds it: for short caches the latency of the chain of launches; for long ones HBM (the scores travel through
 // memory once more, 8 bytes per head and token next to 136 bytes of codes and scales per token).
 #include <type_traits>
