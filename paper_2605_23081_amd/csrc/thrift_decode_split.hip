@@ -547,7 +547,10 @@ __global__ void __launch_bounds__(256, 4) decode_split_values_kernel(DecodeSplit
             v4i col;
 #pragma unroll
             for (int u = 0; u < 4; ++u) col[u] = (int)__builtin_amdgcn_perm((uint32_t)v[2 * u + 1][e >> 1], (uint32_t)v[2 * u][e >> 1], sel);
-            o[e] = mfma16<T>(__builtin_bit_cast(v8s, col), pf, o[e]);
+            // zero times an infinity or NaN of V is not zero: the heads that take the block in 4 bits keep their sums
+            const v4f sum = mfma16<T>(__builtin_bit_cast(v8s, col), pf, o[e]);
+            o[e] = mine ? sum : o[e];
+            asm volatile("" : "+v"(o[e]));                     // chosen here: both values of all eight tiles do not fit
             if (e & 1) __builtin_amdgcn_sched_barrier(0);      // the transposed pieces are formed as they are used, not all ahead
           }
         }

@@ -120,3 +120,23 @@ def test_a_key_of_nan_reaches_the_results_it_reaches_in_one_pass(T, Hq, Hkv):
                                          workspace=torch.zeros(n, dtype=torch.uint8, device="cuda"))[0] for n in (need, need - 256))
         assert torch.equal(torch.isnan(two), torch.isnan(one))
         assert float(torch.nan_to_num(two - one).norm() / torch.nan_to_num(one).norm()) <= REL
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (2, 2), (16, 2)])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_an_infinite_value_stays_with_the_heads_that_read_it(T, Hq, Hkv, bad):
+    """A value that is not finite reaches the heads that have promoted its block and no other head of their KV group (a
+    4-bit code is always finite), in the channel it has."""
+    print(f"decode split V={bad} Hq={Hq} Hkv={Hkv}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=1, N=4096, Hq=Hq, Hkv=Hkv)
+    q, k, v = W.make_decode(wl, device="cuda")
+    v[0, 1, 1000, 5] = bad
+    k4, ks = T.thrift_quantize_mxfp4(k, 0)
+    v4, vs = T.thrift_quantize_mxfp4(v, 1)
+    args = (q, k, v, k4, ks, v4, vs, T.thrift_block_means(k, 64))
+    for budget in (0.0, 0.25, 0.5, 1.0):
+        out, idx, _ = T.thrift_attn_decode(*args, 64, budget, out_dtype=torch.float32, return_selection=True)
+        reads = (idx[0] == 1000 // 64).any(-1) & (torch.arange(Hq, device="cuda") >= Hq // Hkv)
+        want = torch.zeros_like(out, dtype=torch.bool)
+        want[0, :, 5] = reads
+        assert torch.equal(~torch.isfinite(out), want)
