@@ -84,10 +84,13 @@ struct DecodeSplitLayout {
   int nsplit, nparts, words, cw, nsub;
 };
 
+// Key blocks per partition: a size of the whole row or more is one partition (and no sum with it can overflow).
+int partition_blocks(int Tk, int split_blocks) { return split_blocks < Tk ? split_blocks : Tk; }
+
 DecodeSplitLayout decode_split_layout(int B, int Hq, int Hkv, int Nkv, int Bk, int split_blocks) {
   DecodeSplitLayout L;
-  const int Tk = Nkv / Bk, part = split_blocks < Tk ? split_blocks : Tk;
-  L.nsplit = (Tk + split_blocks - 1) / split_blocks;
+  const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks);
+  L.nsplit = (Tk + part - 1) / part;
   L.words = (Tk + 63) / 64;
   L.cw = decode_split_chunk(B, Hkv, Tk);
   L.nsub = (part + 4 * L.cw - 1) / (4 * L.cw);
@@ -106,8 +109,8 @@ DecodeSplitLayout decode_split_layout(int B, int Hq, int Hkv, int Nkv, int Bk, i
 
 DecodeLayout decode_layout(int B, int Hq, int Hkv, int Nkv, int Bk, int split_blocks) {
   DecodeLayout L;
-  const int Tk = Nkv / Bk;
-  L.nsplit = (Tk + split_blocks - 1) / split_blocks;
+  const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks);
+  L.nsplit = (Tk + part - 1) / part;
   L.nparts = L.nsplit + 1;                       // one partial per partition + one for a partly filled last block
   L.words = (Tk + 63) / 64;
   size_t off = 0;
@@ -366,8 +369,8 @@ static size_t decode_least_workspace(int B, int Hq, int Hkv, int Nkv, int D, int
 size_t thrift_attn_decode_workspace(int B, int Hq, int Hkv, int Nkv, int D, int Bk, int split_blocks) {
   const size_t least = decode_least_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks);
   if (least == 0 || Hq % Hkv != 0) return least;
-  const int nsplit = (Nkv / Bk + split_blocks - 1) / split_blocks;
-  if (!decode_split_wanted(B, Hq, Hkv, Nkv / Bk, nsplit, split_blocks, true)) return least;   // lengths: the wider rule
+  const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks), nsplit = (Tk + part - 1) / part;
+  if (!decode_split_wanted(B, Hq, Hkv, Tk, nsplit, split_blocks, true)) return least;   // lengths: the wider rule
   const size_t split = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks).total;
   return split > least ? split : least;
 }
@@ -416,7 +419,7 @@ static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void
       a.k4 = k4; a.ks = ks; a.v4 = v4; a.vs = vs; a.seqlens = seqlens;
       a.bitmap = kneed > 0 ? bitmap : nullptr; a.bitmap_words = S.words;
       a.out = out; a.part_o = (float*)(ws + S.part_o); a.part_ml = (float*)(ws + S.part_ml); a.order = nullptr;
-      a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.Nkv = Nkv; a.split_blocks = split_blocks < Tk ? split_blocks : Tk; a.nsplit = S.nsplit; a.nparts = S.nparts; a.nmerge = S.nparts;
+      a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.Nkv = Nkv; a.split_blocks = partition_blocks(Tk, split_blocks); a.nsplit = S.nsplit; a.nparts = S.nparts; a.nmerge = S.nparts;
       a.scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)D);
       a.dt = dt; a.out_dt = out_dt;
       s.scores = (float*)(ws + S.scores); s.cmax = (float*)(ws + S.cmax);
@@ -439,7 +442,7 @@ static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void
   a.out = out; a.part_o = (float*)(ws + L.part_o); a.part_ml = (float*)(ws + L.part_ml);
   // heaviest-first launch order of the split-K workgroups; without promoted blocks and without lengths all items weigh the same
   a.order = (L.order_items > 0 && (kneed > 0 || seqlens != nullptr)) ? (int*)(ws + L.order) : nullptr;
-  a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.Nkv = Nkv; a.split_blocks = split_blocks; a.nsplit = L.nsplit; a.nparts = L.nparts; a.nmerge = seqlens ? L.nparts : L.nparts - 1;
+  a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.Nkv = Nkv; a.split_blocks = partition_blocks(Tk, split_blocks); a.nsplit = L.nsplit; a.nparts = L.nparts; a.nmerge = seqlens ? L.nparts : L.nparts - 1;
   a.scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)D);
   a.dt = dt; a.out_dt = out_dt;
   launch_decode(a, st);

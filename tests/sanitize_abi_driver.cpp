@@ -51,6 +51,7 @@ int main() {
   acc += thrift_select_kmax(1024, 2048, 128, 64, 1, 0.05, -1, 0) + thrift_select_kmax(0, 0, 128, 64, 1, 0.05, -1, 0);
   acc += (long)(thrift_attn_decode_workspace(16, 32, 8, 131072, 128, 64, 256) >> 20) + (long)thrift_attention_forward_workspace(1, 32, 8, 131072, 128, 128, 64, 1, 0.05, -1);
   acc += (long)thrift_attn_decode_workspace(1 << 15, 1 << 15, 8, 262144, 128, 64, 4) & 1;
+  acc += (long)thrift_attn_decode_workspace(1, 32, 8, 262144, 128, 64, 0x7fffffff) & 1;
   for (int s = 0; s < 9; ++s) acc += thrift_status_string((thrift_status)s)[0];
   printf("abi sanitizer pass: %s (%d mismatches, checksum %ld)\n", bad ? "FAILED" : "ok", bad, acc);
   return bad != 0;

@@ -98,6 +98,14 @@ def test_validation_errors_come_before_any_launch():
     assert "gfx950" in T.status_string(6)
 
 
+def test_a_partition_of_the_whole_row_or_more_is_one_partition():
+    """Sizes up to the largest int name the same problem as the row's own number of key blocks."""
+    for Hq, Hkv, N in ((32, 8, 4096), (8, 8, 131072), (24, 2, 1024), (4, 4, 64)):
+        need = T.decode_workspace_bytes(2, Hq, Hkv, N, 128, 64, N // 64)
+        for split in (N // 64 + 1, 1 << 20, 2 ** 31 - N // 64, 2 ** 31 - 1):
+            assert T.decode_workspace_bytes(2, Hq, Hkv, N, 128, 64, split) == need
+
+
 def test_peak_probe_validates_before_launching():
     L = T.lib()
     fake, work = C.c_void_p(0x1000), C.c_double(0.0)

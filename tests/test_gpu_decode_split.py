@@ -140,3 +140,13 @@ def test_an_infinite_value_stays_with_the_heads_that_read_it(T, Hq, Hkv, bad):
         want = torch.zeros_like(out, dtype=torch.bool)
         want[0, :, 5] = reads
         assert torch.equal(~torch.isfinite(out), want)
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (24, 2)])
+def test_partition_sizes_beyond_the_row(T, Hq, Hkv):
+    """The largest int as partition size is one partition, in the two passes (8 / 2 heads) and in the walk (24 / 2)."""
+    print(f"decode partition size beyond the row Hq={Hq} Hkv={Hkv}", flush=True)
+    args = _cache(T, W.scaled(W.DECODE_131K, B=1, N=2048, Hq=Hq, Hkv=Hkv))
+    want = T.thrift_attn_decode(*args, 64, 0.1, split_blocks=2048 // 64)
+    for split in (2048 // 64 + 1, 2 ** 31 - 1):
+        assert torch.equal(T.thrift_attn_decode(*args, 64, 0.1, split_blocks=split), want)
