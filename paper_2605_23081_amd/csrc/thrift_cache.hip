@@ -23,7 +23,6 @@ __global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
   constexpr int kRow = kD + 8;   // padded LDS row in 16-bit elements
   __shared__ __align__(16) uint16_t ktile[kBk * kRow];
   __shared__ __align__(16) uint16_t vtile[kBk * kRow];
-  __shared__ double upper[kD];   // channel sums of rows 32 .. 63
   const int tid = threadIdx.x;
   const int slot = blockIdx.x % a.blocks_per_unit;            // which of the blocks this append can touch
   const int unit = blockIdx.x / a.blocks_per_unit;            // (sequence, KV head)
@@ -77,14 +76,16 @@ __global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
     }
   }
 
-  // ---- K mean of the block: fp64 sum of 16-bit values is exact, so the order of additions does not matter, and the rows
-  // past the last token are zeros: two threads per channel take 32 rows each, all LDS reads in flight together (one thread
-  // walking `count` rows waited for each of them: 3 us of a one-token append) ----
+  // ---- K mean of the block: one thread per channel adds its rows in order (16-bit floats that lie far apart do not add
+  // exactly in fp64 either).  The rows past the last token are zeros and change no sum, so that all 64 LDS reads are in flight
+  // together: a loop over `count` rows waited for each of them, 3 us of a one-token append ----
   const size_t blk = (size_t)unit * (a.Nkv / kBk) + j;
-  double sum = 0.0;
+  if (tid < kD) {
+    double sum = 0.0;
 #pragma unroll
-  for (int r = 0; r < 32; ++r) sum += (double)T::to_float(ktile[(32 * (tid >> 7) + r) * kRow + (tid & 127)]);
-  if (tid >= kD) upper[tid - kD] = sum;
+    for (int r = 0; r < kBk; ++r) sum += (double)T::to_float(ktile[r * kRow + tid]);
+    a.kmean[blk * kD + tid] = (float)(sum / (double)count);
+  }
 
   // ---- V: both 32-token groups of the block; thread = (group, channel) walks down a column ----
   {
@@ -99,8 +100,6 @@ __global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
     *reinterpret_cast<uint4*>(a.v4 + (blk * kD + c) * 32 + g * 16) = make_uint4(out[0], out[1], out[2], out[3]);
     a.vs[(blk * 2 + g) * kD + c] = (uint8_t)sb;
   }
-  __syncthreads();
-  if (tid < kD) a.kmean[blk * kD + tid] = (float)((sum + upper[tid]) / (double)count);
 }
 
 void launch_cache_append(const CacheAppendArgs& a, thrift_dtype dt, hipStream_t st) {

@@ -67,3 +67,20 @@ def test_device_tensors_of_wrong_shape_or_type_raise_as_before():
     assert cache.seqlens.tolist() == [128]                   # the capacity
     with pytest.raises(AssertionError):
         cache.append(new.float(), new.float())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("count", [64, 41, 33])
+def test_the_mean_of_an_appended_block_adds_its_tokens_in_order(oracle, count):
+    """Keys that lie further apart than a double reaches: the sum depends on its order, which is that of the tokens."""
+    print(f"append mean count={count}", flush=True)
+    g = torch.Generator().manual_seed(count)
+    k = torch.randn(1, 2, count, 128, generator=g)
+    k[:, 0, 0], k[:, 0, 40 if count > 40 else 20] = 2.0 ** 100, -2.0 ** 100
+    k = k.to(torch.bfloat16)
+    cache = T.KVCache(1, 2, 64, 128, 64, torch.bfloat16, "cuda", fill=0)
+    kg = k.cuda()
+    cache.append(kg[:, :, :7].contiguous(), kg[:, :, :7].contiguous())
+    cache.append(kg[:, :, 7:].contiguous(), kg[:, :, 7:].contiguous())
+    bits, dt = oracle.bits_of(k)
+    assert torch.equal(cache.kmean.cpu(), torch.from_numpy(oracle.block_means(bits, dt, 64)))
