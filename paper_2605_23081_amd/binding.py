@@ -313,7 +313,7 @@ def thrift_attn_decode(q, k16, v16, k4, ks, v4, vs, kmean, Bk: int, budget: floa
                        group_shared: bool = False):
     if not return_selection and (out is not None or out_dtype is None):
         r = (_call or _native()).decode(q, k16, v16, k4, ks, v4, vs, kmean, Bk, budget, fixed_k, split_blocks, softmax_scale,
-                                        seqlens, out, workspace, int(group_shared), _raw_stream())
+                                        seqlens, out, workspace, bool(group_shared), _raw_stream())
         if r is not None:
             return _result(r, "thrift_attn_decode_shared" if group_shared else "thrift_attn_decode")
     for t in (q, k16, v16, k4, ks, v4, vs, kmean):

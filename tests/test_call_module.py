@@ -84,3 +84,16 @@ def test_the_mean_of_an_appended_block_adds_its_tokens_in_order(oracle, count):
     cache.append(kg[:, :, 7:].contiguous(), kg[:, :, 7:].contiguous())
     bits, dt = oracle.bits_of(k)
     assert torch.equal(cache.kmean.cpu(), torch.from_numpy(oracle.block_means(bits, dt, 64)))
+
+
+@pytest.mark.gpu
+def test_group_shared_is_taken_for_its_truth_value():
+    a = _args("cuda")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    for i in (0, 2):                                                         # V in 16 bits alone: which block is promoted shows
+        a[i].copy_(torch.randn(a[i].shape, generator=g, device="cuda"))
+    a[7].copy_(a[0].float().view(a[7].shape))                                # head i of a group prefers block i
+    own, shared = (T.thrift_attn_decode(*a, 64, 0.5, group_shared=x) for x in (False, True))
+    assert not torch.equal(own, shared)
+    for x, want in ((None, own), (0, own), ("", own), (0.5, shared), (2 ** 40, shared), ([0], shared)):
+        assert torch.equal(T.thrift_attn_decode(*a, 64, 0.5, group_shared=x), want)
