@@ -473,9 +473,9 @@ class PrefillPlan:
     def run(self, q, k, v, softmax_scale: float = 0.0, prepass: bool = True, attention: bool = True) -> torch.Tensor:
         B, Hq, Hkv, N, D, Bq, Bk, causal, budget, fixed_k = self.args
         if prepass:
-            if Bk == 64 and Bq in (64, 128):
+            if Bk == 64 and Bq in (64, 128) and q.dtype == k.dtype == v.dtype:
                 thrift_prefill_prepass(q, k, v, Bq, Bk, self.qmean, self.kmean, self.q4, self.qs, self.k4, self.ks, self.v4, self.vs)
-            else:                                           # blocks that only the single calls take
+            else:                                           # blocks and mixed types that only the single calls take
                 thrift_block_means(q, Bq, out=self.qmean)
                 thrift_block_means(k, Bk, out=self.kmean)
                 thrift_quantize_mxfp4(q, 0, self.q4, self.qs)

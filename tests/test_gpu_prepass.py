@@ -44,3 +44,21 @@ def test_selection_chunks_and_row_counts(rows, Tk):
         idx_o, cnt_o = oracle.select_topk(qm, km, 64, 64, causal, 0.3)
         idx, cnt = T.thrift_select_topk(torch.from_numpy(qm).cuda(), torch.from_numpy(km).cuda(), 64, 64, causal, 0.3)
         assert check_selection(to_np(idx), to_np(cnt), idx_o, cnt_o, oracle.block_scores(qm, km)) == 0
+
+
+def test_plan_prepass_takes_each_tensor_in_its_own_type():
+    """The pre-pass of a plan alone, with K in another 16-bit type than Q and V."""
+    from paper_2605_23081_amd import binding as T
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    mk = lambda H, dt: torch.randn(1, H, 300, 128, generator=g, device="cuda").to(dt)
+    q, k, v = mk(4, torch.float16), mk(2, torch.bfloat16), mk(2, torch.float16)
+    plan = T.PrefillPlan(1, 4, 2, 300, 128, 128, 64, True, 0.3, torch.float16, "cuda")
+    plan.run(q, k, v, attention=False)
+    qm, km = T.thrift_block_means(q, 128), T.thrift_block_means(k, 64)
+    want = [qm, km, *T.thrift_quantize_mxfp4(q, 0), *T.thrift_quantize_mxfp4(k, 0), *T.thrift_quantize_mxfp4(v, 1),
+            *T.thrift_select_topk(qm, km, 128, 64, True, 0.3)]
+    for a, b in zip((plan.qmean, plan.kmean, plan.q4, plan.qs, plan.k4, plan.ks, plan.v4, plan.vs, plan.idx, plan.cnt), want):
+        assert torch.equal(a, b)
+    with pytest.raises(AssertionError):
+        plan.run(q, k, v)                                    # the attention itself takes one type
