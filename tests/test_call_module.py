@@ -44,6 +44,43 @@ def test_tensors_without_storage_are_left_to_the_general_path():
     assert seen == [None] * 3
 
 
+def _without_module(monkeypatch):
+    """binding as it is where the module cannot be loaded."""
+    import sys
+    import paper_2605_23081_amd as package
+    monkeypatch.setattr(T, "_call", None)
+    monkeypatch.delattr(package, "_call", raising=False)
+    monkeypatch.setitem(sys.modules, package.__name__ + "._call", None)      # what an import that fails finds
+    with pytest.warns(RuntimeWarning, match="_call"):
+        return T._native()
+
+
+def test_a_module_that_cannot_be_loaded_leaves_the_calls_to_the_general_path(monkeypatch):
+    m = _without_module(monkeypatch)
+    assert m.decode() is None and m.append() is None and m.attention() is None and T._native() is m
+    with pytest.raises(AssertionError):
+        T.thrift_attn_decode(*_args("cpu"), 64, 0.05)
+
+
+@pytest.mark.gpu
+def test_the_general_path_gives_the_same_results(monkeypatch):
+    g = torch.Generator().manual_seed(1)
+    q, k, v = (torch.randn(1, H, 200, 128, generator=g).half().cuda() for H in (4, 2, 2))
+
+    def results():
+        cache = T.KVCache(1, 2, 256, 128, 64, torch.float16, "cuda", fill=0)
+        cache.append(k, v)
+        cache.append(k[:, :, :1].contiguous(), v[:, :, :1].contiguous())
+        c = (cache.k16, cache.v16, cache.k4, cache.ks, cache.v4, cache.vs, cache.kmean)
+        return [T.thrift_attn_decode(q[:, :, 7].contiguous(), *c, 64, 0.5, seqlens=cache.seqlens), T.thrift_attention(q, k, v, budget=0.3),
+                cache.seqlens, *c]
+
+    want = results()
+    _without_module(monkeypatch)
+    for a, b in zip(results(), want):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.gpu
 def test_device_tensors_of_wrong_shape_or_type_raise_as_before():
     a = _args("cuda")
