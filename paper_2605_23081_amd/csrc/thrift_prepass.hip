@@ -439,10 +439,11 @@ __global__ void __launch_bounds__(NW * 64) select_topk_kernel(SelectArgs p) {
 void launch_select_topk(const SelectArgs& p, hipStream_t st) {
   const int G = p.shared ? 1 : p.Hq / p.Hkv;
   const int chunks = (p.Tk + 63) / 64;
-  // 16 rows per workgroup where the keys of a row fit 128 registers per lane and that many rows leave no CU without a
-  // workgroup: a CU works through the chains of its rows one SIMD each, so few rows are better spread (2048 tokens, one
-  // head: 18 us with 2 workgroups of 16 rows)
-  const int nw = (chunks <= 32 && (long)p.B * p.Hkv * ((p.Tq * G + 15) / 16) >= 256) ? 16 : 4;
+  // 16 rows per workgroup where the keys of a row fit 128 registers per lane, a (b, kv head) has more rows than one workgroup
+  // of 4 takes and that many rows leave no CU without a workgroup: a CU works through the chains of its rows one SIMD each,
+  // so few rows are better spread (2048 tokens, one head: 18 us with 2 workgroups of 16 rows).  With 16 / 4 rows per
+  // workgroup: 71 / 54 us for 4 rows in each of 1024 units and 512 key blocks, 80 / 90 us for 6 rows
+  const int nw = (chunks <= 32 && p.Tq * G > 4 && (long)p.B * p.Hkv * ((p.Tq * G + 15) / 16) >= 256) ? 16 : 4;
   const int wgs_per_unit = (p.Tq * G + nw - 1) / nw;
   const dim3 grid((unsigned)((long)p.B * p.Hkv * wgs_per_unit));
   if (nw == 16) {

@@ -349,14 +349,14 @@ def test_select_single_row_and_offset(T, oracle):
 
 
 @pytest.mark.parametrize("Hq,Hkv,Tq,Tk,causal,off", [
-    (4, 2, 9, 300, False, 0),          # 18 rows per KV head: a full workgroup of 16 rows and a ragged one; 5 chunks (a part group of 4)
+    (4, 2, 9, 300, False, 0),          # 18 rows per KV head: ragged workgroups; 5 chunks (a part group of 4)
     (2, 1, 20, 2048, True, 2008 * 64), # 40 rows, 32 chunks, a causal frontier that differs from row to row
-    (1, 1, 5, 2100, False, 0),         # more than 2048 key blocks: the 4-row kernel with 64 key registers
-    (8, 2, 3, 70, False, 0),           # fewer than 16 rows per KV head: the 4-row kernel, ragged
+    (1, 1, 5, 2100, False, 0),         # more than 2048 key blocks: 64 key registers
+    (8, 2, 3, 70, False, 0),           # 12 rows per KV head
     (2, 2, 33, 257, True, 225 * 64)])  # one key past a staged group of 256
 def test_select_topk_kernel_shapes(T, oracle, Hq, Hkv, Tq, Tk, causal, off):
-    """Every instantiation of the selection kernel (rows per workgroup, key registers per lane) against the oracle,
-    bit for bit, per-head and group-shared."""
+    """The key registers per lane of the selection kernel with 4 rows per workgroup against the oracle, bit for bit, per-head
+    and group-shared (16 rows per workgroup: test_selection_rows_per_workgroup)."""
     _say(f"select shapes Hq={Hq} Hkv={Hkv} Tq={Tq} Tk={Tk} causal={causal} off={off}")
     g = torch.Generator().manual_seed(1000 * Tq + Tk)
     qm = torch.randn(1, Hq, Tq, 128, generator=g)

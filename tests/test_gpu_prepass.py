@@ -29,7 +29,7 @@ def test_prepass_equals_the_single_calls(B, Hq, Hkv, N, Bq, dtype):
 
 @pytest.mark.parametrize("rows,Tk", [(1, 1), (5, 64), (17, 65), (16, 128), (33, 129), (15, 300)])
 def test_selection_chunks_and_row_counts(rows, Tk):
-    """Rows per workgroup and 64-key chunks per lane at the edges of the dispatch."""
+    """64-key chunks left out at the end of a row, ragged last workgroups; few rows, hence 4 per workgroup."""
     import numpy as np
     from oracle import thrift_oracle as oracle
     from paper_2605_23081_amd import binding as T
@@ -44,6 +44,30 @@ def test_selection_chunks_and_row_counts(rows, Tk):
         idx_o, cnt_o = oracle.select_topk(qm, km, 64, 64, causal, 0.3)
         idx, cnt = T.thrift_select_topk(torch.from_numpy(qm).cuda(), torch.from_numpy(km).cuda(), 64, 64, causal, 0.3)
         assert check_selection(to_np(idx), to_np(cnt), idx_o, cnt_o, oracle.block_scores(qm, km)) == 0
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Tq,Tk,causal,off,shared", [
+    (16, 8, 8, 17, 65, False, 0, False),               # 256 workgroups of 16 rows, the fewest; the last of a unit has one row
+    (16, 8, 8, 16, 65, False, 0, False),               # 128 would be too few: 4 rows each
+    (32, 8, 8, 5, 300, False, 0, False),               # one ragged workgroup of 16 rows per unit
+    (32, 8, 8, 4, 300, False, 0, False),               # four rows are one workgroup of 4
+    (32, 16, 8, 9, 300, True, 291 * 64, False),        # 18 rows in the order (query block, head), a causal frontier
+    (32, 16, 8, 18, 600, True, 582 * 64, True),        # 16 chunks per lane, one set per KV head
+    (16, 16, 8, 9, 2048, True, 2039 * 64, False),      # 32 chunks
+    (16, 8, 8, 18, 2048, False, 0, False),
+    (16, 8, 8, 18, 2049, False, 0, False),             # one key block more than 16 rows' registers hold
+])
+def test_selection_rows_per_workgroup(B, Hq, Hkv, Tq, Tk, causal, off, shared):
+    """The selection kernel on both sides of the rule for its rows per workgroup."""
+    from oracle import thrift_oracle as oracle
+    from paper_2605_23081_amd import binding as T
+    print(f"select B={B} Hq={Hq} Hkv={Hkv} Tq={Tq} Tk={Tk} causal={causal} off={off} shared={shared}", flush=True)
+    g = torch.Generator().manual_seed(100 * Tq + Tk)
+    qm, km = torch.randn(B, Hq, Tq, 128, generator=g), torch.randn(B, Hkv, Tk, 128, generator=g)
+    idx_o, cnt_o = oracle.select_topk(qm.numpy(), km.numpy(), 64, 64, causal, 0.05, q_block_offset=off, group_shared=shared)
+    idx, cnt = T.thrift_select_topk(qm.cuda(), km.cuda(), 64, 64, causal, 0.05, q_block_offset=off, group_shared=shared)
+    assert torch.equal(cnt.cpu(), torch.from_numpy(cnt_o))
+    assert torch.equal(idx.cpu()[..., :idx_o.shape[-1]], torch.from_numpy(idx_o)) and bool((idx[..., idx_o.shape[-1]:] == -1).all())
 
 
 def test_plan_prepass_takes_each_tensor_in_its_own_type():
