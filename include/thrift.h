@@ -313,11 +313,13 @@ thrift_status thrift_attn_decode_shared(const void* q, thrift_dtype dt, const vo
 
 /*
  * thrift_attn_decode for callers that cannot allocate device memory or hand over a workspace: code under HIP
- * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and results as
- * thrift_attn_decode, without the workspace: the score keys, the selection bitmap and the split-K partials live
- * in a static device array of THRIFT_DECODE_STATIC_SCRATCH_BYTES that every GPU the library runs on holds until
- * the process ends.  The call allocates and frees nothing.  A problem whose thrift_attn_decode_workspace(...)
- * exceeds that size returns THRIFT_ERR_WORKSPACE (nothing launched).  All calls on one GPU share the array:
+ * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments as thrift_attn_decode,
+ * without the workspace: the score keys, the selection bitmap and the split-K partials live in a static device
+ * array of THRIFT_DECODE_STATIC_SCRATCH_BYTES that every GPU the library runs on holds until the process ends.
+ * The results are, bit for bit, those of thrift_attn_decode with a workspace of that size: the two-pass form where
+ * thrift_attn_decode_workspace(...) asks for no more, otherwise the one-pass form.  The call allocates and frees
+ * nothing.  A problem whose one-pass form does not fit either (thrift_attn_decode then refuses a workspace of that
+ * size, too) returns THRIFT_ERR_WORKSPACE (nothing launched).  All calls on one GPU share the array:
  * calls that overlap on one GPU (different streams, different host threads) race on it; calls on one stream
  * are ordered and safe.  Nothing in the array has to be cleared between calls: every byte a call reads it has
  * written itself.

@@ -478,7 +478,7 @@ thrift_status thrift_attn_decode_static(const void* q, thrift_dtype dt, const vo
                                         double budget, int fixed_k, int split_blocks, float softmax_scale,
                                         void* out, thrift_dtype out_dt, int32_t* idx_out, int32_t* cnt_out, int kmax_out,
                                         void* stream) {
-  // sizes first: a problem whose workspace does not fit the static array is refused before anything else happens
+  // sizes first: a problem no form of which fits the static array is refused before anything else happens
   const size_t need = decode_least_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks);
   if (need == 0) return THRIFT_ERR_SHAPE;
   if (need > kStaticScratchBytes) return THRIFT_ERR_WORKSPACE;

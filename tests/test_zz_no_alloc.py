@@ -67,3 +67,32 @@ def test_static_scratch_decode_rejects_oversized_problem(T):
                                              u8.data_ptr(), u8.data_ptr(), u8.data_ptr(), None, B, Hq, Hkv, Nkv, D, Bk,
                                              0.05, -1, 256, 0.0, u8.data_ptr(), T.F32, None, None, 0, None)
     assert code == 5    # THRIFT_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,N,lens,fits", [
+    (1, 32, 8, 8192, [8001], True),              # the two-pass form within the array
+    (4, 64, 8, 32768, None, False),              # its scores alone would fill it: the one-pass form
+    (16, 8, 1, 65536, [65536 - 4099 * b for b in range(16)], False),
+])
+def test_static_scratch_decode_takes_the_form_that_fits(T, B, Hq, Hkv, N, lens, fits):
+    """Default partitions, where the chip would be left idle: the result is that of the call with a workspace of the
+    array's size, on either side of what the two passes need."""
+    size = T.DECODE_STATIC_SCRATCH_BYTES
+    need = T.decode_workspace_bytes(B, Hq, Hkv, N, 128, 64, 256)
+    print(f"decode_static B={B} N={N} Hq={Hq} Hkv={Hkv} two-pass bytes={need}", flush=True)
+    assert (need <= size) == fits
+    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv)
+    q, k, v = W.make_decode(wl, device="cuda")
+    k4, ks = T.thrift_quantize_mxfp4(k, 0)
+    v4, vs = T.thrift_quantize_mxfp4(v, 1)
+    args = (q, k, v, k4, ks, v4, vs, T.thrift_block_means(k, 64))
+    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+    kw = dict(split_blocks=256, seqlens=sl)
+    out = torch.full((B, Hq, 128), float("nan"), dtype=torch.float32, device="cuda")
+    T.thrift_attn_decode_static(*args, 64, 0.05, out, **kw)
+    want = torch.empty_like(out)
+    T.thrift_attn_decode(*args, 64, 0.05, out=want, workspace=torch.empty(size, dtype=torch.uint8, device="cuda"), **kw)
+    assert torch.equal(out, want)
+    full = torch.empty_like(out)
+    T.thrift_attn_decode(*args, 64, 0.05, out=full, **kw)
+    assert torch.equal(out, full) == fits        # the other form adds in another order
