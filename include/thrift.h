@@ -292,7 +292,8 @@ size_t thrift_attn_decode_workspace(int B, int Hq, int Hkv, int Nkv, int D, int 
  *     (kmax_out >= thrift_select_kmax(1, Nkv/Bk, 1, Bk, 0, budget, fixed_k, 0))
  *   workspace: thrift_attn_decode_workspace(...) bytes (where short caches or few sequences leave the chip idle the
  *     call works in two passes over finer pieces, which takes more of it; with a smaller workspace that still holds the
- *     one-pass form, that form runs: the same selection and the same codes of P, sums in another order)
+ *     one-pass form, that form runs: the same selection, the same running maximum in front of every block, and scores and
+ *     sums that agree to fp32 accumulation; a P on a rounding boundary of its 4-bit or 16-bit type may fall to either side)
  */
 thrift_status thrift_attn_decode(const void* q, thrift_dtype dt, const void* k16, const void* v16,
                                  const uint8_t* k4, const uint8_t* ks, const uint8_t* v4, const uint8_t* vs,

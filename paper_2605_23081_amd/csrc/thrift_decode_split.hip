@@ -4,8 +4,13 @@
 // recurrences.  It can be computed in two passes that need no order between workgroups:
 //   decode_split_scores_kernel  the raw scores of every (query head, key) and the largest score of every chunk;
 //   decode_split_values_kernel  softmax, P quantiser and P.V of a chunk, started from the largest score of the chunks in
-//                               front of it in the partition: the running maximum of every block, hence every code of P, is
-//                               the one of the serial walk.
+//                               front of it in the partition: every block sees the running maximum of its partition, as in
+//                               the serial walk.
+// The scores come from 16 x 16 instead of 32 x 32 matrix instructions.  16-bit scores had equal bits in all of 16 million
+// compared; a 4-bit score is exact in both where the products of a row's group scales lie within 2^9 (14 bits hold the sum of
+// 128 products of two codes), so that all codes of P are the walk's and only the order of the fp32 sums differs.  With scales
+// spread over 2^40, 2.8 % of the scores differed in their last bit, neither side further from 64 bits than the other; a
+// probability on a rounding boundary may then fall to either side.
 // A chunk is `cw` key blocks and belongs to ONE wavefront, which takes all heads of the KV group at once (a row or
 // column of the matrix tiles each: up to 8 heads cost the matrix instructions of one), with tiles in its own LDS and no
 // barrier between its blocks.  Four chunks that follow each other make a workgroup,

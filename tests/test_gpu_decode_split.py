@@ -1,8 +1,11 @@
 """The two-pass decode (short caches, few sequences) against the oracle and against the one-pass form.
 
-Both forms give every block the running maximum of its partition, hence the same codes of P and the same selection: their
-fp32 results differ by the order of the sums and of the rescaling factors alone, a few 2^-24 per addition over at most some
-hundred partials.  A workspace that is too small for the two-pass form selects the one-pass form.
+Both forms give every block the running maximum of its partition and the same selection.  Their raw scores come from matrix
+instructions of different shapes.  16-bit scores had equal bits in every comparison; 4-bit scores are sums of 128 products
+that fp32 holds exactly where a row's products of group scales lie within 2^9 of each other, and none of two million with
+these inputs' outlier channels differed.  The codes of P are then the same, and the fp32 results differ by the order of the
+sums and of the rescaling factors alone, a few 2^-24 per addition over at most some hundred partials, whatever the input type.  A workspace that is too small for the two-pass form selects the one-pass
+form.
 """
 import numpy as np
 import pytest
@@ -31,6 +34,7 @@ def _cache(T, wl):
     return q, k, v, k4, ks, v4, vs, T.thrift_block_means(k, wl.Bk)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("Hq,Hkv,B,N,split,lens,budget", [
     (1, 1, 1, 64, 256, None, 0.05),                                          # one key block
     (4, 2, 3, 1152, 256, [1152, 1, 0], 0.05),                                # a full cache, one token, none
@@ -44,9 +48,9 @@ def _cache(T, wl):
     (16, 16, 11, 2176, 17, [2176 - 197 * b for b in range(11)], 0.25),       # one head per KV head: 352 partitions
     (16, 16, 16, 2176, 17, [2175] * 16, 0.05),                               # 512, the most
 ])
-def test_two_pass_decode_equals_one_pass(T, Hq, Hkv, B, N, split, lens, budget):
-    print(f"decode split Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} lens={lens} budget={budget}", flush=True)
-    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv)
+def test_two_pass_decode_equals_one_pass(T, Hq, Hkv, B, N, split, lens, budget, dtype):
+    print(f"decode split Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} lens={lens} budget={budget} {dtype}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv, dtype=dtype)
     args = _cache(T, wl)
     sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
     need = T.decode_workspace_bytes(B, Hq, Hkv, N, wl.D, 64, split)
@@ -63,18 +67,57 @@ def test_two_pass_decode_equals_one_pass(T, Hq, Hkv, B, N, split, lens, budget):
     assert torch.equal(two, again)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("Hq,Hkv,B,N,split,lens,budget", [
     (8, 2, 2, 1536, 256, None, 0.1), (5, 1, 1, 1024, 256, [833], 0.25), (8, 1, 2, 2048, 24, [2048, 1300], 0.05), (3, 3, 1, 704, 256, None, 1.0),
+    (4, 2, 1, 1344, 256, None, 0.1), (6, 2, 2, 1024, 256, [1024, 300], 0.25),
 ])
-def test_two_pass_decode_matches_the_oracle(T, Hq, Hkv, B, N, split, lens, budget):
+def test_two_pass_decode_matches_the_oracle(T, Hq, Hkv, B, N, split, lens, budget, dtype):
     from oracle import thrift_oracle as oracle
-    print(f"decode split vs oracle Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} lens={lens} budget={budget}", flush=True)
-    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv)
+    print(f"decode split vs oracle Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} lens={lens} budget={budget} {dtype}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv, dtype=dtype)
     lens = None if lens is None else [n // 64 * 64 for n in lens]            # the helper's selection takes whole blocks
     got, want, swaps = _decode_case(T, oracle, wl, budget, split, lens)
     assert swaps == 0 and np.abs(got - want).max() <= TOLMIX
 
 
+@pytest.mark.parametrize("Hq,Hkv,B,N,split,dtype", [
+    (8, 2, 1, 69632, 1088, "f16"), (8, 2, 1, 36864, 576, "bf16"),             # one head per wavefront
+    (16, 2, 1, 40960, 640, "f16"), (16, 2, 1, 36864, 576, "bf16"),            # two
+])
+def test_walk_reloads_its_window(T, Hq, Hkv, B, N, split, dtype):
+    """The one-pass form over partitions longer than its window of cached selection words (512 key blocks)."""
+    from oracle import thrift_oracle as oracle
+    print(f"decode walk Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} {dtype}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv, dtype=dtype)
+    got, want, swaps = _decode_case(T, oracle, wl, 0.1, split, one_pass=True)
+    assert swaps == 0 and np.abs(got - want).max() <= TOLMIX
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 8])
+def test_what_lies_past_the_tokens_is_not_read(T, G, dtype):
+    """Lengths that leave the last key block partly filled, in a cache whose unwritten bytes are all ones (NaN in every type,
+    an E8M0 scale of NaN) or zeros: the same bits, in both forms, which agree with each other."""
+    lens, Hkv, cap = [4095, 2049 + 31, 1985, 161, 64, 33, 1], 2, 4096
+    B, Hq = len(lens), G * Hkv
+    print(f"decode past the tokens G={G} {dtype}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=B, N=cap, Hq=Hq, Hkv=Hkv, dtype="f16" if dtype == torch.float16 else "bf16")
+    q, k, v = W.make_decode(wl, device="cuda")
+    need = T.decode_workspace_bytes(B, Hq, Hkv, cap, 128, 64, 256)
+    caches = [T.KVCache(B, Hkv, cap, 128, 64, dtype, "cuda", fill=fill) for fill in (0xFF, 0)]
+    for c in caches:
+        c.append(k, v, torch.tensor(lens, dtype=torch.int32, device="cuda"))
+    for budget in (0.0, 0.25, 1.0):
+        one, two = ([T.thrift_attn_decode(q, c.k16, c.v16, c.k4, c.ks, c.v4, c.vs, c.kmean, 64, budget, seqlens=c.seqlens,
+                                          out_dtype=torch.float32, return_selection=True,
+                                          workspace=torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda"))[0] for c in caches]
+                    for n in (need - 256, need))
+        assert bool(torch.isfinite(two[0]).all()) and torch.equal(two[0], two[1]) and torch.equal(one[0], one[1])
+        assert float((two[0] - one[0]).norm() / one[0].norm()) <= REL
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("Hq,Hkv,B,N,lens,budget,fixed_k,shared,ties", [
     (4, 1, 1, 64, None, 0.05, -1, False, False),                              # one key block
     (8, 2, 3, 4096, [4096, 1, 0], 0.05, -1, False, False),                    # a full row, one token, none
@@ -85,11 +128,11 @@ def test_two_pass_decode_matches_the_oracle(T, Hq, Hkv, B, N, split, lens, budge
     (8, 2, 2, 16384, [16384, 9001], 0.05, -1, True, False),                   # one set per KV head
     (4, 1, 1, 8192, None, 0.1, -1, False, True),                              # equal keys: the smaller ids
 ])
-def test_selection_inside_the_scores_pass(T, Hq, Hkv, B, N, lens, budget, fixed_k, shared, ties):
+def test_selection_inside_the_scores_pass(T, Hq, Hkv, B, N, lens, budget, fixed_k, shared, ties, dtype):
     """Without lists to write, the scores pass selects for itself; the kernel that writes the lists selects the same blocks:
     equal bits of the results."""
-    print(f"decode selection in the pass Hq={Hq} Hkv={Hkv} B={B} N={N} lens={lens} f={budget} k={fixed_k} {shared} {ties}", flush=True)
-    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv)
+    print(f"decode selection in the pass Hq={Hq} Hkv={Hkv} B={B} N={N} lens={lens} f={budget} k={fixed_k} {shared} {ties} {dtype}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv, dtype=dtype)
     args = list(_cache(T, wl))
     if ties:
         args[7] = args[7][:, :, :1].expand_as(args[7]).contiguous()

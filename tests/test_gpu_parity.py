@@ -215,7 +215,8 @@ def test_prefill_end_to_end_alg1(T, oracle):
 
 # ------------------------------------------------------------------ decode
 
-def _decode_case(T, oracle, wl, budget, split_blocks, seqlens=None, fixed_k=-1):
+def _decode_case(T, oracle, wl, budget, split_blocks, seqlens=None, fixed_k=-1, one_pass=False):
+    """one_pass: with a workspace that is too small for the two-pass form (which the shape must want)."""
     q, k, v = W.make_decode(wl)
     qb, dt = oracle.bits_of(q); kb, _ = oracle.bits_of(k); vb, _ = oracle.bits_of(v)
     scale = 1 / math.sqrt(wl.D)
@@ -234,8 +235,11 @@ def _decode_case(T, oracle, wl, budget, split_blocks, seqlens=None, fixed_k=-1):
     kg, vg = k.cuda(), v.cuda()
     k4, ks = T.thrift_quantize_mxfp4(kg, 0); v4, vs = T.thrift_quantize_mxfp4(vg, 1)
     kmean = T.thrift_block_means(kg, wl.Bk)
+    ws = None
+    if one_pass:
+        ws = torch.empty(T.decode_workspace_bytes(B, Hq, wl.Hkv, wl.N, wl.D, wl.Bk, split_blocks) - 256, dtype=torch.uint8, device="cuda")
     got, idx_g, cnt_g = T.thrift_attn_decode(q.cuda(), kg, vg, k4, ks, v4, vs, kmean, wl.Bk, budget, fixed_k, split_blocks,
-                                             seqlens=None if sl is None else torch.from_numpy(sl).cuda(),
+                                             seqlens=None if sl is None else torch.from_numpy(sl).cuda(), workspace=ws,
                                              out_dtype=torch.float32, return_selection=True)
     torch.cuda.synchronize()
     scores = np.zeros((B, Hq, Tk))
@@ -373,7 +377,8 @@ def test_select_topk_kernel_shapes(T, oracle, Hq, Hkv, Tq, Tk, causal, off):
 # some with one at G = 5, 6, 7), more (the transposed tiles: G = 12, 32)
 @pytest.mark.parametrize("Hq,Hkv,B,N,split", [(32, 1, 1, 1024, 16), (4, 4, 1, 640, 64), (16, 2, 2, 1536, 4), (12, 2, 2, 1024, 8),
                                               (5, 1, 1, 1024, 16), (3, 1, 2, 1024, 3), (24, 2, 1, 1024, 8), (7, 1, 2, 1536, 5),
-                                              # partitions longer than the kernel's window of cached selection words (8 x 64 blocks)
+                                              # partitions longer than the walk's window of cached selection words (8 x 64 blocks):
+                                              # the first takes the two passes, test_walk_reloads_its_window has it on the walk
                                               (8, 2, 1, 69632, 1088), (16, 1, 1, 40960, 640), (24, 1, 1, 36864, 576),
                                               # launch order: 2048 items (two per thread of the ordering workgroup); 16384 items
                                               # (more than it sorts: natural order)
