@@ -1,8 +1,6 @@
 // Pre-pass kernels of Algorithm 1: block token means (step 3), MXFP4 quantisation (step 2) and
 // block-pair scoring + per-row TopK (step 5).  All three are streaming / latency kernels: coalesced
 // 16-byte loads, wavefront shuffles and ballots for the reductions, no matrix units.
-#include <type_traits>
-
 #include "thrift_device.h"
 #include "thrift_launch.h"
 
@@ -271,10 +269,30 @@ __device__ __forceinline__ uint64_t splitmix64_output(uint64_t seed, uint64_t n)
   return z ^ (z >> 31);
 }
 
+constexpr int kQuarter = kD / 4;                      // channels staged at a time
+constexpr int kStride = kQuarter + 4;                 // padded fp32 quarter row of a staged key mean: conflict-free 16-byte reads
+
+// One staged piece of NC chains per lane: the keys cc * 64 + lane against the row's query mean, U steps of four channels per
+// turn of the loop.
+template <int NC, int U>
+__device__ __forceinline__ void score_piece(const double* q, const float* k, double (&sc)[4]) {
+#pragma unroll U
+  for (int d = 0; d < kQuarter; d += 4) {
+    const double2 qa = *reinterpret_cast<const double2*>(q + d);
+    const double2 qb = *reinterpret_cast<const double2*>(q + d + 2);
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) {
+      const float4 kv = *reinterpret_cast<const float4*>(k + cc * 64 * kStride + d);
+      sc[cc] = fma(qa.x, (double)kv.x, sc[cc]);
+      sc[cc] = fma(qa.y, (double)kv.y, sc[cc]);
+      sc[cc] = fma(qb.x, (double)kv.z, sc[cc]);
+      sc[cc] = fma(qb.y, (double)kv.w, sc[cc]);
+    }
+  }
+}
+
 template <int MAXC, int NW>
 __global__ void __launch_bounds__(NW * 64) select_topk_kernel(SelectArgs p) {
-  constexpr int kQuarter = kD / 4;                      // channels staged at a time
-  constexpr int kStride = kQuarter + 4;                 // padded fp32 quarter row of a staged key mean: conflict-free 16-byte reads
   constexpr int kPer = 2048 / (NW * 64);                // 16-byte pieces of a staged piece per thread
   __shared__ __align__(16) float kst[256 * kStride];
   __shared__ __align__(16) double qsd[NW][kD];          // the row's query mean (shared mode: summed over the group's heads)
@@ -364,25 +382,18 @@ __global__ void __launch_bounds__(NW * 64) select_topk_kernel(SelectArgs p) {
           const int t1 = cg * 4 + h + 1;
           if (t1 < MAXC && (t1 >> 2) * 256 < vis_max) fetch(t1);              // uniform over the workgroup
           __syncthreads();
-          auto chains = [&](auto nc) {
-#pragma unroll
-            for (int d = 0; d < kQuarter; d += 4) {
-              const double2 qa = *reinterpret_cast<const double2*>(&qsd[wave][h * kQuarter + d]);
-              const double2 qb = *reinterpret_cast<const double2*>(&qsd[wave][h * kQuarter + d + 2]);
-#pragma unroll
-              for (int cc = 0; cc < decltype(nc)::value; ++cc) {
-                const float4 kv = *reinterpret_cast<const float4*>(&kst[(cc * 64 + lane) * kStride + d]);
-                sc[cc] = fma(qa.x, (double)kv.x, sc[cc]);
-                sc[cc] = fma(qa.y, (double)kv.y, sc[cc]);
-                sc[cc] = fma(qb.x, (double)kv.z, sc[cc]);
-                sc[cc] = fma(qb.y, (double)kv.w, sc[cc]);
-              }
-            }
-          };
-          // uniform over the wavefront; keys past `vis` are scored and dropped, chunks past it left out by pairs
-          if (cg * 256 + 128 < vis) chains(std::integral_constant<int, 4>{});
-          else if (cg * 256 + 64 < vis) chains(std::integral_constant<int, 2>{});
-          else if (cg * 256 < vis) chains(std::integral_constant<int, 1>{});
+          // Uniform over the wavefront; keys past `vis` are scored and dropped, chunks past it left out.  The pieces of one and
+          // two chunks take registers that the widest kernel does not have (64 chunks: it spilled, 4070 us instead of 3430
+          // for the causal rows of 262144 tokens, 161 instead of 136 for 256 rows of 2100 key blocks), and the kernels of 16
+          // rows run whole rows slower with them (267 us instead of 254 for 2048 rows of 1024 key blocks; 90 instead of 92
+          // where rows end at 505 to 519): those keep pieces of two, in a loop of their own
+          constexpr bool kOne = MAXC == 8 || (NW == 4 && MAXC < 64);
+          constexpr int kUnroll = kOne || NW == 4 ? kQuarter / 4 : 2;
+          const double* qp = &qsd[wave][h * kQuarter];
+          const float* kp = &kst[lane * kStride];
+          if (cg * 256 + 128 < vis) score_piece<4, kQuarter / 4>(qp, kp, sc);
+          else if (kOne && cg * 256 + 64 < vis) score_piece<2, kUnroll>(qp, kp, sc);
+          else if (cg * 256 < vis) score_piece<kOne ? 1 : 2, kUnroll>(qp, kp, sc);
         }
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc)

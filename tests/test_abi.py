@@ -127,6 +127,16 @@ def test_without_a_gpu_valid_calls_fail_loudly():
     assert T.lib().thrift_block_means(fake, 0, 1, 1, 64, 128, 64, fake, None) == 6   # THRIFT_ERR_ARCH, nothing launched
 
 
+def test_pre_pass_kernels_do_not_spill(tmp_path):
+    """The selection keeps a row's keys in registers: up to 128 of them, next to the chains being scored."""
+    import subprocess
+    from paper_2605_23081_amd import build
+    listing = tmp_path / "prepass.s"
+    subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, "thrift_prepass.hip"), "-o", str(listing)],
+                   check=True, capture_output=True)
+    assert build.scratch_in_loops(listing.read_text()) == []
+
+
 def test_spill_check_reads_the_compiler_listing():
     """The build refuses a fused kernel whose listing touches scratch memory inside a loop (and only then)."""
     from paper_2605_23081_amd.build import scratch_in_loops
