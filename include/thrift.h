@@ -268,6 +268,10 @@ thrift_status thrift_attention_forward(const void* q, const void* k, const void*
 /* Host: bytes of workspace thrift_attn_decode needs. */
 size_t thrift_attn_decode_workspace(int B, int Hq, int Hkv, int Nkv, int D, int Bk, int split_blocks);
 
+/* Host: bytes without which the call is refused.  Less than the above where the two-pass form is the faster one: for callers
+ * that have no room for that form's scores (4 bytes per query head and cached token). */
+size_t thrift_attn_decode_least_workspace(int B, int Hq, int Hkv, int Nkv, int D, int Bk, int split_blocks);
+
 /*
  * Decode over a dual KV cache: one query token per (sequence, query head) at position seqlen-1, so
  * every cached key is visible.  The call (i) scores the cached key-block means against the query

@@ -24,7 +24,7 @@ EXPORTS = (
     "thrift_status_string", "thrift_row_budget", "thrift_visible_blocks", "thrift_budget_to_global_k",
     "thrift_select_kmax", "thrift_block_means", "thrift_select_topk", "thrift_select_topk_shared", "thrift_select_ablation", "thrift_quantize_mxfp4", "thrift_prefill_prepass",
     "thrift_attn_prefill_workspace", "thrift_attn_prefill", "thrift_attn_prefill_chunk", "thrift_attn_prefill_ordered",
-    "thrift_attn_decode_workspace", "thrift_attn_decode", "thrift_attn_decode_shared", "thrift_attn_decode_static",
+    "thrift_attn_decode_workspace", "thrift_attn_decode_least_workspace", "thrift_attn_decode", "thrift_attn_decode_shared", "thrift_attn_decode_static",
     "thrift_kv_cache_append", "thrift_kv_cache_append_advance",
     "thrift_attention_forward_workspace", "thrift_attention_forward", "thrift_peak_probe",
 )
@@ -63,8 +63,8 @@ def lib() -> C.CDLL:
         L.thrift_attn_prefill.argtypes = [p, p, p, i, p, p, p, p, p, p, p, p, i, i, i, i, i, i, i, i, i, f, p, i, p, p, sz, p]
         L.thrift_attn_prefill_chunk.argtypes = [p, p, p, i, p, p, p, p, p, p, p, p, i, i, i, i, i, i, i, i, i, i, i, f, p, i, p, p, sz, p]
         L.thrift_attn_prefill_ordered.argtypes = [p, p, p, i, p, p, p, p, p, p, p, p, i, i, i, i, i, i, i, i, i, i, i, i, f, p, i, p, p, sz, p]
-        L.thrift_attn_decode_workspace.restype = sz
-        L.thrift_attn_decode_workspace.argtypes = [i] * 7
+        L.thrift_attn_decode_workspace.restype = L.thrift_attn_decode_least_workspace.restype = sz
+        L.thrift_attn_decode_workspace.argtypes = L.thrift_attn_decode_least_workspace.argtypes = [i] * 7
         L.thrift_attn_decode.argtypes = [p, i, p, p, p, p, p, p, p, p, i, i, i, i, i, i, d, i, i, f, p, i, p, p, i, p, sz, p]
         L.thrift_attn_decode_shared.argtypes = L.thrift_attn_decode.argtypes
         L.thrift_attn_decode_static.argtypes = [p, i, p, p, p, p, p, p, p, p, i, i, i, i, i, i, d, i, i, f, p, i, p, p, i, p]
@@ -319,6 +319,10 @@ def decode_workspace_bytes(B: int, Hq: int, Hkv: int, Nkv: int, D: int, Bk: int,
     return int(lib().thrift_attn_decode_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks))
 
 
+def decode_least_workspace_bytes(B: int, Hq: int, Hkv: int, Nkv: int, D: int, Bk: int, split_blocks: int) -> int:
+    return int(lib().thrift_attn_decode_least_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks))
+
+
 def thrift_attn_decode(q, k16, v16, k4, ks, v4, vs, kmean, Bk: int, budget: float, fixed_k: int = -1,
                        split_blocks: int = 256, softmax_scale: float = 0.0, seqlens: Optional[torch.Tensor] = None,
                        out: Optional[torch.Tensor] = None, out_dtype: Optional[torch.dtype] = None,
@@ -342,8 +346,14 @@ def thrift_attn_decode(q, k16, v16, k4, ks, v4, vs, kmean, Bk: int, budget: floa
         out = torch.empty(B, Hq, D, dtype=out_dtype or q.dtype, device=q.device)
     assert tuple(out.shape) == (B, Hq, D)
     if workspace is None:
-        workspace = torch.empty(max(decode_workspace_bytes(B, Hq, Hkv, Nkv, D, Bk, split_blocks), 16), dtype=torch.uint8,
-                                device=q.device)
+        size = B, Hq, Hkv, Nkv, D, Bk, split_blocks
+        n, least = decode_workspace_bytes(*size), decode_least_workspace_bytes(*size)
+        try:
+            workspace = torch.empty(max(n, 16), dtype=torch.uint8, device=q.device)
+        except torch.OutOfMemoryError:                      # the two-pass form's scores do not fit: the one-pass form
+            if least == n:
+                raise
+            workspace = torch.empty(max(least, 16), dtype=torch.uint8, device=q.device)
     idx = cnt = None
     kmax = 0
     if return_selection:

@@ -358,8 +358,7 @@ thrift_status thrift_attn_prefill(const void* q, const void* k, const void* v, t
                                    softmax_scale, out, out_dt, lse, workspace, workspace_bytes, stream);
 }
 
-// Bytes without which no form of the decode call can run; 0 for sizes that no form takes.
-static size_t decode_least_workspace(int B, int Hq, int Hkv, int Nkv, int D, int Bk, int split_blocks) {
+size_t thrift_attn_decode_least_workspace(int B, int Hq, int Hkv, int Nkv, int D, int Bk, int split_blocks) {
   if (B <= 0 || Hq <= 0 || Hkv <= 0 || Nkv <= 0 || D != kHeadDim || Bk != kKeyBlock || split_blocks <= 0 || Nkv % Bk != 0 ||
       Nkv / Bk > kMaxKeyBlocks || !fits_int(B, Hq, 64))
     return 0;
@@ -367,7 +366,7 @@ static size_t decode_least_workspace(int B, int Hq, int Hkv, int Nkv, int D, int
 }
 
 size_t thrift_attn_decode_workspace(int B, int Hq, int Hkv, int Nkv, int D, int Bk, int split_blocks) {
-  const size_t least = decode_least_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks);
+  const size_t least = thrift_attn_decode_least_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks);
   if (least == 0 || Hq % Hkv != 0) return least;
   const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks), nsplit = (Tk + part - 1) / part;
   if (!decode_split_wanted(B, Hq, Hkv, Tk, nsplit, split_blocks, true)) return least;   // lengths: the wider rule
@@ -479,7 +478,7 @@ thrift_status thrift_attn_decode_static(const void* q, thrift_dtype dt, const vo
                                         void* out, thrift_dtype out_dt, int32_t* idx_out, int32_t* cnt_out, int kmax_out,
                                         void* stream) {
   // sizes first: a problem no form of which fits the static array is refused before anything else happens
-  const size_t need = decode_least_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks);
+  const size_t need = thrift_attn_decode_least_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks);
   if (need == 0) return THRIFT_ERR_SHAPE;
   if (need > kStaticScratchBytes) return THRIFT_ERR_WORKSPACE;
   void* ws = nullptr;

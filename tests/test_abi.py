@@ -106,6 +106,16 @@ def test_a_partition_of_the_whole_row_or_more_is_one_partition():
             assert T.decode_workspace_bytes(2, Hq, Hkv, N, 128, 64, split) == need
 
 
+def test_least_decode_workspace():
+    """Never more than the workspace of the faster form; the same where there is no other form; 0 for what no form takes."""
+    for B, Hq, Hkv, N, split in ((1, 32, 8, 131072, 256), (8, 64, 8, 32768, 256), (16, 32, 8, 131072, 256), (1, 4, 4, 64, 256), (2, 24, 2, 1024, 8)):
+        need, least = (f(B, Hq, Hkv, N, 128, 64, split) for f in (T.decode_workspace_bytes, T.decode_least_workspace_bytes))
+        assert 0 < least <= need
+    assert T.decode_least_workspace_bytes(1, 32, 8, 131072, 128, 64, 256) < T.decode_workspace_bytes(1, 32, 8, 131072, 128, 64, 256)
+    assert T.decode_least_workspace_bytes(16, 32, 8, 131072, 128, 64, 256) == T.decode_workspace_bytes(16, 32, 8, 131072, 128, 64, 256)
+    assert T.decode_least_workspace_bytes(1, 32, 8, 100, 128, 64, 256) == 0
+
+
 def test_peak_probe_validates_before_launching():
     L = T.lib()
     fake, work = C.c_void_p(0x1000), C.c_double(0.0)

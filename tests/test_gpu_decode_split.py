@@ -193,3 +193,27 @@ def test_partition_sizes_beyond_the_row(T, Hq, Hkv):
     want = T.thrift_attn_decode(*args, 64, 0.1, split_blocks=2048 // 64)
     for split in (2048 // 64 + 1, 2 ** 31 - 1):
         assert torch.equal(T.thrift_attn_decode(*args, 64, 0.1, split_blocks=split), want)
+
+
+def test_a_card_without_room_for_two_passes_runs_one(T, monkeypatch):
+    """No workspace given and no memory for the two-pass form's: the call runs the one-pass form."""
+    print("decode without room for the larger workspace", flush=True)
+    Hq, Hkv, N = 32, 8, 131072
+    args = _cache(T, W.scaled(W.DECODE_131K, B=1, N=N, Hq=Hq, Hkv=Hkv))
+    need, least = (f(1, Hq, Hkv, N, 128, 64, 256) for f in (T.decode_workspace_bytes, T.decode_least_workspace_bytes))
+    assert need > (16 << 20) and least < (1 << 20)
+    want = T.thrift_attn_decode(*args, 64, 0.05, workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    two = T.thrift_attn_decode(*args, 64, 0.05, workspace=torch.empty(need, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    got = []
+    try:                                                     # the allocator's own limit: 8 MiB more than it holds
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (8 << 20)) / total)
+        for call in (T._call, T._General):                   # the native entry and the general path
+            monkeypatch.setattr(T, "_call", call)
+            got.append(T.thrift_attn_decode(*args, 64, 0.05))
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert all(torch.equal(x, want) for x in got)
+    assert torch.equal(T.thrift_attn_decode(*args, 64, 0.05), two)
