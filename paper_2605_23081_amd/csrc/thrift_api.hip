@@ -369,7 +369,7 @@ size_t thrift_attn_decode_workspace(int B, int Hq, int Hkv, int Nkv, int D, int 
   const size_t least = thrift_attn_decode_least_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks);
   if (least == 0 || Hq % Hkv != 0) return least;
   const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks), nsplit = (Tk + part - 1) / part;
-  if (!decode_split_wanted(B, Hq, Hkv, Tk, nsplit, split_blocks, true)) return least;   // lengths: the wider rule
+  if (!decode_split_wanted(B, Hq, Hkv, nsplit, split_blocks, true)) return least;   // lengths: the wider rule
   const size_t split = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks).total;
   return split > least ? split : least;
 }
@@ -398,7 +398,7 @@ static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void
   if (thrift_status s = check_arch()) return s;
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  if (decode_split_wanted(B, Hq, Hkv, Tk, L.nsplit, split_blocks, seqlens != nullptr)) {
+  if (decode_split_wanted(B, Hq, Hkv, L.nsplit, split_blocks, seqlens != nullptr)) {
     const DecodeSplitLayout S = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks);
     if (workspace_bytes >= S.total) {              // a caller's (or the static) workspace may hold the one-pass form only
       DecodeSplitArgs s;

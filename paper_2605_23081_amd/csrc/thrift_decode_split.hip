@@ -657,7 +657,7 @@ __global__ void __launch_bounds__(256) decode_split_merge_kernel(DecodeSplitArgs
 // cache of one or two partitions that has lengths: three of a walk's four wavefronts have no head there, its partitions are
 // seldom full, and the scores cost 8 bytes a token.  A serving step with 16/16 heads: 242 / 220 us (16 x 32768 tokens, 5 %),
 // 344 / 300 us (25 %), 727 / 586 us (100 %), 255 / 167 us (14 x 24576, 10 %); without lengths 249 / 266 us (8 x 65536, 5 %).
-bool decode_split_wanted(int B, int Hq, int Hkv, int Tk, int nsplit, int split_blocks, bool lengths) {
+bool decode_split_wanted(int B, int Hq, int Hkv, int nsplit, int split_blocks, bool lengths) {
   if (Hq / Hkv > 8) return false;
   if (nsplit > 1 && split_blocks <= 16) return false;
   return (long)B * Hkv * nsplit <= (lengths && Hq == Hkv && nsplit <= 2 ? kSplitMaxItemsOneHead : kSplitMaxItems);

@@ -93,7 +93,7 @@ bool decode_split_selects(int Hq, int Hkv, int Tk);
 constexpr int kSplitMaxItems = 320;   // partitions up to which the two passes are faster than one walk of a workgroup each
 constexpr int kSplitMaxItemsOneHead = 512;   // the same for one query head per KV head, few partitions and lengths
 constexpr int kSplitMaxChunk = 8;
-bool decode_split_wanted(int B, int Hq, int Hkv, int Tk, int nsplit, int split_blocks, bool lengths);
+bool decode_split_wanted(int B, int Hq, int Hkv, int nsplit, int split_blocks, bool lengths);
 int decode_split_chunk(int B, int Hkv, int Tk);
 void launch_decode_split(const DecodeSplitArgs& s, hipStream_t st);
 // decode-time selection: scores of the cached key-block means against the query heads, then per-row TopK
