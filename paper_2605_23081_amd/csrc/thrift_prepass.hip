@@ -9,8 +9,8 @@ namespace thrift {
 // ------------------------------------------------------------------------------------------------
 // Block means (Sec. 3.2): one workgroup per (b, h, block).  256 threads = 16 row slices x 16 column
 // groups of 8 channels; each thread streams rows slice, slice+16, ... with 16-byte loads and adds
-// in fp64 (the sum of a block of 16-bit values is then exact, so the result does not depend on the
-// order of the additions and matches a serial fp64 mean bit for bit).
+// in fp64 (the sum of a block of 16-bit values is then exact, unless bf16 values lie further apart than
+// 2^38, so the result does not depend on the order of the additions and matches a serial fp64 mean bit for bit).
 // ------------------------------------------------------------------------------------------------
 // N need not be a multiple of the block: a head has ceil(N/block) blocks and the last one is the mean
 // of the tokens it has.
