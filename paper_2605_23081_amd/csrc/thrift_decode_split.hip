@@ -15,11 +15,12 @@
 // column of the matrix tiles each: up to 8 heads cost the matrix instructions of one), with tiles in its own LDS and no
 // barrier between its blocks.  Four chunks that follow each other make a workgroup,
 // whose partials are added up in LDS before they are written.
-// Measured against the walk, whole calls or serving steps: 296 -> 74 us for one sequence of 131072 tokens and 32/8 heads,
-// 303 -> 43 us for one of 32768, 552 -> 191 us for eight of 16384-32768 tokens and 64/8 heads at a 10 % budget (scores pass
-// 70 us, values pass 76 us).
-// What bounds it: for short caches the latency of the chain of launches; for long ones HBM (the scores travel through
-// memory once more, 8 bytes per head and token next to 136 bytes of codes and scales per token).
+// Measured against the walk, whole calls or serving steps: 301 -> 74 us for one sequence of 131072 tokens and 32/8 heads,
+// 306 -> 43 us for one of 32768, 544 -> 192 us for eight of 16384-32768 tokens and 64/8 heads at a 10 % budget (scores pass
+// 70 us, values pass 77 us).
+// What bounds it: for short caches the latency of the chain of launches; for long ones the bytes (the scores travel through
+// memory once more, 8 bytes per head and token next to 136 bytes of codes and scales per token), of which too few are in
+// flight: 4.9 to 5.7 TB/s read and written, against 7.1 of a plain streaming read, with 1.6 to 2.5 wavefronts per SIMD.
 #include <type_traits>
 
 #include "thrift_launch.h"
@@ -666,7 +667,22 @@ bool decode_split_wanted(int B, int Hq, int Hkv, int nsplit, int split_blocks, b
 // With more heads a wavefront would select two rows one after the other: 58.6 us against 57.5 us for 2 x 20480 tokens, 64/8 heads.
 bool decode_split_selects(int Hq, int Hkv, int Tk) { return Hq / Hkv <= 4 && Tk <= kSplitSelectBlocks; }
 
-// key blocks per wavefront: as few as leave about eight wavefronts per CU
+// Key blocks per wavefront: eight to sixteen wavefronts per CU where there are so many blocks, one block each below that.  Longer
+// chunks are longer serial chains, shorter ones more partials and more running maxima to look up.  Chunks of 1 / 2 / 4 / 8,
+// whole serving steps or calls in us (B x tokens, heads, budget):
+//    512 blocks   1 x 4096, 32/8, 5 %      27.9 /  31.6 /  33.7 /  41.3   takes 1
+//   4096          1 x 32768, 32/8, 5 %     47.7 /  41.4 /  43.9 /  49.2         2
+//                 1 x 16384, 16/16, 5 %    37.8 /  31.9 /  32.4 /  36.4         2
+//  16384          1 x 131072, 32/8, 5 %    99.9 /  81.3 /  76.2 /  76.5         8
+//                 16 x 8192, shared, 5 %   79.2 /  60.2 /  54.6 /  54.6         8
+//                 4 x 32768, 32/8, 5 %     94.2 /  74.9 /  68.9 /  74.6         8
+//                 4 x 32768, 64/8, 100 %  128.5 / 124.0 / 122.8 / 142.7         8
+//  32768          8 x 32768, 64/8, 10 %   193.4 / 175.5 / 174.1 / 171.3         8
+//                 16 x 16384, 32/8, 5 %   146.5 / 108.2 /  98.8 / 102.6         8
+//  65536          16 x 32768, 32/8, 25 %  367.3 / 319.2 / 315.2 / 318.0         8
+//                 8 x 32768, 16/16, 10 %  209.6 / 150.2 / 128.0 / 126.3         8
+// The line between 4 and 8 is not the best one for all of them: few sequences of uneven lengths would gain up to 14 % by 4, others
+// lose 1 to 2 %.
 int decode_split_chunk(int B, int Hkv, int Tk) {
   const long blocks = (long)B * Hkv * Tk;
   int cw = 1;
