@@ -11,8 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libthrift_hip.so")
 CALL = os.path.join(HERE, "_call.so")          # the Python entry of the calls of a serving loop (host code only)
-SOURCES = ["thrift_api.hip", "thrift_prepass.hip", "thrift_prefill.hip", "thrift_decode.hip", "thrift_decode_split.hip", "thrift_cache.hip", "thrift_probe.hip"]
-DMA_SOURCES = ["thrift_prefill.hip", "thrift_decode.hip", "thrift_decode_split.hip"]      # kernels whose inline assembly sets M0 and keeps DMA in flight
+SOURCES = ["thrift_api.hip", "thrift_prepass.hip", "thrift_prefill.hip", "thrift_prefill_split.hip", "thrift_decode.hip", "thrift_decode_split.hip", "thrift_cache.hip", "thrift_probe.hip"]
+DMA_SOURCES = ["thrift_prefill.hip", "thrift_prefill_split.hip", "thrift_decode.hip", "thrift_decode_split.hip"]      # kernels whose inline assembly sets M0 and keeps DMA in flight
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # NaN inputs are outside the contract (include/thrift.h); without this every maximum of matrix-unit results
          # is preceded by instructions that only quiet signalling NaNs

@@ -163,6 +163,30 @@ __device__ __forceinline__ float other_half(float x) {
   return __uint_as_float((threadIdx.x & 32) ? lo : hi);
 }
 
+// Largest of a value and its counterpart 32 lanes away, in both.
+__device__ __forceinline__ float both_halves_max(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// Four neighbouring channels of the output, from element `at` on.
+__device__ __forceinline__ void store_out4(void* out, thrift_dtype dt, size_t at, float x0, float x1, float x2, float x3) {
+  if (dt == THRIFT_F32) {
+    *reinterpret_cast<float4*>((float*)out + at) = make_float4(x0, x1, x2, x3);
+  } else if (dt == THRIFT_F16) {
+    uint2 w;
+    w.x = (uint32_t)F16::from_float(x0) | ((uint32_t)F16::from_float(x1) << 16);
+    w.y = (uint32_t)F16::from_float(x2) | ((uint32_t)F16::from_float(x3) << 16);
+    *reinterpret_cast<uint2*>((uint16_t*)out + at) = w;
+  } else {
+    uint2 w;
+    w.x = (uint32_t)BF16::from_float(x0) | ((uint32_t)BF16::from_float(x1) << 16);
+    w.y = (uint32_t)BF16::from_float(x2) | ((uint32_t)BF16::from_float(x3) << 16);
+    *reinterpret_cast<uint2*>((uint16_t*)out + at) = w;
+  }
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 }  // namespace thrift

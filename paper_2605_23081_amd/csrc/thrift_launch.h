@@ -8,6 +8,8 @@
 
 namespace thrift {
 
+constexpr int kCus = 256;                 // compute units of the MI355X, 32 in each of 8 XCDs
+
 void launch_block_means(const void* x, thrift_dtype dt, long heads, int N, int block, float* means, hipStream_t st);
 // block means of q and k, axis-0 codes of both and axis-1 codes of v [B*H, N, D] in one launch (key blocks of 64)
 void launch_prepass(const void* q, const void* k, const void* v, thrift_dtype dt, long heads_q, long heads_kv, int N, int Bq, float* qmean,
@@ -49,6 +51,8 @@ struct PrefillArgs {
   thrift_dtype dt, out_dt;
 };
 void launch_prefill(const PrefillArgs& a, hipStream_t st);
+// Four wavefronts per 32 query rows where the grid is small (thrift_prefill_split.hip), the same bits: true where it was launched
+bool launch_prefill_split(const PrefillArgs& a, hipStream_t st);
 
 struct DecodeArgs {
   const uint16_t* q;

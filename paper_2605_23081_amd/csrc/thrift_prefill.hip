@@ -516,19 +516,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
       const int ch = 32 * n + 8 * q4i + 4 * half;
       if (!row_ok) continue;
       const float x0 = o[n][4 * q4i] * inv, x1 = o[n][4 * q4i + 1] * inv, x2 = o[n][4 * q4i + 2] * inv, x3 = o[n][4 * q4i + 3] * inv;
-      if (a.out_dt == THRIFT_F32) {
-        *reinterpret_cast<float4*>((float*)a.out + orow + ch) = make_float4(x0, x1, x2, x3);
-      } else if (a.out_dt == THRIFT_F16) {
-        uint2 w;
-        w.x = (uint32_t)F16::from_float(x0) | ((uint32_t)F16::from_float(x1) << 16);
-        w.y = (uint32_t)F16::from_float(x2) | ((uint32_t)F16::from_float(x3) << 16);
-        *reinterpret_cast<uint2*>((uint16_t*)a.out + orow + ch) = w;
-      } else {
-        uint2 w;
-        w.x = (uint32_t)BF16::from_float(x0) | ((uint32_t)BF16::from_float(x1) << 16);
-        w.y = (uint32_t)BF16::from_float(x2) | ((uint32_t)BF16::from_float(x3) << 16);
-        *reinterpret_cast<uint2*>((uint16_t*)a.out + orow + ch) = w;
-      }
+      store_out4(a.out, a.out_dt, orow + ch, x0, x1, x2, x3);
     }
   if (a.lse != nullptr && half == 0 && row_ok) a.lse[qh * Nq + lrow_again] = st.m * a.scale + __logf(l);
 #undef THRIFT_ROW_AGAIN
@@ -581,6 +569,7 @@ static bool wide_schedule(const PrefillArgs& a) {
 static bool interleaved_units(const PrefillArgs& a, unsigned grid) { return a.causal && grid <= 8u * 3u * 256u; }
 
 void launch_prefill(const PrefillArgs& args, hipStream_t st) {
+  if (launch_prefill_split(args, st)) return;
   PrefillArgs a = args;
   const unsigned grid = (unsigned)((long)a.B * a.Hq * ((a.Nq + a.Bq - 1) / a.Bq));
   a.interleave = interleaved_units(a, grid);

@@ -147,6 +147,52 @@ constexpr float kEmptyMax = -1.0e30f;
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }   // one v_max3_f32
 
+// The lane's keys at or past n_valid (of the block's 64) get the score -inf.
+__device__ __forceinline__ void mask_scores(v16f (&s)[2], int half, int n_valid) {
+  int lim = n_valid - 32 * half;                        // the lane's keys 16t + i at or past lim are masked
+  asm volatile("" : "+v"(lim));                         // keep one register: no per-element thresholds hoisted out of the key loop
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (16 * t + i >= lim) s[t][i] = -INFINITY;
+}
+// Largest of the lane's 32 scores.
+__device__ __forceinline__ float lane_max(const v16f (&s)[2]) {
+  float mloc = max3(s[0][0], s[0][1], s[0][2]);
+#pragma unroll
+  for (int i = 3; i < 15; i += 2) mloc = max3(mloc, s[0][i], s[0][i + 1]);
+  mloc = max3(mloc, s[0][15], s[1][0]);
+#pragma unroll
+  for (int i = 1; i < 15; i += 2) mloc = max3(mloc, s[1][i], s[1][i + 1]);
+  return fmaxf(mloc, s[1][15]);
+}
+// The lane's 32 scores become the unnormalised probabilities exp(scale*(s - m)); returns their sum.
+// mloc: the largest of the scores.
+__device__ __forceinline__ float probabilities(v16f (&s)[2], float mloc, float m, float c, uint32_t& pbyte) {
+  // Elements use one fused multiply-add, s*c - m*c; its rounding residue (a few 1e-7 relative on p) is
+  // harmless for the codes and the row sum.  The exponent of the group maximum, which fixes the power-of-two
+  // scale of the P quantiser, is formed from (s - m)*c instead: the row maximum then maps to exactly 2^0 and
+  // can never slip under the binade boundary (where the floor rule would scale it to 8 and saturate it to 6).
+  int e;
+  {
+    const float x = (mloc - m) * c;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(e) : "v"(x));        // floor; -inf (nothing visible) saturates to INT_MIN
+  }
+  pbyte = (uint32_t)max(e + 125, 1);
+  const float mc = m * c;
+  float sum;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float p = fast_exp2(__builtin_fmaf(s[t][i], c, -mc));
+      s[t][i] = p;
+      sum = (t == 0 && i == 0) ? p : sum + p;
+    }
+  return sum;
+}
+
 // Online-softmax update for the lane's 32 scores (Alg. 1 steps 10-12 / 16-17): masks, raises the
 // running maximum, turns s into the unnormalised probabilities exp(scale*(s - m_new)) in place and adds
 // them to the partial row sum.  Returns true, for the whole wavefront, when some row raised its maximum:
@@ -158,23 +204,8 @@ __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(
 //   c = softmax_scale * log2(e);  n_valid = number of leading keys of the block this query may see.
 __device__ __forceinline__ bool softmax_update(v16f (&s)[2], int lane, bool mask, int n_valid, float c, RowState& st,
                                                float& alpha, uint32_t& pbyte) {
-  const int half = lane >> 5;
-  if (mask) {
-    int lim = n_valid - 32 * half;                      // the lane's keys 16t + i at or past lim are masked
-    asm volatile("" : "+v"(lim));                       // keep one register: no per-element thresholds hoisted out of the key loop
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (16 * t + i >= lim) s[t][i] = -INFINITY;
-  }
-  float mloc = max3(s[0][0], s[0][1], s[0][2]);
-#pragma unroll
-  for (int i = 3; i < 15; i += 2) mloc = max3(mloc, s[0][i], s[0][i + 1]);
-  mloc = max3(mloc, s[0][15], s[1][0]);
-#pragma unroll
-  for (int i = 1; i < 15; i += 2) mloc = max3(mloc, s[1][i], s[1][i + 1]);
-  mloc = fmaxf(mloc, s[1][15]);
+  if (mask) mask_scores(s, lane >> 5, n_valid);
+  const float mloc = lane_max(s);
   // the other half of the row lives 32 lanes away: after the swap of two copies one register holds the lower
   // half's maximum in every lane and the other the upper half's
   uint32_t lo = __float_as_uint(mloc), hi = lo;
@@ -196,27 +227,7 @@ __device__ __forceinline__ bool softmax_update(v16f (&s)[2], int lane, bool mask
     st.l = l;
   }
   st.m = m_new;
-  // Elements use one fused multiply-add, s*c - m*c; its rounding residue (a few 1e-7 relative on p) is
-  // harmless for the codes and the row sum.  The exponent of the group maximum, which fixes the power-of-two
-  // scale of the P quantiser, is formed from (s - m)*c instead: the row maximum then maps to exactly 2^0 and
-  // can never slip under the binade boundary (where the floor rule would scale it to 8 and saturate it to 6).
-  int e;
-  {
-    const float x = (mloc - m_new) * c;
-    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(e) : "v"(x));        // floor; -inf (nothing visible) saturates to INT_MIN
-  }
-  pbyte = (uint32_t)max(e + 125, 1);
-  const float mc = m_new * c;
-  float sum;
-#pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float p = fast_exp2(__builtin_fmaf(s[t][i], c, -mc));
-      s[t][i] = p;
-      sum = (t == 0 && i == 0) ? p : sum + p;
-    }
-  st.l += sum;
+  st.l += probabilities(s, mloc, m_new, c, pbyte);
   return grew;
 }
 
@@ -331,6 +342,21 @@ __device__ __forceinline__ void pv_16_rounded(const unsigned char* vtile, int la
       const v8s a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
       o[n] = T::mfma(a, pf[s], o[n]);
     }
+  }
+}
+
+// The same on swizzled rows for one of the four channel tiles.
+template <typename T>
+__device__ __forceinline__ void pv_16_tile(const unsigned char* vtile, int lane, int n, const v8s (&pf)[4], v16f& o) {
+  const int half = lane >> 5, r = lane & 31, g = r >> 4, i16 = r & 15;
+  typedef v4s __attribute__((address_space(3))) * lds_v4s_ptr;
+  const uint32_t lane_off = (uint32_t)((32 * half + (i16 >> 2)) * (2 * kD) + (16 * g + 4 * (i16 & 3)) * 2) + 64u * ((i16 >> 2) & 3);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const unsigned char* base = vtile + ((lane_off ^ (64u * n)) + 8u * s * (2 * kD));
+    const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)(base));
+    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)(base + 4 * (2 * kD)));
+    o = T::mfma(__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7), pf[s], o);
   }
 }
 

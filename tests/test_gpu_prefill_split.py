@@ -41,3 +41,56 @@ def test_order_of_the_workgroups(T, B, Hq, Hkv, N, Bq, causal):
             alone = T.thrift_attention(q[b:b + 1, h * G:(h + 1) * G].contiguous(), k[b:b + 1, h:h + 1].contiguous(),
                                        v[b:b + 1, h:h + 1].contiguous(), causal, Bq, 64, 0.1, tile_order=order)
             assert torch.equal(out[b, h * G:(h + 1) * G], alone[0])
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("Hq,Hkv,N,Bq,causal,copies", [
+    (1, 1, 1, 64, True, 600),             # one row, one key
+    (1, 1, 257, 64, True, 80),            # five groups of key blocks, the last one short; a short last row group
+    (2, 1, 700, 128, True, 20),           # four row groups per query block, of which the last has none
+    (3, 1, 1100, 64, False, 8),           # every row sees every block
+    (8, 2, 1024, 128, True, 4),           # 256 row groups, the most with one per workgroup
+    (8, 8, 1025, 128, True, 2),           # 264: two row groups per workgroup
+    (4, 1, 4095, 64, True, 2),            # 512, the most
+    (8, 8, 577, 64, False, 4),            # ten key blocks, the fewest
+])
+def test_four_wavefronts_per_row_group(T, Hq, Hkv, N, Bq, causal, copies, dtype):
+    """The same sequence alone and in a batch that is large enough for the plain kernel: equal bits, LSE included, for lists up
+    to 15 % of the key blocks (none, some, neighbouring blocks)."""
+    print(f"four wavefronts per row group {Hq}/{Hkv} N={N} Bq={Bq} causal={causal} {dtype}", flush=True)
+    q, k, v = _qkv(1, Hq, Hkv, N, dtype)
+    Tk = -(-N // 64)
+    ks = sorted({0, max(1, Tk // 20), max(0, (15 * Tk - 1) // 100)})
+    many = [t.expand(copies, -1, -1, -1).contiguous() for t in (q, k, v)]
+    assert copies * Hq * -(-N // 32) > 512
+    for fixed_k in ks:
+        for order in (0, 1):
+            lse, lse_n = torch.full((1, Hq, N), 7.0, device="cuda"), torch.full((copies, Hq, N), 7.0, device="cuda")
+            a = T.thrift_attention(q, k, v, causal, Bq, 64, fixed_k=fixed_k, tile_order=order, lse=lse)
+            b = T.thrift_attention(*many, causal, Bq, 64, fixed_k=fixed_k, tile_order=order, lse=lse_n)
+            assert bool(torch.isfinite(a).all())
+            for c in {0, copies - 1}:
+                assert torch.equal(a[0], b[c]) and torch.equal(lse[0], lse_n[c])
+
+
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("Nq,off,N,ids", [
+    (128, 30, 4000, [0, 1, 2, 3, 7, 8]),                                     # promoted blocks that follow each other
+    (100, 15, 2050, [31, 32]),                                               # the last blocks, of which one is short
+    (64, 31, 4096, [0, 62, 63]),                                             # some blocks after the rows' own
+])
+def test_four_wavefronts_per_row_group_in_a_chunk(T, Nq, off, N, ids, order):
+    print(f"four wavefronts, chunk of {Nq} at {off} in {N}, ids {ids}, order {order}", flush=True)
+    q, k, v = _qkv(1, 4, 2, N, torch.bfloat16)
+    q = q[:, :, :Nq].contiguous()
+    idx = torch.tensor(ids, dtype=torch.int32, device="cuda").expand(1, 4, -(-Nq // 128), -1).contiguous()
+    cnt = torch.full(idx.shape[:3], len(ids), dtype=torch.int32, device="cuda")
+
+    def run(n):
+        a, b, c = (t.expand(n, -1, -1, -1).contiguous() for t in (q, k, v))
+        codes = [*T.thrift_quantize_mxfp4(a, 0), *T.thrift_quantize_mxfp4(b, 0), *T.thrift_quantize_mxfp4(c, 1)]
+        return T.thrift_attn_prefill_chunk(a, b, c, *codes, idx.expand(n, -1, -1, -1).contiguous(), cnt.expand(n, -1, -1).contiguous(),
+                                           128, 64, True, off, tile_order=order)
+
+    alone, many = run(1), run(80)
+    assert bool(torch.isfinite(alone).all()) and torch.equal(alone[0], many[0]) and torch.equal(alone[0], many[79])
