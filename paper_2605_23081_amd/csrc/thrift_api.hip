@@ -78,9 +78,9 @@ struct DecodeLayout {
   int nsplit, nparts, words, order_items;
 };
 
-// Workspace of the two-pass form; it also fits wherever the one-pass form's does not exceed it.
+// Workspace of the form in finer pieces (two passes over chunks); the walk's fits into it wherever it does not exceed it.
 struct DecodeSplitLayout {
-  size_t keys, bitmap, scores, cmax, part_o, part_ml, total;
+  size_t keys, bitmap, scores, cmax, tickets, tops, taken, part_o, part_ml, total;
   int nsplit, nparts, words, cw, nsub;
 };
 
@@ -92,15 +92,22 @@ DecodeSplitLayout decode_split_layout(int B, int Hq, int Hkv, int Nkv, int Bk, i
   const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks);
   L.nsplit = (Tk + part - 1) / part;
   L.words = (Tk + 63) / 64;
-  L.cw = decode_split_chunk(B, Hkv, Tk);
+  L.cw = decode_split_chunk(B, Hq, Hkv, Tk);
   L.nsub = (part + 4 * L.cw - 1) / (4 * L.cw);
   L.nparts = L.nsplit * L.nsub + 1;              // one partial per workgroup + one for a partly filled last block
   const size_t rows = (size_t)B * Hq;
   size_t off = 0;
   L.keys = off; off += align256(rows * Tk * sizeof(uint64_t));
   L.bitmap = off; off += align256(rows * L.words * sizeof(unsigned long long));
-  L.scores = off; off += align256(rows * Nkv * sizeof(float));
-  L.cmax = off; off += align256(rows * L.nsplit * L.nsub * 4 * sizeof(float));
+  // Two launches hand the scores over through memory; one launch does not need this.  Up to 320 partitions it is asked for all the
+  // same: which problems fit an array of fixed size (the static one among them) stays what it was.
+  const bool both = decode_split_both(B, Hkv, Tk);
+  L.scores = off; off += !both || (long)B * Hkv * L.nsplit <= 320 ? align256(rows * Nkv * sizeof(float)) : 0;
+  // the maxima of the chunks, or of the workgroups and a ticket for each partition: at most half as many words
+  L.cmax = L.tops = off;
+  L.tickets = off + rows * (L.nsplit * L.nsub + 1) * sizeof(unsigned);
+  off += align256(rows * L.nsplit * L.nsub * 4 * sizeof(float));
+  L.taken = off; off += !both && decode_split_selects(Tk, false) ? align256(rows * L.nparts * sizeof(uint32_t)) : 0;
   L.part_o = off; off += align256(rows * L.nparts * kHeadDim * sizeof(float));
   L.part_ml = off; off += align256(rows * L.nparts * 2 * sizeof(float));
   L.total = off;
@@ -369,7 +376,7 @@ size_t thrift_attn_decode_workspace(int B, int Hq, int Hkv, int Nkv, int D, int 
   const size_t least = thrift_attn_decode_least_workspace(B, Hq, Hkv, Nkv, D, Bk, split_blocks);
   if (least == 0 || Hq % Hkv != 0) return least;
   const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks), nsplit = (Tk + part - 1) / part;
-  if (!decode_split_wanted(B, Hq, Hkv, nsplit, split_blocks, true)) return least;   // lengths: the wider rule
+  if (!decode_split_wanted(B, Hq, Hkv, nsplit, split_blocks)) return least;
   const size_t split = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks).total;
   return split > least ? split : least;
 }
@@ -398,31 +405,33 @@ static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void
   if (thrift_status s = check_arch()) return s;
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  if (decode_split_wanted(B, Hq, Hkv, L.nsplit, split_blocks, seqlens != nullptr)) {
+  if (decode_split_wanted(B, Hq, Hkv, L.nsplit, split_blocks)) {
     const DecodeSplitLayout S = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks);
     if (workspace_bytes >= S.total) {              // a caller's (or the static) workspace may hold the one-pass form only
       DecodeSplitArgs s;
       DecodeArgs& a = s.a;
       unsigned long long* bitmap = (unsigned long long*)(ws + S.bitmap);
       const bool select = kneed > 0 || idx_out != nullptr || cnt_out != nullptr;
+      const bool both = decode_split_both(B, Hkv, Tk);
       // nobody asks for the lists and a row fits a wavefront: the scores pass selects
-      const bool in_pass = kneed > 0 && idx_out == nullptr && cnt_out == nullptr && decode_split_selects(Hq, Hkv, Tk);
+      const bool in_pass = kneed > 0 && idx_out == nullptr && cnt_out == nullptr && decode_split_selects(Tk, both);
       s.keys = in_pass ? (const uint64_t*)(ws + S.keys) : nullptr;
-      s.select_out = bitmap; s.fixed_k = fixed_k; s.ppm = fixed_k >= 0 ? 0 : budget_ppm(budget);
+      s.fixed_k = fixed_k; s.ppm = fixed_k >= 0 ? 0 : budget_ppm(budget);
+      s.tickets = (unsigned*)(ws + S.tickets); s.tops = (unsigned*)(ws + S.tops); s.clear = !select; s.both = both;
+      s.scores = (float*)(ws + S.scores); s.cmax = (float*)(ws + S.cmax); s.taken = (uint32_t*)(ws + S.taken); s.chunks = S.nsplit * S.nsub * 4;
+      s.cw = S.cw; s.nsub = S.nsub; s.items = S.nsplit * S.nsub + (seqlens ? 1 : 0); a.nsplit = S.nsplit;
       if (in_pass)
-        launch_decode_block_scores((const uint16_t*)q, dt == THRIFT_BF16 ? 1 : 0, kmean, seqlens, (uint64_t*)(ws + S.keys), B, Hq, Hkv, Tk, shared, st);
+        launch_decode_block_scores((const uint16_t*)q, dt == THRIFT_BF16 ? 1 : 0, kmean, seqlens, (uint64_t*)(ws + S.keys), B, Hq, Hkv, Tk, shared, both ? &s : nullptr, st);
       else if (select)
         launch_decode_select((const uint16_t*)q, dt == THRIFT_BF16 ? 1 : 0, kmean, seqlens, (uint64_t*)(ws + S.keys), bitmap, S.words,
-                             idx_out, cnt_out, kmax_out, B, Hq, Hkv, Tk, fixed_k, fixed_k >= 0 ? 0 : budget_ppm(budget), shared, st);
+                             idx_out, cnt_out, kmax_out, B, Hq, Hkv, Tk, fixed_k, fixed_k >= 0 ? 0 : budget_ppm(budget), shared, both ? &s : nullptr, st);
       a.q = (const uint16_t*)q; a.k16 = (const uint16_t*)k16; a.v16 = (const uint16_t*)v16;
       a.k4 = k4; a.ks = ks; a.v4 = v4; a.vs = vs; a.seqlens = seqlens;
       a.bitmap = kneed > 0 ? bitmap : nullptr; a.bitmap_words = S.words;
       a.out = out; a.part_o = (float*)(ws + S.part_o); a.part_ml = (float*)(ws + S.part_ml); a.order = nullptr;
-      a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.Nkv = Nkv; a.split_blocks = partition_blocks(Tk, split_blocks); a.nsplit = S.nsplit; a.nparts = S.nparts; a.nmerge = S.nparts;
+      a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.Nkv = Nkv; a.split_blocks = partition_blocks(Tk, split_blocks); a.nparts = S.nparts; a.nmerge = S.nparts;
       a.scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)D);
       a.dt = dt; a.out_dt = out_dt;
-      s.scores = (float*)(ws + S.scores); s.cmax = (float*)(ws + S.cmax);
-      s.cw = S.cw; s.nsub = S.nsub; s.chunks = S.nsplit * S.nsub * 4; s.items = S.nsplit * S.nsub + (seqlens ? 1 : 0);
       launch_decode_split(s, st);
       return after_launch();
     }
@@ -431,7 +440,7 @@ static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void
 
   // (i) the query token is its own block mean; score it against the cached key-block means and select
   launch_decode_select((const uint16_t*)q, dt == THRIFT_BF16 ? 1 : 0, kmean, seqlens, (uint64_t*)(ws + L.keys), bitmap, L.words, idx_out, cnt_out, kmax_out,
-                       B, Hq, Hkv, Tk, fixed_k, fixed_k >= 0 ? 0 : budget_ppm(budget), shared, st);
+                       B, Hq, Hkv, Tk, fixed_k, fixed_k >= 0 ? 0 : budget_ppm(budget), shared, nullptr, st);
 
   // (ii) split-K partial attention, (iii) log-sum-exp merge
   DecodeArgs a;

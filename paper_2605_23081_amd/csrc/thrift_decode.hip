@@ -628,7 +628,7 @@ constexpr int kScoreChunksPerWg = 8;
 
 __global__ void __launch_bounds__(256) decode_scores_kernel(const uint16_t* __restrict__ q16, int q_is_bf16, const float* __restrict__ kmean,
                                                             const int32_t* __restrict__ seqlens, uint64_t* __restrict__ keys,
-                                                            int Hq, int Hkv, int Tk, int shared, int per_wg) {
+                                                            int Hq, int Hkv, int Tk, int shared, int per_wg, unsigned* tickets, int nsplit, unsigned* tops, int items) {
   constexpr int kStride = kD + 4;
   __shared__ __align__(16) float kst[64 * kStride];
   __shared__ __align__(16) float qst[32 * kD];
@@ -640,6 +640,11 @@ __global__ void __launch_bounds__(256) decode_scores_kernel(const uint16_t* __re
   const int chunk0 = (blockIdx.x % groups) * per_wg, unit = blockIdx.x / groups;
   const int b = unit / Hkv, kvh = unit % Hkv;
   const int cap = seqlens ? min(Tk, (max(0, seqlens[b]) + kBk - 1) / kBk) : Tk;
+  if (tops != nullptr) {                                    // what the kernel behind counts and waits on
+    const int words = G * items, part = blockIdx.x % groups;
+    for (int e = part * 256 + tid; e < words; e += groups * 256) tops[(size_t)unit * words + e] = kUnset;
+    for (int e = part * 256 + tid; e < nsplit; e += groups * 256) tickets[unit * nsplit + e] = 0u;
+  }
   if (chunk0 * 64 >= cap) return;                           // uniform: nothing of these chunks is valid
   const int chunk_end = min(chunk0 + per_wg, (cap + 63) / 64);
   const float* kunit = kmean + (size_t)unit * Tk * kD;
@@ -818,18 +823,19 @@ __global__ void __launch_bounds__(256) decode_select_kernel(DecodeSelectArgs p, 
 }
 
 void launch_decode_block_scores(const uint16_t* q16, int q_is_bf16, const float* kmean, const int32_t* seqlens, uint64_t* keys,
-                                int B, int Hq, int Hkv, int Tk, int shared, hipStream_t st) {
+                                int B, int Hq, int Hkv, int Tk, int shared, const DecodeSplitArgs* split, hipStream_t st) {
   const int chunks = (Tk + 63) / 64;
   int per_wg = kScoreChunksPerWg;
   while (per_wg > 1 && (long)B * Hkv * ((chunks + per_wg - 1) / per_wg) < 512) per_wg /= 2;
   const int score_groups = (chunks + per_wg - 1) / per_wg;
-  decode_scores_kernel<<<dim3((unsigned)((long)B * Hkv * score_groups)), dim3(256), 0, st>>>(q16, q_is_bf16, kmean, seqlens, keys, Hq, Hkv, Tk, shared, per_wg);
+  decode_scores_kernel<<<dim3((unsigned)((long)B * Hkv * score_groups)), dim3(256), 0, st>>>(q16, q_is_bf16, kmean, seqlens, keys, Hq, Hkv, Tk, shared, per_wg, split ? split->tickets : nullptr,
+                                                                                                             split ? split->a.nsplit : 0, split ? split->tops : nullptr, split ? split->items : 0);
 }
 
 void launch_decode_select(const uint16_t* q16, int q_is_bf16, const float* kmean, const int32_t* seqlens, uint64_t* keys,
                           unsigned long long* bitmap, int words, int32_t* idx_out, int32_t* cnt_out, int kmax_out,
-                          int B, int Hq, int Hkv, int Tk, int fixed_k, long long ppm, int shared, hipStream_t st) {
-  launch_decode_block_scores(q16, q_is_bf16, kmean, seqlens, keys, B, Hq, Hkv, Tk, shared, st);
+                          int B, int Hq, int Hkv, int Tk, int fixed_k, long long ppm, int shared, const DecodeSplitArgs* split, hipStream_t st) {
+  launch_decode_block_scores(q16, q_is_bf16, kmean, seqlens, keys, B, Hq, Hkv, Tk, shared, split, st);
   const int chunks = (Tk + 63) / 64;
   DecodeSelectArgs p;
   p.keys = keys; p.seqlens = seqlens; p.bitmap = bitmap; p.idx_out = idx_out; p.cnt_out = cnt_out;

@@ -1,26 +1,33 @@
 // Decode for caches that give the one-workgroup-per-partition walk too few workgroups (short caches, few sequences).
 //
 // The rounding of P follows the running maximum of the partition, so a partition cannot simply be cut into shorter
-// recurrences.  It can be computed in two passes that need no order between workgroups:
-//   decode_split_scores_kernel  the raw scores of every (query head, key) and the largest score of every chunk;
-//   decode_split_values_kernel  softmax, P quantiser and P.V of a chunk, started from the largest score of the chunks in
-//                               front of it in the partition: every block sees the running maximum of its partition, as in
-//                               the serial walk.
+// recurrences.  It can be computed in two passes over chunks of a few key blocks:
+//   scores  the raw scores of every (query head, key) and the largest score of every chunk;
+//   values  softmax, P quantiser and P.V of a chunk, started from the largest score of the chunks in front of it in the
+//           partition: every block sees the running maximum of its partition, as in the serial walk.
+// A chunk belongs to ONE wavefront, which takes all heads of the KV group at once (a row or column of the matrix tiles each: up
+// to 8 heads cost the matrix instructions of one), with tiles in its own LDS and no barrier between its blocks.  Four chunks
+// that follow each other make a workgroup, whose partials are added up in LDS before they are written.
+//
+// Short sequences and many key blocks in all take one launch (pass BOTH): the scores stay in LDS instead of travelling through
+// memory twice (8 bytes per head and token next to 136 bytes of codes and scales), and V tiles of some workgroups fill the time
+// in which others wait for K.  There a workgroup publishes its largest scores and waits for those of the workgroups in front of
+// it in the partition.  Workgroups take their places in a partition by a ticket as they start, so that they wait only for
+// workgroups that run already and themselves wait only for still earlier ones: every wait ends, whatever else occupies the
+// chip.  Few workgroups with long partitions would mostly wait; there the passes are two launches.
+//
 // The scores come from 16 x 16 instead of 32 x 32 matrix instructions.  16-bit scores had equal bits in all of 16 million
 // compared; a 4-bit score is exact in both where the products of a row's group scales lie within 2^9 (14 bits hold the sum of
 // 128 products of two codes), so that all codes of P are the walk's and only the order of the fp32 sums differs.  With scales
 // spread over 2^40, 2.8 % of the scores differed in their last bit, neither side further from 64 bits than the other; a
 // probability on a rounding boundary may then fall to either side.
-// A chunk is `cw` key blocks and belongs to ONE wavefront, which takes all heads of the KV group at once (a row or
-// column of the matrix tiles each: up to 8 heads cost the matrix instructions of one), with tiles in its own LDS and no
-// barrier between its blocks.  Four chunks that follow each other make a workgroup,
-// whose partials are added up in LDS before they are written.
-// Measured against the walk, whole calls or serving steps: 301 -> 74 us for one sequence of 131072 tokens and 32/8 heads,
-// 306 -> 43 us for one of 32768, 544 -> 192 us for eight of 16384-32768 tokens and 64/8 heads at a 10 % budget (scores pass
-// 70 us, values pass 77 us).
-// What bounds it: for short caches the latency of the chain of launches; for long ones the bytes (the scores travel through
-// memory once more, 8 bytes per head and token next to 136 bytes of codes and scales per token), of which too few are in
-// flight: 4.9 to 5.7 TB/s read and written, against 7.1 of a plain streaming read, with 1.6 to 2.5 wavefronts per SIMD.
+//
+// Measured, whole calls or serving steps, the walk / two launches with a search for the selection everywhere / now: 306 / 41.1 /
+// 38.0 us for one sequence of 32768 tokens and 32/8 heads, 102 / 26.5 / 25.6 for one of 4096; 301 / 75.4 / 75.5 for one of 131072,
+// 544 / 172.8 / 155.8 for eight of 16384-32768 with 64/8 heads at 10 %, 148 / 55.0 / 47.9 for sixteen of 4096-8192 with shared
+// selection, - / 322.7 / 283.0 for sixteen of 16384-32768 at 25 %.
+// What bounds it: for short caches the chain of launches and of dependent loads inside them (a step of one sequence of 4096 tokens
+// reads 0.5 MB); for long ones too few bytes in flight per CU in the chunks' own chains, 5.0 to 5.7 TB/s of 7.1.
 #include <type_traits>
 
 #include "thrift_launch.h"
@@ -29,43 +36,6 @@
 namespace thrift {
 
 namespace {
-
-struct SplitWork {
-  int b, kvh;
-  int item;            // partial slot of the workgroup
-  int j0, j1;          // key blocks of this wavefront (may be none)
-  int first_chunk;     // first chunk of the partition
-  int chunk;           // this wavefront's chunk
-  int n_valid;         // tokens of a block: 64, or those of a partly filled last block
-  bool any;            // the workgroup has work
-  bool tail;           // the partly filled last block, a partition of its own
-};
-
-__device__ __forceinline__ SplitWork split_work(const DecodeSplitArgs& s, int wave) {
-  const DecodeArgs& a = s.a;
-  SplitWork w;
-  const int unit = blockIdx.x / s.items, item = blockIdx.x % s.items;
-  w.b = unit / a.Hkv; w.kvh = unit % a.Hkv; w.item = item;
-  const int len = a.seqlens ? min(a.Nkv, max(0, a.seqlens[w.b])) : a.Nkv;
-  const int full = len / kBk, rest = len % kBk;
-  w.n_valid = kBk;
-  w.chunk = item * 4 + wave;
-  w.tail = item == a.nsplit * s.nsub;
-  if (w.tail) {
-    w.any = rest > 0;
-    w.j0 = full; w.j1 = full + (rest > 0 && wave == 0 ? 1 : 0);
-    w.n_valid = rest;
-    w.first_chunk = w.chunk;
-  } else {
-    const int part = item / s.nsub, p0 = part * a.split_blocks, p1 = min(p0 + a.split_blocks, full);
-    const int base = p0 + (item % s.nsub) * 4 * s.cw;
-    w.any = base < p1;
-    w.j0 = min(base + wave * s.cw, p1);
-    w.j1 = min(w.j0 + s.cw, p1);
-    w.first_chunk = part * s.nsub * 4;
-  }
-  return w;
-}
 
 // Which heads of the group have promoted which of the (at most 32) blocks j0 .. : lane u < G holds head u's bits, bit 0 =
 // block j0.
@@ -99,6 +69,11 @@ __device__ __forceinline__ v4f mfma16(v8s x, v8s y, v4f acc) {
 //   C / D      column r, rows 4 g + i in register i
 // All 128 channels of a 4-bit score are one instruction, and a wavefront's load of 16 keys x 64 bytes is 1 KiB in a row.
 
+// A maximum that is not published yet (no sum of products of numbers has these bits), and how often it is asked for: some
+// hundred milliseconds.  Only a workspace that somebody else writes during the call lets the wait end without it; the result
+// then is NaN.
+constexpr int kSplitPolls = 1 << 19;
+
 // largest value over the lanes that hold the same head (lane % NH), in every one of them: first of each 32 lanes
 template <int NH>
 __device__ __forceinline__ float head_max32(float v) {
@@ -122,87 +97,106 @@ __device__ __forceinline__ float head_sum(float v) {
   return v + other_half(v);
 }
 
-// TopK of one row of at most 64 MAXC order keys by one wavefront: word c of the bitmap to out[c].  The k-th largest key is
-// searched bit by bit from the top, a step being a comparison and a scalar count per 64 keys: no barrier and no LDS, which
-// is what a step of the kernel of its own (decode_select_kernel) waits for.  Ties go to the smaller block id.
-template <int MAXC>
-__device__ __forceinline__ void wave_select(const uint64_t* keys, int vis, int k, int lane, unsigned long long* out) {
-  uint64_t key[MAXC];
+// Which of the blocks first .. first + n - 1 (at most 32) belong to the k largest of a row's order keys, ties to the smaller
+// block id: bit i for block first + i (own: lane i holds its key).  By one wavefront that holds the row, 64 keys per register.
+// A block is taken if fewer than k keys are larger.  A workgroup asks for its own blocks only: the counts for one block, most
+// often of the upper words alone, cost what one step of a search for the k-th largest key costs, of which that takes 25 to 30
+// one after the other.
+template <int NR>
+__device__ __forceinline__ uint32_t rank_select(const uint64_t (&key)[NR], uint64_t own, int k, int first, int n, int lane) {
+  uint32_t taken = 0u;
+  for (int i = 0; i < n; ++i) {
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(own >> 32), i);
+    int larger = 0;
 #pragma unroll
-  for (int c = 0; c < MAXC; ++c) key[c] = c * 64 + lane < vis ? keys[c * 64 + lane] : 0ULL;   // a key is never 0
-  uint64_t T = 0;
-  if (k < vis) {
-    // the upper words alone separate the keys but for a step or two: 32-bit comparisons, none above the largest key
-    uint32_t hi[MAXC], top = 0;
+    for (int c = 0; c < NR; ++c) larger += __popcll(__ballot((uint32_t)(key[c] >> 32) > hi));
+    if (larger >= k) continue;
+    const uint64_t x = ((uint64_t)hi << 32) | (uint32_t)__builtin_amdgcn_readlane((int)own, i);
+    larger = 0;                                            // larger, or equal with a smaller id
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-      hi[c] = (uint32_t)(key[c] >> 32);
-      top = max(top, hi[c]);
-    }
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) top = max(top, (uint32_t)__shfl_xor((int)top, d));
-    top = __builtin_amdgcn_readfirstlane(top);
-    uint32_t t = 0;
-    int n = 0;
-    for (int bit = 31; bit >= 0; --bit) {
-      const uint32_t cand = t | (1u << bit);
-      if (cand > top) continue;                            // no key
-      n = 0;
-#pragma unroll
-      for (int c = 0; c < MAXC; ++c)
-        if (c * 64 < vis) n += __popcll(__ballot(hi[c] >= cand));
-      if (n >= k) t = cand;
-      if (n == k) break;                                   // exactly the k largest lie at or above cand
-    }
-    T = (uint64_t)t << 32;
-    if (n != k)
-      for (int bit = 31; bit >= 0; --bit) {
-        const uint64_t cand = T | (1ULL << bit);
-        n = 0;
-#pragma unroll
-        for (int c = 0; c < MAXC; ++c)
-          if (c * 64 < vis) n += __popcll(__ballot(key[c] >= cand));
-        if (n >= k) T = cand;
-        if (n == k) break;
-      }
+    for (int c = 0; c < NR; ++c) larger += __popcll(__ballot(key[c] > x || (key[c] == x && 64 * c + lane < first + i)));
+    if (larger < k) taken |= 1u << i;
   }
-  int n_gt = 0;
-#pragma unroll
-  for (int c = 0; c < MAXC; ++c)
-    if (c * 64 < vis) n_gt += __popcll(__ballot(key[c] > T));
-  const int need = k - n_gt;                               // keys equal to T that are taken
-  int seen = 0;
-  const uint64_t below = (1ULL << lane) - 1ULL;
-#pragma unroll
-  for (int c = 0; c < MAXC; ++c) {
-    const bool tie = c * 64 + lane < vis && key[c] == T;
-    const uint64_t ties = __ballot(tie);
-    const uint64_t sel = __ballot(key[c] > T || (tie && seen + __popcll(ties & below) < need));
-    seen += __popcll(ties);
-    if (lane == 0) out[c] = sel;
-  }
+  return taken;
 }
 
-// NH: heads per KV group, rounded up to 1, 2, 4 or 8.  SELECT: the promoted blocks come from the order keys, selected by every
-// workgroup for itself (one row per wavefront) while its first tile is on its way; the first workgroup of a (sequence, KV head)
-// leaves the bitmap for the pass behind.  A step of a serving loop, with and without a launch for the selection: 26.2 / 28.8 us
-// (1 x 4096 tokens, 32/8 heads), 40.4 / 41.9 us (1 x 32768), 52.8 / 56.1 us (16 x 8192), 176.4 / 178.1 us (16 x 32768).
-template <typename T, int NH, bool SELECT>
-__global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplitArgs s) {
+// What one launch computes: everything (BOTH), or the raw scores and the largest of every chunk (SCORES) and what comes behind
+// them (VALUES).
+enum Pass { BOTH, SCORES, VALUES };
+
+// Key blocks per wavefront; with both passes in one the LDS holds their scores.
+constexpr int chunk_limit(int nh, bool both) { return both && nh > 4 ? kSplitMaxChunk / 2 : kSplitMaxChunk; }
+
+// NH: heads per KV group, rounded up to 1, 2, 4 or 8.
+// NR: the promoted blocks come from the order keys of rows of up to 64 NR key blocks, every workgroup asking for its own blocks
+// (a row or two per wavefront); 0: from the bitmap of a launch before.
+template <typename T, int NH, Pass PASS, int NR>
+__global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel(DecodeSplitArgs s) {
   const DecodeArgs& a = s.a;
-  __shared__ __align__(1024) unsigned char half_tiles[4][kTile16 / 2];
+  constexpr bool SELECT = NR > 0;
+  constexpr int kSlot = 4096 + 256;                            // codes and scales of a V block
+  constexpr int NC = PASS != BOTH ? 1 : chunk_limit(NH, true);
+  // per wavefront: half a 16-bit K tile; then two V blocks, which give way to its partial sums, and behind them its
+  // maxima and sums
+  constexpr int kTops = 2 * kSlot, kMl = kTops + 64, kOwn = PASS == SCORES ? kTile16 / 2 : kMl + 64;
+  __shared__ __align__(1024) unsigned char tiles[4][kOwn];
+  static_assert(NH * kD * 4 <= 2 * kSlot && kTile16 / 2 <= 2 * kSlot && NH * 8 <= 64, "they take the tile's place");
+  // BOTH: raw scores of the wavefront's blocks, [block][head][key]; those of a block give way to what P.V reads: the
+  // probabilities rounded to 16 bits [head][key], the codes of P [head][key / 2] and their E8M0 bytes [head][group].  Before the
+  // first scores: the workgroup's place in its partition and the heads' selections
+  __shared__ __align__(16) float scores[4][NC][NH * 64];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const SplitWork w = split_work(s, wave);
-  if (SELECT ? !w.any && w.item != 0 : w.j0 >= w.j1) return;       // uniform over the workgroup where there is a barrier below
+  // y: (partition, workgroup of it), or the partly filled last block.  Two launches walk through the cache of one unit after the
+  // other; where workgroups wait for each other the first places of all partitions of all units start first.
+  const unsigned units = (unsigned)(a.B * a.Hkv), unit_of_grid = PASS == BOTH ? blockIdx.x % units : blockIdx.x / s.items;
+  const int y = (int)(PASS == BOTH ? blockIdx.x / units : blockIdx.x % s.items);
+  const bool tail = y == a.nsplit * s.nsub;
+  const int part = tail ? 0 : PASS == BOTH ? y % a.nsplit : y / s.nsub;
+  const int len = __builtin_amdgcn_readfirstlane(a.seqlens ? min(a.Nkv, max(0, a.seqlens[unit_of_grid / a.Hkv])) : a.Nkv);
+  const int full = len / kBk, rest = len % kBk;
+  if (tail ? rest == 0 : part * a.split_blocks >= full) return;                  // uniform over the workgroup
+  // Where workgroups wait for each other they take the places of a partition in the order in which they start: whoever waits
+  // below for the ones in front of it waits for workgroups that run already.
+  if constexpr (PASS == BOTH) {
+    if (tid == 0) {
+      const int at = tail ? 0 : (int)atomicAdd(s.tickets + unit_of_grid * a.nsplit + part, 1u);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) reinterpret_cast<int*>(scores[v][0])[16] = at;
+    }
+  }
+  int unit = (int)unit_of_grid;
+  asm volatile("" : "+s"(unit));                               // scalar behind the branch: the DMA statements take scalar bases
   const int G = a.Hq / a.Hkv;
-  const size_t group0 = (size_t)w.b * a.Hq + (size_t)w.kvh * G, kh = (size_t)w.b * a.Hkv + w.kvh;
+  const size_t group0 = (size_t)(unit / a.Hkv) * a.Hq + (size_t)(unit % a.Hkv) * G, kh = (size_t)unit;
+  constexpr int kRows = NH > 4 ? 2 : 1;                        // rows of keys per wavefront: heads wave, wave + 4
+  uint64_t key[kRows][SELECT ? NR : 1];
+  const int vis = (len + kBk - 1) / kBk, Tk = a.Nkv / kBk;
+  if constexpr (SELECT && PASS != VALUES) {
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      const uint64_t* row = s.keys + (group0 + min(wave + 4 * u, G - 1)) * Tk;
+#pragma unroll
+      for (int c = 0; c < NR; ++c) key[u][c] = 64 * c + lane < vis ? row[64 * c + lane] : 0ULL;     // a key is never 0
+    }
+  }
+  int place = tail ? 0 : y % s.nsub;
+  if constexpr (PASS == BOTH) {
+    lds_barrier();
+    place = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(scores[wave][0])[16]);
+  }
+  const int item = tail ? y : part * s.nsub + place;           // partial slot
+  const int p1 = tail ? full + 1 : min((part + 1) * a.split_blocks, full);
+  const int base = tail ? full : part * a.split_blocks + place * 4 * s.cw;
+  if (base >= p1) return;                                      // uniform over the workgroup
+  const int j0 = min(base + wave * s.cw, p1), n_blocks = min(j0 + s.cw, p1) - j0;        // this wavefront's key blocks (may be none)
+  const int n_valid = tail ? rest : kBk;
   const uint8_t* k4base = a.k4 + kh * a.Nkv * 64;
   const uint8_t* ksbase = a.ks + kh * a.Nkv * 4;
   const uint8_t* k16base = reinterpret_cast<const uint8_t*>(a.k16 + kh * a.Nkv * kD);
   const uint32_t k4off = (uint32_t)(64 * r + 16 * g), ksoff = (uint32_t)(4 * r + g);   // key 16t + r, channels 32g .. 32g + 31
-
   const int all = (1 << G) - 1;
+  const float c = a.scale * 1.4426950408889634f;
 
   struct Keys {
     v4i k[4];            // key 16t + r, channels 32g .. 32g + 31
@@ -217,41 +211,48 @@ __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplit
     }
     return x;
   };
-  // a block that every head takes in 16 bits is not read in 4
-  Keys next;
-  uint32_t bits;
-  int Mnext;
-  if constexpr (SELECT) {
-    static_assert(NH <= 4, "a row per wavefront");
-    __shared__ unsigned long long sel[NH][kSplitSelectBlocks / 64];
-    const int vis = a.seqlens ? (min(a.Nkv, max(0, a.seqlens[w.b])) + kBk - 1) / kBk : a.Nkv / kBk;
-    const int k = decode_row_budget(vis, s.fixed_k, s.ppm);
-    if (w.j0 < w.j1 && k < vis) next = load4(w.j0);
-    if (wave < G) wave_select<kSplitSelectBlocks / 64>(s.keys + (group0 + wave) * (a.Nkv / kBk), vis, k, lane, sel[wave]);
-    __syncthreads();
-    if (w.item == 0 && tid < NH * (kSplitSelectBlocks / 64)) {
-      const int u = tid / (kSplitSelectBlocks / 64), word = tid % (kSplitSelectBlocks / 64);
-      if (u < G && word < a.bitmap_words) s.select_out[(group0 + u) * a.bitmap_words + word] = sel[u][word];
-    }
-    if (w.j0 >= w.j1) return;
-    bits = 0u;
-    if (lane < G) {
-      const int word = w.j0 >> 6, sh = w.j0 & 63;
-      unsigned long long x = sel[lane][word] >> sh;
-      if (sh != 0 && word + 1 < kSplitSelectBlocks / 64) x |= sel[lane][word + 1] << (64 - sh);
-      bits = (uint32_t)x;
-    }
-    Mnext = promoted_mask(bits, 0);
+  Keys kt;                                                     // of the next block, unless every head takes it in 16 bits
+  // which heads have promoted which of the wavefront's blocks: lane u < G holds head u's bits
+  uint32_t bits = 0u;
+  auto load_next = [&](int i) {
+    if (i < n_blocks && promoted_mask(bits, i) != all) kt = load4(j0 + i);
+  };
+  if constexpr (SELECT && PASS == VALUES) {
+    if (lane < G) bits = s.taken[(group0 + lane) * s.items + item] >> (wave * s.cw);
+  } else if constexpr (SELECT) {
+    const int k = decode_row_budget(vis, s.fixed_k, s.ppm), n = min(4 * s.cw, p1 - base);
+    if (n_blocks > 0 && k < vis) kt = load4(j0);
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+      if (wave + 4 * u < G) {
+        const uint64_t own = s.keys[(group0 + wave + 4 * u) * Tk + min(base + lane, Tk - 1)];
+        const uint32_t taken = k >= vis ? ~0u : rank_select(key[u], own, k, base, n, lane);
+        if (lane < 4) reinterpret_cast<uint32_t*>(scores[lane][0])[wave + 4 * u] = taken;
+        if (PASS == SCORES && lane == 0) s.taken[(group0 + wave + 4 * u) * s.items + item] = taken;
+      }
+    lds_barrier();
+    if (lane < G) bits = reinterpret_cast<const uint32_t*>(scores[wave][0])[lane] >> (wave * s.cw);
   } else {
-    bits = promoted_bits(a, group0, G, w.j0, lane);
-    Mnext = promoted_mask(bits, 0);
-    if (Mnext != all) next = load4(w.j0);
+    if (n_blocks > 0) bits = promoted_bits(a, group0, G, j0, lane);
+    if constexpr (PASS != VALUES) load_next(0);
   }
 
-  // the query rows as A operand: head r % NR in row r, so that every lane's accumulator registers i are heads
-  // (4 g + i) % NR; the lane quantises the MXFP4 group it carries
-  constexpr int NR = NH > 4 ? 8 : 4;
-  const int hq = r & (NR - 1);
+  unsigned char* slots = tiles[wave];
+  const uint32_t lds0 = lds_address(slots);
+  // 16-bit K rows by DMA, whole lines per instruction (only such reads may carry the streaming hint): row 4 q + g, its chunk c
+  // at position c ^ (row & 7).  Rows past the cached tokens reach only their own keys' scores, which are masked.
+  auto issue_k16 = [&](int j, int q0, int n) __attribute__((always_inline)) {
+    const uint8_t* tile = k16base + (size_t)__builtin_amdgcn_readfirstlane(j) * kTile16 + 1024 * q0;
+#pragma unroll
+    for (int q = 0; q < n; ++q) dma_b128<true>(tile + 1024 * q, (uint32_t)(256 * g + 16 * (r ^ (4 * (q & 1) + g))), lds0 + 1024 * q);
+  };
+  RowState st = {kEmptyMax, 0.f};
+  auto tops = [&](int v) { return reinterpret_cast<float*>(tiles[v] + kTops); };
+  if constexpr (PASS != VALUES) {   // ---- scores of the wavefront's blocks and the largest of them ----
+
+  // the query rows as A operand: head r % 4 (8) in row r, so that every lane's accumulator registers i are heads
+  // (4 g + i) % 4 (8); the lane quantises the MXFP4 group it carries
+  const int hq = r & (NH > 4 ? 7 : 3);
   const bool qlane = hq < G;
   const uint16_t* qrow = a.q + (group0 + (qlane ? hq : 0)) * kD;
   v4i qf4 = {0, 0, 0, 0};
@@ -284,64 +285,78 @@ __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplit
       }
     }
   };
-  const unsigned char* half_tile = half_tiles[wave];
-  const uint32_t lds0 = lds_address(half_tile);
   float top[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) top[i] = kEmptyMax;
-  float* out = s.scores + (group0 + h0) * a.Nkv + key0;
-  for (int j = w.j0; j < w.j1; ++j) {
-    const int M = Mnext;
-    float v4[NS][NV], v16[NS][NV];
-    if (M != all) {
-      v4f acc[4];
+  auto keep = [&](int i, int head, int key, float z) __attribute__((always_inline)) {
+    if constexpr (PASS == BOTH) scores[wave][i][head * 64 + key] = z;
+    else __builtin_nontemporal_store(z, s.scores + (group0 + head) * a.Nkv + (size_t)(j0 + i) * kBk + key);
+  };
+  // 4-bit scores of a block for all heads, 16-bit scores for those that have promoted it (which then replace the former)
+  auto scores4 = [&](const Keys& x, int i, int M) __attribute__((always_inline)) {
+    v4f acc[4];
+    float v4[NS][NV];
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
-        acc[t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(widen(qf4), widen(next.k[t]), (v4f){0.f, 0.f, 0.f, 0.f}, 4, 4, 0, qsc, 0, next.ks[t]);
-      mine(acc, v4);
-    }
-    Mnext = j + 1 < w.j1 ? promoted_mask(bits, j + 1 - w.j0) : all;
-    if (Mnext != all) next = load4(j + 1);
-    if (M != 0) {
-      // Half a tile of 32 keys at a time through the wavefront's own LDS: a DMA instruction reads four whole rows, and only
-      // reads of whole lines may carry the streaming hint (fragments read from memory directly are 64 bytes of a line each).
-      // Rows past the cached tokens reach only their own keys' scores, which are masked below.
-      const uint8_t* tile = k16base + (size_t)__builtin_amdgcn_readfirstlane(j) * kTile16;
-      v4f acc[4];
-      v8s qf[4];
-#pragma unroll
-      for (int s4 = 0; s4 < 4; ++s4)
-        qf[s4] = qlane ? *reinterpret_cast<const v8s*>(qrow + 32 * s4 + 8 * g) : (v8s){0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the reads of the half before are over
-        // row 4 q + g of the half; its chunk c stands at position c ^ (row & 7)
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-          dma_b128<true>(tile + 8192 * hf + 1024 * q, (uint32_t)(256 * g + 16 * (r ^ (4 * (q & 1) + g))), lds0 + 1024 * q);
-        vm_wait<0>();
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          acc[2 * hf + t] = (v4f){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int s4 = 0; s4 < 4; ++s4)
-            acc[2 * hf + t] = mfma16<T>(qf[s4], *reinterpret_cast<const v8s*>(half_tile + 4096 * t + 256 * r + 16 * ((4 * s4 + g) ^ (r & 7))), acc[2 * hf + t]);
-        }
-      }
-      mine(acc, v16);
-    }
+    for (int t = 0; t < 4; ++t)
+      acc[t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(widen(qf4), widen(x.k[t]), (v4f){0.f, 0.f, 0.f, 0.f}, 4, 4, 0, qsc, 0, x.ks[t]);
+    mine(acc, v4);
 #pragma unroll
     for (int q = 0; q < NS; ++q)
 #pragma unroll
-      for (int i = 0; i < NV; ++i)
-        if (h0 + i < G) {
-          float v = ((M >> (h0 + i)) & 1) ? v16[q][i] : v4[q][i];
-          if (key0 + 32 * q >= w.n_valid) v = -INFINITY;
-          __builtin_nontemporal_store(v, out + (size_t)i * a.Nkv + (size_t)j * kBk + 32 * q);
-          top[i] = fmaxf(top[i], v);
+      for (int u = 0; u < NV; ++u)
+        if (h0 + u < G) {
+          const float z = key0 + 32 * q < n_valid ? v4[q][u] : -INFINITY;
+          if (PASS == BOTH || ((M >> (h0 + u)) & 1) == 0) keep(i, h0 + u, key0 + 32 * q, z);
+          top[u] = fmaxf(top[u], ((M >> (h0 + u)) & 1) ? kEmptyMax : z);
         }
-  }
-  if (w.tail) return;                                          // a partition of its own: no chunk follows it
+  };
+  auto keep16 = [&](const v4f (&acc)[4], int i, int M) __attribute__((always_inline)) {
+    float v16[NS][NV];
+    mine(acc, v16);
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+      for (int u = 0; u < NV; ++u)
+        if (h0 + u < G && ((M >> (h0 + u)) & 1)) {
+          const float z = key0 + 32 * q < n_valid ? v16[q][u] : -INFINITY;
+          keep(i, h0 + u, key0 + 32 * q, z);
+          top[u] = fmaxf(top[u], z);
+        }
+  };
+  auto scores16 = [&](const v8s (&qf)[4], int t0, int n, v4f (&acc)[4]) __attribute__((always_inline)) {        // sub-tiles of 16 keys, from the tile's start
+#pragma unroll
+    for (int t = 0; t < n; ++t) {
+      acc[t0 + t] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s4 = 0; s4 < 4; ++s4)
+        acc[t0 + t] = mfma16<T>(qf[s4], *reinterpret_cast<const v8s*>(slots + 4096 * t + 256 * r + 16 * ((4 * s4 + g) ^ (r & 7))), acc[t0 + t]);
+    }
+  };
+  auto query16 = [&](v8s (&qf)[4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4)
+      qf[s4] = qlane ? *reinterpret_cast<const v8s*>(qrow + 32 * s4 + 8 * g) : (v8s){0, 0, 0, 0, 0, 0, 0, 0};
+  };
+
+    for (int i = 0; i < n_blocks; ++i) {
+      const int M = promoted_mask(bits, i);
+      if (M != all) scores4(kt, i, M);
+      load_next(i + 1);
+      if (M != 0) {
+        v4f acc[4];
+        v8s qf[4];
+        query16(qf);
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the reads of the half before are over
+          issue_k16(j0 + i, 8 * hf, 8);
+          vm_wait<0>();
+          scores16(qf, 2 * hf, 2, acc);
+        }
+        keep16(acc, i, M);
+      }
+    }
+
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     float m = top[i];                                          // over the 16 keys of the lane's row of lanes, then over the rows with the same heads
@@ -355,125 +370,135 @@ __global__ void __launch_bounds__(256, 4) decode_split_scores_kernel(DecodeSplit
       m = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     }
     m = fmaxf(m, other_half(m));
-    if (r == 0 && g < (NH > 4 ? 2 : 1) && h0 + i < G) s.cmax[(group0 + h0 + i) * s.chunks + w.chunk] = m;
+    if (r == 0 && g < (NH > 4 ? 2 : 1)) {
+      if (PASS == BOTH && h0 + i < NH) tops(wave)[h0 + i] = m;
+      if (PASS == SCORES && h0 + i < G && n_blocks > 0 && !tail) s.cmax[(group0 + h0 + i) * s.chunks + item * 4 + wave] = m;
+    }
   }
-}
+  }
+  if constexpr (PASS == SCORES) return;
 
-// Softmax layout: lane = NH kg + h holds the NH keys NH kg .. of head h, so that every step of the recurrence that is not
-// an exponential costs the heads of a group one instruction together, and each 32 lanes hold one MXFP4 group of P per head.
-// The operands of P.V (column = head) are formed through a few hundred bytes of the wavefront's own LDS.
-// The accumulators hold channel 8 (4 g + i) + e of head r in o[e][i]: row r of tile e is channel 8 r + e, because a lane's
-// 16 bytes of a 16-bit V row are 8 neighbouring channels, which are transposed against 8 rows inside the lane.
-template <typename T, int NH>
-__global__ void __launch_bounds__(256, 4) decode_split_values_kernel(DecodeSplitArgs s) {
-  const DecodeArgs& a = s.a;
-  constexpr int kSlot = 4096 + 256;                            // codes and scales of a V block
-  __shared__ __align__(1024) unsigned char slots[4][2][kSlot]; // per wavefront; its partial sums at the end
-  __shared__ __align__(16) uint16_t prow[4][NH * 64];          // probabilities rounded to 16 bits: [head][key]
-  __shared__ __align__(16) uint8_t pcode[4][NH * 32];          // codes of P: [head][key / 2]
-  __shared__ uint8_t pscale[4][NH * 2];                        // their E8M0 bytes: [head][group]
-  __shared__ float ml[4][NH][2];
-  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r = lane & 15;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const SplitWork w = split_work(s, wave);
-  if (!w.any) return;                                          // uniform over the workgroup
-  const int G = a.Hq / a.Hkv;
-  const size_t group0 = (size_t)w.b * a.Hq + (size_t)w.kvh * G, kh = (size_t)w.b * a.Hkv + w.kvh;
-  const float c = a.scale * 1.4426950408889634f;
-
+  const uint8_t* v4base = a.v4 + kh * (size_t)(a.Nkv / 64) * 4096;
+  const uint8_t* vsbase = a.vs + kh * (size_t)(a.Nkv / 32) * kD;
+  const uint8_t* v16base = reinterpret_cast<const uint8_t*>(a.v16 + kh * a.Nkv * kD);
+  const uint32_t v16off = (uint32_t)(2048 * g + 16 * r);
+  // The 4-bit tile of a block travels one block ahead of the arithmetic by LDS DMA, whole lines per instruction.  Its 256
+  // bytes of channels 8 R .. 8 R + 7 hold chunk c (channel 8 R + c / 2, token group c & 1) at position c ^ R, so that the
+  // 16 rows of a fragment lie in different banks.
+  const uint32_t dma_off = (uint32_t)(256 * g + 16 * (r ^ g));              // R = 4 m + g in instruction m
+  auto issue4 = [&](int j, int slot) {
+    const int j_ = __builtin_amdgcn_readfirstlane(j);
+    const uint32_t to = lds0 + (uint32_t)(__builtin_amdgcn_readfirstlane(slot) * kSlot);
+    uint32_t off = dma_off;
+    asm volatile("" : "+v"(off));                              // one offset kept, not four
+#pragma unroll
+    for (int m = 0; m < 4; ++m) dma_b128<true>(v4base + (size_t)j_ * 4096 + 1024 * m, off ^ (64u * m), to + 1024 * m);
+    dma_b32<true>(vsbase + (size_t)j_ * 256, (uint32_t)(4 * lane), to + 4096);
+  };
+  // Half q of the 16-bit rows of a block, keys 32 q + 8 g .. + 7, channels 8 r ..
+  v4i v[8];
+  auto load16 = [&](int j, int q0) __attribute__((always_inline)) {
+    const uint8_t* tile = v16base + (size_t)j * kTile16 + 8192 * q0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(tile + v16off + 256 * u));
+  };
+  int Mnext = n_blocks > 0 ? promoted_mask(bits, 0) : all;
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // the last reads of K are over
+  if (Mnext != all) issue4(j0, 0);
+  // ---- the running maximum in front of the wavefront's blocks ----
   const int h = lane & (NH - 1), kg = lane / NH;               // softmax layout
-  const size_t qh = group0 + min(h, G - 1);                    // lanes of a padding head follow the last one and are never read
-  RowState st = {kEmptyMax, 0.f};
+  const int hg = min(h, G - 1);                                // lanes of a padding head follow the last one and are never read
+  // VALUES: the scores of a block are asked for one block ahead
+  struct Scores { float v[NH]; };
+  const float* sbase = s.scores + group0 * a.Nkv;              // scalar; the lane's head and keys in 32 bits
+  const uint32_t soff = (uint32_t)(hg * a.Nkv + NH * kg);
+  auto load_scores = [&](int j) {
+    Scores x;
+    if constexpr (NH >= 4) {
+#pragma unroll
+      for (int u = 0; u < NH; u += 4) {
+        const float4 z = *reinterpret_cast<const float4*>(sbase + (size_t)j * kBk + soff + u);
+        x.v[u] = z.x; x.v[u + 1] = z.y; x.v[u + 2] = z.z; x.v[u + 3] = z.w;
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < NH; ++u) x.v[u] = (sbase + (size_t)j * kBk)[soff + u];
+    }
+    return x;
+  };
+  Scores next;
+  float m = kEmptyMax;
+  if constexpr (PASS == VALUES) {
+    if (n_blocks > 0) next = load_scores(j0);
+    const int ahead = n_blocks > 0 && !tail ? place * 4 + wave : 0;              // chunks of the partition in front
+    const float* cm = s.cmax + (group0 + hg) * s.chunks + item * 4 + wave - ahead;
+    for (int e = kg; e < ahead; e += 64 / NH) m = fmaxf(m, cm[e]);
+  } else {
+    lds_barrier();
+    unsigned* published = s.tops + (group0 + hg) * s.items + item;
+    if (wave == 0 && lane < G && !tail) {
+      const uint32_t t = __float_as_uint(fmaxf(fmaxf(tops(0)[lane], tops(1)[lane]), fmaxf(tops(2)[lane], tops(3)[lane])));
+      __hip_atomic_store(published, t == kUnset ? 0x7fc00000u : t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    for (int e = kg; e < place; e += 64 / NH) {
+      uint32_t x = __hip_atomic_load(published - place + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int tries = 0; x == kUnset && tries < kSplitPolls; ++tries) {
+        __builtin_amdgcn_s_sleep(1);
+        x = __hip_atomic_load(published - place + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (x == kUnset) st.l = __uint_as_float(0x7fc00000u);
+      m = fmaxf(m, __uint_as_float(x));
+    }
+    for (int u = 0; u < wave; ++u) m = fmaxf(m, tops(u)[hg]);
+  }
+  m = head_max32<NH>(m);
+  st.m = fmaxf(m, other_half(m));
+
+  // ---- softmax, codes of P and P.V of the wavefront's blocks ----
+  // Softmax layout: lane = NH kg + h holds the NH keys NH kg .. of head h, so that every step of the recurrence that is not
+  // an exponential costs the heads of a group one instruction together, and each 32 lanes hold one MXFP4 group of P per head.
+  // The accumulators hold channel 8 (4 g + i) + e of head r in o[e][i]: row r of tile e is channel 8 r + e, because a lane's
+  // 16 bytes of a 16-bit V row are 8 neighbouring channels, which are transposed against 8 rows inside the lane.
   v4f o[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) o[e] = (v4f){0.f, 0.f, 0.f, 0.f};
-
-  if (w.j0 < w.j1) {
-    const uint8_t* v4base = a.v4 + kh * (size_t)(a.Nkv / 64) * 4096;
-    const uint8_t* vsbase = a.vs + kh * (size_t)(a.Nkv / 32) * kD;
-    const uint8_t* v16base = reinterpret_cast<const uint8_t*>(a.v16 + kh * a.Nkv * kD);
-    const uint32_t v16off = (uint32_t)(2048 * g + 16 * r);
-    // The 4-bit tile of a block travels one block ahead of the arithmetic by LDS DMA, whole lines per instruction.  Its 256
-    // bytes of channels 8 R .. 8 R + 7 hold chunk c (channel 8 R + c / 2, token group c & 1) at position c ^ R, so that the
-    // 16 rows of a fragment lie in different banks.
-    const uint32_t lds0 = lds_address(&slots[wave][0][0]);
-    const uint32_t dma_off = (uint32_t)(256 * g + 16 * (r ^ g));              // R = 4 m + g in instruction m
-    auto issue4 = [&](int j, int slot) {
-      const int j_ = __builtin_amdgcn_readfirstlane(j);
-      const uint32_t to = lds0 + (uint32_t)(__builtin_amdgcn_readfirstlane(slot) * kSlot);
-      uint32_t off = dma_off;
-      asm volatile("" : "+v"(off));                            // one offset kept, not four
-#pragma unroll
-      for (int m = 0; m < 4; ++m) dma_b128<true>(v4base + (size_t)j_ * 4096 + 1024 * m, off ^ (64u * m), to + 1024 * m);
-      dma_b32<true>(vsbase + (size_t)j_ * 256, (uint32_t)(4 * lane), to + 4096);
-    };
-    const float* sbase = s.scores + group0 * a.Nkv;                          // scalar; the lane's head and keys in 32 bits
-    const uint32_t soff = (uint32_t)(min(h, G - 1) * a.Nkv + NH * kg);
-    uint16_t* prow_w = prow[wave];
-    uint8_t* pcode_w = pcode[wave];
-    uint8_t* pscale_w = pscale[wave];
-    const uint32_t bits = promoted_bits(a, group0, G, w.j0, lane);
-    const int all = (1 << G) - 1, n_blocks = w.j1 - w.j0;
-    struct Scores { float v[NH]; };
-    auto load_scores = [&](int j) {
-      Scores x;
-      if constexpr (NH >= 4) {
-#pragma unroll
-        for (int u = 0; u < NH; u += 4) {
-          const float4 y = *reinterpret_cast<const float4*>(sbase + (size_t)j * kBk + soff + u);
-          x.v[u] = y.x; x.v[u + 1] = y.y; x.v[u + 2] = y.z; x.v[u + 3] = y.w;
-        }
-      } else {
-#pragma unroll
-        for (int u = 0; u < NH; ++u) x.v[u] = (sbase + (size_t)j * kBk)[soff + u];
-      }
-      return x;
-    };
-    // keys 32 q + 8 g .. + 7 of block j, channels 8 r ..
-    auto load16 = [&](int j, int q, v4i (&row)[8]) {
-      const uint8_t* tile = v16base + (size_t)j * kTile16 + 8192 * q;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) row[u] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(tile + v16off + 256 * u));
-    };
-    // rows past the cached tokens hold whatever lies there, and zero times that need not be zero
-    auto clear16 = [&](int q, v4i (&row)[8]) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (32 * q + 8 * g + u >= w.n_valid) row[u] = (v4i){0, 0, 0, 0};
-    };
-    int Mnext = promoted_mask(bits, 0);
-    if (Mnext != all) issue4(w.j0, 0);
-    Scores next = load_scores(w.j0);
-    // running maximum in front of the chunk
-    const int ahead = w.chunk - w.first_chunk;
-    if (ahead > 0) {
-      const float* cm = s.cmax + qh * s.chunks + w.first_chunk;
-      float m = kEmptyMax;
-      for (int e = kg; e < ahead; e += 64 / NH) m = fmaxf(m, cm[e]);
-      m = head_max32<NH>(m);
-      st.m = fmaxf(m, other_half(m));
-    }
+  if (n_blocks > 0) {
     for (int i = 0; i < n_blocks; ++i) {
-      const int j = w.j0 + i;
+      const int j = j0 + i;
       const int M = Mnext;
-      // everything in flight was asked for a block ago: the scores of this one and its 4-bit tile.  The statements on the
-      // registers keep the compiler from waiting for the scores again behind the loads issued next.
-      vm_wait<0>();
-      Scores x = next;
+      vm_wait<0>();                                            // the tiles of this block, asked for a block ago or earlier
+      float x[NH];
+      if constexpr (PASS == VALUES) {
 #pragma unroll
-      for (int u = 0; u < NH; ++u) asm volatile("" : "+v"(x.v[u]));
-      v4i v[8];
-      if (M != 0) load16(j, 0, v);                             // needed after the softmax
-      Mnext = i + 1 < n_blocks ? promoted_mask(bits, i + 1) : all;
-      if (Mnext != all) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the reads of the slot's last block are over
-        issue4(j + 1, (i + 1) & 1);
+        for (int u = 0; u < NH; ++u) {
+          x[u] = next.v[u];
+          asm volatile("" : "+v"(x[u]));                       // no second wait for them behind the loads issued next
+        }
+        if (i + 1 < n_blocks) next = load_scores(j + 1);
+      } else {
+        const float* own = scores[wave][i] + hg * 64 + NH * kg;
+        if constexpr (NH >= 4) {
+#pragma unroll
+          for (int u = 0; u < NH; u += 4) {
+            const float4 z = *reinterpret_cast<const float4*>(own + u);
+            x[u] = z.x; x[u + 1] = z.y; x[u + 2] = z.z; x[u + 3] = z.w;
+          }
+        } else {
+#pragma unroll
+          for (int u = 0; u < NH; ++u) x[u] = own[u];
+        }
       }
-      if (i + 1 < n_blocks) next = load_scores(j + 1);
+      uint16_t* prow_w = reinterpret_cast<uint16_t*>(scores[wave][PASS == BOTH ? i : 0]);
+      uint8_t* pcode_w = reinterpret_cast<uint8_t*>(prow_w + NH * 64);
+      uint8_t* pscale_w = pcode_w + NH * 32;
+      if (M != 0) load16(j, 0);                                // needed after the softmax
+      Mnext = i + 1 < n_blocks ? promoted_mask(bits, i + 1) : all;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the scores are here, the reads of the other slot's block are over
+      if (Mnext != all) issue4(j + 1, (i + 1) & 1);
       // ---- online softmax (Alg. 1 steps 10-12 / 16-17) of all heads ----
-      float gmax = x.v[0];
+      float gmax = x[0];
 #pragma unroll
-      for (int u = 1; u < NH; ++u) gmax = fmaxf(gmax, x.v[u]);
+      for (int u = 1; u < NH; ++u) gmax = fmaxf(gmax, x[u]);
       gmax = head_max32<NH>(gmax);                             // the lane's 32-key group
       const uint32_t gb = __float_as_uint(gmax);
       const auto s32 = __builtin_amdgcn_permlane32_swap(gb, gb, false, false);
@@ -495,7 +520,7 @@ __global__ void __launch_bounds__(256, 4) decode_split_values_kernel(DecodeSplit
       float p[NH];
 #pragma unroll
       for (int u = 0; u < NH; ++u) {
-        p[u] = fast_exp2(__builtin_fmaf(x.v[u], c, -mc));
+        p[u] = fast_exp2(__builtin_fmaf(x[u], c, -mc));
         st.l += p[u];
       }
       if (M != all) {
@@ -525,7 +550,7 @@ __global__ void __launch_bounds__(256, 4) decode_split_values_kernel(DecodeSplit
           pbl = pscale_w[r * 2 + g];
         }
         const v8i pq8 = widen(pq);
-        const unsigned char* slot = slots[wave][i & 1];
+        const unsigned char* slot = slots + (i & 1) * kSlot;
         const uint2 vs = *reinterpret_cast<const uint2*>(slot + 4096 + (g & 1) * kD + 8 * r);
         const uint32_t frag = (uint32_t)(256 * r + 16 * (r ^ (g & 1)));     // groups 2 and 3 meet zeros of P: anything finite
 #define THRIFT_PV4(E) o[E] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(widen(*reinterpret_cast<const v4i*>(slot + (frag ^ (32u * (E))))), pq8, o[E], 4, 4, (E) & 3, (E) < 4 ? vs.x : vs.y, 0, pbl);
@@ -543,9 +568,13 @@ __global__ void __launch_bounds__(256, 4) decode_split_values_kernel(DecodeSplit
         for (int q = 0; q < 2; ++q) {                          // keys 32 q + 8 g .. + 7
           if (q == 1) {
             __builtin_amdgcn_sched_barrier(0);                 // into the registers of the first half
-            load16(j, 1, v);
+            load16(j, 1);
           }
-          if (w.n_valid != kBk) clear16(q, v);
+          if (n_valid != kBk) {                                // rows past the cached tokens hold whatever lies there, and zero times that need not be zero
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+              if (32 * q + 8 * g + u >= n_valid) v[u] = (v4i){0, 0, 0, 0};
+          }
           const v8s pf = mine ? *reinterpret_cast<const v8s*>(prow_w + r_ * 64 + 32 * q + 8 * g_) : (v8s){0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
@@ -562,20 +591,21 @@ __global__ void __launch_bounds__(256, 4) decode_split_values_kernel(DecodeSplit
         }
       }
     }
-    static_assert(NH * kD * 4 <= 2 * kSlot, "the sums of a wavefront take the place of its tiles");
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (r < G) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        float* to = reinterpret_cast<float*>(slots[wave][0]) + r * kD + 8 * (4 * g + i);
+        float* to = reinterpret_cast<float*>(slots) + r * kD + 8 * (4 * g + i);
         *reinterpret_cast<float4*>(to) = make_float4(o[0][i], o[1][i], o[2][i], o[3][i]);
         *reinterpret_cast<float4*>(to + 4) = make_float4(o[4][i], o[5][i], o[6][i], o[7][i]);
       }
     }
   }
+  auto ml = [&](int v, int u) { return reinterpret_cast<float*>(tiles[v] + kMl) + 2 * u; };
   {
+    float* own_ml = ml(wave, 0);
     const float l = head_sum<NH>(st.l);
-    if (lane < NH) { ml[wave][lane][0] = st.m; ml[wave][lane][1] = l; }
+    if (lane < NH) { own_ml[2 * lane] = st.m; own_ml[2 * lane + 1] = l; }
   }
   __syncthreads();
   // the workgroup's partial.  A wavefront without blocks has left its sums unwritten; it is skipped by its row sum of zero
@@ -583,23 +613,30 @@ __global__ void __launch_bounds__(256, 4) decode_split_values_kernel(DecodeSplit
   // compared, because comparisons of numbers are compiled as if there were no NaN).
   for (int e = tid; e < G * kD; e += 256) {
     const int u = e >> 7, ch = e & (kD - 1);
-    float m = ml[0][u][0];
+    float m = ml(0, u)[0];
 #pragma unroll
-    for (int v = 1; v < 4; ++v) m = fmaxf(m, ml[v][u][0]);
+    for (int v = 1; v < 4; ++v) m = fmaxf(m, ml(v, u)[0]);
     float l = 0.f, sum = 0.f;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const float lv = ml[v][u][1];
+      const float lv = ml(v, u)[1];
       if (__float_as_uint(lv) != 0u) {
-        const float f = fast_exp2((ml[v][u][0] - m) * c);
+        const float f = fast_exp2((ml(v, u)[0] - m) * c);
         l += f * lv;
-        sum += f * reinterpret_cast<const float*>(slots[v][0])[u * kD + ch];
+        sum += f * reinterpret_cast<const float*>(tiles[v])[u * kD + ch];
       }
     }
-    const size_t slot = (group0 + u) * a.nparts + w.item;
+    const size_t slot = (group0 + u) * a.nparts + item;
     a.part_o[slot * kD + ch] = sum;
     if (ch == 0) { a.part_ml[2 * slot] = m; a.part_ml[2 * slot + 1] = l; }
   }
+}
+
+// The tickets and maxima of a call without selection (otherwise decode_scores_kernel clears them).
+__global__ void __launch_bounds__(256) decode_split_clear_kernel(unsigned* tickets, int n_tickets, unsigned* tops, long n_tops) {
+  const long at = (long)blockIdx.x * 256 + threadIdx.x;
+  if (at < n_tickets) tickets[at] = 0u;
+  if (at < n_tops) tops[at] = kUnset;
 }
 
 // Log-sum-exp merge of the partials of one (sequence, query head): 32 channel quads x 8 slots at a time, so that the
@@ -653,40 +690,54 @@ __global__ void __launch_bounds__(256) decode_split_merge_kernel(DecodeSplitArgs
 // The split is used where the walk over whole partitions leaves the chip idle.  A walk takes its 256 key blocks one after
 // the other whatever else runs, so with fewer workgroups than the CUs take at once (two each) its time does not shrink.
 // Groups of more than 8 heads do not fit the row layout.  Partitions of at most 16 blocks are short walks already.
-// Above kSplitMaxItems the walk is the faster one (32/8 heads at 5 %, walk / two passes: 315 / 322 us for 6 x 131072 tokens,
-// 353 / 418 us for 8, 681 / 804 us for 16; 16/8 heads, 16 x 65536: 282 / 321 us), but for one query head per KV head in a
-// cache of one or two partitions that has lengths: three of a walk's four wavefronts have no head there, its partitions are
-// seldom full, and the scores cost 8 bytes a token.  A serving step with 16/16 heads: 242 / 220 us (16 x 32768 tokens, 5 %),
-// 344 / 300 us (25 %), 727 / 586 us (100 %), 255 / 167 us (14 x 24576, 10 %); without lengths 249 / 266 us (8 x 65536, 5 %).
-bool decode_split_wanted(int B, int Hq, int Hkv, int nsplit, int split_blocks, bool lengths) {
+// Partitions, walk / one launch: 384: 319 / 275 us (6 x 131072 tokens, 32/8 heads, 5 %), 304 / 230 (16 x 40960); 512: 355 / 366 (8 x
+// 131072), 678 / 685 (the same at 25 %), 574 / 528 (16 x 51200, 64/8, 10 %); 1024: 692 / 697 (16 x 131072).  With one query head per
+// KV head three of a walk's four wavefronts have no head: 512: 245 / 194 us (a serving step, 16 x 32768, 16/16), 248 / 237 (8 x 65536).
+bool decode_split_wanted(int B, int Hq, int Hkv, int nsplit, int split_blocks) {
   if (Hq / Hkv > 8) return false;
   if (nsplit > 1 && split_blocks <= 16) return false;
-  return (long)B * Hkv * nsplit <= (lengths && Hq == Hkv && nsplit <= 2 ? kSplitMaxItemsOneHead : kSplitMaxItems);
+  return (long)B * Hkv * nsplit <= (Hq == Hkv ? kSplitMaxItemsOneHead : kSplitMaxItems);
 }
 
-// With more heads a wavefront would select two rows one after the other: 58.6 us against 57.5 us for 2 x 20480 tokens, 64/8 heads.
-bool decode_split_selects(int Hq, int Hkv, int Tk) { return Hq / Hkv <= 4 && Tk <= kSplitSelectBlocks; }
+constexpr int kSelectBoth = 128;
 
-// Key blocks per wavefront: eight to sixteen wavefronts per CU where there are so many blocks, one block each below that.  Longer
-// chunks are longer serial chains, shorter ones more partials and more running maxima to look up.  Chunks of 1 / 2 / 4 / 8,
-// whole serving steps or calls in us (B x tokens, heads, budget):
-//    512 blocks   1 x 4096, 32/8, 5 %      27.9 /  31.6 /  33.7 /  41.3   takes 1
-//   4096          1 x 32768, 32/8, 5 %     47.7 /  41.4 /  43.9 /  49.2         2
-//                 1 x 16384, 16/16, 5 %    37.8 /  31.9 /  32.4 /  36.4         2
-//  16384          1 x 131072, 32/8, 5 %    99.9 /  81.3 /  76.2 /  76.5         8
-//                 16 x 8192, shared, 5 %   79.2 /  60.2 /  54.6 /  54.6         8
-//                 4 x 32768, 32/8, 5 %     94.2 /  74.9 /  68.9 /  74.6         8
-//                 4 x 32768, 64/8, 100 %  128.5 / 124.0 / 122.8 / 142.7         8
-//  32768          8 x 32768, 64/8, 10 %   193.4 / 175.5 / 174.1 / 171.3         8
-//                 16 x 16384, 32/8, 5 %   146.5 / 108.2 /  98.8 / 102.6         8
-//  65536          16 x 32768, 32/8, 25 %  367.3 / 319.2 / 315.2 / 318.0         8
-//                 8 x 32768, 16/16, 10 %  209.6 / 150.2 / 128.0 / 126.3         8
-// The line between 4 and 8 is not the best one for all of them: few sequences of uneven lengths would gain up to 14 % by 4, others
-// lose 1 to 2 %.
-int decode_split_chunk(int B, int Hkv, int Tk) {
+// One launch for both passes, or two.  One launch reads and writes no scores and saves the gap between two; but the places of a
+// partition wait for each other, and with few of them in long partitions that wait is what the call takes.  Up to kSelectBoth key
+// blocks a sequence nobody waits for long.  Two / one in us, B x tokens, heads, budget:
+//   short      1 x 512, 32/8, 5 %   25.7 /  23.0    10 x 3072, 64/8, 5 %     41.6 /  32.5    16 x 3072, 32/8, 5 %   41.0 / 37.8
+//   <= 8192    1 x 32768, 32/8      38.0 /  51.7    3 x 20480, 32/8, 100 %   63.0 /  67.5    1 x 65536, 32/8, 5 %   51.6 / 56.3
+//   more       4 x 32768, 32/8      73.5 /  67.4    1 x 131072, 32/8, 5 %    80.4 /  75.5    4 x 32768, 64/8, 100 %  147 /  105
+bool decode_split_both(int B, int Hkv, int Tk) { return Tk <= kSelectBoth || (long)B * Hkv * Tk > 8192; }
+
+// Where the kernels select for themselves instead of a launch of its own: rows of key blocks that a wavefront holds, and with one
+// launch (whose workgroups ask for more blocks each, among others that wait) only as many as two registers hold: 156 us with a
+// launch, 175 without for 8 x 32768 tokens, 64/8 heads; 47.9 us without for 16 x 8192.
+bool decode_split_selects(int Tk, bool both) { return Tk <= (both ? kSelectBoth : kSplitSelectBlocks); }
+
+// Key blocks per wavefront.  Longer chunks are longer serial chains, shorter ones more partials and more running maxima to look
+// up.  Chunks of 1 / 2 / 4 / 8, whole serving steps or calls in us (blocks of all KV heads; B x tokens, heads, budget):
+//   one launch
+//     512 blocks   1 x 4096, 32/8, 5 %      25.6 /  28.7 /  32.9 /  42.4   takes 1
+//    2048          8 x 2048, 32/8, 5 %      27.9 /  29.5                        2
+//    2048          4 x 4096, 32/8, 5 %             28.7 /  30.1                 2
+//    6144          6 x 8192, 16/8, 5 %                    38.5                  4
+//   16384          1 x 131072, 32/8, 5 %   115.5 /  88.6 /  78.0 /  76.4         8
+//                  16 x 8192, shared, 5 %   80.5 /  60.1 /  54.0 /  47.5         8
+//                  4 x 32768, 64/8, 100 %  145.2 / 119.0 / 105.9               4 (eight heads: no more fit the LDS)
+//   65536          16 x 32768, 32/8, 25 %  377.4 / 304.7 / 277.6 / 279.7         8
+//   two launches
+//    1280 blocks   1 x 10240, 32/8, 5 %     29.2 /  31.6 /  36.8              takes 1
+//    2560          1 x 20480, 32/8, 5 %     36.3 /  34.7 /  39.0                  2
+//    7168          2 x 28672, 32/8, 25 %    66.1 /  62.7 /  70.9                  2
+//    8192          1 x 65536, 32/8, 5 %     62.2 /  52.7 /  51.6                  4
+//                  4 x 16384, 64/8, 5 %     87.6 /  71.0 /  63.4                  4
+//    3072          2 x 12288, 64/8, 5 %     43.0 /  46.1 /  50.1                  1 (more than four heads: up to 4096)
+int decode_split_chunk(int B, int Hq, int Hkv, int Tk) {
   const long blocks = (long)B * Hkv * Tk;
+  const int heads = Hq / Hkv;
+  if (!decode_split_both(B, Hkv, Tk)) return blocks < (heads > 4 ? 4096 : 2048) ? 1 : blocks < 8192 ? 2 : 4;
   int cw = 1;
-  while (cw < kSplitMaxChunk && blocks >= 4096L * cw) cw *= 2;
+  while (cw < chunk_limit(heads, true) && blocks > 1536L * cw) cw *= 2;
   return cw;
 }
 
@@ -694,11 +745,21 @@ void launch_decode_split(const DecodeSplitArgs& s, hipStream_t st) {
   const DecodeArgs& a = s.a;
   const dim3 grid((unsigned)((long)a.B * a.Hkv * s.items)), block(256);
   const int G = a.Hq / a.Hkv;
-#define THRIFT_SPLIT(T, NH)                                            \
-  do {                                                                 \
-    if (s.keys != nullptr) decode_split_scores_kernel<T, NH, (NH <= 4)><<<grid, block, 0, st>>>(s);  \
-    else decode_split_scores_kernel<T, NH, false><<<grid, block, 0, st>>>(s);                        \
-    decode_split_values_kernel<T, NH><<<grid, block, 0, st>>>(s);      \
+  if (s.clear && s.both) {
+    const long n_tops = (long)a.B * a.Hq * s.items;
+    decode_split_clear_kernel<<<dim3((unsigned)((n_tops + 255) / 256)), block, 0, st>>>(s.tickets, a.B * a.Hkv * a.nsplit, s.tops, n_tops);
+  }
+#define THRIFT_SPLIT(T, NH)                                                                               \
+  do {                                                                                                    \
+    if (s.both && s.keys != nullptr) decode_split_kernel<T, NH, BOTH, kSelectBoth / 64><<<grid, block, 0, st>>>(s);       \
+    else if (s.both) decode_split_kernel<T, NH, BOTH, 0><<<grid, block, 0, st>>>(s);                      \
+    else if (s.keys != nullptr) {                                                                         \
+      decode_split_kernel<T, NH, SCORES, kSplitSelectBlocks / 64><<<grid, block, 0, st>>>(s);             \
+      decode_split_kernel<T, NH, VALUES, kSplitSelectBlocks / 64><<<grid, block, 0, st>>>(s);             \
+    } else {                                                                                              \
+      decode_split_kernel<T, NH, SCORES, 0><<<grid, block, 0, st>>>(s);                                   \
+      decode_split_kernel<T, NH, VALUES, 0><<<grid, block, 0, st>>>(s);                                   \
+    }                                                                                                     \
   } while (0)
 #define THRIFT_SPLIT_T(T)                  \
   do {                                     \

@@ -80,34 +80,39 @@ int decode_order_items(int B, int Hkv, int nsplit);
 // Two-pass decode for caches that leave the chip idle otherwise (thrift_decode_split.hip)
 struct DecodeSplitArgs {
   DecodeArgs a;           // nparts: partial slots per head here: nsplit * nsub + 1; bitmap may be nullptr (no block promoted)
-  float* scores;          // [B,Hq,Nkv] raw scores
-  float* cmax;            // [B,Hq,chunks] largest raw score of every chunk
+  float* scores;          // two launches: [B,Hq,Nkv] raw scores
+  float* cmax;            // two launches: [B,Hq,chunks] largest raw score of every chunk
+  uint32_t* taken;        // two launches, with keys: [B,Hq,items] which of the workgroup's blocks the head has promoted, bit i = its block i
+  unsigned* tickets;      // one launch: [B,Hkv,nsplit] workgroups of a partition that have started
+  unsigned* tops;         // one launch: [B,Hq,items] largest raw score of every workgroup's blocks, as it becomes known
   int cw;                 // key blocks per chunk (wavefront)
   int nsub;               // workgroups (of four chunks) per partition
-  int chunks;             // nsplit * nsub * 4
   int items;              // workgroups per (sequence, KV head): nsplit * nsub, + 1 where lengths can leave a block partly filled
-  const uint64_t* keys;   // nullable [B,Hq,Nkv/64]: order keys of the block scores; the scores pass then selects and writes `select_out`
-  unsigned long long* select_out;     // = a.bitmap
+  int both;               // decode_split_both: both passes in one launch
+  int chunks;             // nsplit * nsub * 4
+  int clear;              // no selection has cleared tickets and tops: a launch of its own does
+  const uint64_t* keys;   // nullable [B,Hq,Nkv/64]: order keys of the block scores; the kernels then select
   int fixed_k;            // the budget of that selection, as in SelectArgs
   long long ppm;
 };
-// Key blocks up to which the scores pass selects for itself: a row is eight keys per lane of one wavefront.  Every workgroup
-// repeats the selection of its KV group, 1-2 us next to the 4-6 us of a launch of its own.
-constexpr int kSplitSelectBlocks = 512;
-bool decode_split_selects(int Hq, int Hkv, int Tk);
-constexpr int kSplitMaxItems = 320;   // partitions up to which the two passes are faster than one walk of a workgroup each
-constexpr int kSplitMaxItemsOneHead = 512;   // the same for one query head per KV head, few partitions and lengths
+constexpr int kSplitSelectBlocks = 512;      // key blocks up to which the kernels select for themselves: eight keys per lane of a wavefront
+bool decode_split_both(int B, int Hkv, int Tk);
+bool decode_split_selects(int Tk, bool both);
+constexpr int kSplitMaxItems = 448;          // partitions up to which the split is faster than one walk of a workgroup each
+constexpr int kSplitMaxItemsOneHead = 512;   // the same for one query head per KV head
 constexpr int kSplitMaxChunk = 8;
-bool decode_split_wanted(int B, int Hq, int Hkv, int nsplit, int split_blocks, bool lengths);
-int decode_split_chunk(int B, int Hkv, int Tk);
+constexpr uint32_t kUnset = 0xffffffffu;   // a maximum that is not known yet: no sum of products of numbers has these bits
+bool decode_split_wanted(int B, int Hq, int Hkv, int nsplit, int split_blocks);
+int decode_split_chunk(int B, int Hq, int Hkv, int Tk);
 void launch_decode_split(const DecodeSplitArgs& s, hipStream_t st);
 // decode-time selection: scores of the cached key-block means against the query heads, then per-row TopK
 // as a bitmap ([B*Hq][words], bit j%64 of word j/64) and optionally as ascending id lists
+// `split`: nullable; the block scores also clear its tickets and tops
 void launch_decode_block_scores(const uint16_t* q16, int q_is_bf16, const float* kmean, const int32_t* seqlens, uint64_t* keys,
-                                int B, int Hq, int Hkv, int Tk, int shared, hipStream_t st);
+                                int B, int Hq, int Hkv, int Tk, int shared, const DecodeSplitArgs* split, hipStream_t st);
 void launch_decode_select(const uint16_t* q16, int q_is_bf16, const float* kmean, const int32_t* seqlens, uint64_t* keys,
                           unsigned long long* bitmap, int words, int32_t* idx_out, int32_t* cnt_out, int kmax_out,
-                          int B, int Hq, int Hkv, int Tk, int fixed_k, long long ppm, int shared, hipStream_t st);
+                          int B, int Hq, int Hkv, int Tk, int fixed_k, long long ppm, int shared, const DecodeSplitArgs* split, hipStream_t st);
 
 // Append to the dual cache: tokens seqlens[b] .. seqlens[b] + n - 1 of every (sequence, KV head)
 struct CacheAppendArgs {

@@ -1,4 +1,5 @@
-"""The two-pass decode (short caches, few sequences) against the oracle and against the one-pass form.
+"""The decode in finer pieces (two passes over chunks, in two launches or one; short caches, few sequences) against the oracle and
+against the walk over whole partitions, here the one-pass form.
 
 Both forms give every block the running maximum of its partition and the same selection.  Their raw scores come from matrix
 instructions of different shapes.  16-bit scores had equal bits in every comparison; 4-bit scores are sums of 128 products
@@ -65,6 +66,70 @@ def test_two_pass_decode_equals_one_pass(T, Hq, Hkv, B, N, split, lens, budget, 
     assert err <= REL
     again, _, _ = T.thrift_attn_decode(*args, 64, budget, workspace=big, **kw)
     assert torch.equal(two, again)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("Hq,Hkv,B,N,split,lens,budget,shared", [
+    (8, 8, 9, 8192, 256, [8192 - 517 * b for b in range(9)], 0.05, False),   # 9216 key blocks: one launch; it selects for itself
+    (12, 4, 17, 8192, 31, [8191 - 481 * b for b in range(17)], 0.25, False),             # rows of two registers, partitions of 31 blocks
+    (40, 8, 9, 8192, 256, None, 0.1, True),                                  # five heads, one set for them; no lengths
+    (16, 16, 5, 8256, 129, [8256, 8255, 64, 1, 0], 0.05, False),             # 129 key blocks: one more than it selects itself
+    (14, 2, 5, 65536, 256, [65535 - 13000 * b for b in range(5)], 0.1, False),           # seven heads
+    (16, 8, 6, 16384, 100, [16384, 9000, 0, 6463, 6400, 6401], 0.0, False),  # no block promoted: no selection clears the tickets
+    (32, 4, 9, 16384, 256, [16384] * 9, 1.0, False),                         # every block
+    (8, 2, 56, 32768, 512, [32768 - 577 * b for b in range(56)], 0.05, False),           # longer partitions; 112
+    (16, 8, 28, 32768, 256, None, 0.05, False),                              # 448 partitions, the most
+])
+def test_both_passes_in_one_launch_equal_the_walk(T, Hq, Hkv, B, N, split, lens, budget, shared, dtype):
+    """More than 8192 key blocks.  The workspace starts from bytes that look like published maxima and tickets (zeros), like
+    maxima still to come (ones) and from what the call before has left."""
+    print(f"decode in one launch Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} budget={budget} {dtype}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv, dtype=dtype)
+    assert B * Hkv * (N // 64) > 8192
+    args = _cache(T, wl)
+    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+    size = B, Hq, Hkv, N, wl.D, 64, split
+    need, least = T.decode_workspace_bytes(*size), T.decode_least_workspace_bytes(*size)
+    assert need > least
+    kw = dict(split_blocks=split, seqlens=sl, group_shared=shared)
+    run = lambda ws: T.thrift_attn_decode(*args, 64, budget, out=torch.empty(B, Hq, 128, dtype=torch.float32, device="cuda"), workspace=ws, **kw)
+    one = run(torch.empty(least, dtype=torch.uint8, device="cuda"))
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    got = []
+    for fill in (0, 0xFF, None, 0x55):
+        if fill is not None:
+            ws.fill_(fill)
+        got.append(run(ws))
+    assert bool(torch.isfinite(got[0]).all()) and all(torch.equal(x, got[0]) for x in got)
+    err = float((got[0] - one).norm() / one.norm())
+    print(f"  rel {err:.2e}", flush=True)
+    assert err <= REL
+    listed, _, _ = T.thrift_attn_decode(*args, 64, budget, out_dtype=torch.float32, return_selection=True, workspace=ws, **kw)
+    assert torch.equal(listed, got[0])                                       # selected by a launch of its own
+
+
+@pytest.mark.parametrize("Hq,Hkv,B,N", [(32, 8, 9, 8192), (8, 2, 2, 4096)])
+def test_decode_in_a_graph(T, Hq, Hkv, B, N):
+    """Tickets and maxima are cleared inside the call: every replay gives what the eager call gives, on new values too."""
+    print(f"decode in a graph Hq={Hq} Hkv={Hkv} B={B} N={N}", flush=True)
+    args = list(_cache(T, W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv)))
+    ws = torch.empty(T.decode_workspace_bytes(B, Hq, Hkv, N, 128, 64, 256), dtype=torch.uint8, device="cuda")
+    sl = torch.full((B,), N - 5, dtype=torch.int32, device="cuda")
+    for budget in (0.05, 0.0):
+        out, kw = torch.empty_like(args[0]), dict(seqlens=sl, workspace=ws)
+        T.thrift_attn_decode(*args, 64, budget, out=out, **kw)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            T.thrift_attn_decode(*args, 64, budget, out=out, **kw)
+        for n in range(3):
+            args[0].mul_(0.75)
+            sl.sub_(61)
+            out.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            want = T.thrift_attn_decode(*args, 64, budget, seqlens=sl)
+            assert torch.equal(out, want)
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
