@@ -212,6 +212,52 @@ def test_selection_inside_the_scores_pass(T, Hq, Hkv, B, N, lens, budget, fixed_
         assert torch.equal(out, want)
 
 
+@pytest.mark.parametrize("Tk", [1, 64, 65, 256, 257, 512, 513, 1025, 2048, 2049, 4096])
+def test_listed_selection_is_the_k_largest(T, Tk):
+    """The selection of a launch of its own against a stable sort: scores that its bins separate, that crowd one bin, that fp32 does
+    not tell apart, that tie or are infinite.  The query's first two channels alone are not zero, so that the scores are exact."""
+    print(f"decode listed selection Tk={Tk}", flush=True)
+    gen = torch.Generator().manual_seed(Tk)
+    normal = torch.randn(Tk, generator=gen, dtype=torch.float64)
+    j = torch.randperm(Tk, generator=gen).double()
+    rows = {                                                                 # (first, second channel of the key block means)
+        "normal": (normal, None),
+        "outlier": (torch.where(j == 0, 1e30, normal), None),
+        "geometric": (torch.exp2(-(j % 120)) * torch.where(j % 2 == 0, 1., -1.), None),       # every round splits off a few
+        "below fp32": (torch.ones(Tk).double(), j * 2.0 ** -20),
+        "equal": (torch.full((Tk,), -3.0).double(), None),
+        "two values": ((j % 2), None),
+        "few values": ((j % 7) - 3, None),                                   # more ties than a wavefront ranks
+        "infinite": (torch.where(j % 9 == 0, float("inf"), torch.where(j % 9 == 1, -float("inf"), normal)), None),
+    }
+    B, N = len(rows), Tk * 64
+    kmean, score = torch.zeros(B, 1, Tk, 128), torch.empty(B, Tk, dtype=torch.float64)
+    for b, (x, y) in enumerate(rows.values()):
+        kmean[b, 0, :, 0] = x.float()
+        score[b] = x.float().double()
+        if y is not None:
+            kmean[b, 0, :, 1] = y.float()
+            score[b] += y.float().double() * 2.0 ** -10
+    q = torch.zeros(B, 2, 128, dtype=torch.float16)
+    q[..., 0], q[..., 1] = 1.0, 2.0 ** -10
+    k = torch.zeros(B, 1, N, 128, dtype=torch.float16, device="cuda")
+    k4, ks = T.thrift_quantize_mxfp4(k, 0)
+    v4, vs = T.thrift_quantize_mxfp4(k, 1)
+    args = (q.cuda(), k, k, k4, ks, v4, vs, kmean.cuda())
+    for lens in (None, [max(1, N - 64 * 3 * b - 17) for b in range(B)]):
+        sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+        for fixed_k in sorted({1, 2, max(1, Tk // 20), max(1, Tk // 2), max(1, Tk - 1), Tk}):
+            _, idx, cnt = T.thrift_attn_decode(*args, 64, 0.0, fixed_k=fixed_k, seqlens=sl, return_selection=True)
+            for b in range(B):
+                vis = Tk if lens is None else (lens[b] + 63) // 64
+                n = min(fixed_k, vis)
+                want = torch.sort(score[b, :vis], descending=True, stable=True).indices[:n].sort().values
+                for h in range(2):
+                    assert int(cnt[b, h]) == n
+                    assert torch.equal(idx[b, h, :n].cpu().long(), want), (list(rows)[b], fixed_k, vis)
+                    assert bool((idx[b, h, n:] == -1).all())
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(8, 2), (2, 2)])
 def test_a_key_of_nan_reaches_the_results_it_reaches_in_one_pass(T, Hq, Hkv):
     """Its row sums are NaN, in whichever chunk it lies, and what they divide is not a result of the other chunks alone."""
