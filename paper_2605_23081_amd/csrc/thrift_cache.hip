@@ -18,8 +18,10 @@
 
 namespace thrift {
 
+constexpr int kAppendThreads = 256 + kD;     // K rows and V columns; the K mean's channels
+
 template <typename T>
-__global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
+__global__ void __launch_bounds__(kAppendThreads) cache_append_kernel(CacheAppendArgs a) {
   constexpr int kRow = kD + 8;   // padded LDS row in 16-bit elements
   __shared__ __align__(16) uint16_t ktile[kBk * kRow];
   __shared__ __align__(16) uint16_t vtile[kBk * kRow];
@@ -44,8 +46,9 @@ __global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
 
   // ---- stage both tiles; new rows also go to the 16-bit cache ----
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int chunk = tid + 256 * u;                          // 1024 chunks of 8 elements per tile
+  for (int u = 0; u < 3; ++u) {
+    const int chunk = tid + kAppendThreads * u;               // 1024 chunks of 8 elements per tile
+    if (chunk >= kBk * kD / 8) break;
     const int row = chunk >> 4, col = (chunk & 15) * 8;
     const int tok = tok0 + row;
     uint4 kw = make_uint4(0, 0, 0, 0), vw = make_uint4(0, 0, 0, 0);
@@ -64,7 +67,7 @@ __global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
   __syncthreads();
 
   // ---- K: 4-bit rows of the new tokens; thread = (row, group of 32 channels) ----
-  {
+  if (tid < 256) {
     const int row = tid >> 2, g = tid & 3, tok = tok0 + row;
     if (tok >= len_old && tok < len_new) {
       uint32_t pair[16], out[4];
@@ -78,13 +81,16 @@ __global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
 
   // ---- K mean of the block: one thread per channel adds its rows in order (16-bit floats that lie far apart do not add
   // exactly in fp64 either).  The rows past the last token are zeros and change no sum, so that all 64 LDS reads are in flight
-  // together: a loop over `count` rows waited for each of them, 3 us of a one-token append ----
+  // together: a loop over `count` rows waited for each of them, 3 us of a one-token append.  Wavefronts of its own: the chain
+  // of 64 additions behind the K rows and before the V columns made 4.8 us of a token for one sequence, beside them it is 4.2 ----
   const size_t blk = (size_t)unit * (a.Nkv / kBk) + j;
-  if (tid < kD) {
+  if (tid >= 256) {
+    const int c = tid - 256;
     double sum = 0.0;
 #pragma unroll
-    for (int r = 0; r < kBk; ++r) sum += (double)T::to_float(ktile[r * kRow + tid]);
-    a.kmean[blk * kD + tid] = (float)(sum / (double)count);
+    for (int r = 0; r < kBk; ++r) sum += (double)T::to_float(ktile[r * kRow + c]);
+    a.kmean[blk * kD + c] = (float)(sum / (double)count);
+    return;
   }
 
   // ---- V: both 32-token groups of the block; thread = (group, channel) walks down a column ----
@@ -104,8 +110,8 @@ __global__ void __launch_bounds__(256) cache_append_kernel(CacheAppendArgs a) {
 
 void launch_cache_append(const CacheAppendArgs& a, thrift_dtype dt, hipStream_t st) {
   const unsigned grid = (unsigned)((long)a.B * a.Hkv * a.blocks_per_unit);
-  if (dt == THRIFT_F16) cache_append_kernel<F16><<<dim3(grid), dim3(256), 0, st>>>(a);
-  else cache_append_kernel<BF16><<<dim3(grid), dim3(256), 0, st>>>(a);
+  if (dt == THRIFT_F16) cache_append_kernel<F16><<<dim3(grid), dim3(kAppendThreads), 0, st>>>(a);
+  else cache_append_kernel<BF16><<<dim3(grid), dim3(kAppendThreads), 0, st>>>(a);
 }
 
 }  // namespace thrift
