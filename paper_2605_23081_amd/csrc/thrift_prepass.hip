@@ -294,6 +294,8 @@ __device__ __forceinline__ void score_piece(const double* q, const float* k, dou
 template <int MAXC, int NW>
 __global__ void __launch_bounds__(NW * 64) select_topk_kernel(SelectArgs p) {
   constexpr int kPer = 2048 / (NW * 64);                // 16-byte pieces of a staged piece per thread
+  constexpr int kKeys = MAXC < 4 ? 64 * MAXC : 256;     // keys of a staged piece ..
+  constexpr int kQuarters = 256 / kKeys;                // .. and quarters of their channels
   __shared__ __align__(16) float kst[256 * kStride];
   __shared__ __align__(16) double qsd[NW][kD];          // the row's query mean (shared mode: summed over the group's heads)
   const int tid = threadIdx.x, lane = tid & 63;
@@ -312,6 +314,27 @@ __global__ void __launch_bounds__(NW * 64) select_topk_kernel(SelectArgs p) {
   const int unit = blockIdx.x % units;
   const int row0 = (wgs_per_unit - 1 - (int)(blockIdx.x / units)) * NW;
   const int b = unit / p.Hkv, kvh = unit % p.Hkv;
+  const float* kbase = p.kmean + (size_t)unit * p.Tk * kD;
+
+  // Every step of a key's chain reads the key mean (per lane) and the query mean (the same address in all lanes, but a
+  // full read all the same); with one chain per lane those reads took most of the CU's one LDS pipe.  So a lane walks the
+  // chains of four keys (one of each of four 64-key chunks) side by side and reads the query mean once for the four:
+  // half the LDS reads per score, and four independent chains of fused multiply-adds.  256 key means are staged a quarter of their channels at a time (36 KiB), fetched into registers while
+  // the quarter before is being scored and handed to LDS between two barriers; the workgroup's rows share every
+  // staged piece (16 rows: a quarter of the L2 reads of 4).  Rows of one or two chunks, whose time is the waits alone, take four
+  // or two quarters of their channels at a time into the same place, and the first piece is asked for before anything else is
+  // worked out: 5.0 us instead of 8.9 for 8 workgroups over 32 key blocks, 5.6 / 9.8 for 192 over 47, 9.7 / 13.0 for 512 over 128.
+  float4 nx[kPer];
+  auto fetch = [&](int t) {                              // piece t of MAXC >= 4: keys 256*(t/4) .. +255, channels 32*(t%4) .. +31
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int chunk = tid + NW * 64 * u;               // 2048 pieces of 4 floats, [quarter][key][channel]
+      const int r = (chunk >> 3) % kKeys, q = (chunk >> 3) / kKeys, col = (chunk & 7) * 4;
+      const int key0 = MAXC < 4 ? 0 : (t >> 2) * 256, ch0 = MAXC < 4 ? (t * kQuarters + q) * kQuarter : (t & 3) * kQuarter;
+      nx[u] = key0 + r < p.Tk ? *reinterpret_cast<const float4*>(kbase + (size_t)(key0 + r) * kD + ch0 + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  };
+  if (p.selector == 0) fetch(0);
   const int row = row0 + wave;
   const bool active = row < rows_per_unit;
   const int i = active ? row / GR : 0;
@@ -334,24 +357,6 @@ __global__ void __launch_bounds__(NW * 64) select_topk_kernel(SelectArgs p) {
     qsd[wave][lane] = q0;
     qsd[wave][lane + 64] = q1;
   }
-  const float* kbase = p.kmean + ((size_t)b * p.Hkv + kvh) * p.Tk * kD;
-
-  // Every step of a key's chain reads the key mean (per lane) and the query mean (the same address in all lanes, but a
-  // full read all the same); with one chain per lane those reads took most of the CU's one LDS pipe.  So a lane walks the
-  // chains of four keys (one of each of four 64-key chunks) side by side and reads the query mean once for the four:
-  // half the LDS reads per score, and four independent chains of fused multiply-adds.  256 key means are staged a quarter of their channels at a time (36 KiB), fetched into registers while
-  // the quarter before is being scored and handed to LDS between two barriers; the workgroup's rows share every
-  // staged piece (16 rows: a quarter of the L2 reads of 4).
-  float4 nx[kPer];
-  auto fetch = [&](int t) {                              // piece t: keys 256*(t/4) .. +255, channels 32*(t%4) .. +31
-    const int key0 = (t >> 2) * 256, ch0 = (t & 3) * kQuarter;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int chunk = tid + NW * 64 * u;               // 2048 pieces of 4 floats
-      const int r = chunk >> 3, col = (chunk & 7) * 4;
-      nx[u] = key0 + r < p.Tk ? *reinterpret_cast<const float4*>(kbase + (size_t)(key0 + r) * kD + ch0 + col) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  };
 
   uint64_t key[MAXC];
 #pragma unroll
@@ -364,8 +369,26 @@ __global__ void __launch_bounds__(NW * 64) select_topk_kernel(SelectArgs p) {
       const int j = c * 64 + lane;
       if (j < vis) key[c] = p.selector == 1 ? splitmix64_output(p.seed, (((uint64_t)rowid << 32) | (uint64_t)j) + 1ULL) : (uint64_t)j + 1ULL;
     }
+  } else if constexpr (MAXC < 4) {
+    double sc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < 4 / kQuarters; ++t) {
+      if (t > 0) __syncthreads();                        // the piece before has been scored by every row
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int chunk = tid + NW * 64 * u;
+        *reinterpret_cast<float4*>(&kst[(chunk >> 3) * kStride + (chunk & 7) * 4]) = nx[u];
+      }
+      if (t + 1 < 4 / kQuarters) fetch(t + 1);
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kQuarters; ++q)
+        if (vis > 0) score_piece<MAXC, kQuarter / 4>(&qsd[wave][(t * kQuarters + q) * kQuarter], &kst[(q * kKeys + lane) * kStride], sc);
+    }
+#pragma unroll
+    for (int cc = 0; cc < MAXC; ++cc)
+      if (cc * 64 + lane < vis) key[cc] = order_key(sc[cc]);
   } else {
-    if (vis_max > 0) fetch(0);
 #pragma unroll
     for (int cg = 0; cg < MAXC / 4; ++cg) {
       if (cg * 256 < vis_max) {                          // uniform over the workgroup
@@ -458,11 +481,15 @@ void launch_select_topk(const SelectArgs& p, hipStream_t st) {
   const int wgs_per_unit = (p.Tq * G + nw - 1) / nw;
   const dim3 grid((unsigned)((long)p.B * p.Hkv * wgs_per_unit));
   if (nw == 16) {
-    if (chunks <= 8) select_topk_kernel<8, 16><<<grid, dim3(1024), 0, st>>>(p);
+    if (chunks <= 1) select_topk_kernel<1, 16><<<grid, dim3(1024), 0, st>>>(p);
+    else if (chunks <= 2) select_topk_kernel<2, 16><<<grid, dim3(1024), 0, st>>>(p);
+    else if (chunks <= 8) select_topk_kernel<8, 16><<<grid, dim3(1024), 0, st>>>(p);
     else if (chunks <= 16) select_topk_kernel<16, 16><<<grid, dim3(1024), 0, st>>>(p);
     else select_topk_kernel<32, 16><<<grid, dim3(1024), 0, st>>>(p);
   } else {
-    if (chunks <= 8) select_topk_kernel<8, 4><<<grid, dim3(256), 0, st>>>(p);
+    if (chunks <= 1) select_topk_kernel<1, 4><<<grid, dim3(256), 0, st>>>(p);
+    else if (chunks <= 2) select_topk_kernel<2, 4><<<grid, dim3(256), 0, st>>>(p);
+    else if (chunks <= 8) select_topk_kernel<8, 4><<<grid, dim3(256), 0, st>>>(p);
     else if (chunks <= 16) select_topk_kernel<16, 4><<<grid, dim3(256), 0, st>>>(p);
     else if (chunks <= 32) select_topk_kernel<32, 4><<<grid, dim3(256), 0, st>>>(p);
     else select_topk_kernel<64, 4><<<grid, dim3(256), 0, st>>>(p);

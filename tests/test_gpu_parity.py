@@ -373,6 +373,24 @@ def test_select_topk_kernel_shapes(T, oracle, Hq, Hkv, Tq, Tk, causal, off):
         assert np.array_equal(to_np(idx_g)[..., :idx_r.shape[-1]], idx_r) and np.all(to_np(idx_g)[..., idx_r.shape[-1]:] == -1)
 
 
+@pytest.mark.parametrize("Tk", [1, 63, 64, 65, 127, 128, 129])
+@pytest.mark.parametrize("Hq,Hkv,Tq", [(6, 2, 3), (256, 256, 5)])            # 4 and 16 rows per workgroup
+def test_select_topk_short_rows(T, oracle, Hq, Hkv, Tq, Tk):
+    """One or two key registers per lane: the key means arrive four or two quarters of their channels at a time."""
+    _say(f"select short rows Hq={Hq} Hkv={Hkv} Tq={Tq} Tk={Tk}")
+    g = torch.Generator().manual_seed(1000 * Tq + Tk)
+    qm = torch.randn(1, Hq, Tq, 128, generator=g)
+    km = torch.randn(1, Hkv, Tk, 128, generator=g)
+    for causal, off, fixed_k in ((False, 0, 3), (True, Tk - Tq, -1)):
+        if off < 0:
+            continue
+        idx_r, cnt_r = oracle.select_topk(qm.numpy(), km.numpy(), 64, 64, causal, 0.07, fixed_k, q_block_offset=off)
+        idx_g, cnt_g = T.thrift_select_topk(qm.cuda(), km.cuda(), 64, 64, causal, 0.07, fixed_k, q_block_offset=off)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_np(cnt_g), cnt_r)
+        assert np.array_equal(to_np(idx_g)[..., :idx_r.shape[-1]], idx_r) and np.all(to_np(idx_g)[..., idx_r.shape[-1]:] == -1)
+
+
 # head groups of every kernel shape: one head per wavefront (G <= 4, some wavefronts without a head at G = 3), two (G <= 8,
 # some with one at G = 5, 6, 7), more (the transposed tiles: G = 12, 32)
 @pytest.mark.parametrize("Hq,Hkv,B,N,split", [(32, 1, 1, 1024, 16), (4, 4, 1, 640, 64), (16, 2, 2, 1536, 4), (12, 2, 2, 1024, 8),
