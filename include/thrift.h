@@ -326,8 +326,8 @@ thrift_status thrift_attn_decode_shared(const void* q, thrift_dtype dt, const vo
  * nothing.  A problem whose one-pass form does not fit either (thrift_attn_decode then refuses a workspace of that
  * size, too) returns THRIFT_ERR_WORKSPACE (nothing launched).  All calls on one GPU share the array:
  * calls that overlap on one GPU (different streams, different host threads) race on it; calls on one stream
- * are ordered and safe.  Nothing in the array has to be cleared between calls: every byte a call reads it has
- * written itself.
+ * are ordered and safe.  Nothing in the array has to be cleared between calls: no result depends on a byte that
+ * the call has not written itself.
  */
 #define THRIFT_DECODE_STATIC_SCRATCH_BYTES (32u << 20)
 thrift_status thrift_attn_decode_static(const void* q, thrift_dtype dt, const void* k16, const void* v16,

@@ -128,14 +128,14 @@ enum Pass { BOTH, SCORES, VALUES };
 constexpr int chunk_limit(int nh, bool both) { return both && nh > 4 ? kSplitMaxChunk / 2 : kSplitMaxChunk; }
 
 // NH: heads per KV group, rounded up to 1, 2, 4 or 8.
+// NC: key blocks per wavefront, at most, whose scores one launch holds in LDS.
 // NR: the promoted blocks come from the order keys of rows of up to 64 NR key blocks, every workgroup asking for its own blocks
 // (a row or two per wavefront); 0: from the bitmap of a launch before.
-template <typename T, int NH, Pass PASS, int NR>
+template <typename T, int NH, Pass PASS, int NR, int NC = 1>
 __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel(DecodeSplitArgs s) {
   const DecodeArgs& a = s.a;
   constexpr bool SELECT = NR > 0;
   constexpr int kSlot = 4096 + 256;                            // codes and scales of a V block
-  constexpr int NC = PASS != BOTH ? 1 : chunk_limit(NH, true);
   // per wavefront: half a 16-bit K tile; then two V blocks, which give way to its partial sums, and behind them its
   // maxima and sums
   constexpr int kTops = 2 * kSlot, kMl = kTops + 64, kOwn = PASS == SCORES ? kTile16 / 2 : kMl + 64;
@@ -755,7 +755,15 @@ bool decode_split_selects(int Tk, bool both) { return Tk <= (both ? kSelectBoth 
 //   16384          1 x 131072, 32/8, 5 %   115.5 /  88.6 /  78.0 /  76.4         8
 //                  16 x 8192, shared, 5 %   80.5 /  60.1 /  54.0 /  47.5         8
 //                  4 x 32768, 64/8, 100 %  145.2 / 119.0 / 105.9               4 (eight heads: no more fit the LDS)
-//   65536          16 x 32768, 32/8, 25 %  377.4 / 304.7 / 277.6 / 279.7         8
+// Three or four heads per KV head: the scores of eight blocks leave a CU room for two workgroups, those of four for three.  So
+// eight are taken where the grid is one round of two (up to 16384 blocks), unless three of half the length and short rows end
+// sooner, and in rows of more than 1024 blocks, where shorter chunks have too many maxima to look up.  Four / eight:
+//    9216          9 x 8192, 32/8, 5 %      40.7 /  47.1                        4
+//   12288          3 x 32768, 32/8, 5 %     60.5 /  56.1                        8
+//   14336          14 x 8192, 32/8, 5 %     54.4 /  55.2                        4
+//   20480          10 x 16384, 32/8, 5 %    75.5 /  81.8                        4
+//   65536          16 x 32768, 32/8, 25 %  272.3 / 278.1                        4
+//                  4 x 131072, 32/8, 25 %  342.0 / 334.7                        8
 //   two launches
 //    1280 blocks   1 x 10240, 32/8, 5 %     29.2 /  31.6 /  36.8              takes 1
 //    2560          1 x 20480, 32/8, 5 %     36.3 /  34.7 /  39.0                  2
@@ -769,6 +777,7 @@ int decode_split_chunk(int B, int Hq, int Hkv, int Tk) {
   if (!decode_split_both(B, Hkv, Tk)) return blocks < (heads > 4 ? 4096 : 2048) ? 1 : blocks < 8192 ? 2 : 4;
   int cw = 1;
   while (cw < chunk_limit(heads, true) && blocks > 1536L * cw) cw *= 2;
+  if (cw == 8 && heads > 2 && Tk <= 1024 && (blocks > 16384 || (Tk <= 256 && blocks <= 14336))) cw = 4;
   return cw;
 }
 
@@ -780,10 +789,15 @@ void launch_decode_split(const DecodeSplitArgs& s, hipStream_t st) {
     const long n_tops = (long)a.B * a.Hq * s.items;
     decode_split_clear_kernel<<<dim3((unsigned)((n_tops + 255) / 256)), block, 0, st>>>(s.tickets, a.B * a.Hkv * a.nsplit, s.tops, n_tops);
   }
+#define THRIFT_BOTH(T, NH, NC)                                                                            \
+  do {                                                                                                    \
+    if (s.keys != nullptr) decode_split_kernel<T, NH, BOTH, kSelectBoth / 64, NC><<<grid, block, 0, st>>>(s);             \
+    else decode_split_kernel<T, NH, BOTH, 0, NC><<<grid, block, 0, st>>>(s);                              \
+  } while (0)
 #define THRIFT_SPLIT(T, NH)                                                                               \
   do {                                                                                                    \
-    if (s.both && s.keys != nullptr) decode_split_kernel<T, NH, BOTH, kSelectBoth / 64><<<grid, block, 0, st>>>(s);       \
-    else if (s.both) decode_split_kernel<T, NH, BOTH, 0><<<grid, block, 0, st>>>(s);                      \
+    if (s.both && s.cw <= 4) THRIFT_BOTH(T, NH, (NH == 4 ? 4 : chunk_limit(NH, true)));                   \
+    else if (s.both) THRIFT_BOTH(T, NH, (chunk_limit(NH, true)));                                         \
     else if (s.keys != nullptr) {                                                                         \
       decode_split_kernel<T, NH, SCORES, kSplitSelectBlocks / 64><<<grid, block, 0, st>>>(s);             \
       decode_split_kernel<T, NH, VALUES, kSplitSelectBlocks / 64><<<grid, block, 0, st>>>(s);             \
@@ -803,6 +817,7 @@ void launch_decode_split(const DecodeSplitArgs& s, hipStream_t st) {
   else THRIFT_SPLIT_T(BF16);
 #undef THRIFT_SPLIT_T
 #undef THRIFT_SPLIT
+#undef THRIFT_BOTH
   decode_split_merge_kernel<<<dim3((unsigned)((long)a.B * a.Hq)), block, 0, st>>>(s);
 }
 

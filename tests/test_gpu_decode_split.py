@@ -79,6 +79,8 @@ def test_two_pass_decode_equals_one_pass(T, Hq, Hkv, B, N, split, lens, budget, 
     (32, 4, 9, 16384, 256, [16384] * 9, 1.0, False),                         # every block
     (8, 2, 56, 32768, 512, [32768 - 577 * b for b in range(56)], 0.05, False),           # longer partitions; 112
     (16, 8, 28, 32768, 256, None, 0.05, False),                              # 448 partitions, the most
+    (32, 8, 16, 8192, 256, [8192 - 333 * b for b in range(16)], 0.05, False),            # four heads, eight blocks per wavefront
+    (32, 8, 3, 32768, 256, [32767, 20000, 16384], 0.1, False),               # the same, selected by a launch of its own
 ])
 def test_both_passes_in_one_launch_equal_the_walk(T, Hq, Hkv, B, N, split, lens, budget, shared, dtype):
     """More than 8192 key blocks.  The workspace starts from bytes that look like published maxima and tickets (zeros), like
