@@ -22,12 +22,12 @@
 // spread over 2^40, 2.8 % of the scores differed in their last bit, neither side further from 64 bits than the other; a
 // probability on a rounding boundary may then fall to either side.
 //
-// Measured, whole calls or serving steps, the walk / two launches with a search for the selection everywhere / now: 306 / 41.1 /
-// 38.0 us for one sequence of 32768 tokens and 32/8 heads, 102 / 26.5 / 25.6 for one of 4096; 301 / 75.4 / 75.5 for one of 131072,
-// 544 / 172.8 / 155.8 for eight of 16384-32768 with 64/8 heads at 10 %, 148 / 55.0 / 47.9 for sixteen of 4096-8192 with shared
-// selection, - / 322.7 / 283.0 for sixteen of 16384-32768 at 25 %.
+// Measured, whole calls or serving steps, the walk / two launches with a search for every selection / now: 306 / 43.2 / 38.5 us
+// for one sequence of 32768 tokens and 32/8 heads, 102 / 28.0 / 22.9 for one of 4096; 301 / 74.0 / 67.7 for one of 131072,
+// 544 / 192.4 / 161.7 for eight of 16384-32768 with 64/8 heads at 10 %, 148 / 53.4 / 46.3 for sixteen of 4096-8192 with shared
+// selection, - / 324.5 / 269.3 for sixteen of 16384-32768 at 25 %.
 // What bounds it: for short caches the chain of launches and of dependent loads inside them (a step of one sequence of 4096 tokens
-// reads 0.5 MB); for long ones too few bytes in flight per CU in the chunks' own chains, 5.0 to 5.7 TB/s of 7.1.
+// reads 0.5 MB); for long ones too few bytes in flight per CU in the chunks' own chains, 4.1 to 5.2 TB/s of 7.1.
 #include <type_traits>
 
 #include "thrift_launch.h"
