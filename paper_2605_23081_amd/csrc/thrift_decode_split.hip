@@ -764,6 +764,12 @@ bool decode_split_selects(int Tk, bool both) { return Tk <= (both ? kSelectBoth 
 //   20480          10 x 16384, 32/8, 5 %    75.5 /  81.8                        4
 //   65536          16 x 32768, 32/8, 25 %  272.3 / 278.1                        4
 //                  4 x 131072, 32/8, 25 %  342.0 / 334.7                        8
+// One or two heads fit three workgroups per CU with eight blocks too, so that only the number of wavefronts decides.  Four / eight:
+//    8384          2 x 16768, 16/16, 25 %   44.4 /  49.4                        4
+//                  4 x 16768, 16/8, 25 %    55.9 /  61.3                        4
+//   10000          2 x 40000, 16/8, 5 %     49.1 /  44.4                        8
+//   32768          4 x 32768, 16/16, 25 %   89.0 /  94.7                        4 (one head)
+//   20480          5 x 32768, 16/8, 5 %     63.0 /  60.5                        8
 //   two launches
 //    1280 blocks   1 x 10240, 32/8, 5 %     29.2 /  31.6 /  36.8              takes 1
 //    2560          1 x 20480, 32/8, 5 %     36.3 /  34.7 /  39.0                  2
@@ -778,6 +784,7 @@ int decode_split_chunk(int B, int Hq, int Hkv, int Tk) {
   int cw = 1;
   while (cw < chunk_limit(heads, true) && blocks > 1536L * cw) cw *= 2;
   if (cw == 8 && heads > 2 && Tk <= 1024 && (blocks > 16384 || (Tk <= 256 && blocks <= 14336))) cw = 4;
+  if (cw == 8 && heads <= 2 && (blocks <= 9216 || (heads == 1 && blocks > 24576))) cw = 4;
   return cw;
 }
 
