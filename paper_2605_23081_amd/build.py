@@ -82,6 +82,98 @@ def m0_outside_inline_asm(asm_text: str) -> int:
     return count
 
 
+_REGISTERS = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
+
+
+def _registers(operand):
+    return {(m[1], n) for m in _REGISTERS.finditer(operand)
+            for n in range(int(m[2] or m[4]), int(m[3] or m[4]) + 1)}
+
+
+def matrix_results_read_early(asm_text: str):
+    """(kernel, instruction) of every hand-written instruction that touches a matrix result before it is written.
+
+    A matrix instruction of 32 x 32 (16 x 16) values writes its result 8 (4) passes later; a vector instruction has to stay
+    12 (8) wait states away from it, and here as far from overwriting the addend as well.  The compiler spaces its own instructions
+    like that but not the inside of an asm statement, so the listing is followed along every branch: an instruction between
+    the ASMSTART / ASMEND markers must find no result or addend of its registers in flight."""
+    early = []
+    kernel, inside, statements, matrix = None, False, 0, 0
+    blocks, block = {}, None                               # per kernel: label -> (instructions, labels that follow)
+
+    def close():
+        # the wait states that each register still needs at a block's start, over all ways to it
+        if kernel is None:
+            return
+        start, todo, found = {b: {} for b in blocks}, list(blocks), set()
+        while todo:
+            b = todo.pop()
+            wait = dict(start[b])
+            instructions, follow = blocks[b]
+            for line, op, operands, by_hand in instructions:
+                if by_hand and op[:2] != "s_":
+                    touched = set().union(*map(_registers, operands)) if operands else set()
+                    written = _registers(operands[0]) if operands else set()
+                    if any(wait.get(("d", r), 0) > 0 for r in touched) or any(wait.get(("c", r), 0) > 0 for r in written):
+                        found.add((line, op + " " + ", ".join(operands)))
+                states = int(operands[0], 0) + 1 if op == "s_nop" else 1
+                wait = {r: n - states for r, n in wait.items() if n > states}
+                if op.startswith(("v_mfma", "v_smfmac")):
+                    n = 12 if "_32x32x" in op else 8
+                    for r in _registers(operands[0]):
+                        wait["d", r] = n
+                    for r in _registers(operands[3]):
+                        wait["c", r] = n
+            for f in follow:
+                if f in start:
+                    more = {r: n for r, n in wait.items() if n > start[f].get(r, 0)}
+                    if more:
+                        start[f].update(more)
+                        todo.append(f)
+        early.extend((kernel, what) for _, what in sorted(found))
+
+    for number, line in enumerate(asm_text.splitlines()):
+        t = line.strip()
+        if t.startswith("_Z") and t.split(":")[0].isidentifier() and ":" in t:
+            close()
+            kernel, blocks, block = t.split(":")[0], {}, t.split(":")[0]
+            blocks[block] = ([], [])
+        elif t.startswith(";;#ASMSTART"):
+            inside = True
+            statements += 1
+        elif t.startswith(";;#ASMEND"):
+            inside = False
+        elif kernel is None or not t or t.startswith((";", "//")):
+            pass
+        elif t.startswith(".LBB"):
+            label = t.split(":")[0]
+            if block is not None:
+                blocks[block][1].append(label)
+            block = label
+            blocks[block] = ([], [])
+        elif line[:1] == "\t" and t[:1].isalpha():
+            if block is None:                              # behind an unconditional branch without a label: never reached
+                continue
+            op, _, rest = t.split(";")[0].strip().partition(" ")
+            operands = [x.strip() for x in re.split(r",(?![^\[]*\])", rest)] if rest else []
+            matrix += op.startswith("v_mfma")
+            blocks[block][0].append((number, op, operands, inside))
+            if op == "s_branch" or op.startswith("s_cbranch"):
+                blocks[block][1].append(operands[0])
+            if op.startswith("s_cbranch"):                 # what follows is a block of its own
+                name = f"{block}+{number}"
+                blocks[block][1].append(name)
+                block = name
+                blocks[block] = ([], [])
+            elif op in ("s_branch", "s_endpgm", "s_setpc_b64"):
+                block = None
+    close()
+    if statements == 0 or matrix == 0:
+        raise RuntimeError("the listing shows no inline assembly or no matrix instructions: the wait-state check cannot read "
+                           "this compiler's output")
+    return early
+
+
 def _start_call_module(obj):
     """Compile csrc/thrift_call.cpp against the headers of the installed torch (host compiler)."""
     import sysconfig
@@ -115,7 +207,7 @@ def build(verbose: bool = False, extra=()):
         objs.append(obj)
     call_obj = os.path.join(CSRC, "thrift_call.o")
     procs.append(_start_call_module(call_obj))
-    # the device listings of the kernels that stage by LDS DMA, for the spill and M0 checks (run beside the object builds)
+    # the device listings of the kernels that stage by LDS DMA, for the spill, M0 and wait-state checks (run beside the object builds)
     listings = []
     for src in DMA_SOURCES:
         listing = os.path.join(CSRC, src.replace(".hip", ".gfx950.s"))
@@ -142,6 +234,9 @@ def build(verbose: bool = False, extra=()):
             raise RuntimeError(f"{src}: spilled registers are reloaded inside a loop: " + ", ".join(spilling))
         if m0_outside_inline_asm(text):
             raise RuntimeError(f"{src}: the compiler uses M0: the LDS DMA statements would clobber it")
+        early = matrix_results_read_early(text)
+        if early:
+            raise RuntimeError(f"{src}: hand-written instructions read matrix results too early: " + ", ".join(sorted({f"{k}: {i}" for k, i in early})[:8]))
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
     _link_call_module(call_obj)

@@ -227,15 +227,13 @@ __device__ __forceinline__ void prefill_split_item(const PrefillArgs& a, unsigne
       issue16(v16base, g.own, false, lds0 + L::v16);
     }
   };
+  // Ordinary arithmetic: a matrix instruction that writes o may just have been issued, and the compiler keeps the 12 wait states
+  // behind it only for instructions of its own, not for those inside an asm statement.
   auto rescale_by = [&](float f) {
-    asm volatile("s_nop 1\n\tv_mul_f32 %0, %1, %0" : "+v"(l) : "v"(f));
+    l *= f;
+    asm volatile("" : "+v"(l));                          // rounded here, not fused with the addition behind
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      float x = o[e];
-      asm volatile("v_mul_f32 %0, %1, %0" : "+v"(x) : "v"(f));
-      o[e] = x;
-    }
-    asm volatile("s_nop 4");
+    for (int e = 0; e < 16; ++e) o[e] *= f;
   };
 
   // Step n: the scores of group n and P.V of group n - 1 between one pair of barriers, the probabilities of group n behind

@@ -206,3 +206,45 @@ def test_m0_check_reads_the_compiler_listing():
                     "\tv_add_u32_e32 v0, v1, v2", "; a comment that mentions m0"])
     assert m0_outside_inline_asm(ok) == 0
     assert m0_outside_inline_asm(ok + "\n\ts_mov_b32 m0, -1\n\tds_gws_init v0 gds") == 1
+
+
+def _listing(source, path):
+    import subprocess
+    from paper_2605_23081_amd import build
+    subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", str(path)], check=True, capture_output=True)
+    return path.read_text()
+
+
+@pytest.mark.parametrize("source", ["thrift_prefill_split.hip", "thrift_prefill.hip"])
+def test_hand_written_instructions_wait_for_matrix_results(tmp_path, source):
+    """The factors of a raised maximum multiply the accumulators that a matrix instruction before them may still be writing."""
+    from paper_2605_23081_amd.build import matrix_results_read_early
+    assert matrix_results_read_early(_listing(source, tmp_path / "listing.s")) == []
+
+
+def test_wait_state_check_reads_the_compiler_listing():
+    from paper_2605_23081_amd.build import matrix_results_read_early
+
+    def kernel(*between, op="v_mfma_scale_f32_32x32x64_f8f6f4 v[0:15], v[16:19], v[20:23], v[0:15], v24, v25 cbsz:4 blgp:4", read="v_mul_f32 v15, v30, v15"):
+        return "\n".join(["_ZN6thrift4walkEv:", "; %bb.0:", "\t" + op, *between, "\t;;#ASMSTART", "\t" + read, "\t;;#ASMEND", "\ts_endpgm"])
+
+    found = [("_ZN6thrift4walkEv", "v_mul_f32 v15, v30, v15")]
+    assert matrix_results_read_early(kernel("\ts_nop 10")) == found
+    assert matrix_results_read_early(kernel("\ts_nop 11")) == []
+    assert matrix_results_read_early(kernel("\ts_nop 9", "\tv_add_f32_e32 v40, v41, v42 ; a comment")) == found
+    assert matrix_results_read_early(kernel(read="v_mul_f32 v16, v30, v16")) == []                       # an operand, not the result
+    small = "v_mfma_f32_16x16x32_f16 a[4:7], v[16:19], v[20:23], 0"
+    assert matrix_results_read_early(kernel("\ts_nop 6", op=small, read="v_add_f32 v1, a7, v2")) == [("_ZN6thrift4walkEv", "v_add_f32 v1, a7, v2")]
+    assert matrix_results_read_early(kernel("\ts_nop 7", op=small, read="v_add_f32 v1, a7, v2")) == []
+    # two ways to the statement: past the wait, and around it; and once more around a loop
+    around = ["\ts_cbranch_scc1 .LBB0_2", "; %bb.1:", "\ts_nop 15", ".LBB0_2:"]
+    assert matrix_results_read_early(kernel(*around)) == found
+    past = ["\ts_branch .LBB0_3", ".LBB0_2:", "\ts_endpgm", ".LBB0_3:", "\ts_nop 9"]
+    assert matrix_results_read_early(kernel(*past)) == found
+    assert matrix_results_read_early(kernel(*past, "\ts_nop 0")) == []
+    loop = "\n".join(["_ZN6thrift4walkEv:", ".LBB0_1:", "\t;;#ASMSTART", "\tv_mul_f32 v3, v30, v3", "\t;;#ASMEND",
+                      "\tv_mfma_f32_32x32x16_f16 v[0:15], v[16:19], v[20:23], v[0:15]", "\ts_cbranch_scc1 .LBB0_1", "\ts_endpgm"])
+    assert matrix_results_read_early(loop) == [("_ZN6thrift4walkEv", "v_mul_f32 v3, v30, v3")]
+    for text in ("", kernel().replace("\t;;#ASMSTART\n", ""), kernel(op="v_add_f32_e32 v0, v1, v2")):
+        with pytest.raises(RuntimeError):
+            matrix_results_read_early(text)
