@@ -387,7 +387,7 @@ static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void
                                       int B, int Hq, int Hkv, int Nkv, int D, int Bk,
                                       double budget, int fixed_k, int split_blocks, float softmax_scale,
                                       void* out, thrift_dtype out_dt, int32_t* idx_out, int32_t* cnt_out, int kmax_out,
-                                      void* workspace, size_t workspace_bytes, int shared, void* stream) {
+                                      void* workspace, size_t workspace_bytes, int shared, void* stream, int polls = kSplitPolls) {
   if (!q || !k16 || !v16 || !k4 || !ks || !v4 || !vs || !kmean || !out) return THRIFT_ERR_NULL;
   if (!is16(dt) || !is_out(out_dt)) return THRIFT_ERR_DTYPE;
   if (B <= 0 || Hq <= 0 || Hkv <= 0 || Hq % Hkv != 0 || Hq / Hkv > 32 || Nkv <= 0 || D != kHeadDim || Bk != kKeyBlock ||
@@ -417,7 +417,7 @@ static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void
       const bool in_pass = kneed > 0 && idx_out == nullptr && cnt_out == nullptr && decode_split_selects(Tk, both);
       s.keys = in_pass ? (const uint64_t*)(ws + S.keys) : nullptr;
       s.fixed_k = fixed_k; s.ppm = fixed_k >= 0 ? 0 : budget_ppm(budget);
-      s.tickets = (unsigned*)(ws + S.tickets); s.tops = (unsigned*)(ws + S.tops); s.clear = !select; s.both = both;
+      s.tickets = (unsigned*)(ws + S.tickets); s.tops = (unsigned*)(ws + S.tops); s.clear = !select; s.both = both; s.polls = polls;
       s.scores = (float*)(ws + S.scores); s.cmax = (float*)(ws + S.cmax); s.taken = (uint32_t*)(ws + S.taken); s.chunks = S.nsplit * S.nsub * 4;
       s.cw = S.cw; s.nsub = S.nsub; s.items = S.nsplit * S.nsub + (seqlens ? 1 : 0); a.nsplit = S.nsplit;
       if (in_pass)
@@ -477,6 +477,20 @@ thrift_status thrift_attn_decode_shared(const void* q, thrift_dtype dt, const vo
                                         void* workspace, size_t workspace_bytes, void* stream) {
   return attn_decode_impl(q, dt, k16, v16, k4, ks, v4, vs, kmean, seqlens, B, Hq, Hkv, Nkv, D, Bk, budget, fixed_k, split_blocks,
                           softmax_scale, out, out_dt, idx_out, cnt_out, kmax_out, workspace, workspace_bytes, 1, stream);
+}
+
+// Not part of the ABI: thrift_attn_decode whose workgroups ask `polls` times for the maxima in front of them.  With none every wait
+// ends without an answer, which a test cannot bring about otherwise.
+extern "C" thrift_status thrift_test_attn_decode_polls(const void* q, thrift_dtype dt, const void* k16, const void* v16,
+                                                       const uint8_t* k4, const uint8_t* ks, const uint8_t* v4, const uint8_t* vs,
+                                                       const float* kmean, const int32_t* seqlens,
+                                                       int B, int Hq, int Hkv, int Nkv, int D, int Bk,
+                                                       double budget, int fixed_k, int split_blocks, float softmax_scale,
+                                                       void* out, thrift_dtype out_dt, int32_t* idx_out, int32_t* cnt_out, int kmax_out,
+                                                       void* workspace, size_t workspace_bytes, void* stream, int polls) {
+  if (polls < 0 || polls > kSplitPolls) return THRIFT_ERR_SHAPE;
+  return attn_decode_impl(q, dt, k16, v16, k4, ks, v4, vs, kmean, seqlens, B, Hq, Hkv, Nkv, D, Bk, budget, fixed_k, split_blocks,
+                          softmax_scale, out, out_dt, idx_out, cnt_out, kmax_out, workspace, workspace_bytes, 0, stream, polls);
 }
 
 thrift_status thrift_attn_decode_static(const void* q, thrift_dtype dt, const void* k16, const void* v16,

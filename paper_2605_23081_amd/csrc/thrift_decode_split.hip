@@ -69,11 +69,6 @@ __device__ __forceinline__ v4f mfma16(v8s x, v8s y, v4f acc) {
 //   C / D      column r, rows 4 g + i in register i
 // All 128 channels of a 4-bit score are one instruction, and a wavefront's load of 16 keys x 64 bytes is 1 KiB in a row.
 
-// A maximum that is not published yet (no sum of products of numbers has these bits), and how often it is asked for: some
-// hundred milliseconds.  Only a workspace that somebody else writes during the call lets the wait end without it; the result
-// then is NaN.
-constexpr int kSplitPolls = 1 << 19;
-
 // largest value over the lanes that hold the same head (lane % NH), in every one of them: first of each 32 lanes
 template <int NH>
 __device__ __forceinline__ float head_max32(float v) {
@@ -439,6 +434,7 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
   };
   Scores next;
   float m = kEmptyMax;
+  bool unanswered = false;                                     // BOTH: a wait has ended without a maximum
   if constexpr (PASS == VALUES) {
     if (n_blocks > 0) next = load_scores(j0);
     const int ahead = n_blocks > 0 && !tail ? place * 4 + wave : 0;              // chunks of the partition in front
@@ -451,15 +447,17 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
       const uint32_t t = __float_as_uint(fmaxf(fmaxf(tops(0)[lane], tops(1)[lane]), fmaxf(tops(2)[lane], tops(3)[lane])));
       __hip_atomic_store(published, t == kUnset ? 0x7fc00000u : t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    bool lost = false;
     for (int e = kg; e < place; e += 64 / NH) {
-      uint32_t x = __hip_atomic_load(published - place + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      for (int tries = 0; x == kUnset && tries < kSplitPolls; ++tries) {
-        __builtin_amdgcn_s_sleep(1);
+      uint32_t x = kUnset;
+      for (int tries = 0; x == kUnset && tries < s.polls; ++tries) {
+        if (tries > 0) __builtin_amdgcn_s_sleep(1);
         x = __hip_atomic_load(published - place + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      if (x == kUnset) st.l = __uint_as_float(0x7fc00000u);
-      m = fmaxf(m, __uint_as_float(x));
+      if (x == kUnset) lost = true;
+      else m = fmaxf(m, __uint_as_float(x));
     }
+    unanswered = __builtin_amdgcn_ballot_w64(lost) != 0ULL;
     for (int u = 0; u < wave; ++u) m = fmaxf(m, tops(u)[hg]);
   }
   m = head_max32<NH>(m);
@@ -471,8 +469,15 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
   // The accumulators hold channel 8 (4 g + i) + e of head r in o[e][i]: row r of tile e is channel 8 r + e, because a lane's
   // 16 bytes of a 16-bit V row are 8 neighbouring channels, which are transposed against 8 rows inside the lane.
   v4f o[8];
+  // The sums of a wavefront that knows no maximum to start from are NaN, not its row sums: a row sum that is not positive divides
+  // nothing in the merge.
+  float none = 0.f;
+  if constexpr (PASS == BOTH) {
+    none = unanswered ? __builtin_nanf("") : 0.f;
+    asm volatile("" : "+v"(none));                             // arithmetic is compiled as if there were no NaN
+  }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = (v4f){0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < 8; ++e) o[e] = (v4f){none, none, none, none};
   if (n_blocks > 0) {
     for (int i = 0; i < n_blocks; ++i) {
       const int j = j0 + i;

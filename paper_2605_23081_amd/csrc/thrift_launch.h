@@ -90,6 +90,7 @@ struct DecodeSplitArgs {
   int items;              // workgroups per (sequence, KV head): nsplit * nsub, + 1 where lengths can leave a block partly filled
   int both;               // decode_split_both: both passes in one launch
   int chunks;             // nsplit * nsub * 4
+  int polls;              // one launch: how often a maximum is asked for that is not published yet (kSplitPolls)
   int clear;              // no selection has cleared tickets and tops: a launch of its own does
   const uint64_t* keys;   // nullable [B,Hq,Nkv/64]: order keys of the block scores; the kernels then select
   int fixed_k;            // the budget of that selection, as in SelectArgs
@@ -101,7 +102,10 @@ bool decode_split_selects(int Tk, bool both);
 constexpr int kSplitMaxItems = 448;          // partitions up to which the split is faster than one walk of a workgroup each
 constexpr int kSplitMaxItemsOneHead = 512;   // the same for one query head per KV head
 constexpr int kSplitMaxChunk = 8;
-constexpr uint32_t kUnset = 0xffffffffu;   // a maximum that is not known yet: no sum of products of numbers has these bits
+constexpr uint32_t kUnset = 0xffffffffu;   // a maximum that is not published yet: no sum of products of numbers has these bits
+// Some hundred milliseconds.  Only a workspace that somebody else writes during the call lets a wait end without its maximum; the
+// results of that sequence's KV head then are NaN.
+constexpr int kSplitPolls = 1 << 19;
 bool decode_split_wanted(int B, int Hq, int Hkv, int nsplit, int split_blocks);
 int decode_split_chunk(int B, int Hq, int Hkv, int Tk);
 void launch_decode_split(const DecodeSplitArgs& s, hipStream_t st);

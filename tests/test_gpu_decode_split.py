@@ -110,6 +110,43 @@ def test_both_passes_in_one_launch_equal_the_walk(T, Hq, Hkv, B, N, split, lens,
     assert torch.equal(listed, got[0])                                       # selected by a launch of its own
 
 
+@pytest.mark.parametrize("Hq,Hkv,B,N,split,lens", [
+    (1, 1, 2, 4096, 256, [4095, 4096 - 64]),                                 # one head, 16 workgroups or more per partition
+    (12, 4, 3, 8192, 31, [8191, 2000, 64]),                                  # three heads; partitions of one workgroup and of several
+    (16, 2, 9, 8192, 256, None),                                             # eight
+])
+def test_a_wait_without_an_answer_gives_nan(T, Hq, Hkv, B, N, split, lens):
+    """One launch, whose workgroups may not ask once for the largest scores in front of them: NaN wherever a partition has more
+    than one workgroup, never numbers that lack what was not waited for; then, asking, the results again."""
+    print(f"decode without answers Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} lens={lens}", flush=True)
+    import ctypes as C
+    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv)
+    assert N // 64 <= 128                                                    # short rows: one launch whatever the grid
+    args = _cache(T, wl)
+    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+    ws = torch.empty(T.decode_workspace_bytes(B, Hq, Hkv, N, 128, 64, split), dtype=torch.uint8, device="cuda")
+    call = T.lib().thrift_test_attn_decode_polls
+    call.argtypes = [*T.lib().thrift_attn_decode.argtypes, C.c_int]
+
+    def run(polls):
+        out = torch.full((B, Hq, 128), 7.0, dtype=torch.float32, device="cuda")
+        code = call(args[0].data_ptr(), T.F16 if args[0].dtype == torch.float16 else T.BF16, *(t.data_ptr() for t in args[1:]),
+                    None if sl is None else sl.data_ptr(), B, Hq, Hkv, N, 128, 64, 0.1, -1, split, 0.0, out.data_ptr(), T.F32, None, None, 0,
+                    ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream, polls)
+        assert code == 0
+        return out
+
+    want = torch.empty(B, Hq, 128, dtype=torch.float32, device="cuda")
+    T.thrift_attn_decode(*args, 64, 0.1, split_blocks=split, seqlens=sl, out=want, workspace=ws)
+    assert bool(torch.isfinite(want).all())
+    got = run(0)
+    nan = torch.isnan(got)
+    for b in range(B):
+        blocks = (N if lens is None else lens[b]) // 64
+        assert bool(nan[b].all()) if min(blocks, split) > 32 else torch.equal(got[b], want[b]) or bool(nan[b].all())     # 4 x 8 blocks at most per workgroup
+    assert torch.equal(run(1 << 19), want)
+
+
 @pytest.mark.parametrize("Hq,Hkv,B,N", [(32, 8, 9, 8192), (8, 2, 2, 4096)])
 def test_decode_in_a_graph(T, Hq, Hkv, B, N):
     """Tickets and maxima are cleared inside the call: every replay gives what the eager call gives, on new values too."""
