@@ -78,7 +78,7 @@ struct DecodeLayout {
   int nsplit, nparts, words, order_items;
 };
 
-// Workspace of the form in finer pieces (two passes over chunks); the walk's fits into it wherever it does not exceed it.
+// Workspace of the form in finer pieces (two passes over chunks).
 struct DecodeSplitLayout {
   size_t keys, bitmap, scores, cmax, tickets, tops, taken, part_o, part_ml, total;
   int nsplit, nparts, words, cw, nsub;
@@ -86,33 +86,6 @@ struct DecodeSplitLayout {
 
 // Key blocks per partition: a size of the whole row or more is one partition (and no sum with it can overflow).
 int partition_blocks(int Tk, int split_blocks) { return split_blocks < Tk ? split_blocks : Tk; }
-
-DecodeSplitLayout decode_split_layout(int B, int Hq, int Hkv, int Nkv, int Bk, int split_blocks) {
-  DecodeSplitLayout L;
-  const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks);
-  L.nsplit = (Tk + part - 1) / part;
-  L.words = (Tk + 63) / 64;
-  L.cw = decode_split_chunk(B, Hq, Hkv, Tk);
-  L.nsub = (part + 4 * L.cw - 1) / (4 * L.cw);
-  L.nparts = L.nsplit * L.nsub + 1;              // one partial per workgroup + one for a partly filled last block
-  const size_t rows = (size_t)B * Hq;
-  size_t off = 0;
-  L.keys = off; off += align256(rows * Tk * sizeof(uint64_t));
-  L.bitmap = off; off += align256(rows * L.words * sizeof(unsigned long long));
-  // Two launches hand the scores over through memory; one launch does not need this.  Up to 320 partitions it is asked for all the
-  // same: which problems fit an array of fixed size (the static one among them) stays what it was.
-  const bool both = decode_split_both(B, Hkv, Tk);
-  L.scores = off; off += !both || (long)B * Hkv * L.nsplit <= 320 ? align256(rows * Nkv * sizeof(float)) : 0;
-  // the maxima of the chunks, or of the workgroups and a ticket for each partition: at most half as many words
-  L.cmax = L.tops = off;
-  L.tickets = off + rows * (L.nsplit * L.nsub + 1) * sizeof(unsigned);
-  off += align256(rows * L.nsplit * L.nsub * 4 * sizeof(float));
-  L.taken = off; off += !both && decode_split_selects(Tk, false) ? align256(rows * L.nparts * sizeof(uint32_t)) : 0;
-  L.part_o = off; off += align256(rows * L.nparts * kHeadDim * sizeof(float));
-  L.part_ml = off; off += align256(rows * L.nparts * 2 * sizeof(float));
-  L.total = off;
-  return L;
-}
 
 DecodeLayout decode_layout(int B, int Hq, int Hkv, int Nkv, int Bk, int split_blocks) {
   DecodeLayout L;
@@ -128,6 +101,34 @@ DecodeLayout decode_layout(int B, int Hq, int Hkv, int Nkv, int Bk, int split_bl
   L.order_items = decode_order_items(B, Hkv, L.nsplit);
   L.order = off; off += align256((size_t)L.order_items * sizeof(int));
   L.total = off;
+  return L;
+}
+
+DecodeSplitLayout decode_split_layout(int B, int Hq, int Hkv, int Nkv, int Bk, int split_blocks) {
+  DecodeSplitLayout L;
+  const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks);
+  L.nsplit = (Tk + part - 1) / part;
+  L.words = (Tk + 63) / 64;
+  L.cw = decode_split_chunk(B, Hq, Hkv, Tk);
+  L.nsub = (part + 4 * L.cw - 1) / (4 * L.cw);
+  L.nparts = L.nsplit * L.nsub + 1;              // one partial per workgroup + one for a partly filled last block
+  const size_t rows = (size_t)B * Hq;
+  size_t off = 0;
+  L.keys = off; off += align256(rows * Tk * sizeof(uint64_t));
+  L.bitmap = off; off += align256(rows * L.words * sizeof(unsigned long long));
+  const bool both = decode_split_both(B, Hkv, Tk);
+  L.scores = off; off += both ? 0 : align256(rows * Nkv * sizeof(float));      // two launches hand the scores over through memory
+  // the maxima of the chunks, or of the workgroups and a ticket for each partition: nsplit * nsub + 1 words per head and nsplit
+  // per KV head are no more than the four of every workgroup
+  L.cmax = L.tops = off;
+  L.tickets = off + rows * (L.nsplit * L.nsub + 1) * sizeof(unsigned);
+  off += align256(rows * L.nsplit * L.nsub * 4 * sizeof(float));
+  L.taken = off; off += !both && decode_split_selects(Tk, false) ? align256(rows * L.nparts * sizeof(uint32_t)) : 0;
+  L.part_o = off; off += align256(rows * L.nparts * kHeadDim * sizeof(float));
+  L.part_ml = off; off += align256(rows * L.nparts * 2 * sizeof(float));
+  // always more than the walk's: the size of a workspace says which form it holds
+  const size_t walk = decode_layout(B, Hq, Hkv, Nkv, Bk, split_blocks).total;
+  L.total = off > walk ? off : walk + 256;
   return L;
 }
 
@@ -377,8 +378,7 @@ size_t thrift_attn_decode_workspace(int B, int Hq, int Hkv, int Nkv, int D, int 
   if (least == 0 || Hq % Hkv != 0) return least;
   const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks), nsplit = (Tk + part - 1) / part;
   if (!decode_split_wanted(B, Hq, Hkv, nsplit, split_blocks)) return least;
-  const size_t split = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks).total;
-  return split > least ? split : least;
+  return decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks).total;
 }
 
 static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void* k16, const void* v16,

@@ -208,6 +208,24 @@ def test_m0_check_reads_the_compiler_listing():
     assert m0_outside_inline_asm(ok + "\n\ts_mov_b32 m0, -1\n\tds_gws_init v0 gds") == 1
 
 
+def test_decode_workspace_holds_scores_for_two_launches_only():
+    """What one launch keeps in LDS is not asked for, so that the form fits wherever the two launches with their scores would; and
+    the form in finer pieces always asks for more than the walk, since the size of a workspace chooses between them."""
+    size = lambda B, Hq, Hkv, Tk, split=256: T.decode_workspace_bytes(B, Hq, Hkv, 64 * Tk, 128, 64, split)
+    scores = lambda B, Hq, Tk: B * Hq * Tk * 64 * 4
+    for B, Hq, Hkv, Tk in ((1, 32, 8, 64), (1, 32, 8, 2048), (4, 64, 8, 512), (16, 32, 8, 128), (7, 8, 8, 2048)):
+        assert size(B, Hq, Hkv, Tk) < scores(B, Hq, Tk)                      # one launch
+    for B, Hq, Hkv, Tk in ((1, 32, 8, 1024), (1, 64, 8, 1024), (1, 32, 8, 129)):
+        assert scores(B, Hq, Tk) < size(B, Hq, Hkv, Tk)                      # two
+    for Hq, Hkv in ((1, 1), (16, 16), (16, 8), (32, 8), (64, 8), (7, 1)):
+        for B in (1, 3, 16):
+            for Tk in (1, 2, 63, 128, 129, 512, 1024):
+                for split in (17, 256, 4096):
+                    least = T.decode_least_workspace_bytes(B, Hq, Hkv, 64 * Tk, 128, 64, split)
+                    if B * Hkv * -(-Tk // min(split, Tk)) <= 448:
+                        assert size(B, Hq, Hkv, Tk, split) >= least + 256
+
+
 def _listing(source, path):
     import subprocess
     from paper_2605_23081_amd import build

@@ -348,7 +348,7 @@ def test_partition_sizes_beyond_the_row(T, Hq, Hkv):
 def test_a_card_without_room_for_two_passes_runs_one(T, monkeypatch):
     """No workspace given and no memory for the two-pass form's: the call runs the one-pass form."""
     print("decode without room for the larger workspace", flush=True)
-    Hq, Hkv, N = 32, 8, 131072
+    Hq, Hkv, N = 64, 8, 65536
     args = _cache(T, W.scaled(W.DECODE_131K, B=1, N=N, Hq=Hq, Hkv=Hkv))
     need, least = (f(1, Hq, Hkv, N, 128, 64, 256) for f in (T.decode_workspace_bytes, T.decode_least_workspace_bytes))
     assert need > (16 << 20) and least < (1 << 20)
@@ -356,6 +356,10 @@ def test_a_card_without_room_for_two_passes_runs_one(T, monkeypatch):
     two = T.thrift_attn_decode(*args, 64, 0.05, workspace=torch.empty(need, dtype=torch.uint8, device="cuda"))
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
+    held = []                                                # what the allocator holds has no room for it either
+    while not held or torch.cuda.memory_reserved() == before:
+        before = torch.cuda.memory_reserved()
+        held.append(torch.empty(need, dtype=torch.uint8, device="cuda"))
     total = torch.cuda.get_device_properties(0).total_memory
     got = []
     try:                                                     # the allocator's own limit: 8 MiB more than it holds

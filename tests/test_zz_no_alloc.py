@@ -71,8 +71,11 @@ def test_static_scratch_decode_rejects_oversized_problem(T):
 
 @pytest.mark.parametrize("B,Hq,Hkv,N,lens,fits", [
     (1, 32, 8, 8192, [8001], True),              # the two-pass form within the array
-    (4, 64, 8, 32768, None, False),              # its scores alone would fill it: the one-pass form
-    (16, 8, 1, 65536, [65536 - 4099 * b for b in range(16)], False),
+    (1, 64, 8, 65536, None, True),               # with its scores in memory
+    (4, 64, 8, 32768, None, True),               # in one launch, without them
+    (16, 8, 1, 65536, [65536 - 4099 * b for b in range(16)], True),
+    (7, 64, 8, 131072, None, False),             # its partials alone would fill it: the one-pass form
+    (14, 64, 8, 65536, [65536 - 2099 * b for b in range(14)], False),
 ])
 def test_static_scratch_decode_takes_the_form_that_fits(T, B, Hq, Hkv, N, lens, fits):
     """Default partitions, where the chip would be left idle: the result is that of the call with a workspace of the
