@@ -43,18 +43,30 @@ def test_order_of_the_workgroups(T, B, Hq, Hkv, N, Bq, causal):
             assert torch.equal(out[b, h * G:(h + 1) * G], alone[0])
 
 
+def _form(B, Hq, Nq, N, kmax):
+    """Row groups per workgroup of the four-wavefront kernel, 0: the plain one (launch_prefill_split's rule)."""
+    groups, Tk = B * Hq * -(-Nq // 32), -(-N // 64)
+    if kmax * 100 >= Tk * 15:
+        return 0
+    return 1 if groups <= 256 else 2 if groups <= 512 and Tk >= 10 else 0
+
+
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
-@pytest.mark.parametrize("Hq,Hkv,N,Bq,causal,copies", [
-    (1, 1, 1, 64, True, 600),             # one row, one key
-    (1, 1, 257, 64, True, 80),            # five groups of key blocks, the last one short; a short last row group
-    (2, 1, 700, 128, True, 20),           # four row groups per query block, of which the last has none
-    (3, 1, 1100, 64, False, 8),           # every row sees every block
-    (8, 2, 1024, 128, True, 4),           # 256 row groups, the most with one per workgroup
-    (8, 8, 1025, 128, True, 2),           # 264: two row groups per workgroup
-    (4, 1, 4095, 64, True, 2),            # 512, the most
-    (8, 8, 577, 64, False, 4),            # ten key blocks, the fewest
+@pytest.mark.parametrize("Hq,Hkv,N,Bq,causal,copies,form", [
+    (1, 1, 385, 64, True, 50, 1),         # seven key blocks, the fewest: groups of four and three; one key and one row in the last
+    (2, 1, 448, 128, False, 30, 1),       # the same, all whole; every row sees every block
+    (1, 1, 513, 64, True, 40, 1),         # nine: the last group of key blocks is one block
+    (2, 1, 700, 128, True, 20, 1),        # four row groups per query block, of which the last has none
+    (3, 1, 1100, 64, False, 8, 1),        # every row sees every block
+    (8, 2, 1024, 128, True, 4, 1),        # 256 row groups, the most with one per workgroup
+    (8, 8, 1025, 128, True, 2, 2),        # 264: two row groups per workgroup
+    (16, 16, 577, 64, False, 2, 2),       # ten key blocks, the fewest with two; a last workgroup of one row group of one row
+    (16, 4, 640, 128, True, 2, 2),        # ten whole ones
+    (16, 4, 609, 64, True, 2, 2),         # both row groups of the last workgroup, one of them with one row
+    (4, 1, 4095, 64, True, 2, 2),         # 512 row groups, the most
+    (16, 16, 576, 64, True, 2, 0),        # nine key blocks: the plain kernel
 ])
-def test_four_wavefronts_per_row_group(T, Hq, Hkv, N, Bq, causal, copies, dtype):
+def test_four_wavefronts_per_row_group(T, Hq, Hkv, N, Bq, causal, copies, form, dtype):
     """The same sequence alone and in a batch that is large enough for the plain kernel: equal bits, LSE included, for lists up
     to 15 % of the key blocks (none, some, neighbouring blocks)."""
     print(f"four wavefronts per row group {Hq}/{Hkv} N={N} Bq={Bq} causal={causal} {dtype}", flush=True)
@@ -62,8 +74,8 @@ def test_four_wavefronts_per_row_group(T, Hq, Hkv, N, Bq, causal, copies, dtype)
     Tk = -(-N // 64)
     ks = sorted({0, max(1, Tk // 20), max(0, (15 * Tk - 1) // 100)})
     many = [t.expand(copies, -1, -1, -1).contiguous() for t in (q, k, v)]
-    assert copies * Hq * -(-N // 32) > 512
     for fixed_k in ks:
+        assert _form(1, Hq, N, N, max(1, fixed_k)) == form and _form(copies, Hq, N, N, max(1, fixed_k)) == 0
         for order in (0, 1):
             lse, lse_n = torch.full((1, Hq, N), 7.0, device="cuda"), torch.full((copies, Hq, N), 7.0, device="cuda")
             a = T.thrift_attention(q, k, v, causal, Bq, 64, fixed_k=fixed_k, tile_order=order, lse=lse)
@@ -74,12 +86,13 @@ def test_four_wavefronts_per_row_group(T, Hq, Hkv, N, Bq, causal, copies, dtype)
 
 
 @pytest.mark.parametrize("order", [0, 1])
-@pytest.mark.parametrize("Nq,off,N,ids", [
-    (128, 30, 4000, [0, 1, 2, 3, 7, 8]),                                     # promoted blocks that follow each other
-    (100, 15, 2050, [31, 32]),                                               # the last blocks, of which one is short
-    (64, 31, 4096, [0, 62, 63]),                                             # some blocks after the rows' own
+@pytest.mark.parametrize("Nq,off,N,ids,form", [
+    (128, 30, 4000, [0, 1, 2, 3, 7, 8], 1),                                  # promoted blocks that follow each other
+    (100, 15, 2050, [31, 32], 1),                                            # the last blocks, of which one is short
+    (64, 31, 4096, [0, 62, 63], 1),                                          # some blocks after the rows' own
+    (2113, 15, 4090, [0, 1, 2, 3, 7, 8, 62, 63], 2),                         # two row groups per workgroup; all of it
 ])
-def test_four_wavefronts_per_row_group_in_a_chunk(T, Nq, off, N, ids, order):
+def test_four_wavefronts_per_row_group_in_a_chunk(T, Nq, off, N, ids, form, order):
     print(f"four wavefronts, chunk of {Nq} at {off} in {N}, ids {ids}, order {order}", flush=True)
     q, k, v = _qkv(1, 4, 2, N, torch.bfloat16)
     q = q[:, :, :Nq].contiguous()
@@ -92,5 +105,7 @@ def test_four_wavefronts_per_row_group_in_a_chunk(T, Nq, off, N, ids, order):
         return T.thrift_attn_prefill_chunk(a, b, c, *codes, idx.expand(n, -1, -1, -1).contiguous(), cnt.expand(n, -1, -1).contiguous(),
                                            128, 64, True, off, tile_order=order)
 
-    alone, many = run(1), run(80)
-    assert bool(torch.isfinite(alone).all()) and torch.equal(alone[0], many[0]) and torch.equal(alone[0], many[79])
+    copies = 80 if form == 1 else 2
+    assert _form(1, 4, Nq, N, len(ids)) == form and _form(copies, 4, Nq, N, len(ids)) == 0
+    alone, many = run(1), run(copies)
+    assert bool(torch.isfinite(alone).all()) and torch.equal(alone[0], many[0]) and torch.equal(alone[0], many[copies - 1])
