@@ -147,6 +147,29 @@ def test_a_wait_without_an_answer_gives_nan(T, Hq, Hkv, B, N, split, lens):
     assert torch.equal(run(1 << 19), want)
 
 
+def test_calls_in_one_launch_on_two_streams(T):
+    """Workgroups that wait for each other, of two calls at a time with a workspace each, more than the chip holds: every call gives
+    what it gives alone."""
+    print("decode in one launch on two streams", flush=True)
+    calls = []
+    for Hq, Hkv, B, N, budget in ((32, 8, 16, 16384, 0.05), (16, 16, 12, 8192, 0.25)):
+        args = _cache(T, W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv))
+        sl = torch.tensor([N - 731 * b for b in range(B)], dtype=torch.int32, device="cuda")
+        ws = torch.empty(T.decode_workspace_bytes(B, Hq, Hkv, N, 128, 64, 256), dtype=torch.uint8, device="cuda")
+        outs = [torch.full((B, Hq, 128), float("nan"), dtype=torch.float32, device="cuda") for _ in range(21)]
+        run = lambda out, args=args, budget=budget, sl=sl, ws=ws: T.thrift_attn_decode(*args, 64, budget, seqlens=sl, out=out, workspace=ws)
+        run(outs[0])
+        calls.append((run, outs, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for n in range(1, 21):
+        for run, outs, stream in calls:
+            with torch.cuda.stream(stream):
+                run(outs[n])
+    torch.cuda.synchronize()
+    for _, outs, _ in calls:
+        assert bool(torch.isfinite(outs[0]).all()) and all(torch.equal(x, outs[0]) for x in outs)
+
+
 @pytest.mark.parametrize("Hq,Hkv,B,N", [(32, 8, 9, 8192), (8, 2, 2, 4096)])
 def test_decode_in_a_graph(T, Hq, Hkv, B, N):
     """Tickets and maxima are cleared inside the call: every replay gives what the eager call gives, on new values too."""
