@@ -116,7 +116,7 @@ DecodeSplitLayout decode_split_layout(int B, int Hq, int Hkv, int Nkv, int Bk, i
   size_t off = 0;
   L.keys = off; off += align256(rows * Tk * sizeof(uint64_t));
   L.bitmap = off; off += align256(rows * L.words * sizeof(unsigned long long));
-  const bool both = decode_split_both(B, Hkv, Tk);
+  const bool both = decode_split_both(B, Hq, Hkv, Tk);
   L.scores = off; off += both ? 0 : align256(rows * Nkv * sizeof(float));      // two launches hand the scores over through memory
   // the maxima of the chunks, or of the workgroups and a ticket for each partition: nsplit * nsub + 1 words per head and nsplit
   // per KV head are no more than the four of every workgroup
@@ -412,7 +412,7 @@ static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void
       DecodeArgs& a = s.a;
       unsigned long long* bitmap = (unsigned long long*)(ws + S.bitmap);
       const bool select = kneed > 0 || idx_out != nullptr || cnt_out != nullptr;
-      const bool both = decode_split_both(B, Hkv, Tk);
+      const bool both = decode_split_both(B, Hq, Hkv, Tk);
       // nobody asks for the lists and a row fits a wavefront: the scores pass selects
       const bool in_pass = kneed > 0 && idx_out == nullptr && cnt_out == nullptr && decode_split_selects(Tk, both);
       s.keys = in_pass ? (const uint64_t*)(ws + S.keys) : nullptr;

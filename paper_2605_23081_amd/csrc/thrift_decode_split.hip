@@ -739,11 +739,18 @@ constexpr int kSelectBoth = 128;
 
 // One launch for both passes, or two.  One launch reads and writes no scores and saves the gap between two; but the places of a
 // partition wait for each other, and with few of them in long partitions that wait is what the call takes.  Up to kSelectBoth key
-// blocks a sequence nobody waits for long.  Two / one in us, B x tokens, heads, budget:
-//   short      1 x 512, 32/8, 5 %   25.7 /  23.0    10 x 3072, 64/8, 5 %     41.6 /  32.5    16 x 3072, 32/8, 5 %   41.0 / 37.8
-//   <= 8192    1 x 32768, 32/8      38.0 /  51.7    3 x 20480, 32/8, 100 %   63.0 /  67.5    1 x 65536, 32/8, 5 %   51.6 / 56.3
-//   more       4 x 32768, 32/8      73.5 /  67.4    1 x 131072, 32/8, 5 %    80.4 /  75.5    4 x 32768, 64/8, 100 %  147 /  105
-bool decode_split_both(int B, int Hkv, int Tk) { return Tk <= kSelectBoth || (long)B * Hkv * Tk > 8192; }
+// blocks a sequence nobody waits for long.  Between 129 and kSplitSelectBlocks one launch also needs a launch for the selection that
+// two do not.  Two / one in us, B x key blocks of a sequence, heads, budget (blocks of all KV heads):
+//   short         1 x    8, 32/8, 5 %   25.7 /  23.0    10 x   48, 64/8, 5 %     41.6 /  32.5    16 x   48, 32/8, 5 %   41.0 / 37.8
+//   up to 8192    1 x  512, 32/8        38.0 /  51.7     3 x  320, 32/8, 100 %   63.0 /  67.5     1 x 1024, 32/8, 5 %   51.6 / 56.3
+//    8256         1 x 1032, 32/8, 5 %   54.6 /  53.2     1 x 1032, 64/8, 5 %     71.0 /  74.0
+//    8448         4 x  264, 32/8, 5 %   48.6 /  53.1     the same at 25 %        68.2 /  76.6     4 x  264, 64/8, 5 %   64.5 / 64.5
+//    9216         2 x  576, 32/8, 5 %   51.6 /  52.0     2 x  576, 16/8, 5 %     44.3 /  45.8     2 x  576, 64/8, 5 %   65.5 / 72.0
+//   10240         1 x 1280, 32/8, 5 %   58.3 /  57.7     5 x  256, 16/8, 5 %     45.2 /  42.4     1 x 1280, 64/8, 5 %   76.0 / 81.0
+//   12288         3 x  512, 32/8, 25 %  91.5 /  82.8     3 x  512, 16/8, 25 %    71.2 /  65.6     3 x  512, 64/8, 25 %   114 /  108
+//   14336         7 x  256, 32/8, 25 %  94.9 /  87.9     7 x  256, 16/8, 25 %    73.1 /  68.6     7 x  256, 64/8, 25 %   117 /  109
+//   more          4 x  512, 32/8        73.5 /  67.4     1 x 2048, 32/8, 5 %     80.4 /  75.5     4 x  512, 64/8, 100 %  147 /  105
+bool decode_split_both(int B, int Hq, int Hkv, int Tk) { return Tk <= kSelectBoth || (long)B * Hkv * Tk > (Hq / Hkv > 4 ? 10240 : 9216); }
 
 // Where the kernels select for themselves instead of a launch of its own: rows of key blocks that a wavefront holds, and with one
 // launch (whose workgroups ask for more blocks each, among others that wait) only as many as two registers hold: 156 us with a
@@ -770,8 +777,8 @@ bool decode_split_selects(int Tk, bool both) { return Tk <= (both ? kSelectBoth 
 //   65536          16 x 32768, 32/8, 25 %  272.3 / 278.1                        4
 //                  4 x 131072, 32/8, 25 %  342.0 / 334.7                        8
 // One or two heads fit three workgroups per CU with eight blocks too, so that only the number of wavefronts decides.  Four / eight:
-//    8384          2 x 16768, 16/16, 25 %   44.4 /  49.4                        4
-//                  4 x 16768, 16/8, 25 %    55.9 /  61.3                        4
+//    8192          4 x 8192, 16/16, 25 %    38.0 /  42.6                        4
+//    8960          10 x 7168, 16/8, 25 %    46.0 /  52.3                        4
 //   10000          2 x 40000, 16/8, 5 %     49.1 /  44.4                        8
 //   32768          4 x 32768, 16/16, 25 %   89.0 /  94.7                        4 (one head)
 //   20480          5 x 32768, 16/8, 5 %     63.0 /  60.5                        8
@@ -781,11 +788,13 @@ bool decode_split_selects(int Tk, bool both) { return Tk <= (both ? kSelectBoth 
 //    7168          2 x 28672, 32/8, 25 %    66.1 /  62.7 /  70.9                  2
 //    8192          1 x 65536, 32/8, 5 %     62.2 /  52.7 /  51.6                  4
 //                  4 x 16384, 64/8, 5 %     87.6 /  71.0 /  63.4                  4
+//    8384          2 x 16768, 16/16, 5 %            40.4 /  36.6                  4
+//                  4 x 16768, 16/8, 25 %            54.0 /  53.6                  4
 //    3072          2 x 12288, 64/8, 5 %     43.0 /  46.1 /  50.1                  1 (more than four heads: up to 4096)
 int decode_split_chunk(int B, int Hq, int Hkv, int Tk) {
   const long blocks = (long)B * Hkv * Tk;
   const int heads = Hq / Hkv;
-  if (!decode_split_both(B, Hkv, Tk)) return blocks < (heads > 4 ? 4096 : 2048) ? 1 : blocks < 8192 ? 2 : 4;
+  if (!decode_split_both(B, Hq, Hkv, Tk)) return blocks < (heads > 4 ? 4096 : 2048) ? 1 : blocks < 8192 ? 2 : 4;
   int cw = 1;
   while (cw < chunk_limit(heads, true) && blocks > 1536L * cw) cw *= 2;
   if (cw == 8 && heads > 2 && Tk <= 1024 && (blocks > 16384 || (Tk <= 256 && blocks <= 14336))) cw = 4;

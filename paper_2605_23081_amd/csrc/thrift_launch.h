@@ -97,7 +97,7 @@ struct DecodeSplitArgs {
   long long ppm;
 };
 constexpr int kSplitSelectBlocks = 512;      // key blocks up to which the kernels select for themselves: eight keys per lane of a wavefront
-bool decode_split_both(int B, int Hkv, int Tk);
+bool decode_split_both(int B, int Hq, int Hkv, int Tk);
 bool decode_split_selects(int Tk, bool both);
 constexpr int kSplitMaxItems = 448;          // partitions up to which the split is faster than one walk of a workgroup each
 constexpr int kSplitMaxItemsOneHead = 512;   // the same for one query head per KV head

@@ -226,6 +226,17 @@ def test_decode_workspace_holds_scores_for_two_launches_only():
                         assert size(B, Hq, Hkv, Tk, split) >= least + 256
 
 
+def test_decode_takes_one_launch_where_it_is_the_faster_form():
+    """Known by the scores in the workspace: four query heads per KV head just above 8192 key blocks are slower in one launch (53.1
+    us against 48.6 for 4 sequences of 264 blocks), eight up to 10240 (81.0 against 76.0 for one of 1280)."""
+    two = lambda B, Hq, Hkv, Tk: T.decode_workspace_bytes(B, Hq, Hkv, 64 * Tk, 128, 64, 256) > B * Hq * Tk * 64 * 4
+    assert two(4, 32, 8, 264) and two(2, 32, 8, 576) and two(2, 16, 8, 576) and two(1, 16, 16, 576)
+    assert not two(1, 32, 8, 1153) and not two(5, 16, 8, 256) and not two(2, 16, 16, 384)
+    assert two(2, 64, 8, 576) and two(1, 64, 8, 1280) and two(2, 40, 8, 640)
+    assert not two(1, 64, 8, 1281) and not two(3, 64, 8, 512)
+    assert not two(16, 32, 8, 128) and not two(16, 64, 8, 64)                # short rows, whatever the grid
+
+
 def _listing(source, path):
     import subprocess
     from paper_2605_23081_amd import build

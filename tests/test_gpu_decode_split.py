@@ -46,6 +46,9 @@ def _cache(T, wl):
     (32, 8, 2, 16384, 100, [16384, 9000], 0.05),                             # 2 key blocks per wavefront
     (8, 8, 2, 65536, 256, [65535, 40001], 0.05),                             # 4
     (16, 8, 2, 131072, 250, [131072, 70000], 0.25),                          # 8
+    (32, 8, 4, 16896, 256, [16896 - 1500 * b for b in range(4)], 0.25),      # 4 in two launches, above 8192 key blocks; a partition of 8
+    (16, 8, 2, 36864, 256, None, 0.05),                                      # 9216, the most in two launches
+    (64, 8, 2, 40960, 250, [40959, 33000], 0.1),                             # 10240, the most with eight heads
     (16, 16, 11, 2176, 17, [2176 - 197 * b for b in range(11)], 0.25),       # one head per KV head: 352 partitions
     (16, 16, 16, 2176, 17, [2175] * 16, 0.05),                               # 512, the most
 ])
@@ -83,7 +86,7 @@ def test_two_pass_decode_equals_one_pass(T, Hq, Hkv, B, N, split, lens, budget, 
     (32, 8, 3, 32768, 256, [32767, 20000, 16384], 0.1, False),               # the same, selected by a launch of its own
 ])
 def test_both_passes_in_one_launch_equal_the_walk(T, Hq, Hkv, B, N, split, lens, budget, shared, dtype):
-    """More than 8192 key blocks.  The workspace starts from bytes that look like published maxima and tickets (zeros), like
+    """Many key blocks, or short rows.  The workspace starts from bytes that look like published maxima and tickets (zeros), like
     maxima still to come (ones) and from what the call before has left."""
     print(f"decode in one launch Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} budget={budget} {dtype}", flush=True)
     wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv, dtype=dtype)
