@@ -826,8 +826,11 @@ __global__ void __launch_bounds__(256) decode_select_kernel(DecodeSelectArgs p, 
       int at[MAXC];
 #pragma unroll
       for (int c = 0; c < MAXC; ++c) {
-        at[c] = min(255, (int)((f[c] - lo) * scale));
-        if ((in >> c) & 1u) atomicAdd(&bin[at[c]], 1);
+        at[c] = -1;                                          // no candidate: its quotient need not fit an int
+        if ((in >> c) & 1u) {
+          at[c] = min(255, (int)((f[c] - lo) * scale));
+          atomicAdd(&bin[at[c]], 1);
+        }
       }
       __syncthreads();
       const int4 x = reinterpret_cast<const int4*>(bin)[lane];
