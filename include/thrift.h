@@ -286,7 +286,8 @@ size_t thrift_attn_decode_least_workspace(int B, int Hq, int Hkv, int Nkv, int D
  *     NULL = Nkv.  A length that is not a multiple of Bk leaves the last key block partly filled: its keys past
  *     the length are masked, its kmean entry must be the mean of the tokens it has and its V groups must have
  *     been quantised from those tokens alone (what thrift_kv_cache_append, or the pre-pass on a tensor of that
- *     length, produces).  Cache contents past that block are never read.  A sequence of length 0 yields zeros.
+ *     length, produces).  Cache contents past that block reach no result (of kmean they may be read, up to Nkv/Bk rows,
+ *     before the length is known).  A sequence of length 0 yields zeros.
  *     Split-K: the full key blocks are cut into the partitions; a partly filled last block is a partition of its own.
  *   split_blocks: key blocks per partition (> 0): each (query head, partition) is one recurrence of Alg. 1 over the
  *     partition's key blocks in ascending order; the rounding of P on the 4-bit path follows the running maximum, so

@@ -506,8 +506,9 @@ thrift_status thrift_attn_decode_static(const void* q, thrift_dtype dt, const vo
   if (need > kStaticScratchBytes) return THRIFT_ERR_WORKSPACE;
   void* ws = nullptr;
   if (thrift_status s = static_scratch(&ws)) return s;
-  // Every byte of the workspace that the kernels read is written earlier in the same call (score keys and bitmap
-  // words of the visible blocks, one partial per partition slot), so nothing has to be cleared between calls.
+  // No result depends on a byte of the workspace that the call has not written before (score keys and bitmap words of the
+  // visible blocks, tickets and maxima, one partial per slot in use), so nothing has to be cleared between calls.  Keys and
+  // partials past the length are read while the length is still on its way, and dropped.
   return attn_decode_impl(q, dt, k16, v16, k4, ks, v4, vs, kmean, seqlens, B, Hq, Hkv, Nkv, D, Bk, budget, fixed_k, split_blocks,
                           softmax_scale, out, out_dt, idx_out, cnt_out, kmax_out, ws, kStaticScratchBytes, 0, stream);
 }
