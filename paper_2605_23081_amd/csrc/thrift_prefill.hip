@@ -566,7 +566,7 @@ static bool wide_schedule(const PrefillArgs& a) {
 // the chip was about to run empty: 142 -> 118 us for 2 x 4096 tokens, 16/16 heads, 387 -> 340 us for 2 x 8192, 208 -> 189 us
 // for 2 x 4096 with 32/8, 1252 -> 1079 us for 32768 with 8/2.  In grids of more than eight rounds of three workgroups per CU
 // the ends weigh little and the units' K/V streams want the L2 one after the other: 1210 / 1260 us for 2 x 8192, 64/8 heads.
-static bool interleaved_units(const PrefillArgs& a, unsigned grid) { return a.causal && grid <= 8u * 3u * 256u; }
+static bool interleaved_units(const PrefillArgs& a, unsigned grid) { return a.causal && grid <= 8u * 3u * kCus; }
 
 void launch_prefill(const PrefillArgs& args, hipStream_t st) {
   if (launch_prefill_split(args, st)) return;
@@ -576,7 +576,7 @@ void launch_prefill(const PrefillArgs& args, hipStream_t st) {
   if (a.tile_order == 4 && a.Bq == 128) {
     // persistent launch of the Sec. 3.3 order: three workgroups per CU.  One counter per device: two such launches
     // must not overlap on a device.  The counter is cleared by a kernel (a memset node misbehaves under graph capture).
-    int dev = 0, cus = 256;
+    int dev = 0, cus = kCus;
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const unsigned resident = (unsigned)min((long)grid, 3L * cus);
     prefill_reset_counter_kernel<<<dim3(1), dim3(1), 0, st>>>();

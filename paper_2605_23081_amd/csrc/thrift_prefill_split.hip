@@ -406,7 +406,7 @@ static void launch_split(const PrefillArgs& a, hipStream_t st) {
 // tokens the walk of 8 key blocks is too short to gain (28.0 / 27.6 us; 27.9 / 28.3 in the order of Sec. 3.3).
 // Promoted blocks come one to a group here, and one at a time where they come last: at 10 % 477 / 330 us for the chunk of 128
 // row groups, at 25 % 459 / 547.
-constexpr int kSplitRowGroups = 256;
+constexpr int kSplitRowGroups = kCus;
 constexpr int kSplitLeastBlocks = 10;        // key blocks, beyond kSplitRowGroups
 constexpr int kSplitPercent = 15;            // list length / key blocks (in %) from which the plain kernel is the faster one
 
