@@ -14,8 +14,8 @@
 // while LDS DMA brings group n + 1.  Every score, maximum, code and sum is formed from the same operands in the same order as by
 // one wavefront: the results have the same bits.
 //
-// A step of four blocks takes 1.8 us where one wavefront takes 3.3 (one head of 2048 tokens: 41 -> 21 us, 54 -> 35 with the
-// launches before it).  What bounds it: the instruction issue of a lone wavefront, about 1200 cycles for the probabilities, 1300
+// A step of four blocks takes 1.8 us where one wavefront takes 3.3 (one head of 2048 tokens: 41 -> 22.5 us, 54 -> 31 with
+// the launches before it).  What bounds it: the instruction issue of a lone wavefront, about 1200 cycles for the probabilities, 1300
 // for scores and P.V, 1300 for the maxima, the walk and the DMA instructions.
 //
 // RG row groups share the staged blocks of a workgroup of RG x KS wavefronts.

@@ -234,7 +234,8 @@ __device__ __forceinline__ bool softmax_update(v16f (&s)[2], int lane, bool mask
 __device__ __forceinline__ void rescale(v16f (&o)[4], bool grew, float alpha) {
   // Skipping is exact: alpha == 1 leaves every accumulator unchanged.  The multiplies are written as
   // in-place instructions so that the accumulators keep their registers on both sides of the branch
-  // (otherwise the skip path pays 64 register copies per key block).
+  // (otherwise the skip path pays 64 register copies per key block).  The matrix instructions that wrote them lie a whole
+  // softmax behind; the build follows the listing and refuses hand-written instructions that come too early.
   if (grew) {
 #pragma unroll
     for (int n = 0; n < 4; ++n)
