@@ -139,7 +139,11 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
   // BOTH: raw scores of the wavefront's blocks, [block][head][key]; those of a block give way to what P.V reads: the
   // probabilities rounded to 16 bits [head][key], the codes of P [head][key / 2] and their E8M0 bytes [head][group].  Before the
   // first scores: the workgroup's place in its partition and the heads' selections
-  __shared__ __align__(16) float scores[4][NC][NH * 64];
+  // VALUES: those alone.  With eight heads the area of a block's scores would leave a CU three workgroups instead of four, and 912 of
+  // them (2 x 14464 tokens, 64/8 heads, no block promoted) a second round: 20.8 us, now 16.9.
+  constexpr int kArea = PASS == VALUES ? (NH * (64 * 2 + 32 + 2) + 15) / 16 * 4 : NH * 64;
+  __shared__ __align__(16) float scores[4][NC][kArea];
+  static_assert(PASS != VALUES || 4 * (kOwn + 4 * kArea) <= 160 * 1024 / 4, "four workgroups per CU");
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // y: (partition, workgroup of it), or the partly filled last block.  Two launches walk through the cache of one unit after the
