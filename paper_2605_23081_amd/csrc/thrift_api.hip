@@ -104,19 +104,19 @@ DecodeLayout decode_layout(int B, int Hq, int Hkv, int Nkv, int Bk, int split_bl
   return L;
 }
 
-DecodeSplitLayout decode_split_layout(int B, int Hq, int Hkv, int Nkv, int Bk, int split_blocks) {
+DecodeSplitLayout decode_split_layout(int B, int Hq, int Hkv, int Nkv, int Bk, int split_blocks, bool promoted) {
   DecodeSplitLayout L;
   const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks);
   L.nsplit = (Tk + part - 1) / part;
   L.words = (Tk + 63) / 64;
-  L.cw = decode_split_chunk(B, Hq, Hkv, Tk);
+  L.cw = decode_split_chunk(B, Hq, Hkv, Tk, promoted);
   L.nsub = (part + 4 * L.cw - 1) / (4 * L.cw);
   L.nparts = L.nsplit * L.nsub + 1;              // one partial per workgroup + one for a partly filled last block
   const size_t rows = (size_t)B * Hq;
   size_t off = 0;
   L.keys = off; off += align256(rows * Tk * sizeof(uint64_t));
   L.bitmap = off; off += align256(rows * L.words * sizeof(unsigned long long));
-  const bool both = decode_split_both(B, Hq, Hkv, Tk);
+  const bool both = decode_split_both(B, Hq, Hkv, Tk, promoted);
   L.scores = off; off += both ? 0 : align256(rows * Nkv * sizeof(float));      // two launches hand the scores over through memory
   // the maxima of the chunks, or of the workgroups and a ticket for each partition: nsplit * nsub + 1 words per head and nsplit
   // per KV head are no more than the four of every workgroup
@@ -130,6 +130,13 @@ DecodeSplitLayout decode_split_layout(int B, int Hq, int Hkv, int Nkv, int Bk, i
   const size_t walk = decode_layout(B, Hq, Hkv, Nkv, Bk, split_blocks).total;
   L.total = off > walk ? off : walk + 256;
   return L;
+}
+
+// What holds the form in finer pieces whatever the call's budget.
+size_t decode_split_bytes(int B, int Hq, int Hkv, int Nkv, int Bk, int split_blocks) {
+  const size_t some = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks, true).total;
+  const size_t none = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks, false).total;
+  return some > none ? some : none;
 }
 
 // Workspace of the one-call form of Alg. 1: block means, selection, codes and scales of one problem.
@@ -378,7 +385,7 @@ size_t thrift_attn_decode_workspace(int B, int Hq, int Hkv, int Nkv, int D, int 
   if (least == 0 || Hq % Hkv != 0) return least;
   const int Tk = Nkv / Bk, part = partition_blocks(Tk, split_blocks), nsplit = (Tk + part - 1) / part;
   if (!decode_split_wanted(B, Hq, Hkv, nsplit, split_blocks)) return least;
-  return decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks).total;
+  return decode_split_bytes(B, Hq, Hkv, Nkv, Bk, split_blocks);
 }
 
 static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void* k16, const void* v16,
@@ -406,13 +413,13 @@ static thrift_status attn_decode_impl(const void* q, thrift_dtype dt, const void
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
   if (decode_split_wanted(B, Hq, Hkv, L.nsplit, split_blocks)) {
-    const DecodeSplitLayout S = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks);
-    if (workspace_bytes >= S.total) {              // a caller's (or the static) workspace may hold the one-pass form only
+    const DecodeSplitLayout S = decode_split_layout(B, Hq, Hkv, Nkv, Bk, split_blocks, kneed > 0);
+    if (workspace_bytes >= decode_split_bytes(B, Hq, Hkv, Nkv, Bk, split_blocks)) {      // a caller's (or the static) workspace may hold the one-pass form only
       DecodeSplitArgs s;
       DecodeArgs& a = s.a;
       unsigned long long* bitmap = (unsigned long long*)(ws + S.bitmap);
       const bool select = kneed > 0 || idx_out != nullptr || cnt_out != nullptr;
-      const bool both = decode_split_both(B, Hq, Hkv, Tk);
+      const bool both = decode_split_both(B, Hq, Hkv, Tk, kneed > 0);
       // nobody asks for the lists and a row fits a wavefront: the scores pass selects
       const bool in_pass = kneed > 0 && idx_out == nullptr && cnt_out == nullptr && decode_split_selects(Tk, both);
       s.keys = in_pass ? (const uint64_t*)(ws + S.keys) : nullptr;

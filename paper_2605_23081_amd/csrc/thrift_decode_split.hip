@@ -754,7 +754,30 @@ constexpr int kSelectBoth = 128;
 //   12288         3 x  512, 32/8, 25 %  91.5 /  82.8     3 x  512, 16/8, 25 %    71.2 /  65.6     3 x  512, 64/8, 25 %   114 /  108
 //   14336         7 x  256, 32/8, 25 %  94.9 /  87.9     7 x  256, 16/8, 25 %    73.1 /  68.6     7 x  256, 64/8, 25 %   117 /  109
 //   more          4 x  512, 32/8        73.5 /  67.4     1 x 2048, 32/8, 5 %     80.4 /  75.5     4 x  512, 64/8, 100 %  147 /  105
-bool decode_split_both(int B, int Hq, int Hkv, int Tk) { return Tk <= kSelectBoth || (long)B * Hkv * Tk > (Hq / Hkv > 4 ? 10240 : 9216); }
+// Without promoted blocks nothing in front of one launch clears its tickets and maxima: it needs a launch of its own for that, and
+// gains less the fewer heads read and write scores.  So there two launches go further.  Two / one, no promoted block, serving steps
+// (+ append) and calls over full caches:
+//    1024         1 x  128, 32/8         16.7 /  19.1    1 x  128, 64/8, call    14.5 /  17.1     1 x   64, 16/16, call  10.1 / 12.6
+//    1344         2 x   84, 32/8         17.1 /  21.5    the same, call          13.5 /  18.6     2 x   84, 64/8         19.7 / 23.9
+//    2048         2 x  128, 32/8         18.0 /  19.0    4 x   64, 64/8          20.4 /  18.9     8 x   32, 64/8         21.0 / 20.0
+//    4096         4 x  128, 32/8         20.7 /  19.8    4 x  128, 64/8          24.6 /  21.8     2 x  128, 16/8, call   13.8 / 14.8
+//    8192         8 x  128, 32/8         26.8 /  25.9    8 x  128, 16/8, call    20.8 /  22.6     4 x  128, 16/16, call  19.1 / 22.3
+//   10240         1 x 1280, 16/8         29.6 /  32.7    1 x 1280, 64/8          39.8 /  46.6
+//   12288         3 x  512, 32/8         35.0 /  32.5    3 x  512, 64/8          41.2 /  46.1     3 x  512, 16/8         32.2 / 30.6
+//   14336         7 x  256, 32/8         35.5 /  32.1    7 x  256, 64/8          42.9 /  44.8     7 x  256, 16/8         32.2 / 30.8
+//   16384         2 x 1024, 32/8         41.5 /  42.0    2 x 1024, 64/8          47.1 /  49.2     8 x  128, 16/16        32.4 / 32.4
+//   32768         8 x  512, 64/8         76.7 /  70.7    2 x 1024, 16/16         54.7 /  55.7     16 x 128, 16/16        51.9 / 54.2
+//   40960         5 x  512, 16/16        60.5 /  58.9
+// In short rows the line lies where the chunks of one launch become longer than a block (decode_split_chunk), and with them fewer
+// maxima to wait for.  Up to 12800 blocks the scores of eight heads fit the 32 MiB of thrift_attn_decode_static with the rest.
+bool decode_split_both(int B, int Hq, int Hkv, int Tk, bool promoted) {
+  const long blocks = (long)B * Hkv * Tk;
+  const int heads = Hq / Hkv;
+  if (promoted) return Tk <= kSelectBoth || blocks > (heads > 4 ? 10240 : 9216);
+  if (heads <= 2) return blocks > (heads == 1 ? 32768 : 10240);
+  if (Tk <= kSelectBoth) return blocks > 1536;
+  return blocks > (heads > 4 ? 12800 : 9216);
+}
 
 // Where the kernels select for themselves instead of a launch of its own: rows of key blocks that a wavefront holds, and with one
 // launch (whose workgroups ask for more blocks each, among others that wait) only as many as two registers hold: 156 us with a
@@ -795,10 +818,12 @@ bool decode_split_selects(int Tk, bool both) { return Tk <= (both ? kSelectBoth 
 //    8384          2 x 16768, 16/16, 5 %            40.4 /  36.6                  4
 //                  4 x 16768, 16/8, 25 %            54.0 /  53.6                  4
 //    3072          2 x 12288, 64/8, 5 %     43.0 /  46.1 /  50.1                  1 (more than four heads: up to 4096)
-int decode_split_chunk(int B, int Hq, int Hkv, int Tk) {
+//   16384          8 x 8192, 16/16, 0 %                     33.5 / 32.4            8 (short rows: they get here without promoted blocks only)
+int decode_split_chunk(int B, int Hq, int Hkv, int Tk, bool promoted) {
   const long blocks = (long)B * Hkv * Tk;
   const int heads = Hq / Hkv;
-  if (!decode_split_both(B, Hq, Hkv, Tk)) return blocks < (heads > 4 ? 4096 : 2048) ? 1 : blocks < 8192 ? 2 : 4;
+  if (!decode_split_both(B, Hq, Hkv, Tk, promoted))
+    return blocks < (heads > 4 ? 4096 : 2048) ? 1 : blocks < 8192 ? 2 : Tk <= kSelectBoth && blocks >= 16384 ? 8 : 4;
   int cw = 1;
   while (cw < chunk_limit(heads, true) && blocks > 1536L * cw) cw *= 2;
   if (cw == 8 && heads > 2 && Tk <= 1024 && (blocks > 16384 || (Tk <= 256 && blocks <= 14336))) cw = 4;

@@ -97,7 +97,8 @@ struct DecodeSplitArgs {
   long long ppm;
 };
 constexpr int kSplitSelectBlocks = 512;      // key blocks up to which the kernels select for themselves: eight keys per lane of a wavefront
-bool decode_split_both(int B, int Hq, int Hkv, int Tk);
+// `promoted`: the call's budget promotes some block; the form depends on it
+bool decode_split_both(int B, int Hq, int Hkv, int Tk, bool promoted);
 bool decode_split_selects(int Tk, bool both);
 constexpr int kSplitMaxItems = 448;          // partitions up to which the split is faster than one walk of a workgroup each
 constexpr int kSplitMaxItemsOneHead = 512;   // the same for one query head per KV head
@@ -107,7 +108,7 @@ constexpr uint32_t kUnset = 0xffffffffu;   // a maximum that is not published ye
 // results of that sequence's KV head then are NaN.
 constexpr int kSplitPolls = 1 << 19;
 bool decode_split_wanted(int B, int Hq, int Hkv, int nsplit, int split_blocks);
-int decode_split_chunk(int B, int Hq, int Hkv, int Tk);
+int decode_split_chunk(int B, int Hq, int Hkv, int Tk, bool promoted);
 void launch_decode_split(const DecodeSplitArgs& s, hipStream_t st);
 // decode-time selection: scores of the cached key-block means against the query heads, then per-row TopK
 // as a bitmap ([B*Hq][words], bit j%64 of word j/64) and optionally as ascending id lists

@@ -209,13 +209,14 @@ def test_m0_check_reads_the_compiler_listing():
 
 
 def test_decode_workspace_holds_scores_for_two_launches_only():
-    """What one launch keeps in LDS is not asked for, so that the form fits wherever the two launches with their scores would; and
-    the form in finer pieces always asks for more than the walk, since the size of a workspace chooses between them."""
+    """What one launch keeps in LDS is not asked for where no budget takes two launches, so that the form fits wherever two launches
+    with their scores would; and the form in finer pieces always asks for more than the walk, since the size of a workspace chooses
+    between them."""
     size = lambda B, Hq, Hkv, Tk, split=256: T.decode_workspace_bytes(B, Hq, Hkv, 64 * Tk, 128, 64, split)
     scores = lambda B, Hq, Tk: B * Hq * Tk * 64 * 4
-    for B, Hq, Hkv, Tk in ((1, 32, 8, 64), (1, 32, 8, 2048), (4, 64, 8, 512), (16, 32, 8, 128), (7, 8, 8, 2048)):
+    for B, Hq, Hkv, Tk in ((3, 32, 8, 128), (1, 32, 8, 2048), (4, 64, 8, 512), (16, 32, 8, 128), (7, 8, 8, 2048)):
         assert size(B, Hq, Hkv, Tk) < scores(B, Hq, Tk)                      # one launch
-    for B, Hq, Hkv, Tk in ((1, 32, 8, 1024), (1, 64, 8, 1024), (1, 32, 8, 129)):
+    for B, Hq, Hkv, Tk in ((1, 32, 8, 1024), (1, 64, 8, 1024), (1, 32, 8, 129), (1, 32, 8, 64)):
         assert scores(B, Hq, Tk) < size(B, Hq, Hkv, Tk)                      # two
     for Hq, Hkv in ((1, 1), (16, 16), (16, 8), (32, 8), (64, 8), (7, 1)):
         for B in (1, 3, 16):
@@ -227,14 +228,17 @@ def test_decode_workspace_holds_scores_for_two_launches_only():
 
 
 def test_decode_takes_one_launch_where_it_is_the_faster_form():
-    """Known by the scores in the workspace: four query heads per KV head just above 8192 key blocks are slower in one launch (53.1
-    us against 48.6 for 4 sequences of 264 blocks), eight up to 10240 (81.0 against 76.0 for one of 1280)."""
+    """Known by the scores in the workspace, which any budget's two launches ask for.  Four query heads per KV head just above 8192 key
+    blocks are slower in one launch (53.1 us against 48.6 for 4 sequences of 264 blocks), eight up to 10240 (81.0 against 76.0 for one
+    of 1280); without promoted blocks short rows of few blocks are (21.5 against 17.1 for 2 x 84 with four heads), one head up to 32768
+    and eight heads in long rows (47.6 against 42.3 for 2 x 800)."""
     two = lambda B, Hq, Hkv, Tk: T.decode_workspace_bytes(B, Hq, Hkv, 64 * Tk, 128, 64, 256) > B * Hq * Tk * 64 * 4
     assert two(4, 32, 8, 264) and two(2, 32, 8, 576) and two(2, 16, 8, 576) and two(1, 16, 16, 576)
-    assert not two(1, 32, 8, 1153) and not two(5, 16, 8, 256) and not two(2, 16, 16, 384)
+    assert not two(1, 32, 8, 1153) and not two(5, 16, 8, 257) and not two(1, 16, 16, 2049)
     assert two(2, 64, 8, 576) and two(1, 64, 8, 1280) and two(2, 40, 8, 640)
-    assert not two(1, 64, 8, 1281) and not two(3, 64, 8, 512)
-    assert not two(16, 32, 8, 128) and not two(16, 64, 8, 64)                # short rows, whatever the grid
+    assert two(2, 32, 8, 84) and two(1, 64, 8, 128) and two(2, 32, 8, 96) and two(4, 16, 16, 128) and two(16, 16, 16, 128) and two(2, 64, 8, 800)
+    assert not two(2, 32, 8, 97) and not two(4, 64, 8, 64) and not two(1, 64, 8, 1601)
+    assert not two(16, 32, 8, 128) and not two(16, 64, 8, 64)                # short rows of many blocks
 
 
 def _listing(source, path):

@@ -113,6 +113,40 @@ def test_both_passes_in_one_launch_equal_the_walk(T, Hq, Hkv, B, N, split, lens,
     assert torch.equal(listed, got[0])                                       # selected by a launch of its own
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("Hq,Hkv,B,N,split,lens", [
+    (32, 8, 2, 6144, 256, [6143, 5000]),                                     # 1536 key blocks: the most in two launches of short rows, ..
+    (24, 8, 2, 6208, 23, [6208, 77]),                                        # .. and one launch above
+    (16, 16, 16, 8192, 256, [8192 - 300 * b for b in range(16)]),            # one head, 32768, the most in two; 8 per wavefront
+    (16, 16, 17, 8192, 256, None),
+    (16, 8, 2, 40960, 256, [40959, 20000]),                                  # two heads, 10240, the most in two
+    (16, 8, 3, 28672, 100, None),
+    (64, 8, 2, 51200, 256, [51200, 44444]),                                  # eight heads, 12800, the most in two of long rows
+    (40, 8, 3, 34816, 250, [34815, 1, 30000]),
+])
+def test_no_promoted_block(T, Hq, Hkv, B, N, split, lens, dtype):
+    """The form without promoted blocks, on both sides of its rules, against the walk; with and without the (empty) lists, over any
+    bytes in the workspace."""
+    print(f"decode without promoted blocks Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} lens={lens} {dtype}", flush=True)
+    wl = W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv, dtype=dtype)
+    args = _cache(T, wl)
+    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+    size = B, Hq, Hkv, N, wl.D, 64, split
+    need, least = T.decode_workspace_bytes(*size), T.decode_least_workspace_bytes(*size)
+    kw = dict(split_blocks=split, seqlens=sl, out_dtype=torch.float32, return_selection=True)
+    one, idx, cnt = T.thrift_attn_decode(*args, 64, 0.0, workspace=torch.full((least,), 0xFF, dtype=torch.uint8, device="cuda"), **kw)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    got, idx2, cnt2 = T.thrift_attn_decode(*args, 64, 0.0, workspace=ws, **kw)
+    assert int(cnt.sum()) == 0 and torch.equal(cnt, cnt2) and torch.equal(idx, idx2)
+    assert bool(torch.isfinite(got).all()) and float((got - one).norm() / one.norm()) <= REL
+    for fill in (0, None, 0xFF):
+        if fill is not None:
+            ws.fill_(fill)
+        out = torch.full_like(got, float("nan"))
+        T.thrift_attn_decode(*args, 64, 0.0, split_blocks=split, seqlens=sl, out=out, workspace=ws)
+        assert torch.equal(out, got)
+
+
 @pytest.mark.parametrize("Hq,Hkv,B,N,split,lens", [
     (1, 1, 2, 4096, 256, [4095, 4096 - 64]),                                 # one head, 16 workgroups or more per partition
     (12, 4, 3, 8192, 31, [8191, 2000, 64]),                                  # three heads; partitions of one workgroup and of several
