@@ -768,8 +768,7 @@ constexpr int kSelectBoth = 128;
 //   16384         2 x 1024, 32/8         41.5 /  42.0    2 x 1024, 64/8          47.1 /  49.2     8 x  128, 16/16        32.4 / 32.4
 //   32768         8 x  512, 64/8         76.7 /  70.7    2 x 1024, 16/16         54.7 /  55.7     16 x 128, 16/16        51.9 / 54.2
 //   40960         5 x  512, 16/16        60.5 /  58.9
-// In short rows the line lies where the chunks of one launch become longer than a block (decode_split_chunk), and with them fewer
-// maxima to wait for.  Up to 12800 blocks the scores of eight heads fit the 32 MiB of thrift_attn_decode_static with the rest.
+// Up to 12800 blocks the scores of eight heads fit the 32 MiB of thrift_attn_decode_static with the rest.
 bool decode_split_both(int B, int Hq, int Hkv, int Tk, bool promoted) {
   const long blocks = (long)B * Hkv * Tk;
   const int heads = Hq / Hkv;
@@ -788,6 +787,9 @@ bool decode_split_selects(int Tk, bool both) { return Tk <= (both ? kSelectBoth 
 // up.  Chunks of 1 / 2 / 4 / 8, whole serving steps or calls in us (blocks of all KV heads; B x tokens, heads, budget):
 //   one launch
 //     512 blocks   1 x 4096, 32/8, 5 %      25.6 /  28.7 /  32.9 /  42.4   takes 1
+//    1344          2 x 5376, 32/8, 100 %    30.0 /  26.6                        2 (more than 20 places in a partition)
+//    1280          4 x 2560, 32/8, 5 %      23.7 /  23.9                        1
+//                  16 x 640, 64/8, 100 %    27.4 /  30.6                        1
 //    2048          8 x 2048, 32/8, 5 %      27.9 /  29.5                        2
 //    2048          4 x 4096, 32/8, 5 %             28.7 /  30.1                 2
 //    6144          6 x 8192, 16/8, 5 %                    38.5                  4
@@ -826,6 +828,7 @@ int decode_split_chunk(int B, int Hq, int Hkv, int Tk, bool promoted) {
     return blocks < (heads > 4 ? 4096 : 2048) ? 1 : blocks < 8192 ? 2 : Tk <= kSelectBoth && blocks >= 16384 ? 8 : 4;
   int cw = 1;
   while (cw < chunk_limit(heads, true) && blocks > 1536L * cw) cw *= 2;
+  if (cw == 1 && blocks >= 1024 && Tk > 80) cw = 2;
   if (cw == 8 && heads > 2 && Tk <= 1024 && (blocks > 16384 || (Tk <= 256 && blocks <= 14336))) cw = 4;
   if (cw == 8 && heads <= 2 && (blocks <= 9216 || (heads == 1 && blocks > 24576))) cw = 4;
   return cw;

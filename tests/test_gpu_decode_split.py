@@ -43,6 +43,8 @@ def _cache(T, wl):
     (10, 2, 2, 1600, 17, [1537, 63], 1.0),                                   # five heads of eight columns, every block promoted
     (16, 2, 2, 4096, 256, [4095, 2049], 0.0),                                # eight heads, no block promoted
     (7, 1, 1, 4096, 40, None, 0.1),
+    (32, 8, 2, 5376, 256, [5376, 4000], 1.0),                                # one launch, 2 key blocks per wavefront; 1 in shorter rows
+    (32, 8, 16, 640, 256, [640 - 37 * b for b in range(16)], 0.1),
     (32, 8, 2, 16384, 100, [16384, 9000], 0.05),                             # 2 key blocks per wavefront
     (8, 8, 2, 65536, 256, [65535, 40001], 0.05),                             # 4
     (16, 8, 2, 131072, 250, [131072, 70000], 0.25),                          # 8
