@@ -1,7 +1,7 @@
 // Fused mixed-precision flash attention for prefill (Algorithm 1 steps 4-23; Sec. 3.3).
 //
-// One workgroup = one (batch, query head, query block); wavefront w owns query rows 32w .. 32w+31 of
-// the block and keeps Q, the online-softmax state and the O^T accumulators in registers.  Two walks over
+// One workgroup = one query block of one (batch, query head), or two of 64 rows; wavefront w owns rows
+// 32w .. 32w+31 and keeps Q, the online-softmax state and the O^T accumulators in registers.  Two walks over
 // the key blocks are built, both dispatching per tile to the scaled-FP4 or the 16-bit MFMA path:
 //   ORDER 0  ascending block order, Alg. 1 as written (a second staging schedule, WIDE, serves high budgets);
 //   ORDER 1  the order of the kernel in Sec. 3.3: every 4-bit block first, then the promoted blocks with the
@@ -38,18 +38,26 @@ constexpr int kWideSlot = 2 * kTile16;                       // 32768
 constexpr int kLdsPrefillWide = 2 * kWideSlot;               // 65536: two workgroups per CU
 constexpr int kWidePercent = 15;                             // list length / key blocks (in %) from which the wide schedule is used
 
-// One work item: a (sequence, query head, query block) and all its key blocks.  `work` is the item's position in the
+// One work item: 32 NW query rows of a (sequence, query head) and all their key blocks.  `work` is the item's position in the
 // launch order (what blockIdx.x is in the one-item-per-workgroup launch).
-template <typename T, int NW, int ORDER, int WIDE>
+// NL: query blocks among these rows, each with a list of promoted blocks of its own: one, or two of 64 rows.  With two the
+// walk takes the blocks of both: a block that only one of them has promoted is staged in both precisions, and each wavefront
+// computes what its own list says.  A workgroup per query block of 64 rows had two wavefronts for the LDS of four, one and a half per
+// SIMD, and staged every block for half the rows.  One query block / two, 5 %: 542 / 314 us for 8192 tokens, 32/8 heads; 200 / 141
+// for 2 x 3000, 16/16, 25 %, no mask; 730 / 597 for a chunk of 1000 on 30720, 10 %; 160 / 120 for 2000, 64/8, 100 %.
+template <typename T, int NW, int NL, int ORDER, int WIDE>
 __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char* lds, unsigned work) {
+  static_assert(NL == 1 || !WIDE, "a slot of the wide schedule holds a block in one precision");
   constexpr int KF = 4 / NW;                 // 1 KiB fragments of a 4-bit K (and of a V) tile per wavefront
   constexpr int C16 = 16 / NW;               // ... for one 16-bit K or V tile
   constexpr int kSlotStride = WIDE ? kWideSlot : kLdsBytes4;
 
   const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, r = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform: loop bounds stay scalar
-  const int N = a.N, Nq = a.Nq, Bq = NW * 32, G = a.Hq / a.Hkv;
-  const int Tq = (Nq + Bq - 1) / Bq, Tk = (N + kBk - 1) / kBk;   // the last query / key block may be short
+  const int N = a.N, Nq = a.Nq, G = a.Hq / a.Hkv;
+  constexpr int kRows = NW * 32, kRowsPerList = kRows / NL;     // of an item; of a query block
+  const int Tw = (Nq + kRows - 1) / kRows, Tk = (N + kBk - 1) / kBk;   // the last item / key block may be short
+  const int Tq = (Nq + kRowsPerList - 1) / kRowsPerList;
 
   // ---- work item: heavy (late) query blocks first; KV heads spread over the 8 XCDs so that the query
   // heads and neighbouring query blocks that share a KV head also share an L2 ----
@@ -61,19 +69,20 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     unit = rest / G;
     within = t / (units_here * G) * G + rest % G;
   } else {
-    unit = t / (G * Tq);
-    within = t % (G * Tq);
+    unit = t / (G * Tw);
+    within = t % (G * Tw);
   }
   unit = work % xcds + xcds * unit;
   const int b = unit / a.Hkv, kvh = unit % a.Hkv;
-  const int i = Tq - 1 - within / G;
+  const int i = Tw - 1 - within / G;
   const int hq = kvh * G + within % G;
   const size_t qh = (size_t)b * a.Hq + hq, kh = (size_t)b * a.Hkv + kvh;
-  const int q0 = (i + a.q_off) * Bq + wave * 32;        // sequence position of this wavefront's first query row
+  const int q_first = a.q_off * kRowsPerList + i * kRows;   // sequence position of the first query row
+  const int q0 = q_first + wave * 32;                   // ... of this wavefront's
   // The lane's query row inside the head.  Rows past the last query repeat it and are never stored.  Only this
   // 32-bit index is kept; addresses are rebuilt from it and scalar bases where they are needed (registers are
   // what limits this kernel to three wavefronts per SIMD).
-  const int lrow = min(i * Bq + wave * 32 + r, Nq - 1);
+  const int lrow = min(i * kRows + wave * 32 + r, Nq - 1);
   const size_t qrow = qh * Nq + lrow;
 
   // ---- Q fragments ----
@@ -84,21 +93,39 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
   const uint32_t qsc = *reinterpret_cast<const uint32_t*>(a.qs + qrow * 4) >> (16 * half);
   const uint8_t* q16head = reinterpret_cast<const uint8_t*>(a.q + qh * Nq * kD);   // wavefront-uniform
 
-  const int vis = a.causal ? min(Tk, ((i + a.q_off + 1) * Bq - 1) / kBk + 1) : Tk;
-  const int32_t* sel = a.idx + (qh * Tq + i) * a.kmax;
-  const int nsel = min(a.cnt[qh * Tq + i], a.kmax);      // a count beyond the list length is cut, never followed
-  // Entry t of the row's list, through the scalar data path.  The list index is wavefront-uniform, but the compiler
+  const int vis = a.causal ? min(Tk, (q_first + kRows - 1) / kBk + 1) : Tk;
+  const int own = NL == 1 ? 0 : wave / (NW / NL);      // this wavefront's list
+  const int32_t* sel[NL];
+  int nsel[NL];
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    const bool there = l == 0 || NL * i + l < Tq;                  // the last item may have one query block
+    const size_t row = qh * Tq + NL * i + (there ? l : 0);
+    sel[l] = a.idx + row * a.kmax;
+    nsel[l] = there ? min(a.cnt[row], a.kmax) : 0;                 // a count beyond the list length is cut, never followed
+  }
+  // Entry t of list l, through the scalar data path.  The list index is wavefront-uniform, but the compiler
   // cannot prove that (it depends on list entries read earlier) nor that the list is not written here, and turns a
   // plain read into a vector load plus a wait for EVERY vector load in flight, the tile DMAs included.
-  auto sel_at = [&](int t) -> int {
-    const int32_t* p = sel + __builtin_amdgcn_readfirstlane(t);
+  constexpr int kNone = 0x7fffffff;
+  auto sel_at = [&](int l, int t) -> int {
+    const int32_t* p = sel[l] + __builtin_amdgcn_readfirstlane(t);
     int v;
     asm volatile("s_load_dword %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(p) : "memory");
     return min(max(v, 0), Tk - 1);                      // whatever the list holds, only ids of existing key blocks become addresses
   };
-  // the next two promoted block ids at or after the current block (ascending list)
-  int ps = 0;
-  int n0 = nsel > 0 ? sel_at(0) : 0x7fffffff, n1 = nsel > 1 ? sel_at(1) : 0x7fffffff;
+  // the next two promoted block ids of each list at or after the current block (ascending lists)
+  int ps[NL], n0[NL], n1[NL];
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    ps[l] = 0;
+    n0[l] = nsel[l] > 0 ? sel_at(l, 0) : kNone;
+    n1[l] = nsel[l] > 1 ? sel_at(l, 1) : kNone;
+  }
+  // block J, whose next entries are X: promoted by some list, by all of them, by this wavefront's
+  auto some = [&](const int (&x)[NL], int j) { return NL == 1 ? x[0] == j : x[0] == j || x[NL - 1] == j; };
+  auto all = [&](const int (&x)[NL], int j) { return NL == 1 ? x[0] == j : x[0] == j && x[NL - 1] == j; };
+  auto mine = [&](const int (&x)[NL], int j) { return (NL == 1 || own == 0 ? x[0] : x[NL - 1]) == j; };
 
   const uint8_t* k4base = a.k4 + kh * N * 64;
   const uint8_t* v4base = a.v4 + kh * (size_t)Tk * 4096;
@@ -147,8 +174,8 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     asm volatile("" : "+s"(wave_));   /* LDS destinations are formed here from one scalar, not kept per slot and fragment */ \
     const uint32_t sl_ = lds0 + kLdsRing + s_ * kSlotStride + (uint32_t)(wave_ * (KF * 1024));                 \
     if ((j_ + 1) * kBk <= N) {                                                                                 \
-      _Pragma("unroll") for (int u = 0; u < KF; ++u) dma_b128(kt_, k4off[u], sl_ + kLdsK4 + u * 1024); \
-      dma_b32(scbase + (size_t)j_ * 256, scoff, sl_ - (uint32_t)(wave_ * (KF * 1024)) + sclds);                                                  \
+      _Pragma("unroll") for (int u = 0; u < KF; ++u) dma_b128(kt_, k4off[u], sl_ + kLdsK4 + u * 1024);         \
+      dma_b32(scbase + (size_t)j_ * 256, scoff, sl_ - (uint32_t)(wave_ * (KF * 1024)) + sclds);                \
     } else {                                                                                                   \
       uint32_t last_ = (uint32_t)last_key_row;                                                                 \
       asm volatile("" : "+s"(last_));                                                                          \
@@ -159,7 +186,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
               sl_ - (uint32_t)(wave_ * (KF * 1024)) + sclds);                                                  \
     }                                                                                                          \
     /* V codes: whole blocks */                                                                                \
-    _Pragma("unroll") for (int u = 0; u < KF; ++u) dma_b128(vt_, v4off[u], sl_ + kLdsV4 + u * 1024); \
+    _Pragma("unroll") for (int u = 0; u < KF; ++u) dma_b128(vt_, v4off[u], sl_ + kLdsV4 + u * 1024);           \
   } while (0)
   // 16-bit tiles: instruction q_ covers rows 4 q_ .. 4 q_ + 3
 #define THRIFT_ISSUE_TILE16(BASE, J, OFFEXPR, LDSBASE)                                                         \
@@ -200,21 +227,21 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
   // (causal) and only keys that exist
   const int key_limit = a.causal ? min(q0 + r + 1, N) : N;
 
-  // One step of the staging pipeline at block J, with P0 / P1 = "block J / J+1 is promoted".
+  // One step of the staging pipeline at block J, with P0 = "some list has promoted block J", P1 / ALL1 = "some / every list
+  // has promoted block J+1".
   //  SYNC:  wait for this wavefront's share of block J, then meet the others: block J is complete in LDS
   //         and everyone has finished block J-1 (whose buffers are free again).
-  //  ISSUE: block J+1 — a 4-bit block into the other slot; a promoted block into the 16-bit buffers,
-  //         unless block J is using them (then its K tile follows the score phase of block J and its V
+  //  ISSUE: block J+1 — its 4-bit tiles into the other slot, unless every list has promoted it; the tiles of a promoted block into
+  //         the 16-bit buffers, unless block J is using them (then its K tile follows the score phase of block J and its V
   //         tile the start of step J+1: late_v).
   bool late_v = false;                                  // block J is promoted and its V tile is not issued yet
 #define THRIFT_SYNC()                                                                                          \
   vm_wait<0>();                                                                                                \
   lds_barrier();
-#define THRIFT_ISSUE(J, P0, P1)                                                                                \
+#define THRIFT_ISSUE(J, P0, P1, ALL1)                                                                          \
   if ((J) + 1 < vis) {                                                                                         \
-    if (!(P1)) {                                                                                               \
-      THRIFT_ISSUE4((J) + 1);                                                                                  \
-    } else if (!(P0)) {                                                                                        \
+    if (!(ALL1)) THRIFT_ISSUE4((J) + 1);                                                                       \
+    if ((P1) && !(P0)) {                                                                                       \
       THRIFT_ISSUE_K16((J) + 1);                                                                               \
       THRIFT_ISSUE_V16((J) + 1);                                                                               \
     }                                                                                                          \
@@ -222,15 +249,29 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
 #define THRIFT_MASK(J)                                                                                         \
   const bool mask = (a.causal && (J) * kBk + kBk - 1 > q0) || ((J) + 1) * kBk > N;                             \
   const int n_valid = key_limit - (J) * kBk;   /* leading keys of the block this query may see */
-#define THRIFT_NEXT_PROMOTED()                                                                                 \
-  ++ps;                                                                                                        \
-  n0 = n1;                                                                                                     \
-  n1 = ps + 1 < nsel ? sel_at(ps + 1) : 0x7fffffff;
+  auto next_promoted = [&](int l) {
+    ++ps[l];
+    n0[l] = n1[l];
+    n1[l] = ps[l] + 1 < nsel[l] ? sel_at(l, ps[l] + 1) : kNone;
+  };
   // List entries behind the walk's position (a list that is not strictly ascending breaks the contract) are
   // dropped, at the same point of every wavefront's walk: the wavefronts of a workgroup must take identical
   // staging and barrier decisions whatever the list holds.
-#define THRIFT_DROP_STALE(J)                                                                                   \
-  while (n0 < (J)) { THRIFT_NEXT_PROMOTED() }
+  auto drop_stale = [&](int j) {
+#pragma unroll
+    for (int l = 0; l < NL; ++l)
+      while (n0[l] < j) next_promoted(l);
+  };
+  // the lists' entries behind block j, which is the current one
+  auto behind = [&](int j, int (&x)[NL]) {
+#pragma unroll
+    for (int l = 0; l < NL; ++l) x[l] = n0[l] == j ? n1[l] : n0[l];
+  };
+  auto advance = [&](int j) {
+#pragma unroll
+    for (int l = 0; l < NL; ++l)
+      if (n0[l] == j) next_promoted(l);
+  };
 
   // 16-bit query fragments of the lane's row (the wide schedule keeps them in registers for the whole walk; the
   // three-workgroup schedule has no registers to spare and fetches them again at every promoted block)
@@ -244,7 +285,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
 #define THRIFT_ROW_AGAIN(UNCLAMPED)                                                                            \
   int UNCLAMPED = (int)(threadIdx.x & 31);                                                                     \
   asm volatile("" : "+v"(UNCLAMPED));                                                                          \
-  UNCLAMPED += i * Bq + wave * 32;
+  UNCLAMPED += i * kRows + wave * 32;
 
   if constexpr (WIDE) {
     // ---- wide schedule: every block, 4-bit or promoted, is fetched one whole step ahead into the slot the
@@ -262,14 +303,14 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     // the 16-bit query fragments stay in registers (this schedule has 256 of them)
     v8s qf[8];
     THRIFT_LOAD_Q16(qf)
-    if (vis > 0) { THRIFT_ISSUE_WIDE(0, n0 == 0) }
+    if (vis > 0) { THRIFT_ISSUE_WIDE(0, n0[0] == 0) }
     int j = 0;
     while (j < vis_wave) {
-      THRIFT_DROP_STALE(j)
-      const int run_end = min(vis_wave, n0);
+      drop_stale(j);
+      const int run_end = min(vis_wave, n0[0]);
       for (; j < run_end; ++j) {                          // a run of 4-bit blocks
         THRIFT_SYNC()
-        THRIFT_ISSUE_WIDE(j + 1, j + 1 == n0)
+        THRIFT_ISSUE_WIDE(j + 1, j + 1 == n0[0])
         THRIFT_MASK(j)
         const unsigned char* slot = lds + (j & 1) * kWideSlot;
         v16f s[2];
@@ -280,9 +321,9 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
         rescale(o, grew, alpha);
         pv_fp4(slot, lane, s, pb, o);
       }
-      if (j < vis_wave) {                                 // j == n0: a promoted block
+      if (j < vis_wave) {                                 // j == n0[0]: a promoted block
         THRIFT_SYNC()
-        THRIFT_ISSUE_WIDE(j + 1, j + 1 == n1)
+        THRIFT_ISSUE_WIDE(j + 1, j + 1 == n1[0])
         THRIFT_MASK(j)
         const unsigned char* slot = lds + (j & 1) * kWideSlot;
         v16f s[2];
@@ -292,34 +333,67 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
         const bool grew = softmax_update(s, lane, mask, n_valid, c, st, alpha, pb);
         rescale(o, grew, alpha);
         pv_16<T, true>(slot + kTile16, lane, s, o);
-        THRIFT_NEXT_PROMOTED()
+        next_promoted(0);
         ++j;
       }
     }
     for (; j < vis; ++j) {                                // staging only: blocks that later wavefronts still need
-      THRIFT_DROP_STALE(j)
-      const bool p0 = j == n0;
+      drop_stale(j);
+      const bool p0 = j == n0[0];
       THRIFT_SYNC()
-      THRIFT_ISSUE_WIDE(j + 1, j + 1 == (p0 ? n1 : n0))
-      if (p0) { THRIFT_NEXT_PROMOTED() }
+      THRIFT_ISSUE_WIDE(j + 1, j + 1 == (p0 ? n1[0] : n0[0]))
+      if (p0) next_promoted(0);
     }
 #undef THRIFT_ISSUE_WIDE
   } else if constexpr (ORDER == 1) {
     // ---- the order of Sec. 3.3: every 4-bit block in ascending order, then the promoted blocks in ascending
     // order.  Same staging rules; the ring slot follows the step number because block ids now skip. ----
-    int nselv = nsel;                                   // promoted ids inside the visible range (the list is ascending)
-    if (nsel > 0 && sel_at(nsel - 1) >= vis) {
-      nselv = 0;
-      while (nselv < nsel && sel_at(nselv) < vis) ++nselv;
+    int nselv[NL];                                      // promoted ids inside the visible range (the list is ascending)
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      nselv[l] = nsel[l];
+      if (nsel[l] > 0 && sel_at(l, nsel[l] - 1) >= vis) {
+        nselv[l] = 0;
+        while (nselv[l] < nsel[l] && sel_at(l, nselv[l]) < vis) ++nselv[l];
+      }
     }
-    int pa = 0;                                         // promoted ids the 4-bit walk has passed
-    const int first_promoted = nselv > 0 ? sel_at(0) : 0x7fffffff;
-    int nx = first_promoted;                            // the next promoted id at or after the 4-bit walk's position
-    int j = 0;
-    while (j == nx) { ++j; ++pa; nx = pa < nselv ? sel_at(pa) : 0x7fffffff; }
+    // the lists' next entries at or after a walk's position: of the 4-bit walk, then of the promoted one
+    int nx[NL];
+#pragma unroll
+    for (int l = 0; l < NL; ++l) nx[l] = nselv[l] > 0 ? n0[l] : kNone;
+    auto first_of = [&](const int (&x)[NL]) { return NL == 1 ? x[0] : min(x[0], x[NL - 1]); };
+    auto pass = [&](int l) {                            // to the list's entry behind this one
+      ++ps[l];
+      nx[l] = ps[l] < nselv[l] ? sel_at(l, ps[l]) : kNone;
+    };
+    const int first_promoted = first_of(nx);
+    int next4;                                          // the next block that some list takes in 4 bits
+    bool own4 = true, next_own4;                        // this wavefront's list takes the current / that block in 4 bits
+    auto seek = [&](int j) {
+      if constexpr (NL == 1) {
+        while (j == nx[0]) { ++j; pass(0); }
+        next_own4 = true;
+      } else {
+        for (;;) {
+          bool p[NL];
+#pragma unroll
+          for (int l = 0; l < NL; ++l) {
+            while (nx[l] < j) pass(l);
+            p[l] = nx[l] == j;
+          }
+          next_own4 = !(own == 0 ? p[0] : p[NL - 1]);
+          if (!(p[0] && p[NL - 1])) break;
+          ++j;
+        }
+      }
+      next4 = j;
+    };
+    seek(0);
+    int j = next4;
+    own4 = next_own4;
     if (j < vis) {
       THRIFT_ISSUE4_SLOT(j, 0);
-    } else if (nselv > 0) {
+    } else if (first_promoted < vis) {
       THRIFT_ISSUE_K16(first_promoted);
       THRIFT_ISSUE_V16(first_promoted);
     }
@@ -327,16 +401,15 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     // read of the step is then a lane-constant address register plus an immediate offset, no address arithmetic.
     auto step_a = [&](auto slot_c) __attribute__((always_inline)) {
       constexpr int SLOT = decltype(slot_c)::value;
-      int jn = j + 1;
-      while (jn == nx) { ++jn; ++pa; nx = pa < nselv ? sel_at(pa) : 0x7fffffff; }
+      seek(j + 1);
       THRIFT_SYNC()
-      if (jn < vis) {
-        THRIFT_ISSUE4_SLOT(jn, SLOT ^ 1);
-      } else if (nselv > 0) {
+      if (next4 < vis) {
+        THRIFT_ISSUE4_SLOT(next4, SLOT ^ 1);
+      } else if (first_promoted < vis) {
         THRIFT_ISSUE_K16(first_promoted);
         THRIFT_ISSUE_V16(first_promoted);
       }
-      if (j < vis_wave) {
+      if ((NL == 1 || own4) && j < vis_wave) {
         THRIFT_MASK(j)
         const unsigned char* slot = lds + kLdsRing + SLOT * kLdsBytes4;
         v16f s[2];
@@ -347,7 +420,8 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
         rescale(o, grew, alpha);
         pv_fp4(slot, lane, s, pb, o);
       }
-      j = jn;
+      j = next4;
+      own4 = next_own4;
     };
     while (j < vis) {                                   // phase A
       step_a(std::integral_constant<int, 0>{});
@@ -361,19 +435,32 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     // soon as everyone has finished with tile t-3.  That puts K(b+1) in flight at the start of block b and V(b+1)
     // right after the scores of block b, half a block earlier each than two fixed buffers allow.
     v8s qf[8];
-    if (nselv > 0 && first_promoted < vis_wave) {
+    if (first_promoted < vis_wave) {
       THRIFT_ROW_AGAIN(row_b)
       THRIFT_LOAD_Q16_ROW(qf, min(row_b, Nq - 1))
     }
     // buffer 0: the K region (holds K of the first promoted block), 1: the V region (its V), 2: the 4-bit slots' region
 #define THRIFT_TILE_BUFFER(X) ((X) == 0 ? kLdsK16 : (X) == 1 ? kLdsV16 : kLdsRing)
     int kbuf = 0;
-    int jb_next = first_promoted;
-    for (int sidx = 0; sidx < nselv; ++sidx) {
-      const int jb = jb_next;
-      const bool p1 = sidx + 1 < nselv;
-      if (p1) jb_next = sel_at(sidx + 1);
-      const bool mine = jb < vis_wave;
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      ps[l] = 0;
+      nx[l] = nselv[l] > 0 ? n0[l] : kNone;
+    }
+    int jb = first_promoted;
+    while (jb < vis) {
+      const bool own16 = NL == 1 || mine(nx, jb), use = own16 && jb < vis_wave;
+      if constexpr (NL == 1) {
+        pass(0);
+      } else {
+        do {                                            // (an entry that is not larger than the one before breaks the contract)
+#pragma unroll
+          for (int l = 0; l < NL; ++l)
+            if (nx[l] <= jb) pass(l);
+        } while (first_of(nx) <= jb);
+      }
+      const int jb_next = first_of(nx);
+      const bool p1 = jb_next < vis;
       const int vbuf = kbuf == 2 ? 0 : kbuf + 1;
       const int kbuf_next = vbuf == 2 ? 0 : vbuf + 1;
       vm_wait<C16>();                                   // this wavefront's share of K(b); V(b) may still be on its way
@@ -384,12 +471,12 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
       }
       THRIFT_MASK(jb)
       v16f s[2];
-      if (mine) scores_16<T>(lds + THRIFT_TILE_BUFFER(kbuf), lane, qf, s);
+      if (use) scores_16<T>(lds + THRIFT_TILE_BUFFER(kbuf), lane, qf, s);
       if (p1) vm_wait<C16>();                           // V(b); K(b+1) may still be on its way
       else vm_wait<0>();
       lds_barrier();                                    // V(b) complete; everyone has its scores, K(b)'s buffer is free
       if (p1) { THRIFT_ISSUE_TILE16(v16base, jb_next, THRIFT_V16OFF(), lds0 + (uint32_t)THRIFT_TILE_BUFFER(kbuf)); }
-      if (mine) {
+      if (use) {
         float alpha;
         uint32_t pb;
         const bool grew = softmax_update(s, lane, mask, n_valid, c, st, alpha, pb);
@@ -397,27 +484,41 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
         pv_16<T, true>(lds + THRIFT_TILE_BUFFER(vbuf), lane, s, o);
       }
       kbuf = kbuf_next;
+      jb = jb_next;
     }
 #undef THRIFT_TILE_BUFFER
   } else {
   // prologue: block 0 on its way
   if (vis > 0) {
-    if (n0 == 0) {
+    if (!all(n0, 0)) THRIFT_ISSUE4(0);
+    if (some(n0, 0)) {
       THRIFT_ISSUE_K16(0);
       THRIFT_ISSUE_V16(0);
-    } else {
-      THRIFT_ISSUE4(0);
     }
   }
+  // What every wavefront does between its scores and its softmax, and in front of P.V, where some list has promoted block j (P0),
+  // whichever path the wavefront itself takes; P1: block j+1 too.
+#define THRIFT_BEHIND_SCORES(P0, P1)                                                                           \
+  if ((P0) && (P1)) {                                   /* the K buffer is free once every wavefront has its scores */ \
+    lds_barrier();                                                                                             \
+    THRIFT_ISSUE_K16(j + 1);                                                                                   \
+  }
+#define THRIFT_BEFORE_PV(P0, P1)                                                                               \
+  if ((P0) && late_v) {                                 /* this block's V tile was issued in this step */      \
+    if (P1) vm_wait<C16>();                                                                                    \
+    else vm_wait<0>();                                                                                         \
+    lds_barrier();                                                                                             \
+  }
+  int j = 0;
+  if constexpr (NL == 1) {
   // The walk alternates between runs of 4-bit blocks (tight loop: only the scaled-FP4 path, accumulators
   // updated in place) and single promoted blocks.
-  int j = 0;
   while (j < vis_wave) {
-    THRIFT_DROP_STALE(j)
-    const int run_end = min(vis_wave, n0);
+    drop_stale(j);
+    const int run_end = min(vis_wave, n0[0]);
     for (; j < run_end; ++j) {
       THRIFT_SYNC()
-      THRIFT_ISSUE(j, false, j + 1 == n0)
+      THRIFT_ISSUE(j, false, j + 1 == n0[0], j + 1 == n0[0])
       THRIFT_MASK(j)
       const unsigned char* slot = lds + kLdsRing + (j & 1) * kLdsBytes4;
       v16f s[2];
@@ -429,13 +530,13 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
       pv_fp4(slot, lane, s, pb, o);
       late_v = false;
     }
-    if (j < vis_wave) {                                 // j == n0: a promoted block
-      const bool p1 = j + 1 == n1 && j + 1 < vis;
+    if (j < vis_wave) {                                 // j == n0[0]: a promoted block
+      const bool p1 = j + 1 == n1[0] && j + 1 < vis;
       v16f s[2];
       float alpha;
       uint32_t pb;
       THRIFT_SYNC()
-      THRIFT_ISSUE(j, true, j + 1 == n1)
+      THRIFT_ISSUE(j, true, p1, j + 1 == n1[0])
       if (late_v) THRIFT_ISSUE_V16(j);
       THRIFT_MASK(j)
       {
@@ -443,46 +544,62 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
         THRIFT_LOAD_Q16(qf)
         scores_16<T>(lds + kLdsK16, lane, qf, s);
       }
-      if (p1) {                                         // the K buffer is free once every wavefront has its scores
-        lds_barrier();
-        THRIFT_ISSUE_K16(j + 1);
-      }
+      THRIFT_BEHIND_SCORES(true, p1)
       const bool grew = softmax_update(s, lane, mask, n_valid, c, st, alpha, pb);
       rescale(o, grew, alpha);
-      if (late_v) {                                     // this block's V tile was issued in this step
-        if (p1) vm_wait<C16>();
-        else vm_wait<0>();
-        lds_barrier();
-      }
+      THRIFT_BEFORE_PV(true, p1)
       pv_16<T, true>(lds + kLdsV16, lane, s, o);
-      THRIFT_NEXT_PROMOTED()
+      next_promoted(0);
       late_v = p1;
       ++j;
     }
   }
-  for (; j < vis; ++j) {                                // staging only
-    THRIFT_DROP_STALE(j)
-    const bool p0 = j == n0;
-    const bool p1 = (p0 ? j + 1 == n1 : j + 1 == n0);
+  }
+  // Two lists: every block in one loop, whose wavefronts take the path of their own list.  One list: blocks that later wavefronts
+  // still need, staged only.
+  for (; j < vis; ++j) {
+    drop_stale(j);
+    int x[NL];
+    behind(j, x);
+    const bool p0 = some(n0, j), p1 = some(x, j + 1) && j + 1 < vis;
+    const bool use = NL > 1 && j < vis_wave, own16 = mine(n0, j);
     THRIFT_SYNC()
-    THRIFT_ISSUE(j, p0, p1)
-    if (p0) {
-      const bool p1v = p1 && j + 1 < vis;
-      if (late_v) THRIFT_ISSUE_V16(j);
-      if (p1v) {
-        lds_barrier();
-        THRIFT_ISSUE_K16(j + 1);
-      }
-      if (late_v) {
-        if (p1v) vm_wait<C16>();
-        else vm_wait<0>();
-        lds_barrier();
-      }
-      THRIFT_NEXT_PROMOTED()
-      late_v = p1v;
-    } else {
-      late_v = false;
+    THRIFT_ISSUE(j, p0, p1, all(x, j + 1))
+    if (p0 && late_v) THRIFT_ISSUE_V16(j);
+    THRIFT_MASK(j)
+    if (use && !own16) {
+      const unsigned char* slot = lds + kLdsRing + (j & 1) * kLdsBytes4;
+      v16f s[2];
+      float alpha;
+      uint32_t pb;
+      scores_fp4(slot, lane, qf4, qsc, s);
+      THRIFT_BEHIND_SCORES(p0, p1)
+      const bool grew = softmax_update(s, lane, mask, n_valid, c, st, alpha, pb);
+      rescale(o, grew, alpha);
+      THRIFT_BEFORE_PV(p0, p1)
+      pv_fp4(slot, lane, s, pb, o);
     }
+    if (use && own16) {
+      v16f s[2];
+      float alpha;
+      uint32_t pb;
+      {
+        v8s qf[8];
+        THRIFT_LOAD_Q16(qf)
+        scores_16<T>(lds + kLdsK16, lane, qf, s);
+      }
+      THRIFT_BEHIND_SCORES(true, p1)
+      const bool grew = softmax_update(s, lane, mask, n_valid, c, st, alpha, pb);
+      rescale(o, grew, alpha);
+      THRIFT_BEFORE_PV(true, p1)
+      pv_16<T, true>(lds + kLdsV16, lane, s, o);
+    }
+    if (!use) {
+      THRIFT_BEHIND_SCORES(p0, p1)
+      THRIFT_BEFORE_PV(p0, p1)
+    }
+    advance(j);
+    late_v = p0 && p1;
   }
   }
   vm_wait<0>();
@@ -490,9 +607,9 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
 #undef THRIFT_LOAD_Q16
 #undef THRIFT_LOAD_Q16_ROW
 #undef THRIFT_ISSUE
+#undef THRIFT_BEHIND_SCORES
+#undef THRIFT_BEFORE_PV
 #undef THRIFT_MASK
-#undef THRIFT_NEXT_PROMOTED
-#undef THRIFT_DROP_STALE
 #undef THRIFT_ISSUE4
 #undef THRIFT_ISSUE4_SLOT
 #undef THRIFT_ISSUE_V16
@@ -522,10 +639,10 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
 #undef THRIFT_ROW_AGAIN
 }
 
-template <typename T, int NW, int ORDER, int WIDE>
-__global__ void __launch_bounds__(NW * 64, WIDE ? 2 : 3) prefill_kernel(PrefillArgs a) {
+template <typename T, int NW, int NL, int ORDER, int WIDE>
+__global__ void __launch_bounds__(NW * 64, WIDE ? 2 : 12 / NW) prefill_kernel(PrefillArgs a) {
   __shared__ __align__(1024) unsigned char lds[WIDE ? kLdsPrefillWide : kLdsPrefill];
-  prefill_item<T, NW, ORDER, WIDE>(a, lds, blockIdx.x);
+  prefill_item<T, NW, NL, ORDER, WIDE>(a, lds, blockIdx.x);
 }
 
 // The same items from a persistent launch: as many workgroups as the chip holds at once, each taking the next item
@@ -535,8 +652,8 @@ static __device__ unsigned int prefill_next_item[64];       // one counter per l
 
 __global__ void prefill_reset_counter_kernel() { prefill_next_item[0] = 0u; }
 
-template <typename T, int NW, int ORDER>
-__global__ void __launch_bounds__(NW * 64, 3) prefill_persistent_kernel(PrefillArgs a, unsigned items) {
+template <typename T, int ORDER>
+__global__ void __launch_bounds__(256, 3) prefill_persistent_kernel(PrefillArgs a, unsigned items) {
   __shared__ __align__(1024) unsigned char lds[kLdsPrefill];
   __shared__ unsigned next;
   // the workgroup's position on its XCD decides nothing here: items keep the XCD of their KV head only while the
@@ -547,7 +664,7 @@ __global__ void __launch_bounds__(NW * 64, 3) prefill_persistent_kernel(PrefillA
     const unsigned work = next;
     __syncthreads();
     if (work >= items) break;
-    prefill_item<T, NW, ORDER, 0>(a, lds, work);
+    prefill_item<T, 4, 1, ORDER, 0>(a, lds, work);
   }
 }
 
@@ -568,10 +685,27 @@ static bool wide_schedule(const PrefillArgs& a) {
 // the ends weigh little and the units' K/V streams want the L2 one after the other: 1210 / 1260 us for 2 x 8192, 64/8 heads.
 static bool interleaved_units(const PrefillArgs& a, unsigned grid) { return a.causal && grid <= 8u * 3u * kCus; }
 
+// Query blocks of 64 rows one to a workgroup of two wavefronts instead of two to one of four: where promoted blocks are frequent
+// and the workgroups are one round, what counts is the length of a row's walk, which two lists lengthen.  With causal rows the
+// second round is the short ones.  One / two query blocks per workgroup (64-row query blocks in the grid):
+//    608   chunk of 1200 on 30720, 32/8, 25 %, Sec. 3.3    806 /  962      640   2500, 16/16, 100 %, no mask              132 /  136
+//    768   1500 tokens, 32/8, 25 %, ascending             52.4 / 54.9            the same in the order of Sec. 3.3     50.8 / 57.9
+//   1120   2200 tokens, 32/8, 25 %                        71.9 / 77.0           100 %, Sec. 3.3                        90.3 / 109
+//   1136   4500, 16/16, 25 %, no mask                      266 /  187            causal                                 128 /  136
+//   1216   chunk of 2400 on 30720, 32/8, 25 %             1587 / 1104
+//   1504   3000 tokens, 32/8, 25 %                         114 / 97.4           100 %                                   161 /  157
+//    768   1500 tokens, 32/8, 10 %                        48.7 / 48.1     1120  2200, 10 %                             69.2 / 64.2
+static bool one_query_block(const PrefillArgs& a) {
+  const long blocks = (long)a.B * a.Hq * ((a.Nq + 63) / 64), Tk = (a.N + kBk - 1) / kBk;
+  if ((long)a.kmax * 100L < Tk * (long)kWidePercent) return false;
+  return blocks <= (a.causal && a.q_off == 0 ? 5L : 3L) * kCus;
+}
+
 void launch_prefill(const PrefillArgs& args, hipStream_t st) {
   if (launch_prefill_split(args, st)) return;
   PrefillArgs a = args;
-  const unsigned grid = (unsigned)((long)a.B * a.Hq * ((a.Nq + a.Bq - 1) / a.Bq));
+  const int rows = a.Bq == 64 && one_query_block(a) ? 64 : 128;    // of a workgroup
+  const unsigned grid = (unsigned)((long)a.B * a.Hq * ((a.Nq + rows - 1) / rows));
   a.interleave = interleaved_units(a, grid);
   if (a.tile_order == 4 && a.Bq == 128) {
     // persistent launch of the Sec. 3.3 order: three workgroups per CU.  One counter per device: two such launches
@@ -580,24 +714,27 @@ void launch_prefill(const PrefillArgs& args, hipStream_t st) {
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const unsigned resident = (unsigned)min((long)grid, 3L * cus);
     prefill_reset_counter_kernel<<<dim3(1), dim3(1), 0, st>>>();
-    if (a.dt == THRIFT_F16) prefill_persistent_kernel<F16, 4, 1><<<dim3(resident), dim3(256), 0, st>>>(a, grid);
-    else prefill_persistent_kernel<BF16, 4, 1><<<dim3(resident), dim3(256), 0, st>>>(a, grid);
+    if (a.dt == THRIFT_F16) prefill_persistent_kernel<F16, 1><<<dim3(resident), dim3(256), 0, st>>>(a, grid);
+    else prefill_persistent_kernel<BF16, 1><<<dim3(resident), dim3(256), 0, st>>>(a, grid);
     return;
   }
-#define THRIFT_LAUNCH(T, NW)                                                                                   \
+#define THRIFT_LAUNCH(T, NW, NL)                                                                               \
   do {                                                                                                         \
-    if (a.tile_order == 1 || a.tile_order == 4) prefill_kernel<T, NW, 1, 0><<<dim3(grid), dim3(NW * 64), 0, st>>>(a);               \
-    else prefill_kernel<T, NW, 0, 0><<<dim3(grid), dim3(NW * 64), 0, st>>>(a);                                 \
+    if (a.tile_order == 1 || a.tile_order == 4) prefill_kernel<T, NW, NL, 1, 0><<<dim3(grid), dim3(NW * 64), 0, st>>>(a);           \
+    else prefill_kernel<T, NW, NL, 0, 0><<<dim3(grid), dim3(NW * 64), 0, st>>>(a);                             \
   } while (0)
   if (wide_schedule(a)) {
-    if (a.dt == THRIFT_F16) prefill_kernel<F16, 4, 0, 1><<<dim3(grid), dim3(256), 0, st>>>(a);
-    else prefill_kernel<BF16, 4, 0, 1><<<dim3(grid), dim3(256), 0, st>>>(a);
+    if (a.dt == THRIFT_F16) prefill_kernel<F16, 4, 1, 0, 1><<<dim3(grid), dim3(256), 0, st>>>(a);
+    else prefill_kernel<BF16, 4, 1, 0, 1><<<dim3(grid), dim3(256), 0, st>>>(a);
   } else if (a.Bq == 128) {
-    if (a.dt == THRIFT_F16) THRIFT_LAUNCH(F16, 4);
-    else THRIFT_LAUNCH(BF16, 4);
+    if (a.dt == THRIFT_F16) THRIFT_LAUNCH(F16, 4, 1);
+    else THRIFT_LAUNCH(BF16, 4, 1);
+  } else if (rows == 128) {
+    if (a.dt == THRIFT_F16) THRIFT_LAUNCH(F16, 4, 2);
+    else THRIFT_LAUNCH(BF16, 4, 2);
   } else {
-    if (a.dt == THRIFT_F16) THRIFT_LAUNCH(F16, 2);
-    else THRIFT_LAUNCH(BF16, 2);
+    if (a.dt == THRIFT_F16) THRIFT_LAUNCH(F16, 2, 1);
+    else THRIFT_LAUNCH(BF16, 2, 1);
   }
 #undef THRIFT_LAUNCH
 }

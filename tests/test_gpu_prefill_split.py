@@ -28,8 +28,8 @@ def _qkv(B, Hq, Hkv, N, dtype, seed=7):
     (3, 8, 1, 333, 64, True),            # three units, not a multiple of the XCDs
     (1, 8, 2, 65, 128, True),
     (2, 6, 2, 700, 64, False),           # no causal mask: one unit after the other
-    (4, 64, 8, 1536, 64, True),          # the last grid that is interleaved (6144 workgroups)
-    (4, 64, 8, 1537, 64, True),          # the first that is not
+    (4, 64, 8, 1536, 64, True),          # 3072 workgroups of two query blocks each
+    (4, 64, 8, 1537, 64, True),          # 3328, the last of them with one row
 ])
 def test_order_of_the_workgroups(T, B, Hq, Hkv, N, Bq, causal):
     print(f"order of the workgroups B={B} {Hq}/{Hkv} N={N} Bq={Bq} causal={causal}", flush=True)
@@ -109,3 +109,64 @@ def test_four_wavefronts_per_row_group_in_a_chunk(T, Nq, off, N, ids, form, orde
     assert _form(1, 4, Nq, N, len(ids)) == form and _form(copies, 4, Nq, N, len(ids)) == 0
     alone, many = run(1), run(copies)
     assert bool(torch.isfinite(alone).all()) and torch.equal(alone[0], many[0]) and torch.equal(alone[0], many[copies - 1])
+
+
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("Nq,off,N,even,odd", [
+    (64, 0, 64, [0], []),                                                     # one query block: the other list does not exist
+    (65, 0, 65, [0], [0, 1]),                                                 # one row in the second
+    (128, 0, 1000, [1, 3, 5, 7], [2, 4, 6, 8]),                               # neighbours in turn: a promoted block behind every one
+    (192, 5, 1000, [], [0, 1, 2, 3]),                                         # a run of one list alone; an odd offset and number of blocks
+    (577, 3, 1024, [0, 1, 2, 9, 15], [1, 2, 3, 4, 10, 15]),                   # overlapping runs
+    (640, 6, 1024, list(range(16)), [0, 4, 8, 12, 13]),                       # one list has everything
+    (640, 0, 640, list(range(10)), list(range(10))),                          # no 4-bit block at all
+    (333, 4, 700, [9, 10], []),                                               # the last blocks, of which one is short
+])
+def test_two_query_blocks_per_workgroup(T, Nq, off, N, even, odd, causal, order):
+    """Query blocks of 64 rows go in pairs, each with its own list, where the grid is large: every row has the bits it has in a
+    query block of 128 rows with its list."""
+    print(f"two query blocks per workgroup: {Nq} at {off} in {N}, {even} / {odd}, causal {causal}, order {order}", flush=True)
+    dtype = torch.bfloat16 if N % 2 else torch.float16
+    q, k, v = _qkv(1, 4, 2, N, dtype)
+    q = q[:, :, :Nq].contiguous()
+    Tq, Tk = -(-Nq // 64), -(-N // 64)
+    lists = torch.full((2, Tk), -1, dtype=torch.int32, device="cuda")         # as wide as the row: the plain kernel at any size
+    for i, ids in enumerate((even, odd)):
+        lists[i, :len(ids)] = torch.tensor(ids, dtype=torch.int32)
+    count = torch.tensor([len(even), len(odd)], dtype=torch.int32, device="cuda")
+    codes = [*T.thrift_quantize_mxfp4(q, 0), *T.thrift_quantize_mxfp4(k, 0), *T.thrift_quantize_mxfp4(v, 1)]
+
+    def run(which, Bq, off, n=1):
+        lse = torch.zeros(n, 4, Nq, device="cuda")
+        many = [t.expand(n, *t.shape[1:]).contiguous() for t in (q, k, v, *codes)]
+        out = T.thrift_attn_prefill_chunk(*many, lists[which].expand(n, 4, -1, -1).contiguous(),
+                                          count[which].expand(n, 4, -1).contiguous(), Bq, 64, causal, off,
+                                          out_dtype=torch.float32, lse=lse, tile_order=order)
+        assert torch.equal(out[0], out[n - 1]) and torch.equal(lse[0], lse[n - 1])
+        return out[:1], lse[:1]
+
+    copies = 5 * 256 // (4 * Tq) + 1                                          # past the grids that take one block to a workgroup
+    both, lse = run(torch.arange(Tq, device="cuda") % 2, 64, off, copies)
+    one, lse_one = run(torch.arange(Tq, device="cuda") % 2, 64, off)          # one of those
+    assert torch.equal(both, one) and torch.equal(lse, lse_one)
+    assert bool(torch.isfinite(both).all())
+    if off % 2:                                                               # 128-row blocks start at even offsets only
+        pad = torch.cat([torch.zeros_like(q[:, :, :64]), q], 2)
+        q, Nq, off = pad.contiguous(), Nq + 64, off - 1
+        codes[:2] = T.thrift_quantize_mxfp4(q, 0)
+        both, lse = torch.nn.functional.pad(both, (0, 0, 64, 0)), torch.nn.functional.pad(lse, (64, 0))
+        skip = 64
+    else:
+        skip = 0
+    zero = torch.zeros(-(-Nq // 128), dtype=torch.long, device="cuda")
+    for which in (0, 1):
+        alone, lse_1 = run(zero + which, 128, off // 2)
+        mine = (torch.arange(skip, Nq, device="cuda") - skip) // 64 % 2 == which
+        assert torch.equal(both[:, :, skip:][:, :, mine], alone[:, :, skip:][:, :, mine])
+        assert torch.equal(lse[:, :, skip:][:, :, mine], lse_1[:, :, skip:][:, :, mine])
+
+
+def test_order_of_the_largest_interleaved_grid(T):
+    test_order_of_the_workgroups(T, 4, 64, 8, 3072, 64, True)                 # 6144 workgroups of two query blocks each
+    test_order_of_the_workgroups(T, 4, 64, 8, 3073, 64, True)                 # and the next, one unit after the other
