@@ -62,7 +62,12 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
   // ---- work item: heavy (late) query blocks first; KV heads spread over the 8 XCDs so that the query
   // heads and neighbouring query blocks that share a KV head also share an L2 ----
   const int units = a.B * a.Hkv;
-  const int xcds = (units & 7) == 0 ? 8 : 1, units_here = units / xcds, t = work / xcds;
+  const int xcds = (units & 7) == 0 ? 8 : 1, units_here = units / xcds;
+  int t = work / xcds;
+  if (a.fold) {                                          // the second workgroup of every CU: shortest first
+    const int per = kCus / xcds, end = min(2 * per, (int)gridDim.x / xcds);
+    if (t >= per && t < end) t = per + end - 1 - t;
+  }
   int unit, within;                                      // the unit's on this XCD; (query block from the last one on, head of the group)
   if (a.interleave) {
     const int rest = t % (units_here * G);
@@ -701,18 +706,27 @@ static bool one_query_block(const PrefillArgs& a) {
   return blocks <= (a.causal && a.q_off == 0 ? 5L : 3L) * kCus;
 }
 
+// A grid that the chip holds at once: workgroup n goes to the CU of workgroup n - 256 (read back from the hardware id register), so in
+// descending order the same CU gets the longest row of each third, 47 + 31 + 15 key blocks of 3001 tokens, and another one 33 + 17 + 1.  With the
+// second third turned round they are 47 + 17 + 15 and 33 + 31 + 1.  Descending / folded: 69.7 / 66.6 us for 3001 tokens, 32/8 heads
+// (71.5 / 66.1 in the order of Sec. 3.3), 64.6 / 61.4 for 2 x 2500, 16/16, 47.7 / 45.3 for 1500, 64/8; 49.2 / 48.6 for 2048, 32/8 (two workgroups per CU, of
+// which the longer one alone takes the time).  The last third turned round as well is no better (66.4, 67.1), alone worse (68.5, 69.2).
+static bool folded(const PrefillArgs& a, unsigned grid) { return a.interleave && grid <= 3u * kCus; }
+
 void launch_prefill(const PrefillArgs& args, hipStream_t st) {
   if (launch_prefill_split(args, st)) return;
   PrefillArgs a = args;
   const int rows = a.Bq == 64 && one_query_block(a) ? 64 : 128;    // of a workgroup
   const unsigned grid = (unsigned)((long)a.B * a.Hq * ((a.Nq + rows - 1) / rows));
   a.interleave = interleaved_units(a, grid);
+  a.fold = folded(a, grid);
   if (a.tile_order == 4 && a.Bq == 128) {
     // persistent launch of the Sec. 3.3 order: three workgroups per CU.  One counter per device: two such launches
     // must not overlap on a device.  The counter is cleared by a kernel (a memset node misbehaves under graph capture).
     int dev = 0, cus = kCus;
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const unsigned resident = (unsigned)min((long)grid, 3L * cus);
+    a.fold = 0;                                          // its workgroups take the items as they come
     prefill_reset_counter_kernel<<<dim3(1), dim3(1), 0, st>>>();
     if (a.dt == THRIFT_F16) prefill_persistent_kernel<F16, 1><<<dim3(resident), dim3(256), 0, st>>>(a, grid);
     else prefill_persistent_kernel<BF16, 1><<<dim3(resident), dim3(256), 0, st>>>(a, grid);

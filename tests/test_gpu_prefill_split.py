@@ -51,6 +51,31 @@ def _form(B, Hq, Nq, N, kmax):
     return 1 if groups <= 256 else 2 if groups <= 512 and Tk >= 10 else 0
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,Bq", [
+    (1, 32, 8, 1024, 128),               # 256 workgroups: one third, as it comes
+    (1, 32, 8, 1025, 128),               # 288: a second third of 32
+    (3, 11, 11, 1153, 128),              # 330, units not a multiple of the XCDs
+    (2, 16, 16, 2048, 128),              # 512
+    (1, 32, 8, 3072, 128),               # 768
+    (1, 32, 8, 3073, 128),               # 800: more than the chip holds, as it comes
+    (1, 32, 8, 1500, 64),                # two query blocks per workgroup
+])
+def test_folded_order_of_the_workgroups(T, B, Hq, Hkv, N, Bq):
+    """Grids of one round, whose second third runs the other way: every head has the bits it has in a call of its own."""
+    print(f"folded order B={B} {Hq}/{Hkv} N={N} Bq={Bq}", flush=True)
+    q, k, v = _qkv(B, Hq, Hkv, N, torch.bfloat16)
+    G = Hq // Hkv
+    for order in (0, 1, 2):
+        out = torch.full((B, Hq, N, 128), float("nan"), device="cuda")
+        T.thrift_attention(q, k, v, True, Bq, 64, 0.1, tile_order=order, out=out)
+        for b in range(B):
+            for h in range(Hkv):
+                heads = slice(h * G, (h + 1) * G)
+                alone = T.thrift_attention(*(x[b:b + 1, s].contiguous() for x, s in ((q, heads), (k, slice(h, h + 1)), (v, slice(h, h + 1)))),
+                                           True, Bq, 64, 0.1, tile_order=order, out_dtype=torch.float32)
+                assert torch.equal(out[b, heads], alone[0])
+
+
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("Hq,Hkv,N,Bq,causal,copies,form", [
     (1, 1, 385, 64, True, 50, 1),         # seven key blocks, the fewest: groups of four and three; one key and one row in the last
