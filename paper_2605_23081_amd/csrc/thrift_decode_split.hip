@@ -104,7 +104,10 @@ __device__ __forceinline__ uint32_t rank_select(const uint64_t (&key)[NR], uint6
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(own >> 32), i);
     int larger = 0;
 #pragma unroll
-    for (int c = 0; c < NR; ++c) larger += __popcll(__ballot((uint32_t)(key[c] >> 32) > hi));
+    for (int c = 0; c < NR; ++c) {
+      larger += __popcll(__ballot((uint32_t)(key[c] >> 32) > hi));
+      if (c % 2 != 0 && c + 1 < NR && larger >= k) break;      // most blocks are out after two registers
+    }
     if (larger >= k) continue;
     const uint64_t x = ((uint64_t)hi << 32) | (uint32_t)__builtin_amdgcn_readlane((int)own, i);
     larger = 0;                                            // larger, or equal with a smaller id
@@ -169,6 +172,48 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
   const int Tk = a.Nkv / kBk;
   // the query rows as A operand: head r % 4 (8) in row r, so that every lane's accumulator registers i are heads
   // (4 g + i) % 4 (8); the lane quantises the MXFP4 group it carries
+  const int h = lane & (NH - 1), kg = lane / NH;               // softmax layout
+  const int hg = min(h, G - 1);                                // lanes of a padding head follow the last one and are never read
+  // In two launches the workgroup's place is known, too: the keys of its own blocks; its selection, the largest scores in front of
+  // it in the partition and the scores of its first block.  What stands there may never have been written: it is used where the
+  // length says that it was.  Asked for one after the other behind the length they took 2.7 us of the 12 us of the values pass, now 0.7.
+  const int early = min(part * a.split_blocks + y % s.nsub * 4 * s.cw, Tk - 1);          // (not of a partly filled last block)
+  uint64_t own_key[kRows];
+  if constexpr (SELECT && PASS == SCORES) {
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) own_key[u] = s.keys[(group0 + min(wave + 4 * u, G - 1)) * Tk + min(early + lane, Tk - 1)];
+  }
+  constexpr int kFront = 8;
+  float front[kFront];
+  uint32_t own_taken = 0u;
+  struct Scores { float v[NH]; };
+  const float* sbase = s.scores + group0 * a.Nkv;              // scalar; the lane's head and keys in 32 bits
+  const uint32_t soff = (uint32_t)(hg * a.Nkv + NH * kg);
+  auto load_scores = [&](int j) {
+    Scores x;
+    if constexpr (NH >= 4) {
+#pragma unroll
+      for (int u = 0; u < NH; u += 4) {
+        const float4 z = *reinterpret_cast<const float4*>(sbase + (size_t)j * kBk + soff + u);
+        x.v[u] = z.x; x.v[u + 1] = z.y; x.v[u + 2] = z.z; x.v[u + 3] = z.w;
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < NH; ++u) x.v[u] = (sbase + (size_t)j * kBk)[soff + u];
+    }
+    return x;
+  };
+  Scores next;                                                 // VALUES: the scores of a block are asked for one block ahead
+  const int chunk0 = y * 4 + wave, in_front = tail ? 0 : y % s.nsub * 4 + wave;        // chunks of the partition in front
+  const float* cm = s.cmax + (group0 + hg) * s.chunks + chunk0 - in_front;
+  if constexpr (PASS == VALUES) {
+    if constexpr (SELECT) {
+      if (lane < G) own_taken = s.taken[(group0 + lane) * s.items + y];
+    }
+#pragma unroll
+    for (int e = 0; e < kFront; ++e) front[e] = kg + e * (64 / NH) < in_front ? cm[kg + e * (64 / NH)] : kEmptyMax;
+    if (!tail) next = load_scores(min(early + wave * s.cw, Tk - 1));
+  }
   const int hq = r & (NH > 4 ? 7 : 3);
   const bool qlane = hq < G;
   const uint16_t* qrow = a.q + (group0 + (qlane ? hq : 0)) * kD;
@@ -247,14 +292,25 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
     if (i < n_blocks && promoted_mask(bits, i) != all) kt = load4(j0 + i);
   };
   if constexpr (SELECT && PASS == VALUES) {
-    if (lane < G) bits = s.taken[(group0 + lane) * s.items + item] >> (wave * s.cw);
+    bits = own_taken >> (wave * s.cw);
   } else if constexpr (SELECT) {
     const int k = decode_row_budget(vis, s.fixed_k, s.ppm), n = min(4 * s.cw, p1 - base);
     if (n_blocks > 0 && k < vis) kt = load4(j0);
 #pragma unroll
     for (int u = 0; u < kRows; ++u)
       if (wave + 4 * u < G) {
-        const uint64_t own = s.keys[(group0 + wave + 4 * u) * Tk + min(base + lane, Tk - 1)];
+        uint64_t own;
+        if constexpr (PASS == SCORES) {
+          own = u == 0 ? own_key[0] : own_key[kRows - 1];
+          if (tail) own = s.keys[(group0 + wave + 4 * u) * Tk + min(base + lane, Tk - 1)];
+        } else {
+          static_assert(PASS != BOTH || NR <= 2, "one of two registers");
+          own = __shfl(key[u][0], (base + lane) & 63);
+          if constexpr (NR == 2) {
+            const uint64_t x = __shfl(key[u][1], (base + lane) & 63);
+            own = base + lane < 64 ? own : x;
+          }
+        }
         const uint32_t taken = k >= vis ? ~0u : rank_select(key[u], own, k, base, n, lane);
         if (lane < 4) reinterpret_cast<uint32_t*>(scores[lane][0])[wave + 4 * u] = taken;
         if (PASS == SCORES && lane == 0) s.taken[(group0 + wave + 4 * u) * s.items + item] = taken;
@@ -416,34 +472,15 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // the last reads of K are over
   if (Mnext != all) issue4(j0, 0);
   // ---- the running maximum in front of the wavefront's blocks ----
-  const int h = lane & (NH - 1), kg = lane / NH;               // softmax layout
-  const int hg = min(h, G - 1);                                // lanes of a padding head follow the last one and are never read
-  // VALUES: the scores of a block are asked for one block ahead
-  struct Scores { float v[NH]; };
-  const float* sbase = s.scores + group0 * a.Nkv;              // scalar; the lane's head and keys in 32 bits
-  const uint32_t soff = (uint32_t)(hg * a.Nkv + NH * kg);
-  auto load_scores = [&](int j) {
-    Scores x;
-    if constexpr (NH >= 4) {
-#pragma unroll
-      for (int u = 0; u < NH; u += 4) {
-        const float4 z = *reinterpret_cast<const float4*>(sbase + (size_t)j * kBk + soff + u);
-        x.v[u] = z.x; x.v[u + 1] = z.y; x.v[u + 2] = z.z; x.v[u + 3] = z.w;
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < NH; ++u) x.v[u] = (sbase + (size_t)j * kBk)[soff + u];
-    }
-    return x;
-  };
-  Scores next;
   float m = kEmptyMax;
   bool unanswered = false;                                     // BOTH: a wait has ended without a maximum
   if constexpr (PASS == VALUES) {
-    if (n_blocks > 0) next = load_scores(j0);
-    const int ahead = n_blocks > 0 && !tail ? place * 4 + wave : 0;              // chunks of the partition in front
-    const float* cm = s.cmax + (group0 + hg) * s.chunks + item * 4 + wave - ahead;
-    for (int e = kg; e < ahead; e += 64 / NH) m = fmaxf(m, cm[e]);
+    if (tail && n_blocks > 0) next = load_scores(j0);
+    if (n_blocks > 0) {                                        // (chunks without blocks have left no maximum)
+#pragma unroll
+      for (int e = 0; e < kFront; ++e) m = fmaxf(m, front[e]);
+      for (int e = kg + kFront * (64 / NH); e < in_front; e += 64 / NH) m = fmaxf(m, cm[e]);
+    }
   } else {
     lds_barrier();
     unsigned* published = s.tops + (group0 + hg) * s.items + item;
@@ -631,23 +668,26 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
   // the workgroup's partial.  A wavefront without blocks has left its sums unwritten; it is skipped by its row sum of zero
   // (with a key it is positive, or the whole chunk weighs nothing, or it is NaN and has to reach the result: bits are
   // compared, because comparisons of numbers are compiled as if there were no NaN).
-  for (int e = tid; e < G * kD; e += 256) {
-    const int u = e >> 7, ch = e & (kD - 1);
+  for (int e = tid; e < G * (kD / 2); e += 256) {                 // two channels each: one round for up to four heads
+    const int u = e >> 6, ch = 2 * (e & 63);
     float m = ml(0, u)[0];
 #pragma unroll
     for (int v = 1; v < 4; ++v) m = fmaxf(m, ml(v, u)[0]);
-    float l = 0.f, sum = 0.f;
+    float l = 0.f;
+    float2 sum = make_float2(0.f, 0.f);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const float lv = ml(v, u)[1];
       if (__float_as_uint(lv) != 0u) {
         const float f = fast_exp2((ml(v, u)[0] - m) * c);
+        const float2 x = *reinterpret_cast<const float2*>(tiles[v] + 4 * (u * kD + ch));
         l += f * lv;
-        sum += f * reinterpret_cast<const float*>(tiles[v])[u * kD + ch];
+        sum.x += f * x.x;
+        sum.y += f * x.y;
       }
     }
     const size_t slot = (group0 + u) * a.nparts + item;
-    a.part_o[slot * kD + ch] = sum;
+    *reinterpret_cast<float2*>(a.part_o + slot * kD + ch) = sum;
     if (ch == 0) { a.part_ml[2 * slot] = m; a.part_ml[2 * slot + 1] = l; }
   }
 }

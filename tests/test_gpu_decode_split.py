@@ -73,6 +73,27 @@ def test_two_pass_decode_equals_one_pass(T, Hq, Hkv, B, N, split, lens, budget, 
     assert torch.equal(two, again)
 
 
+@pytest.mark.parametrize("Hq,Hkv,B,N,split,lens,budget", [
+    (32, 8, 1, 32768, 256, [31937], 0.05),                                   # places whose last wavefronts have no block
+    (4, 4, 3, 16448, 256, [16448, 8321, 577], 0.25),                         # one head
+    (16, 2, 2, 32768, 509, [32767, 16385], 0.1),                             # more maxima in front than are asked for at once
+    (64, 8, 2, 40960, 250, [40959, 33000], 0.1),                             # a selection of its own launch
+    (8, 4, 2, 5376, 37, [5375, 2368], 0.0),                                  # no block promoted
+])
+def test_two_launches_in_any_workspace(T, Hq, Hkv, B, N, split, lens, budget):
+    """What is asked for before the length is known may never have been written: the results do not depend on what lies there."""
+    print(f"decode in any workspace Hq={Hq} Hkv={Hkv} B={B} N={N} split={split} budget={budget}", flush=True)
+    args = _cache(T, W.scaled(W.DECODE_131K, B=B, N=N, Hq=Hq, Hkv=Hkv))
+    sl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    ws = torch.empty(T.decode_workspace_bytes(B, Hq, Hkv, N, 128, 64, split), dtype=torch.uint8, device="cuda")
+    outs = []
+    for fill in (0, 0xFF, 0x7F, 0x55):                                       # 0x7F7F7F7F: a larger maximum than any
+        ws.fill_(fill)
+        outs.append(T.thrift_attn_decode(*args, 64, budget, split_blocks=split, seqlens=sl, workspace=ws,
+                                         out=torch.empty(B, Hq, 128, dtype=torch.float32, device="cuda")))
+        assert bool(torch.isfinite(outs[-1]).all()) and torch.equal(outs[-1], outs[0])
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("Hq,Hkv,B,N,split,lens,budget,shared", [
     (8, 8, 9, 8192, 256, [8192 - 517 * b for b in range(9)], 0.05, False),   # 9216 key blocks: one launch; it selects for itself
