@@ -132,7 +132,7 @@ constexpr int chunk_limit(int nh, bool both) { return both && nh > 4 ? kSplitMax
 template <typename T, int NH, Pass PASS, int NR, int NC = 1>
 __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel(DecodeSplitArgs s) {
   const DecodeArgs& a = s.a;
-  constexpr bool SELECT = NR > 0;
+  constexpr bool SELECT = NR > 0, kWhole = PASS == BOTH;         // kWhole: registers for both halves of a 16-bit tile
   constexpr int kSlot = 4096 + 256;                            // codes and scales of a V block
   // per wavefront: half a 16-bit K tile; then two V blocks, which give way to its partial sums, and behind them its
   // maxima and sums
@@ -174,9 +174,8 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
   // (4 g + i) % 4 (8); the lane quantises the MXFP4 group it carries
   const int h = lane & (NH - 1), kg = lane / NH;               // softmax layout
   const int hg = min(h, G - 1);                                // lanes of a padding head follow the last one and are never read
-  // In two launches the workgroup's place is known, too: the keys of its own blocks; its selection, the largest scores in front of
-  // it in the partition and the scores of its first block.  What stands there may never have been written: it is used where the
-  // length says that it was.  Asked for one after the other behind the length they took 2.7 us of the 12 us of the values pass, now 0.7.
+  // Two launches: the workgroup's place is known, too: the keys of its own blocks; its selection, the largest scores in front of
+  // it in the partition and the scores of its first block.
   const int early = min(part * a.split_blocks + y % s.nsub * 4 * s.cw, Tk - 1);          // (not of a partly filled last block)
   uint64_t own_key[kRows];
   if constexpr (SELECT && PASS == SCORES) {
@@ -406,18 +405,37 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
 
     for (int i = 0; i < n_blocks; ++i) {
       const int M = promoted_mask(bits, i);
+      // One launch: both halves of a 16-bit K tile are asked for at once, the first by LDS DMA, the second into registers, from
+      // where it takes the first one's place (a half at a time: see load16).
+      v4i second[8];
+      if (kWhole && M != 0) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the reads of the tile before are over
+        issue_k16(j0 + i, 0, 8);
+        const uint8_t* half1 = k16base + (size_t)(j0 + i) * kTile16 + kTile16 / 2 + 16 * lane;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) second[q] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(half1 + 1024 * q));
+      }
       if (M != all) scores4(kt, i, M);
-      load_next(i + 1);
+      if (!kWhole || M == 0) load_next(i + 1);
       if (M != 0) {
         v4f acc[4];
         v8s qf[4];
         query16(qf);
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the reads of the half before are over
-          issue_k16(j0 + i, 8 * hf, 8);
+        if constexpr (kWhole) {
           vm_wait<0>();
-          scores16(qf, 2 * hf, 2, acc);
+          load_next(i + 1);
+          scores16(qf, 0, 2, acc);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) *reinterpret_cast<v4i*>(slots + 1024 * q + 256 * g + 16 * (r ^ (4 * (q & 1) + g))) = second[q];
+          scores16(qf, 2, 2, acc);
+        } else {
+#pragma unroll
+          for (int hf = 0; hf < 2; ++hf) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the reads of the half before are over
+            issue_k16(j0 + i, 8 * hf, 8);
+            vm_wait<0>();
+            scores16(qf, 2 * hf, 2, acc);
+          }
         }
         keep16(acc, i, M);
       }
@@ -462,11 +480,14 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
     dma_b32<true>(vsbase + (size_t)j_ * 256, (uint32_t)(4 * lane), to + 4096);
   };
   // Half q of the 16-bit rows of a block, keys 32 q + 8 g .. + 7, channels 8 r ..
-  v4i v[8];
+  // One launch asks for both at once: 67.0 -> 64.9 us for 1 x 131072 tokens, 32/8 heads, 5 %, 149.6 -> 144.7 for a step of 8 x 16384-32768,
+  // 64/8, 10 %, 46.0 -> 44.3 for 16 x 4096-8192 with shared selection.  In two launches that would leave a CU three workgroups instead of four
+  // (44.4 -> 47.7 us for 2 x 28672), and where three are enough it gains nothing (1 x 32768).
+  v4i v[kWhole ? 16 : 8];
   auto load16 = [&](int j, int q0) __attribute__((always_inline)) {
     const uint8_t* tile = v16base + (size_t)j * kTile16 + 8192 * q0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(tile + v16off + 256 * u));
+    for (int u = 0; u < 8; ++u) v[(kWhole ? 8 * q0 : 0) + u] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(tile + v16off + 256 * u));
   };
   int Mnext = n_blocks > 0 ? promoted_mask(bits, 0) : all;
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // the last reads of K are over
@@ -548,7 +569,10 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
       uint16_t* prow_w = reinterpret_cast<uint16_t*>(scores[wave][PASS == BOTH ? i : 0]);
       uint8_t* pcode_w = reinterpret_cast<uint8_t*>(prow_w + NH * 64);
       uint8_t* pscale_w = pcode_w + NH * 32;
-      if (M != 0) load16(j, 0);                                // needed after the softmax
+      if (M != 0) {                                            // needed after the softmax
+        load16(j, 0);
+        if (kWhole) load16(j, 1);
+      }
       Mnext = i + 1 < n_blocks ? promoted_mask(bits, i + 1) : all;
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the scores are here, the reads of the other slot's block are over
       if (Mnext != all) issue4(j + 1, (i + 1) & 1);
@@ -623,14 +647,15 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
         const bool mine = r_ < G && ((M >> r_) & 1) != 0;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {                          // keys 32 q + 8 g .. + 7
-          if (q == 1) {
+          if (!kWhole && q == 1) {
             __builtin_amdgcn_sched_barrier(0);                 // into the registers of the first half
             load16(j, 1);
           }
+          v4i* vq = v + (kWhole ? 8 * q : 0);
           if (n_valid != kBk) {                                // rows past the cached tokens hold whatever lies there, and zero times that need not be zero
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-              if (32 * q + 8 * g + u >= n_valid) v[u] = (v4i){0, 0, 0, 0};
+              if (32 * q + 8 * g + u >= n_valid) vq[u] = (v4i){0, 0, 0, 0};
           }
           const v8s pf = mine ? *reinterpret_cast<const v8s*>(prow_w + r_ * 64 + 32 * q + 8 * g_) : (v8s){0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
@@ -638,7 +663,7 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
             const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
             v4i col;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) col[u] = (int)__builtin_amdgcn_perm((uint32_t)v[2 * u + 1][e >> 1], (uint32_t)v[2 * u][e >> 1], sel);
+            for (int u = 0; u < 4; ++u) col[u] = (int)__builtin_amdgcn_perm((uint32_t)vq[2 * u + 1][e >> 1], (uint32_t)vq[2 * u][e >> 1], sel);
             // zero times an infinity or NaN of V is not zero: the heads that take the block in 4 bits keep their sums
             const v4f sum = mfma16<T>(__builtin_bit_cast(v8s, col), pf, o[e]);
             o[e] = mine ? sum : o[e];
