@@ -239,6 +239,18 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
   //  ISSUE: block J+1 — its 4-bit tiles into the other slot, unless every list has promoted it; the tiles of a promoted block into
   //         the 16-bit buffers, unless block J is using them (then its K tile follows the score phase of block J and its V
   //         tile the start of step J+1: late_v).
+  // Workgroups with rows of one length that share a CU take turns of 16 key blocks with the higher wavefront priority (take_turns).
+  const int turn = (int)(work / kCus) & 1;
+  bool ahead = false;
+#define THRIFT_TURN(J)                                                                                         \
+  if (a.turns) {                                                                                               \
+    const bool mine_ = (((J) >> 4) & 1) == turn;                                                               \
+    if (mine_ != ahead) {                                                                                      \
+      ahead = mine_;                                                                                           \
+      if (mine_) __builtin_amdgcn_s_setprio(1);                                                                \
+      else __builtin_amdgcn_s_setprio(0);                                                                      \
+    }                                                                                                          \
+  }
   bool late_v = false;                                  // block J is promoted and its V tile is not issued yet
 #define THRIFT_SYNC()                                                                                          \
   vm_wait<0>();                                                                                                \
@@ -314,6 +326,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
       drop_stale(j);
       const int run_end = min(vis_wave, n0[0]);
       for (; j < run_end; ++j) {                          // a run of 4-bit blocks
+        THRIFT_TURN(j)
         THRIFT_SYNC()
         THRIFT_ISSUE_WIDE(j + 1, j + 1 == n0[0])
         THRIFT_MASK(j)
@@ -407,6 +420,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     auto step_a = [&](auto slot_c) __attribute__((always_inline)) {
       constexpr int SLOT = decltype(slot_c)::value;
       seek(j + 1);
+      THRIFT_TURN(j)
       THRIFT_SYNC()
       if (next4 < vis) {
         THRIFT_ISSUE4_SLOT(next4, SLOT ^ 1);
@@ -522,6 +536,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     drop_stale(j);
     const int run_end = min(vis_wave, n0[0]);
     for (; j < run_end; ++j) {
+      THRIFT_TURN(j)
       THRIFT_SYNC()
       THRIFT_ISSUE(j, false, j + 1 == n0[0], j + 1 == n0[0])
       THRIFT_MASK(j)
@@ -609,6 +624,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
   }
   vm_wait<0>();
 #undef THRIFT_SYNC
+#undef THRIFT_TURN
 #undef THRIFT_LOAD_Q16
 #undef THRIFT_LOAD_Q16_ROW
 #undef THRIFT_ISSUE
@@ -713,6 +729,17 @@ static bool one_query_block(const PrefillArgs& a) {
 // which the longer one alone takes the time).  The last third turned round as well is no better (66.4, 67.1), alone worse (68.5, 69.2).
 static bool folded(const PrefillArgs& a, unsigned grid) { return a.interleave && grid <= 3u * kCus; }
 
+// One round of workgroups whose rows are equally long (no mask, or a chunk behind cached tokens).  A SIMD prefers its oldest wavefront, so that
+// the first workgroup of a CU ended when the second was at 60 % (467 and 605 us of a chunk of 2048 tokens on 30720), and the rest ran with
+// one wavefront per SIMD, which uses half of its vector rate.  With turns they end together.  Without / with: 592 / 575 us for that
+// chunk, 814 / 790 for one of 3072, 780 / 744 for 2500; 102.2 / 97.6 for 3001 tokens without a mask, 62.6 / 60.7 for 2048.  In causal prompts the
+// first workgroup of a CU is the longest and should run ahead (68.3 / 71.6 for 3001 tokens), and in larger grids the next workgroup fills the
+// place that is free: 239 / 265 for 5000 tokens without a mask, 1092 / 1134 for a chunk of 4096; two workgroups per CU (wide): 652 / 634 for the
+// chunk of 2048 at 25 %, 123.9 / 127.2 for 3001 tokens without a mask, one and a half rounds.
+static bool take_turns(const PrefillArgs& a, unsigned grid) {
+  return (!a.causal || a.q_off > 0) && grid > 1u * kCus && grid <= (wide_schedule(a) ? 2u : 3u) * kCus;
+}
+
 void launch_prefill(const PrefillArgs& args, hipStream_t st) {
   if (launch_prefill_split(args, st)) return;
   PrefillArgs a = args;
@@ -720,13 +747,14 @@ void launch_prefill(const PrefillArgs& args, hipStream_t st) {
   const unsigned grid = (unsigned)((long)a.B * a.Hq * ((a.Nq + rows - 1) / rows));
   a.interleave = interleaved_units(a, grid);
   a.fold = folded(a, grid);
+  a.turns = take_turns(a, grid);
   if (a.tile_order == 4 && a.Bq == 128) {
     // persistent launch of the Sec. 3.3 order: three workgroups per CU.  One counter per device: two such launches
     // must not overlap on a device.  The counter is cleared by a kernel (a memset node misbehaves under graph capture).
     int dev = 0, cus = kCus;
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const unsigned resident = (unsigned)min((long)grid, 3L * cus);
-    a.fold = 0;                                          // its workgroups take the items as they come
+    a.fold = a.turns = 0;                                // its workgroups take the items as they come
     prefill_reset_counter_kernel<<<dim3(1), dim3(1), 0, st>>>();
     if (a.dt == THRIFT_F16) prefill_persistent_kernel<F16, 1><<<dim3(resident), dim3(256), 0, st>>>(a, grid);
     else prefill_persistent_kernel<BF16, 1><<<dim3(resident), dim3(256), 0, st>>>(a, grid);

@@ -43,6 +43,28 @@ def test_order_of_the_workgroups(T, B, Hq, Hkv, N, Bq, causal):
             assert torch.equal(out[b, h * G:(h + 1) * G], alone[0])
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,Bq,budget", [
+    (1, 32, 8, 1025, 128, 0.05),         # 288 workgroups, 17 key blocks: one turn and one block
+    (2, 16, 16, 2048, 128, 0.05),        # 512
+    (3, 8, 1, 3999, 128, 0.05),          # 768
+    (1, 32, 8, 2048, 128, 0.25),         # 512, the wide schedule in ascending order
+    (1, 32, 8, 2000, 64, 0.05),          # two query blocks per workgroup
+])
+def test_turns_between_workgroups(T, B, Hq, Hkv, N, Bq, budget):
+    """Rows of one length in a grid of one round: the workgroups' priorities change nothing but the time."""
+    print(f"turns B={B} {Hq}/{Hkv} N={N} Bq={Bq} f={budget}", flush=True)
+    q, k, v = _qkv(B, Hq, Hkv, N, torch.float16)
+    G = Hq // Hkv
+    for order in (0, 1):
+        out = T.thrift_attention(q, k, v, False, Bq, 64, budget, tile_order=order, out_dtype=torch.float32)
+        for b in range(B):
+            for h in range(Hkv):
+                heads = slice(h * G, (h + 1) * G)
+                alone = T.thrift_attention(*(x[b:b + 1, s].contiguous() for x, s in ((q, heads), (k, slice(h, h + 1)), (v, slice(h, h + 1)))),
+                                           False, Bq, 64, budget, tile_order=order, out_dtype=torch.float32)
+                assert torch.equal(out[b, heads], alone[0])
+
+
 def _form(B, Hq, Nq, N, kmax):
     """Row groups per workgroup of the four-wavefront kernel, 0: the plain one (launch_prefill_split's rule)."""
     groups, Tk = B * Hq * -(-Nq // 32), -(-N // 64)
