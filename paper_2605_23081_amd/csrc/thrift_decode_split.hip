@@ -22,12 +22,14 @@
 // spread over 2^40, 2.8 % of the scores differed in their last bit, neither side further from 64 bits than the other; a
 // probability on a rounding boundary may then fall to either side.
 //
-// Measured, whole calls or serving steps, the walk / two launches with a search for every selection / now: 306 / 43.2 / 38.5 us
-// for one sequence of 32768 tokens and 32/8 heads, 102 / 28.0 / 22.9 for one of 4096; 301 / 74.0 / 67.7 for one of 131072,
-// 544 / 192.4 / 161.7 for eight of 16384-32768 with 64/8 heads at 10 %, 148 / 53.4 / 46.3 for sixteen of 4096-8192 with shared
-// selection, - / 324.5 / 269.3 for sixteen of 16384-32768 at 25 %.
+// Measured, whole calls or serving steps, the walk / two launches with a search for every selection / now: 306 / 43.2 / 35.4 us
+// for one sequence of 32768 tokens and 32/8 heads, 102 / 28.0 / 21.8 for one of 4096; 301 / 74.0 / 66.1 for one of 131072,
+// 544 / 192.4 / 156.8 for eight of 16384-32768 with 64/8 heads at 10 %, 148 / 53.4 / 45.4 for sixteen of 4096-8192 with shared
+// selection, - / 324.5 / 261.8 for sixteen of 16384-32768 at 25 %.
 // What bounds it: for short caches the chain of launches and of dependent loads inside them (a step of one sequence of 4096 tokens
-// reads 0.5 MB); for long ones too few bytes in flight per CU in the chunks' own chains, 4.1 to 5.2 TB/s of 7.1.
+// reads 0.5 MB; in its 11 us launch 2.0 until the length, the place and the query are there, 1.2 to the first score, 1.0 scores, 2.6 for the
+// maxima in front, 0.9 values, 1.4 the sums); for long ones a workgroup's 11 us without tiles in flight (start, wait and end of 30) and
+// the last, nearly empty round.
 #include <type_traits>
 
 #include "thrift_launch.h"
@@ -174,8 +176,9 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
   // (4 g + i) % 4 (8); the lane quantises the MXFP4 group it carries
   const int h = lane & (NH - 1), kg = lane / NH;               // softmax layout
   const int hg = min(h, G - 1);                                // lanes of a padding head follow the last one and are never read
-  // Two launches: the workgroup's place is known, too: the keys of its own blocks; its selection, the largest scores in front of
-  // it in the partition and the scores of its first block.
+  // In two launches the workgroup's place is known, too: the keys of its own blocks; its selection, the largest scores in front of
+  // it in the partition and the scores of its first block.  What stands there may never have been written: it is used where the
+  // length says that it was.  Asked for one after the other behind the length they took 2.7 us of the 12 us of the values pass, now 0.7.
   const int early = min(part * a.split_blocks + y % s.nsub * 4 * s.cw, Tk - 1);          // (not of a partly filled last block)
   uint64_t own_key[kRows];
   if constexpr (SELECT && PASS == SCORES) {
