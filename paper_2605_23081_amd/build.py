@@ -90,6 +90,82 @@ def _registers(operand):
             for n in range(int(m[2] or m[4]), int(m[3] or m[4]) + 1)}
 
 
+class _Listing:
+    """A device listing as one graph of basic blocks per kernel, in which wait states are followed along every branch."""
+
+    def __init__(self, asm_text: str):
+        self.kernels = []                                  # (kernel, label -> ([(line, op, operands, by_hand)], labels that follow))
+        self.statements = 0                                # inline assembly
+        blocks, block, inside = None, None, False
+        for number, line in enumerate(asm_text.splitlines()):
+            t = line.strip()
+            if t.startswith("_Z") and t.split(":")[0].isidentifier() and ":" in t:
+                block = t.split(":")[0]
+                blocks = {block: ([], [])}
+                self.kernels.append((block, blocks))
+            elif t.startswith(";;#ASMSTART"):
+                inside = True
+                self.statements += 1
+            elif t.startswith(";;#ASMEND"):
+                inside = False
+            elif blocks is None or not t or t.startswith((";", "//")):
+                pass
+            elif t.startswith(".LBB"):
+                label = t.split(":")[0]
+                if block is not None:
+                    blocks[block][1].append(label)
+                block = label
+                blocks[block] = ([], [])
+            elif line[:1] == "\t" and t[:1].isalpha():
+                if block is None:                          # behind an unconditional branch without a label: never reached
+                    continue
+                op, _, rest = t.split(";")[0].strip().partition(" ")
+                operands = [x.strip() for x in re.split(r",(?![^\[]*\])", rest)] if rest else []
+                blocks[block][0].append((number, op, operands, inside))
+                if op == "s_branch" or op.startswith("s_cbranch"):
+                    blocks[block][1].append(operands[0])
+                if op.startswith("s_cbranch"):             # what follows is a block of its own
+                    name = f"{block}+{number}"
+                    blocks[block][1].append(name)
+                    block = name
+                    blocks[block] = ([], [])
+                elif op in ("s_branch", "s_endpgm", "s_setpc_b64"):
+                    block = None
+
+    def instructions(self):
+        return (i for _, blocks in self.kernels for code, _ in blocks.values() for i in code)
+
+    def early(self, reads, writes):
+        """(kernel, instruction) wherever reads(op, operands, by_hand) names a result that is needed longer than it has been there.
+        reads: pairs (result, wait states that may be left); writes(op, operands, by_hand): pairs (result, wait states, 0 for none)."""
+        found = []
+        for kernel, blocks in self.kernels:
+            # the wait states that each result still needs at a block's start, over all ways to it
+            start, todo, here = {b: {} for b in blocks}, list(blocks), set()
+            while todo:
+                b = todo.pop()
+                wait = dict(start[b])
+                instructions, follow = blocks[b]
+                for line, op, operands, by_hand in instructions:
+                    if wait and any(wait.get(r, 0) > left for r, left in reads(op, operands, by_hand)):
+                        here.add((line, op + " " + ", ".join(operands)))
+                    states = int(operands[0], 0) + 1 if op == "s_nop" else 1
+                    wait = {r: n - states for r, n in wait.items() if n > states}
+                    for r, n in writes(op, operands, by_hand):
+                        if n:
+                            wait[r] = n
+                        else:
+                            wait.pop(r, None)
+                for f in follow:
+                    if f in start:
+                        more = {r: n for r, n in wait.items() if n > start[f].get(r, 0)}
+                        if more:
+                            start[f].update(more)
+                            todo.append(f)
+            found.extend((kernel, what) for _, what in sorted(here))
+        return found
+
+
 def matrix_results_read_early(asm_text: str):
     """(kernel, instruction) of every hand-written instruction that touches a matrix result before it is written.
 
@@ -97,81 +173,74 @@ def matrix_results_read_early(asm_text: str):
     12 (8) wait states away from it, and here as far from overwriting the addend as well.  The compiler spaces its own instructions
     like that but not the inside of an asm statement, so the listing is followed along every branch: an instruction between
     the ASMSTART / ASMEND markers must find no result or addend of its registers in flight."""
-    early = []
-    kernel, inside, statements, matrix = None, False, 0, 0
-    blocks, block = {}, None                               # per kernel: label -> (instructions, labels that follow)
-
-    def close():
-        # the wait states that each register still needs at a block's start, over all ways to it
-        if kernel is None:
-            return
-        start, todo, found = {b: {} for b in blocks}, list(blocks), set()
-        while todo:
-            b = todo.pop()
-            wait = dict(start[b])
-            instructions, follow = blocks[b]
-            for line, op, operands, by_hand in instructions:
-                if by_hand and op[:2] != "s_":
-                    touched = set().union(*map(_registers, operands)) if operands else set()
-                    written = _registers(operands[0]) if operands else set()
-                    if any(wait.get(("d", r), 0) > 0 for r in touched) or any(wait.get(("c", r), 0) > 0 for r in written):
-                        found.add((line, op + " " + ", ".join(operands)))
-                states = int(operands[0], 0) + 1 if op == "s_nop" else 1
-                wait = {r: n - states for r, n in wait.items() if n > states}
-                if op.startswith(("v_mfma", "v_smfmac")):
-                    n = 12 if "_32x32x" in op else 8
-                    for r in _registers(operands[0]):
-                        wait["d", r] = n
-                    for r in _registers(operands[3]):
-                        wait["c", r] = n
-            for f in follow:
-                if f in start:
-                    more = {r: n for r, n in wait.items() if n > start[f].get(r, 0)}
-                    if more:
-                        start[f].update(more)
-                        todo.append(f)
-        early.extend((kernel, what) for _, what in sorted(found))
-
-    for number, line in enumerate(asm_text.splitlines()):
-        t = line.strip()
-        if t.startswith("_Z") and t.split(":")[0].isidentifier() and ":" in t:
-            close()
-            kernel, blocks, block = t.split(":")[0], {}, t.split(":")[0]
-            blocks[block] = ([], [])
-        elif t.startswith(";;#ASMSTART"):
-            inside = True
-            statements += 1
-        elif t.startswith(";;#ASMEND"):
-            inside = False
-        elif kernel is None or not t or t.startswith((";", "//")):
-            pass
-        elif t.startswith(".LBB"):
-            label = t.split(":")[0]
-            if block is not None:
-                blocks[block][1].append(label)
-            block = label
-            blocks[block] = ([], [])
-        elif line[:1] == "\t" and t[:1].isalpha():
-            if block is None:                              # behind an unconditional branch without a label: never reached
-                continue
-            op, _, rest = t.split(";")[0].strip().partition(" ")
-            operands = [x.strip() for x in re.split(r",(?![^\[]*\])", rest)] if rest else []
-            matrix += op.startswith("v_mfma")
-            blocks[block][0].append((number, op, operands, inside))
-            if op == "s_branch" or op.startswith("s_cbranch"):
-                blocks[block][1].append(operands[0])
-            if op.startswith("s_cbranch"):                 # what follows is a block of its own
-                name = f"{block}+{number}"
-                blocks[block][1].append(name)
-                block = name
-                blocks[block] = ([], [])
-            elif op in ("s_branch", "s_endpgm", "s_setpc_b64"):
-                block = None
-    close()
-    if statements == 0 or matrix == 0:
+    listing = _Listing(asm_text)
+    if listing.statements == 0 or not any(op.startswith("v_mfma") for _, op, _, _ in listing.instructions()):
         raise RuntimeError("the listing shows no inline assembly or no matrix instructions: the wait-state check cannot read "
                            "this compiler's output")
-    return early
+
+    def reads(op, operands, by_hand):
+        if not by_hand or op[:2] == "s_" or not operands:
+            return []
+        return [(("d", r), 0) for x in operands for r in _registers(x)] + [(("c", r), 0) for r in _registers(operands[0])]
+
+    def writes(op, operands, by_hand):
+        if not op.startswith(("v_mfma", "v_smfmac")):
+            return []
+        n = 12 if "_32x32x" in op else 8
+        return [(("d", r), n) for r in _registers(operands[0])] + [(("c", r), n) for r in _registers(operands[3])]
+
+    return listing.early(reads, writes)
+
+
+_SCALARS = re.compile(r"\bs(?:\[(\d+):(\d+)\]|(\d+)\b)|\b(vcc)(_lo|_hi)?\b")
+
+
+def _scalars(operand):
+    found = set()
+    for m in _SCALARS.finditer(operand):
+        if m[4]:
+            found |= {"vcc" + m[5]} if m[5] else {"vcc_lo", "vcc_hi"}
+        else:
+            found |= set(range(int(m[1] or m[3]), int(m[2] or m[3]) + 1))
+    return found
+
+
+def scalars_read_early(asm_text: str):
+    """(kernel, instruction) of every instruction that reads a scalar register too soon behind the vector instruction that wrote it,
+    where one of the two is hand-written.
+
+    A comparison or another vector instruction that leaves its result in vcc or a scalar register has to stay two wait states
+    away from a vector instruction that reads it (four where it selects a lane, and in front of v_div_fmas) and five
+    from a load or store.  The compiler spaces its own instructions like that but sees nothing of the inside of an asm statement."""
+    listing = _Listing(asm_text)
+    if not any(op.startswith(("v_cmp", "v_readfirstlane")) for _, op, _, _ in listing.instructions()):
+        raise RuntimeError("the listing shows no vector instruction that writes a scalar register: the wait-state check cannot read "
+                           "this compiler's output")
+    longest = 5
+
+    def results(op):                                       # the operands that it writes, of which some are scalar registers
+        if op.startswith(("v_cmp", "v_readfirstlane", "v_readlane")):
+            return 1
+        return 2 if "_co_" in op or op.startswith(("v_div_scale", "v_mad_u64", "v_mad_i64")) else 0
+
+    def reads(op, operands, by_hand):
+        if op.startswith(("global_", "buffer_", "flat_", "scratch_")):
+            apart = 5
+        elif not op.startswith("v_"):
+            return []
+        else:
+            apart = 4 if op.startswith(("v_readlane", "v_writelane", "v_div_fmas")) else 2
+        read = set().union(*map(_scalars, operands[results(op):]), {"vcc_lo", "vcc_hi"} if op.startswith("v_div_fmas") else set())
+        return [((written_by_hand, r), longest - apart) for r in read for written_by_hand in ((False, True) if by_hand else (True,))]
+
+    def writes(op, operands, by_hand):
+        if op.startswith("s_") and not op.startswith(("s_cmp", "s_bitcmp", "s_cbranch")):      # a scalar instruction's result is waited for
+            return [((written_by_hand, r), 0) for x in operands[:1] for r in _scalars(x) for written_by_hand in (False, True)]
+        if not op.startswith("v_"):
+            return []
+        return [((by_hand, r), longest) for x in operands[:results(op)] for r in _scalars(x)]
+
+    return listing.early(reads, writes)
 
 
 def _start_call_module(obj):
@@ -237,6 +306,9 @@ def build(verbose: bool = False, extra=()):
         early = matrix_results_read_early(text)
         if early:
             raise RuntimeError(f"{src}: hand-written instructions read matrix results too early: " + ", ".join(sorted({f"{k}: {i}" for k, i in early})[:8]))
+        early = scalars_read_early(text)
+        if early:
+            raise RuntimeError(f"{src}: scalar registers are read too soon behind or by hand-written instructions: " + ", ".join(sorted({f"{k}: {i}" for k, i in early})[:8]))
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
     _link_call_module(call_obj)

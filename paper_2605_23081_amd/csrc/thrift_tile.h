@@ -147,22 +147,21 @@ constexpr float kEmptyMax = -1.0e30f;
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }   // one v_max3_f32
 
-// The lane's keys at or past n_valid (of the block's 64) get the score -inf.  Compared and chosen one element at a time through
-// vcc: the compiler would form all 32 comparisons first, in 64 scalar registers for which the walk's own had to make room in vector
-// lanes and scratch (106 scalar registers, 2 spilled vector registers in the order of Sec. 3.3; now 72 and none: 71.5 -> 70.4 us for
-// 3001 tokens, 596 -> 592 for a chunk of 2048 on 30720, 32/8 heads, 5 %).  The leading s_nop keeps the first statement
-// clear of the matrix instructions that wrote the scores.
+// The lane's keys at or past n_valid (of the block's 64) get the score -inf, chosen bit by bit (v_bitop3) by a bit per key that
+// v_bfe spreads over a register: two instructions per score, as a comparison and a choice would be.  Of those the compiler
+// forms all 32 comparisons first, in 64 scalar registers for which the walk's own had to make room in vector lanes and scratch (106
+// scalar registers, 2 spilled vector registers in the order of Sec. 3.3; now 73 and none: 71.5 -> 70.4 us for 3001 tokens,
+// 596 -> 592 for a chunk of 2048 on 30720, 32/8 heads, 5 %).  Comparison and choice in one asm statement cost the same but need
+// wait states between them, and behind the scores' matrix instructions, that the compiler does not see.
 __device__ __forceinline__ void mask_scores(v16f (&s)[2], int half, int n_valid) {
-  int lim = n_valid - 32 * half;                        // the lane's keys 16t + i at or past lim are masked
-  asm volatile("s_nop 15" : "+v"(lim));
-  const float none = -INFINITY;
+  const int lim = min(max(n_valid - 32 * half, 0), 32);  // the lane's keys 16t + i at or past lim are masked
+  const uint32_t seen = (uint32_t)((1ull << lim) - 1);
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      float x = s[t][i];
-      asm volatile("v_cmp_lt_i32 vcc, %2, %1\n\tv_cndmask_b32 %0, %3, %0, vcc" : "+v"(x) : "v"(lim), "n"(16 * t + i), "v"(none) : "vcc");
-      s[t][i] = x;
+      const uint32_t x = (uint32_t)__builtin_amdgcn_sbfe((int)seen, 16 * t + i, 1);
+      s[t][i] = __uint_as_float((x & __float_as_uint(s[t][i])) | (~x & 0xff800000u));
     }
 }
 // Largest of the lane's 32 scores.

@@ -241,11 +241,16 @@ def test_decode_takes_one_launch_where_it_is_the_faster_form():
     assert not two(16, 32, 8, 128) and not two(16, 64, 8, 64)                # short rows of many blocks
 
 
+_listings = {}
+
+
 def _listing(source, path):
     import subprocess
     from paper_2605_23081_amd import build
-    subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", str(path)], check=True, capture_output=True)
-    return path.read_text()
+    if source not in _listings:
+        subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", str(path)], check=True, capture_output=True)
+        _listings[source] = path.read_text()
+    return _listings[source]
 
 
 @pytest.mark.parametrize("source", ["thrift_prefill_split.hip", "thrift_prefill.hip"])
@@ -253,6 +258,73 @@ def test_hand_written_instructions_wait_for_matrix_results(tmp_path, source):
     """The factors of a raised maximum multiply the accumulators that a matrix instruction before them may still be writing."""
     from paper_2605_23081_amd.build import matrix_results_read_early
     assert matrix_results_read_early(_listing(source, tmp_path / "listing.s")) == []
+
+
+@pytest.mark.parametrize("source", ["thrift_prefill_split.hip", "thrift_prefill.hip", "thrift_decode.hip", "thrift_decode_split.hip"])
+def test_hand_written_instructions_stay_clear_of_scalar_results(tmp_path, source):
+    """A comparison and the choice by its result need two wait states between them, which nobody inserts inside an asm statement."""
+    from paper_2605_23081_amd.build import scalars_read_early
+    assert scalars_read_early(_listing(source, tmp_path / "listing.s")) == []
+
+
+def test_the_key_mask_waits_for_the_scores(tmp_path):
+    """Right behind the matrix instructions, with nothing between them that happens to take the time."""
+    from paper_2605_23081_amd.build import matrix_results_read_early, scalars_read_early
+    source = tmp_path / "mask.hip"
+    source.write_text("""#include "thrift_tile.h"
+using namespace thrift;
+__global__ void mask_kernel(const v8h* a, const v8h* b, float* out, int n_valid) {
+  const int lane = threadIdx.x & 63;
+  v16f s[2];
+  for (int t = 0; t < 2; ++t) {
+    v16f zero = {0.f};
+    s[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[64 * t + lane], b[lane], zero, 0, 0, 0);
+  }
+  mask_scores(s, lane >> 5, n_valid);
+  for (int i = 0; i < 32; ++i) out[64 * i + lane] = s[i / 16][i % 16];
+  asm volatile("; end");
+}
+""")
+    listing = _listing(str(source), tmp_path / "listing.s")
+    assert matrix_results_read_early(listing) == []
+    if "v_cmp" in listing:                                   # (a mask without comparisons has no scalar results)
+        assert scalars_read_early(listing) == []
+
+
+def test_scalar_wait_state_check_reads_the_compiler_listing():
+    from paper_2605_23081_amd.build import scalars_read_early
+
+    def kernel(write, read, *between, by_hand=(True, True)):
+        lines = ["_ZN6thrift4walkEv:", "; %bb.0:", "\tv_readfirstlane_b32 s90, v9"]
+        for text, hand in ((write, by_hand[0]), (between, False), (read, by_hand[1])):
+            text = list(text) if isinstance(text, tuple) else ["\t" + text]
+            lines += ["\t;;#ASMSTART", *text, "\t;;#ASMEND"] if hand else text
+        return "\n".join(lines + ["\ts_endpgm"])
+
+    mask, compare = "v_cndmask_b32 v1, v2, v1, vcc", "v_cmp_lt_i32 vcc, 3, v4"
+    found = [("_ZN6thrift4walkEv", mask)]
+    for hands, expected in (((True, True), found), ((False, True), found), ((True, False), found), ((False, False), [])):
+        assert scalars_read_early(kernel(compare, mask, by_hand=hands)) == expected
+        assert scalars_read_early(kernel(compare, mask, "\ts_nop 0", by_hand=hands)) == expected
+        assert scalars_read_early(kernel(compare, mask, "\ts_nop 1", by_hand=hands)) == []
+    assert scalars_read_early(kernel(compare, mask, "\tv_add_f32_e32 v9, v9, v9", "\tv_add_f32_e32 v9, v9, v9")) == []
+    assert scalars_read_early(kernel(compare, mask.replace("vcc", "s[2:3]"))) == []
+    assert scalars_read_early(kernel("v_cmp_lt_i32 s[2:3], 3, v4", "v_add_f32 v1, s3, v1")) == [("_ZN6thrift4walkEv", "v_add_f32 v1, s3, v1")]
+    assert scalars_read_early(kernel("v_add_co_u32 v1, vcc, v2, v3", "v_addc_co_u32 v4, s[4:5], v5, v6, vcc"))
+    assert scalars_read_early(kernel("v_add_co_u32 v1, s[4:5], v2, v3", "v_add_co_u32 v4, s[4:5], v5, v6")) == []          # written, not read
+    load = "global_load_lds_dword v1, s[2:3]"
+    assert scalars_read_early(kernel("v_readfirstlane_b32 s3, v4", load, "\ts_nop 3", by_hand=(False, True)))
+    assert scalars_read_early(kernel("v_readfirstlane_b32 s3, v4", load, "\ts_nop 4", by_hand=(False, True))) == []
+    assert scalars_read_early(kernel("v_readfirstlane_b32 s3, v4", load, "\ts_add_i32 s3, s3, 1", by_hand=(False, True))) == []
+    assert scalars_read_early(kernel("v_readfirstlane_b32 s3, v4", load, "\ts_cmp_eq_u32 s3, 1", by_hand=(False, True)))
+    lane = "v_readlane_b32 s5, v4, s3"
+    assert scalars_read_early(kernel("v_readfirstlane_b32 s3, v4", lane, "\ts_nop 2", by_hand=(False, True)))
+    assert scalars_read_early(kernel("v_readfirstlane_b32 s3, v4", lane, "\ts_nop 3", by_hand=(False, True))) == []
+    around = ["\ts_cbranch_scc1 .LBB0_2", "; %bb.1:", "\ts_nop 15", ".LBB0_2:"]
+    assert scalars_read_early(kernel(compare, mask, "\ts_nop 0", *around)) == []
+    assert scalars_read_early(kernel(compare, mask, *around)) == found
+    with pytest.raises(RuntimeError):
+        scalars_read_early("_ZN6thrift4walkEv:\n; %bb.0:\n\ts_endpgm")
 
 
 def test_wait_state_check_reads_the_compiler_listing():
