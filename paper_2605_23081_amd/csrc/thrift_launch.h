@@ -46,7 +46,7 @@ struct PrefillArgs {
   int kmax, B, Hq, Hkv, N, Bq, causal;   // N: key tokens per head
   int tile_order;                         // 0: key blocks ascending (Alg. 1); 1: 4-bit blocks first, then promoted (Sec. 3.3)
   int Nq, q_off;                          // query tokens per head; block position of query block 0 in the sequence
-  int interleave, fold, turns;            // launch_prefill's own: order and priority of the workgroups
+  int interleave, fold;                   // launch_prefill's own: order of the workgroups
   float scale;            // softmax scale (already defaulted)
   thrift_dtype dt, out_dt;
 };

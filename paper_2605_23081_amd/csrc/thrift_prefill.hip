@@ -45,7 +45,12 @@ constexpr int kWidePercent = 15;                             // list length / ke
 // computes what its own list says.  A workgroup per query block of 64 rows had two wavefronts for the LDS of four, one and a half per
 // SIMD, and staged every block for half the rows.  One query block / two, 5 %: 542 / 314 us for 8192 tokens, 32/8 heads; 200 / 141
 // for 2 x 3000, 16/16, 25 %, no mask; 730 / 597 for a chunk of 1000 on 30720, 10 %; 160 / 120 for 2000, 64/8, 100 %.
-template <typename T, int NW, int NL, int ORDER, int WIDE>
+// TURNS: see take_turns.  An instance of its own: asked at every key block the question cost grids of at most one workgroup per CU,
+// where a lone wavefront per SIMD issues every scalar instruction at its own expense, 2 % (chunk of 1000 tokens on 16384, 32/8
+// heads, 5 %: 227.1 us without turns, 231.8 with the question, 224.4 now; 2000 with 16/16: 239.5 / 244.7 / 236.7).  For the same reason the walks
+// say which way their branches mostly go (no mask, no promoted block, a whole 4-bit block, rows that see it): that keeps the
+// rare ways out of line, 230.4 -> 224.4 us.
+template <typename T, int NW, int NL, int ORDER, int WIDE, int TURNS>
 __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char* lds, unsigned work) {
   static_assert(NL == 1 || !WIDE, "a slot of the wide schedule holds a block in one precision");
   constexpr int KF = 4 / NW;                 // 1 KiB fragments of a 4-bit K (and of a V) tile per wavefront
@@ -178,7 +183,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     int wave_ = wave;                                                                                          \
     asm volatile("" : "+s"(wave_));   /* LDS destinations are formed here from one scalar, not kept per slot and fragment */ \
     const uint32_t sl_ = lds0 + kLdsRing + s_ * kSlotStride + (uint32_t)(wave_ * (KF * 1024));                 \
-    if ((j_ + 1) * kBk <= N) {                                                                                 \
+    if (__builtin_expect((j_ + 1) * kBk <= N, 1)) {                                                            \
       _Pragma("unroll") for (int u = 0; u < KF; ++u) dma_b128(kt_, k4off[u], sl_ + kLdsK4 + u * 1024);         \
       dma_b32(scbase + (size_t)j_ * 256, scoff, sl_ - (uint32_t)(wave_ * (KF * 1024)) + sclds);                \
     } else {                                                                                                   \
@@ -242,15 +247,16 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
   // Workgroups with rows of one length that share a CU take turns of 16 key blocks with the higher wavefront priority (take_turns).
   const int turn = (int)(work / kCus) & 1;
   bool ahead = false;
-#define THRIFT_TURN(J)                                                                                         \
-  if (a.turns) {                                                                                               \
-    const bool mine_ = (((J) >> 4) & 1) == turn;                                                               \
-    if (mine_ != ahead) {                                                                                      \
-      ahead = mine_;                                                                                           \
-      if (mine_) __builtin_amdgcn_s_setprio(1);                                                                \
-      else __builtin_amdgcn_s_setprio(0);                                                                      \
-    }                                                                                                          \
-  }
+  auto take_turn = [&](int j) __attribute__((always_inline)) {
+    if constexpr (TURNS) {
+      const bool mine_ = ((j >> 4) & 1) == turn;
+      if (mine_ != ahead) {
+        ahead = mine_;
+        if (mine_) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
+      }
+    }
+  };
   bool late_v = false;                                  // block J is promoted and its V tile is not issued yet
 #define THRIFT_SYNC()                                                                                          \
   vm_wait<0>();                                                                                                \
@@ -326,7 +332,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
       drop_stale(j);
       const int run_end = min(vis_wave, n0[0]);
       for (; j < run_end; ++j) {                          // a run of 4-bit blocks
-        THRIFT_TURN(j)
+        take_turn(j);
         THRIFT_SYNC()
         THRIFT_ISSUE_WIDE(j + 1, j + 1 == n0[0])
         THRIFT_MASK(j)
@@ -389,7 +395,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     bool own4 = true, next_own4;                        // this wavefront's list takes the current / that block in 4 bits
     auto seek = [&](int j) {
       if constexpr (NL == 1) {
-        while (j == nx[0]) { ++j; pass(0); }
+        while (__builtin_expect(j == nx[0], 0)) { ++j; pass(0); }
         next_own4 = true;
       } else {
         for (;;) {
@@ -420,15 +426,15 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     auto step_a = [&](auto slot_c) __attribute__((always_inline)) {
       constexpr int SLOT = decltype(slot_c)::value;
       seek(j + 1);
-      THRIFT_TURN(j)
+      take_turn(j);
       THRIFT_SYNC()
-      if (next4 < vis) {
+      if (__builtin_expect(next4 < vis, 1)) {
         THRIFT_ISSUE4_SLOT(next4, SLOT ^ 1);
       } else if (first_promoted < vis) {
         THRIFT_ISSUE_K16(first_promoted);
         THRIFT_ISSUE_V16(first_promoted);
       }
-      if ((NL == 1 || own4) && j < vis_wave) {
+      if ((NL == 1 || own4) && __builtin_expect(j < vis_wave, 1)) {
         THRIFT_MASK(j)
         const unsigned char* slot = lds + kLdsRing + SLOT * kLdsBytes4;
         v16f s[2];
@@ -536,7 +542,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     drop_stale(j);
     const int run_end = min(vis_wave, n0[0]);
     for (; j < run_end; ++j) {
-      THRIFT_TURN(j)
+      take_turn(j);
       THRIFT_SYNC()
       THRIFT_ISSUE(j, false, j + 1 == n0[0], j + 1 == n0[0])
       THRIFT_MASK(j)
@@ -624,7 +630,6 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
   }
   vm_wait<0>();
 #undef THRIFT_SYNC
-#undef THRIFT_TURN
 #undef THRIFT_LOAD_Q16
 #undef THRIFT_LOAD_Q16_ROW
 #undef THRIFT_ISSUE
@@ -660,10 +665,10 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
 #undef THRIFT_ROW_AGAIN
 }
 
-template <typename T, int NW, int NL, int ORDER, int WIDE>
+template <typename T, int NW, int NL, int ORDER, int WIDE, int TURNS>
 __global__ void __launch_bounds__(NW * 64, WIDE ? 2 : 12 / NW) prefill_kernel(PrefillArgs a) {
   __shared__ __align__(1024) unsigned char lds[WIDE ? kLdsPrefillWide : kLdsPrefill];
-  prefill_item<T, NW, NL, ORDER, WIDE>(a, lds, blockIdx.x);
+  prefill_item<T, NW, NL, ORDER, WIDE, TURNS>(a, lds, blockIdx.x);
 }
 
 // The same items from a persistent launch: as many workgroups as the chip holds at once, each taking the next item
@@ -685,7 +690,7 @@ __global__ void __launch_bounds__(256, 3) prefill_persistent_kernel(PrefillArgs 
     const unsigned work = next;
     __syncthreads();
     if (work >= items) break;
-    prefill_item<T, 4, 1, ORDER, 0>(a, lds, work);
+    prefill_item<T, 4, 1, ORDER, 0, 0>(a, lds, work);
   }
 }
 
@@ -747,38 +752,37 @@ void launch_prefill(const PrefillArgs& args, hipStream_t st) {
   const unsigned grid = (unsigned)((long)a.B * a.Hq * ((a.Nq + rows - 1) / rows));
   a.interleave = interleaved_units(a, grid);
   a.fold = folded(a, grid);
-  a.turns = take_turns(a, grid);
   if (a.tile_order == 4 && a.Bq == 128) {
     // persistent launch of the Sec. 3.3 order: three workgroups per CU.  One counter per device: two such launches
     // must not overlap on a device.  The counter is cleared by a kernel (a memset node misbehaves under graph capture).
     int dev = 0, cus = kCus;
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const unsigned resident = (unsigned)min((long)grid, 3L * cus);
-    a.fold = a.turns = 0;                                // its workgroups take the items as they come
+    a.fold = 0;                                          // its workgroups take the items as they come
     prefill_reset_counter_kernel<<<dim3(1), dim3(1), 0, st>>>();
     if (a.dt == THRIFT_F16) prefill_persistent_kernel<F16, 1><<<dim3(resident), dim3(256), 0, st>>>(a, grid);
     else prefill_persistent_kernel<BF16, 1><<<dim3(resident), dim3(256), 0, st>>>(a, grid);
     return;
   }
-#define THRIFT_LAUNCH(T, NW, NL)                                                                               \
+  auto launch = [&](auto turns) {
+    constexpr int TURNS = decltype(turns)::value;
+    const bool order1 = a.tile_order == 1 || a.tile_order == 4, f16 = a.dt == THRIFT_F16;
+#define THRIFT_LAUNCH(NW, NL, ORDER, WIDE)                                                                     \
   do {                                                                                                         \
-    if (a.tile_order == 1 || a.tile_order == 4) prefill_kernel<T, NW, NL, 1, 0><<<dim3(grid), dim3(NW * 64), 0, st>>>(a);           \
-    else prefill_kernel<T, NW, NL, 0, 0><<<dim3(grid), dim3(NW * 64), 0, st>>>(a);                             \
+    if (f16) prefill_kernel<F16, NW, NL, ORDER, WIDE, TURNS><<<dim3(grid), dim3(NW * 64), 0, st>>>(a);         \
+    else prefill_kernel<BF16, NW, NL, ORDER, WIDE, TURNS><<<dim3(grid), dim3(NW * 64), 0, st>>>(a);            \
   } while (0)
-  if (wide_schedule(a)) {
-    if (a.dt == THRIFT_F16) prefill_kernel<F16, 4, 1, 0, 1><<<dim3(grid), dim3(256), 0, st>>>(a);
-    else prefill_kernel<BF16, 4, 1, 0, 1><<<dim3(grid), dim3(256), 0, st>>>(a);
-  } else if (a.Bq == 128) {
-    if (a.dt == THRIFT_F16) THRIFT_LAUNCH(F16, 4, 1);
-    else THRIFT_LAUNCH(BF16, 4, 1);
-  } else if (rows == 128) {
-    if (a.dt == THRIFT_F16) THRIFT_LAUNCH(F16, 4, 2);
-    else THRIFT_LAUNCH(BF16, 4, 2);
-  } else {
-    if (a.dt == THRIFT_F16) THRIFT_LAUNCH(F16, 2, 1);
-    else THRIFT_LAUNCH(BF16, 2, 1);
-  }
+    if (wide_schedule(a)) THRIFT_LAUNCH(4, 1, 0, 1);
+    else if (a.Bq == 128 && order1) THRIFT_LAUNCH(4, 1, 1, 0);
+    else if (a.Bq == 128) THRIFT_LAUNCH(4, 1, 0, 0);
+    else if (rows == 128 && order1) THRIFT_LAUNCH(4, 2, 1, 0);
+    else if (rows == 128) THRIFT_LAUNCH(4, 2, 0, 0);
+    else if (order1) THRIFT_LAUNCH(2, 1, 1, 0);
+    else THRIFT_LAUNCH(2, 1, 0, 0);
 #undef THRIFT_LAUNCH
+  };
+  if (take_turns(a, grid)) launch(std::integral_constant<int, 1>{});
+  else launch(std::integral_constant<int, 0>{});
 }
 
 }  // namespace thrift

@@ -211,7 +211,7 @@ __device__ __forceinline__ float probabilities(v16f (&s)[2], float mloc, float m
 //   c = softmax_scale * log2(e);  n_valid = number of leading keys of the block this query may see.
 __device__ __forceinline__ bool softmax_update(v16f (&s)[2], int lane, bool mask, int n_valid, float c, RowState& st,
                                                float& alpha, uint32_t& pbyte) {
-  if (mask) mask_scores(s, lane >> 5, n_valid);
+  if (__builtin_expect(mask, 0)) mask_scores(s, lane >> 5, n_valid);
   const float mloc = lane_max(s);
   // the other half of the row lives 32 lanes away: after the swap of two copies one register holds the lower
   // half's maximum in every lane and the other the upper half's

@@ -327,6 +327,15 @@ def test_scalar_wait_state_check_reads_the_compiler_listing():
         scalars_read_early("_ZN6thrift4walkEv:\n; %bb.0:\n\ts_endpgm")
 
 
+def test_only_the_kernels_that_take_turns_set_a_priority(tmp_path):
+    """The question whether a grid takes turns is the launch's, not one of every key block."""
+    text = _listing("thrift_prefill.hip", tmp_path / "listing.s")
+    bodies = {name: body for name, body in re.findall(r"^(_ZN6thrift14prefill_kernel\w+):(.*?)^\.Lfunc_end", text, re.M | re.S)}
+    assert len(bodies) == 28
+    for name, body in bodies.items():
+        assert "s_setprio" not in body or name.endswith("ELi1EEEvNS_11PrefillArgsE"), name
+
+
 def test_wait_state_check_reads_the_compiler_listing():
     from paper_2605_23081_amd.build import matrix_results_read_early
 
