@@ -589,6 +589,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
     behind(j, x);
     const bool p0 = some(n0, j), p1 = some(x, j + 1) && j + 1 < vis;
     const bool use = NL > 1 && j < vis_wave, own16 = mine(n0, j);
+    if constexpr (NL > 1) take_turn(j);
     THRIFT_SYNC()
     THRIFT_ISSUE(j, p0, p1, all(x, j + 1))
     if (p0 && late_v) THRIFT_ISSUE_V16(j);
@@ -737,7 +738,8 @@ static bool folded(const PrefillArgs& a, unsigned grid) { return a.interleave &&
 // One round of workgroups whose rows are equally long (no mask, or a chunk behind cached tokens).  A SIMD prefers its oldest wavefront, so that
 // the first workgroup of a CU ended when the second was at 60 % (467 and 605 us of a chunk of 2048 tokens on 30720), and the rest ran with
 // one wavefront per SIMD, which uses half of its vector rate.  With turns they end together.  Without / with: 592 / 575 us for that
-// chunk, 814 / 790 for one of 3072, 780 / 744 for 2500; 102.2 / 97.6 for 3001 tokens without a mask, 62.6 / 60.7 for 2048.  In causal prompts the
+// chunk, 814 / 790 for one of 3072, 780 / 744 for 2500; 102.2 / 97.6 for 3001 tokens without a mask, 62.6 / 60.7 for 2048; with query blocks of 64 rows, two to a
+// workgroup, in ascending order 109.9 / 103.2 for 3001 without a mask, 624 / 604 for the chunk of 2048.  In causal prompts the
 // first workgroup of a CU is the longest and should run ahead (68.3 / 71.6 for 3001 tokens), and in larger grids the next workgroup fills the
 // place that is free: 239 / 265 for 5000 tokens without a mask, 1092 / 1134 for a chunk of 4096; two workgroups per CU (wide): 652 / 634 for the
 // chunk of 2048 at 25 %, 123.9 / 127.2 for 3001 tokens without a mask, one and a half rounds.
