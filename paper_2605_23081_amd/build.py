@@ -243,6 +243,13 @@ def scalars_read_early(asm_text: str):
     return listing.early(reads, writes)
 
 
+def unmet_launch_bounds(compiler_output: str):
+    """Kernels whose launch bounds ask for more wavefronts per SIMD than their LDS or registers let a CU hold.
+
+    The compiler says so in a warning, drops the bound and allocates registers as if there were none."""
+    return sorted(set(re.findall(r"failed to meet occupancy target given by 'amdgpu-waves-per-eu' in '(\w+)'", compiler_output)))
+
+
 def _start_call_module(obj):
     """Compile csrc/thrift_call.cpp against the headers of the installed torch (host compiler)."""
     import sysconfig

@@ -666,8 +666,10 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, unsigned char
 #undef THRIFT_ROW_AGAIN
 }
 
+// The second bound is wavefronts per SIMD: three workgroups of four per CU, two (wide), or three workgroups of two, which the SIMDs
+// hold as one and a half each and which may have the registers of two.
 template <typename T, int NW, int NL, int ORDER, int WIDE, int TURNS>
-__global__ void __launch_bounds__(NW * 64, WIDE ? 2 : 12 / NW) prefill_kernel(PrefillArgs a) {
+__global__ void __launch_bounds__(NW * 64, WIDE || NW == 2 ? 2 : 3) prefill_kernel(PrefillArgs a) {
   __shared__ __align__(1024) unsigned char lds[WIDE ? kLdsPrefillWide : kLdsPrefill];
   prefill_item<T, NW, NL, ORDER, WIDE, TURNS>(a, lds, blockIdx.x);
 }
@@ -712,20 +714,32 @@ static bool wide_schedule(const PrefillArgs& a) {
 // the ends weigh little and the units' K/V streams want the L2 one after the other: 1210 / 1260 us for 2 x 8192, 64/8 heads.
 static bool interleaved_units(const PrefillArgs& a, unsigned grid) { return a.causal && grid <= 8u * 3u * kCus; }
 
-// Query blocks of 64 rows one to a workgroup of two wavefronts instead of two to one of four: where promoted blocks are frequent
-// and the workgroups are one round, what counts is the length of a row's walk, which two lists lengthen.  With causal rows the
-// second round is the short ones.  One / two query blocks per workgroup (64-row query blocks in the grid):
-//    608   chunk of 1200 on 30720, 32/8, 25 %, Sec. 3.3    806 /  962      640   2500, 16/16, 100 %, no mask              132 /  136
-//    768   1500 tokens, 32/8, 25 %, ascending             52.4 / 54.9            the same in the order of Sec. 3.3     50.8 / 57.9
-//   1120   2200 tokens, 32/8, 25 %                        71.9 / 77.0           100 %, Sec. 3.3                        90.3 / 109
-//   1136   4500, 16/16, 25 %, no mask                      266 /  187            causal                                 128 /  136
-//   1216   chunk of 2400 on 30720, 32/8, 25 %             1587 / 1104
-//   1504   3000 tokens, 32/8, 25 %                         114 / 97.4           100 %                                   161 /  157
-//    768   1500 tokens, 32/8, 10 %                        48.7 / 48.1     1120  2200, 10 %                             69.2 / 64.2
+// Query blocks of 64 rows one to a workgroup of two wavefronts instead of two to one of four.  With the LDS of a CU for three
+// workgroups, two wavefronts each are one and a half per SIMD instead of three, and every block is staged for half the rows; but a row's
+// walk takes only its own list, in fewer instructions per block, and what counts in a grid of one round is the length of that walk.  The
+// second round of causal rows is the short ones, and the more blocks are promoted the longer the second list makes the walk.  Time
+// of one / of two query blocks per workgroup, ascending and in the order of Sec. 3.3 (64-row query blocks in the grid):
+//   causal, from the first key on            0 %          5 %          10 %         25 %         100 %
+//      768   1500 tokens, 32/8           0.91 0.98    0.89 0.91    0.87 0.87    0.83 0.75    0.84 0.84
+//      960   1920, 32/8                  0.97 1.03    0.94 1.02    0.92 0.97
+//     1024   1000, 64/8                  0.99 1.04    1.00 1.04    0.96 0.97
+//     1136   4500, 16/16                 0.97 1.06    0.92 0.99    0.89 0.93    0.82 0.80    0.84 0.71
+//     1280   2560, 32/8                                            0.98 0.98    0.90 0.83    0.84 0.91
+//     1376   2700, 32/8                                            1.02 1.01    0.95 0.87    0.87 0.81
+//     1504   3000, 32/8                  1.15 1.23    1.11 1.14    1.07 1.07    1.00 0.92    0.92 0.83
+//     1600   3200, 32/8                                            1.12 1.11    1.01 0.96    0.92 0.98
+//     2528   5000, 32/8                  1.18 1.28    1.14 1.23    1.11 1.16    1.11 1.05    1.17 1.09
+//   no mask, or a chunk on 16384
+//      416   chunk of 800, 32/8          1.05 1.21    1.00 1.07    0.96 0.98    0.86 0.77    0.86 0.76
+//      480   1900, 16/16                 1.09 1.17    1.06 1.09    1.03 1.04
+//      544   chunk of 1088, 32/8         0.88 0.93    0.85 0.87    0.83 0.80
+//      768   1500, 32/8                  0.94 0.96    0.91 0.92    0.90 0.88    0.86 0.79    0.87 0.89
+//      832   1664, 32/8                                            1.23 1.22    1.18 1.09    1.42 1.29
+//     1216   chunk of 2400, 32/8         1.45 1.46    1.41 1.31    1.38 1.26    1.30 1.10    1.27 1.25
 static bool one_query_block(const PrefillArgs& a) {
-  const long blocks = (long)a.B * a.Hq * ((a.Nq + 63) / 64), Tk = (a.N + kBk - 1) / kBk;
-  if ((long)a.kmax * 100L < Tk * (long)kWidePercent) return false;
-  return blocks <= (a.causal && a.q_off == 0 ? 5L : 3L) * kCus;
+  const long blocks = (long)a.B * a.Hq * ((a.Nq + 63) / 64), Tk = (a.N + kBk - 1) / kBk, percent = a.kmax * 100L / Tk;
+  if (a.causal && a.q_off == 0) return blocks <= (percent >= 20 ? 6L : percent >= 8 ? 5L : 3L) * kCus;
+  return blocks <= 3L * kCus && (blocks > 2L * kCus || percent >= kWidePercent);         // two to a workgroup are one per CU below that
 }
 
 // A grid that the chip holds at once: workgroup n goes to the CU of workgroup n - 256 (read back from the hardware id register), so in

@@ -241,15 +241,15 @@ def test_decode_takes_one_launch_where_it_is_the_faster_form():
     assert not two(16, 32, 8, 128) and not two(16, 64, 8, 64)                # short rows of many blocks
 
 
-_listings = {}
+_listings, _compiler_output = {}, {}
 
 
 def _listing(source, path):
     import subprocess
     from paper_2605_23081_amd import build
     if source not in _listings:
-        subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", str(path)], check=True, capture_output=True)
-        _listings[source] = path.read_text()
+        done = subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", str(path)], check=True, capture_output=True, text=True)
+        _listings[source], _compiler_output[source] = path.read_text(), done.stderr
     return _listings[source]
 
 
@@ -325,6 +325,28 @@ def test_scalar_wait_state_check_reads_the_compiler_listing():
     assert scalars_read_early(kernel(compare, mask, *around)) == found
     with pytest.raises(RuntimeError):
         scalars_read_early("_ZN6thrift4walkEv:\n; %bb.0:\n\ts_endpgm")
+
+
+def test_launch_bounds_are_met(tmp_path):
+    """The compiler drops a bound that it cannot meet, and allocates registers as if there were none."""
+    import subprocess
+    from paper_2605_23081_amd import build
+    for source in ("thrift_prefill.hip",):
+        _listing(source, tmp_path / "listing.s")
+        assert build.unmet_launch_bounds(_compiler_output[source]) == []
+    source = tmp_path / "bounds.hip"
+    for waves_per_simd, unmet in ((2, []), (6, ["_Z13bounds_kernelPf"])):    # workgroups of two wavefronts whose LDS lets a CU hold three
+        source.write_text("""#include <hip/hip_runtime.h>
+__global__ void __launch_bounds__(128, %d) bounds_kernel(float* x) {
+  __shared__ float lds[12544];
+  lds[threadIdx.x] = x[threadIdx.x];
+  __syncthreads();
+  x[threadIdx.x] = lds[127 - threadIdx.x];
+}
+""" % waves_per_simd)
+        done = subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", str(source), "-o", str(tmp_path / "bounds.s")],
+                              check=True, capture_output=True, text=True)
+        assert build.unmet_launch_bounds(done.stderr) == unmet
 
 
 def test_only_the_kernels_that_take_turns_set_a_priority(tmp_path):

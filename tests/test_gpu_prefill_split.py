@@ -49,6 +49,7 @@ def test_order_of_the_workgroups(T, B, Hq, Hkv, N, Bq, causal):
     (3, 8, 1, 3999, 128, 0.05),          # 768
     (1, 32, 8, 2048, 128, 0.25),         # 512, the wide schedule in ascending order
     (1, 32, 8, 2000, 64, 0.05),          # two query blocks per workgroup
+    (1, 32, 8, 1100, 64, 0.05),          # 576 workgroups of one
 ])
 def test_turns_between_workgroups(T, B, Hq, Hkv, N, Bq, budget):
     """Rows of one length in a grid of one round: the workgroups' priorities change nothing but the time."""
@@ -80,7 +81,8 @@ def _form(B, Hq, Nq, N, kmax):
     (2, 16, 16, 2048, 128),              # 512
     (1, 32, 8, 3072, 128),               # 768
     (1, 32, 8, 3073, 128),               # 800: more than the chip holds, as it comes
-    (1, 32, 8, 1500, 64),                # two query blocks per workgroup
+    (1, 32, 8, 1500, 64),                # 768 of two wavefronts, one query block of 64 rows each
+    (1, 32, 8, 2700, 64),                # 704 of two query blocks each, the last of them with one
 ])
 def test_folded_order_of_the_workgroups(T, B, Hq, Hkv, N, Bq):
     """Grids of one round, whose second third runs the other way: every head has the bits it has in a call of its own."""
@@ -193,7 +195,7 @@ def test_two_query_blocks_per_workgroup(T, Nq, off, N, even, odd, causal, order)
         assert torch.equal(out[0], out[n - 1]) and torch.equal(lse[0], lse[n - 1])
         return out[:1], lse[:1]
 
-    copies = 5 * 256 // (4 * Tq) + 1                                          # past the grids that take one block to a workgroup
+    copies = 6 * 256 // (4 * Tq) + 1                                          # past the grids that take one block to a workgroup
     both, lse = run(torch.arange(Tq, device="cuda") % 2, 64, off, copies)
     one, lse_one = run(torch.arange(Tq, device="cuda") % 2, 64, off)          # one of those
     assert torch.equal(both, one) and torch.equal(lse, lse_one)
