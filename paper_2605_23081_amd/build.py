@@ -295,6 +295,9 @@ def build(verbose: bool = False, extra=()):
         if p.returncode != 0:
             sys.stderr.write(out + "\n")
             raise RuntimeError("compilation failed: " + " ".join(cmd))
+        unmet = unmet_launch_bounds(out)
+        if unmet:
+            raise RuntimeError("launch bounds that cannot be met: " + ", ".join(unmet))
         if verbose and out.strip():
             print(out)
     for src, listing, lcmd, lproc in listings:

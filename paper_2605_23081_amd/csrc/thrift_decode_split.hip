@@ -127,12 +127,17 @@ enum Pass { BOTH, SCORES, VALUES };
 // Key blocks per wavefront; with both passes in one the LDS holds their scores.
 constexpr int chunk_limit(int nh, bool both) { return both && nh > 4 ? kSplitMaxChunk / 2 : kSplitMaxChunk; }
 
+// Workgroups of four wavefronts that a CU holds, which is also the wavefronts per SIMD whose registers the kernel may have: where one
+// launch keeps the scores of 32 (block, head) pairs per wavefront its LDS leaves room for two.
+constexpr int kBothOwn = 2 * (4096 + 256) + 128;               // LDS of a wavefront beside its scores
+constexpr int workgroups_per_cu(Pass pass, int nh, int nc) { return pass != BOTH ? 4 : 4 * (kBothOwn + 256 * nh * nc) <= 160 * 1024 / 3 ? 3 : 2; }
+
 // NH: heads per KV group, rounded up to 1, 2, 4 or 8.
 // NC: key blocks per wavefront, at most, whose scores one launch holds in LDS.
 // NR: the promoted blocks come from the order keys of rows of up to 64 NR key blocks, every workgroup asking for its own blocks
 // (a row or two per wavefront); 0: from the bitmap of a launch before.
 template <typename T, int NH, Pass PASS, int NR, int NC = 1>
-__global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel(DecodeSplitArgs s) {
+__global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_split_kernel(DecodeSplitArgs s) {
   const DecodeArgs& a = s.a;
   constexpr bool SELECT = NR > 0, kWhole = PASS == BOTH;         // kWhole: registers for both halves of a 16-bit tile
   constexpr int kSlot = 4096 + 256;                            // codes and scales of a V block
@@ -148,6 +153,7 @@ __global__ void __launch_bounds__(256, PASS == BOTH ? 3 : 4) decode_split_kernel
   // them (2 x 14464 tokens, 64/8 heads, no block promoted) a second round: 20.8 us, now 16.9.
   constexpr int kArea = PASS == VALUES ? (NH * (64 * 2 + 32 + 2) + 15) / 16 * 4 : NH * 64;
   __shared__ __align__(16) float scores[4][NC][kArea];
+  static_assert(PASS != BOTH || (kOwn == kBothOwn && kArea == 64 * NH), "workgroups_per_cu");
   static_assert(PASS != VALUES || 4 * (kOwn + 4 * kArea) <= 160 * 1024 / 4, "four workgroups per CU");
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

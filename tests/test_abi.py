@@ -331,7 +331,7 @@ def test_launch_bounds_are_met(tmp_path):
     """The compiler drops a bound that it cannot meet, and allocates registers as if there were none."""
     import subprocess
     from paper_2605_23081_amd import build
-    for source in ("thrift_prefill.hip",):
+    for source in ("thrift_prefill.hip", "thrift_decode_split.hip"):
         _listing(source, tmp_path / "listing.s")
         assert build.unmet_launch_bounds(_compiler_output[source]) == []
     source = tmp_path / "bounds.hip"
