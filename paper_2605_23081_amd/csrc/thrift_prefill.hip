@@ -747,6 +747,9 @@ static bool one_query_block(const PrefillArgs& a) {
 // second third turned round they are 47 + 17 + 15 and 33 + 31 + 1.  Descending / folded: 69.7 / 66.6 us for 3001 tokens, 32/8 heads
 // (71.5 / 66.1 in the order of Sec. 3.3), 64.6 / 61.4 for 2 x 2500, 16/16, 47.7 / 45.3 for 1500, 64/8; 49.2 / 48.6 for 2048, 32/8 (two workgroups per CU, of
 // which the longer one alone takes the time).  The last third turned round as well is no better (66.4, 67.1), alone worse (68.5, 69.2).
+// In the wide schedule a CU holds two and the last third takes the places that are free first, those of the second third's short
+// rows: 54.5 / 52.9 us for 1500 tokens, 64/8, 25 %, 78.3 / 77.4 for 3000, 32/8, 53.5 / 53.1 for 2100, 67.3 / 68.5 for 2700, equal at 2500
+// and at 100 % (105.2 / 105.1 for 2 x 2900, 16/16, 92.4 / 92.6 for 2700).
 static bool folded(const PrefillArgs& a, unsigned grid) { return a.interleave && grid <= 3u * kCus; }
 
 // One round of workgroups whose rows are equally long (no mask, or a chunk behind cached tokens).  A SIMD prefers its oldest wavefront, so that
@@ -757,6 +760,12 @@ static bool folded(const PrefillArgs& a, unsigned grid) { return a.interleave &&
 // first workgroup of a CU is the longest and should run ahead (68.3 / 71.6 for 3001 tokens), and in larger grids the next workgroup fills the
 // place that is free: 239 / 265 for 5000 tokens without a mask, 1092 / 1134 for a chunk of 4096; two workgroups per CU (wide): 652 / 634 for the
 // chunk of 2048 at 25 %, 123.9 / 127.2 for 3001 tokens without a mask, one and a half rounds.
+// The priority holds against every wavefront of the SIMD.  Decode steps on another stream beside chunks of 32/8 heads one after the other,
+// without / with turns: where a step finds room it takes as long (34 / 34 us median for one sequence of 4096 beside chunks of 3072, 70.7 / 68.5 for 16 x
+// 4096-8192; 39.2 / 38.9 and 86 / 96 beside chunks of 3000 with 16/16 heads, which leave room for most), but the workgroups of a CU leave their places
+// together at the chunk's end and not one at three quarters of it: steps that have to wait for one come to 109 / 142 us in the mean (one
+// of 4096 beside 3072), 150 / 182 (one of 32768 beside 2048), and beside chunks of 2048 to one per chunk (3.9 / 1.7 steps of 4096 tokens per
+// ms); 211 / 224 (16 x 4096-8192), 419 / 438 (8 x 16384-32768, 64/8).  The chunks themselves take 612 / 585, 693 / 678, 725 / 690 and 782 / 762 us there.
 static bool take_turns(const PrefillArgs& a, unsigned grid) {
   return (!a.causal || a.q_off > 0) && grid > 1u * kCus && grid <= (wide_schedule(a) ? 2u : 3u) * kCus;
 }

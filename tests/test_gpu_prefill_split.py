@@ -66,6 +66,37 @@ def test_turns_between_workgroups(T, B, Hq, Hkv, N, Bq, budget):
                 assert torch.equal(out[b, heads], alone[0])
 
 
+@pytest.mark.parametrize("Hq,Hkv,Nq,N,Bq,budget", [
+    (32, 8, 1100, 2380, 128, 0.05),      # 288 workgroups; rows of 21 to 38 key blocks, the last of them short
+    (16, 16, 2048, 4096, 128, 0.1),      # 256: one per CU, no turns
+    (32, 8, 2000, 4048, 128, 0.05),      # 512
+    (32, 8, 2000, 4048, 128, 0.25),      # the wide schedule in ascending order
+    (32, 8, 3072, 5120, 128, 0.0),       # 768, no block promoted
+    (32, 8, 2000, 4048, 64, 0.05),       # two query blocks per workgroup
+    (32, 8, 1100, 2380, 64, 0.25),       # 576 workgroups of one
+])
+def test_turns_between_workgroups_of_a_chunk(T, Hq, Hkv, Nq, N, Bq, budget):
+    """Behind cached tokens the rows are nearly equal in length and take turns as well; every KV head has the bits of a call of its own."""
+    print(f"turns in a chunk of {Nq} of {N} {Hq}/{Hkv} Bq={Bq} f={budget}", flush=True)
+    q, k, v = _qkv(1, Hq, Hkv, N, torch.bfloat16)
+    q = q[:, :, :Nq].contiguous()
+    G, off = Hq // Hkv, (N - Nq) // Bq
+    assert N - Nq == off * Bq
+
+    def run(q, k, v, order):
+        idx, cnt = T.thrift_select_topk(T.thrift_block_means(q, Bq), T.thrift_block_means(k, 64), Bq, 64, True, budget, q_block_offset=off)
+        codes = [*T.thrift_quantize_mxfp4(q, 0), *T.thrift_quantize_mxfp4(k, 0), *T.thrift_quantize_mxfp4(v, 1)]
+        return T.thrift_attn_prefill_chunk(q, k, v, *codes, idx, cnt, Bq, 64, True, off, out_dtype=torch.float32, tile_order=order)
+
+    for order in (0, 1):
+        out = run(q, k, v, order)
+        assert bool(torch.isfinite(out).all())
+        for h in {0, Hkv // 2, Hkv - 1}:
+            heads = slice(h * G, (h + 1) * G)
+            alone = run(*(x.contiguous() for x in (q[:, heads], k[:, h:h + 1], v[:, h:h + 1])), order)
+            assert torch.equal(out[0, heads], alone[0])
+
+
 def _form(B, Hq, Nq, N, kmax):
     """Row groups per workgroup of the four-wavefront kernel, 0: the plain one (launch_prefill_split's rule)."""
     groups, Tk = B * Hq * -(-Nq // 32), -(-N // 64)
@@ -84,20 +115,25 @@ def _form(B, Hq, Nq, N, kmax):
     (1, 32, 8, 1500, 64),                # 768 of two wavefronts, one query block of 64 rows each
     (1, 32, 8, 2700, 64),                # 704 of two query blocks each, the last of them with one
 ])
-def test_folded_order_of_the_workgroups(T, B, Hq, Hkv, N, Bq):
+def test_folded_order_of_the_workgroups(T, B, Hq, Hkv, N, Bq, budget=0.1):
     """Grids of one round, whose second third runs the other way: every head has the bits it has in a call of its own."""
-    print(f"folded order B={B} {Hq}/{Hkv} N={N} Bq={Bq}", flush=True)
+    print(f"folded order B={B} {Hq}/{Hkv} N={N} Bq={Bq} f={budget}", flush=True)
     q, k, v = _qkv(B, Hq, Hkv, N, torch.bfloat16)
     G = Hq // Hkv
     for order in (0, 1, 2):
         out = torch.full((B, Hq, N, 128), float("nan"), device="cuda")
-        T.thrift_attention(q, k, v, True, Bq, 64, 0.1, tile_order=order, out=out)
+        T.thrift_attention(q, k, v, True, Bq, 64, budget, tile_order=order, out=out)
         for b in range(B):
             for h in range(Hkv):
                 heads = slice(h * G, (h + 1) * G)
                 alone = T.thrift_attention(*(x[b:b + 1, s].contiguous() for x, s in ((q, heads), (k, slice(h, h + 1)), (v, slice(h, h + 1)))),
-                                           True, Bq, 64, 0.1, tile_order=order, out_dtype=torch.float32)
+                                           True, Bq, 64, budget, tile_order=order, out_dtype=torch.float32)
                 assert torch.equal(out[b, heads], alone[0])
+
+
+@pytest.mark.parametrize("N", [2048, 2100, 3072])                            # 512, 544 and 768 workgroups, of which a CU holds two
+def test_folded_order_of_the_wide_schedule(T, N):
+    test_folded_order_of_the_workgroups(T, 1, 32, 8, N, 128, 0.25)
 
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
