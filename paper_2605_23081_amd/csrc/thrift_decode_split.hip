@@ -108,7 +108,8 @@ __device__ __forceinline__ uint32_t rank_select(const uint64_t (&key)[NR], uint6
 #pragma unroll
     for (int c = 0; c < NR; ++c) {
       larger += __popcll(__ballot((uint32_t)(key[c] >> 32) > hi));
-      if (c % 2 != 0 && c + 1 < NR && larger >= k) break;      // most blocks are out after two registers
+      // most blocks are out after two registers: 47.0 -> 46.0 us for a step of 4 x 8192-16384 tokens, 34.7 -> 34.4 for 1 x 32768
+      if (c % 2 != 0 && c + 1 < NR && larger >= k) break;
     }
     if (larger >= k) continue;
     const uint64_t x = ((uint64_t)hi << 32) | (uint32_t)__builtin_amdgcn_readlane((int)own, i);
@@ -184,14 +185,19 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
   const int hg = min(h, G - 1);                                // lanes of a padding head follow the last one and are never read
   // In two launches the workgroup's place is known, too: the keys of its own blocks; its selection, the largest scores in front of
   // it in the partition and the scores of its first block.  What stands there may never have been written: it is used where the
-  // length says that it was.  Asked for one after the other behind the length they took 2.7 us of the 12 us of the values pass, now 0.7.
+  // length says that it was.  Asked for one after the other behind the length they took 2.7 us of the 12 us of the values pass, now 0.7:
+  // 35.5 -> 34.4 us for 1 x 32768 tokens, 32/8 heads, 5 %, 37.4 -> 36.0 for 2 x 16384 at 10 %, 30.0 -> 29.2 for 1 x 16384.
   const int early = min(part * a.split_blocks + y % s.nsub * 4 * s.cw, Tk - 1);          // (not of a partly filled last block)
   uint64_t own_key[kRows];
   if constexpr (SELECT && PASS == SCORES) {
 #pragma unroll
     for (int u = 0; u < kRows; ++u) own_key[u] = s.keys[(group0 + min(wave + 4 * u, G - 1)) * Tk + min(early + lane, Tk - 1)];
   }
-  constexpr int kFront = 8;
+  // The first maxima in front, 64 / NH of a head per load: 64 of one head, 128 of two or four, 64 of eight.  Lanes without one read the
+  // last again: loads under conditions of their own, and more of them than the longest partition has use for, cost more than the
+  // wait where little else is to do (one head, no block promoted: 33.6 us for 14 x 4416 tokens, 16.9 for 20480, like this 32.9 and 16.5,
+  // without 32.6 and 16.4).  Only with eight heads, where a load has few, are conditions better (24.8 / 25.1 us for 1 x 32768, 64/8).
+  constexpr int kFront = NH == 1 ? 1 : NH == 2 ? 4 : 8;
   float front[kFront];
   uint32_t own_taken = 0u;
   struct Scores { float v[NH]; };
@@ -213,13 +219,17 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
   };
   Scores next;                                                 // VALUES: the scores of a block are asked for one block ahead
   const int chunk0 = y * 4 + wave, in_front = tail ? 0 : y % s.nsub * 4 + wave;        // chunks of the partition in front
-  const float* cm = s.cmax + (group0 + hg) * s.chunks + chunk0 - in_front;
+  const float* cm = s.cmax + (group0 + hg) * s.chunks + (tail ? 0 : chunk0 - in_front);
   if constexpr (PASS == VALUES) {
     if constexpr (SELECT) {
       if (lane < G) own_taken = s.taken[(group0 + lane) * s.items + y];
     }
 #pragma unroll
-    for (int e = 0; e < kFront; ++e) front[e] = kg + e * (64 / NH) < in_front ? cm[kg + e * (64 / NH)] : kEmptyMax;
+    for (int e = 0; e < kFront; ++e) {
+      const int at_ = kg + e * (64 / NH);
+      if constexpr (NH <= 4) front[e] = cm[max(min(at_, in_front - 1), 0)];
+      else front[e] = at_ < in_front ? cm[at_] : kEmptyMax;
+    }
     if (!tail) next = load_scores(min(early + wave * s.cw, Tk - 1));
   }
   const int hq = r & (NH > 4 ? 7 : 3);
@@ -489,9 +499,12 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
     dma_b32<true>(vsbase + (size_t)j_ * 256, (uint32_t)(4 * lane), to + 4096);
   };
   // Half q of the 16-bit rows of a block, keys 32 q + 8 g .. + 7, channels 8 r ..
-  // One launch asks for both at once: 67.0 -> 64.9 us for 1 x 131072 tokens, 32/8 heads, 5 %, 149.6 -> 144.7 for a step of 8 x 16384-32768,
-  // 64/8, 10 %, 46.0 -> 44.3 for 16 x 4096-8192 with shared selection.  In two launches that would leave a CU three workgroups instead of four
-  // (44.4 -> 47.7 us for 2 x 28672), and where three are enough it gains nothing (1 x 32768).
+  // One launch asks for both at once (of K as well).  By halves / at once, back to back: 26.0 / 24.6 us for a step of 4 x 2048-4096 tokens, 32/8 heads,
+  // 5 %, 44.2 / 43.6 for 16 x 4096-8192, 63.7 / 63.0 for 1 x 131072, 100.3 / 97.5 for 4 x 16384-32768, 64/8, 100 %, 145.6 / 146.1 for 8 at 10 %.
+  // Where every block is promoted and the chip has fewer than two workgroups per CU, the halves are 1 to 4 % better: 28.8 / 29.9 us for 4 x
+  // 5632, 32/8, 100 %, 68.8 / 70.0 for a step of 6 x 4096-8192, 16/16 (but 119 / 115 for 10 x 8192); asking for that here costs the others 2 %.
+  // In two launches the registers would leave a CU three workgroups instead of four (44.4 -> 47.7 us for 2 x 28672), and where three
+  // are enough it gains nothing (1 x 32768).
   v4i v[kWhole ? 16 : 8];
   auto load16 = [&](int j, int q0) __attribute__((always_inline)) {
     const uint8_t* tile = v16base + (size_t)j * kTile16 + 8192 * q0;
@@ -508,7 +521,7 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
     if (tail && n_blocks > 0) next = load_scores(j0);
     if (n_blocks > 0) {                                        // (chunks without blocks have left no maximum)
 #pragma unroll
-      for (int e = 0; e < kFront; ++e) m = fmaxf(m, front[e]);
+      for (int e = 0; e < kFront; ++e) m = fmaxf(m, in_front > 0 ? front[e] : kEmptyMax);
       for (int e = kg + kFront * (64 / NH); e < in_front; e += 64 / NH) m = fmaxf(m, cm[e]);
     }
   } else {
@@ -702,7 +715,7 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
   // the workgroup's partial.  A wavefront without blocks has left its sums unwritten; it is skipped by its row sum of zero
   // (with a key it is positive, or the whole chunk weighs nothing, or it is NaN and has to reach the result: bits are
   // compared, because comparisons of numbers are compiled as if there were no NaN).
-  for (int e = tid; e < G * (kD / 2); e += 256) {                 // two channels each: one round for up to four heads
+  for (int e = tid; e < G * (kD / 2); e += 256) {                 // two channels each: one round for up to four heads (34.9 -> 34.4 us, 1 x 32768)
     const int u = e >> 6, ch = 2 * (e & 63);
     float m = ml(0, u)[0];
 #pragma unroll
