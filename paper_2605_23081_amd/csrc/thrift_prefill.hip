@@ -723,6 +723,8 @@ static bool interleaved_units(const PrefillArgs& a, unsigned grid) { return a.ca
 //      768   1500 tokens, 32/8           0.91 0.98    0.89 0.91    0.87 0.87    0.83 0.75    0.84 0.84
 //      960   1920, 32/8                  0.97 1.03    0.94 1.02    0.92 0.97
 //     1024   1000, 64/8                  0.99 1.04    1.00 1.04    0.96 0.97
+//     1152   1100, 64/8                               1.04 1.06    1.00 1.01    0.93 0.85    0.89 0.90
+//     1152   2 x 549, 64/8 (one block)                1.11 1.06    the same     1.05 1.01    1.00 0.92
 //     1136   4500, 16/16                 0.97 1.06    0.92 0.99    0.89 0.93    0.82 0.80    0.84 0.71
 //     1280   2560, 32/8                                            0.98 0.98    0.90 0.83    0.84 0.91
 //     1376   2700, 32/8                                            1.02 1.01    0.95 0.87    0.87 0.81
@@ -737,7 +739,8 @@ static bool interleaved_units(const PrefillArgs& a, unsigned grid) { return a.ca
 //      832   1664, 32/8                                            1.23 1.22    1.18 1.09    1.42 1.29
 //     1216   chunk of 2400, 32/8         1.45 1.46    1.41 1.31    1.38 1.26    1.30 1.10    1.27 1.25
 static bool one_query_block(const PrefillArgs& a) {
-  const long blocks = (long)a.B * a.Hq * ((a.Nq + 63) / 64), Tk = (a.N + kBk - 1) / kBk, percent = a.kmax * 100L / Tk;
+  const long blocks = (long)a.B * a.Hq * ((a.Nq + 63) / 64), Tk = (a.N + kBk - 1) / kBk;
+  const long percent = (a.kmax * 100L - 50) / Tk;                  // budgets are rounded up to whole blocks: of a short row that is much
   if (a.causal && a.q_off == 0) return blocks <= (percent >= 20 ? 6L : percent >= 8 ? 5L : 3L) * kCus;
   return blocks <= 3L * kCus && (blocks > 2L * kCus || percent >= kWidePercent);         // two to a workgroup are one per CU below that
 }
