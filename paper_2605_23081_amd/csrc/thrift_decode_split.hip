@@ -140,7 +140,9 @@ constexpr int workgroups_per_cu(Pass pass, int nh, int nc) { return pass != BOTH
 template <typename T, int NH, Pass PASS, int NR, int NC = 1>
 __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_split_kernel(DecodeSplitArgs s) {
   const DecodeArgs& a = s.a;
-  constexpr bool SELECT = NR > 0, kWhole = PASS == BOTH;         // kWhole: registers for both halves of a 16-bit tile
+  constexpr bool SELECT = NR > 0;
+  // Both halves of a 16-bit tile asked for at once: of V, of K
+  constexpr bool kWholeV = PASS == BOTH, kWholeK = PASS == BOTH && (SELECT ? NH > 2 && NC == 4 : NH <= 2);
   constexpr int kSlot = 4096 + 256;                            // codes and scales of a V block
   // per wavefront: half a 16-bit K tile; then two V blocks, which give way to its partial sums, and behind them its
   // maxima and sums
@@ -424,10 +426,10 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
 
     for (int i = 0; i < n_blocks; ++i) {
       const int M = promoted_mask(bits, i);
-      // One launch: both halves of a 16-bit K tile are asked for at once, the first by LDS DMA, the second into registers, from
-      // where it takes the first one's place (a half at a time: see load16).
+      // The first half of a 16-bit K tile by LDS DMA, the second at the same time into registers, from where it takes the first one's
+      // place, or behind it (see load16)
       v4i second[8];
-      if (kWhole && M != 0) {
+      if (kWholeK && M != 0) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the reads of the tile before are over
         issue_k16(j0 + i, 0, 8);
         const uint8_t* half1 = k16base + (size_t)(j0 + i) * kTile16 + kTile16 / 2 + 16 * lane;
@@ -435,12 +437,12 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
         for (int q = 0; q < 8; ++q) second[q] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(half1 + 1024 * q));
       }
       if (M != all) scores4(kt, i, M);
-      if (!kWhole || M == 0) load_next(i + 1);
+      if (!kWholeK || M == 0) load_next(i + 1);
       if (M != 0) {
         v4f acc[4];
         v8s qf[4];
         query16(qf);
-        if constexpr (kWhole) {
+        if constexpr (kWholeK) {
           vm_wait<0>();
           load_next(i + 1);
           scores16(qf, 0, 2, acc);
@@ -499,17 +501,22 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
     dma_b32<true>(vsbase + (size_t)j_ * 256, (uint32_t)(4 * lane), to + 4096);
   };
   // Half q of the 16-bit rows of a block, keys 32 q + 8 g .. + 7, channels 8 r ..
-  // One launch asks for both at once (of K as well).  By halves / at once, back to back: 26.0 / 24.6 us for a step of 4 x 2048-4096 tokens, 32/8 heads,
-  // 5 %, 44.2 / 43.6 for 16 x 4096-8192, 63.7 / 63.0 for 1 x 131072, 100.3 / 97.5 for 4 x 16384-32768, 64/8, 100 %, 145.6 / 146.1 for 8 at 10 %.
-  // Where every block is promoted and the chip has fewer than two workgroups per CU, the halves are 1 to 4 % better: 28.8 / 29.9 us for 4 x
-  // 5632, 32/8, 100 %, 68.8 / 70.0 for a step of 6 x 4096-8192, 16/16 (but 119 / 115 for 10 x 8192); asking for that here costs the others 2 %.
+  // One launch asks for both halves of V at once.  At once / by halves, back to back: 24.7 / 25.7 us for 4 x 5632 tokens, 32/8 heads, 5 %, 143.5 / 146 for
+  // a step of 8 x 16384-32768, 64/8, 10 %, 45.4 / 46.3 for 6 x 4096-8192, 16/16, 25 %; 97.5 / 100.3 for 4 x 16384-32768, 64/8, 100 %, but 70.5 / 68.1 for
+  // 4 x 10656-21312, 32/8, 100 %.
+  // Of K at once / by halves: where a wavefront has few blocks the wait for a tile is what it does, in short rows with more than two heads and
+  // at most four blocks 24.2 / 24.9 us for 2 x 4096, 32/8, 25 %, 36.5 / 37.5 for 5 x 3296-6592, 64/8, 5 %; with eight blocks, or in long rows, the other
+  // wavefronts use that time, 45.3 / 43.1 for 16 x 4096-8192, 32/8, 64.8 / 63.1 for 1 x 131072, 146.1 / 143.5 for the 8 x 16384-32768, 41.7 / 40.8 for
+  // 5 x 11648-23296, 64/8, 0 %.  One or two heads leave little but the tile on its way in long rows, 109.3 / 116.2 for 11 x 12288, 16/8, 100 %, 106 / 109 for
+  // 3 x 13088-26176, 16/16 (without promoted blocks the code alone costs 47.3 / 45.6, 14 x 12800), and in short ones 61.5 / 58.9 for 6 x 3584-7168,
+  // 16/16, 100 %, 34.8 / 33.9 for 7 x 3104-6208, 5 % (but 113 / 117 for 10 x 8192, 100 %).
   // In two launches the registers would leave a CU three workgroups instead of four (44.4 -> 47.7 us for 2 x 28672), and where three
   // are enough it gains nothing (1 x 32768).
-  v4i v[kWhole ? 16 : 8];
+  v4i v[kWholeV ? 16 : 8];
   auto load16 = [&](int j, int q0) __attribute__((always_inline)) {
     const uint8_t* tile = v16base + (size_t)j * kTile16 + 8192 * q0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[(kWhole ? 8 * q0 : 0) + u] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(tile + v16off + 256 * u));
+    for (int u = 0; u < 8; ++u) v[(kWholeV ? 8 * q0 : 0) + u] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(tile + v16off + 256 * u));
   };
   int Mnext = n_blocks > 0 ? promoted_mask(bits, 0) : all;
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // the last reads of K are over
@@ -593,7 +600,7 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
       uint8_t* pscale_w = pcode_w + NH * 32;
       if (M != 0) {                                            // needed after the softmax
         load16(j, 0);
-        if (kWhole) load16(j, 1);
+        if (kWholeV) load16(j, 1);
       }
       Mnext = i + 1 < n_blocks ? promoted_mask(bits, i + 1) : all;
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the scores are here, the reads of the other slot's block are over
@@ -669,11 +676,11 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
         const bool mine = r_ < G && ((M >> r_) & 1) != 0;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {                          // keys 32 q + 8 g .. + 7
-          if (!kWhole && q == 1) {
+          if (!kWholeV && q == 1) {
             __builtin_amdgcn_sched_barrier(0);                 // into the registers of the first half
             load16(j, 1);
           }
-          v4i* vq = v + (kWhole ? 8 * q : 0);
+          v4i* vq = v + (kWholeV ? 8 * q : 0);
           if (n_valid != kBk) {                                // rows past the cached tokens hold whatever lies there, and zero times that need not be zero
 #pragma unroll
             for (int u = 0; u < 8; ++u)
