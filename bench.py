@@ -195,7 +195,7 @@ def main() -> int:
         f"{flops / 1e12:.1f} TFLOP -> {flops / (ms_step * 1e-3) / 1e12:.1f} TFLOP/s per step, kernel {achieved:.1f} TFLOP/s "
         f"= {100 * achieved / peak:.1f} % of the blended peak {peak:.0f} (16-bit tile share {100 * frac16:.2f} %)")
 
-    roofline = {"bound": "mfma", "kernel": f"prefill_kernel<BF16,4,1,{args.tile_order},0>", "achieved": round(achieved, 2), "peak": round(peak, 1),
+    roofline = {"bound": "mfma", "kernel": f"prefill_kernel<BF16,4,1,{args.tile_order},0,0>", "achieved": round(achieved, 2), "peak": round(peak, 1),
                 "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                 "target_frac": TARGET_PREFILL_FRAC, "target_met": bool(achieved / peak >= TARGET_PREFILL_FRAC),
                 "traffic": (traffic_for(f"prefill_131k_f0.05_order{args.tile_order}", sha) if (N == 131072 and args.budget == 0.05) else None),

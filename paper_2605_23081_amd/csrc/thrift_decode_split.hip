@@ -22,10 +22,11 @@
 // spread over 2^40, 2.8 % of the scores differed in their last bit, neither side further from 64 bits than the other; a
 // probability on a rounding boundary may then fall to either side.
 //
-// Measured, whole calls or serving steps, the walk / two launches with a search for every selection / now: 306 / 43.2 / 35.4 us
-// for one sequence of 32768 tokens and 32/8 heads, 102 / 28.0 / 21.8 for one of 4096; 301 / 74.0 / 66.1 for one of 131072,
-// 544 / 192.4 / 156.8 for eight of 16384-32768 with 64/8 heads at 10 %, 148 / 53.4 / 45.4 for sixteen of 4096-8192 with shared
-// selection, - / 324.5 / 261.8 for sixteen of 16384-32768 at 25 %.
+// Measured, whole calls or serving steps, every pass on buffers of its own (figures below that are said to be back to back repeat one
+// pass, which takes 3 to 7 % less), the walk / two launches with a search for every selection / now: 306 / 43.2 / 35.9 us
+// for one sequence of 32768 tokens and 32/8 heads, 102 / 28.0 / 21.9 for one of 4096; 301 / 74.0 / 64.2 for one of 131072,
+// 544 / 192.4 / 153.8 for eight of 16384-32768 with 64/8 heads at 10 %, 148 / 53.4 / 43.9 for sixteen of 4096-8192 with shared
+// selection; back to back - / 324.5 / 261.9 for sixteen of 16384-32768 at 25 %.
 // What bounds it: for short caches the chain of launches and of dependent loads inside them (a step of one sequence of 4096 tokens
 // reads 0.5 MB; in its 11 us launch 2.0 until the length, the place and the query are there, 1.2 to the first score, 1.0 scores, 2.6 for the
 // maxima in front, 0.9 values, 1.4 the sums); for long ones a workgroup's 11 us without tiles in flight (start, wait and end of 30) and
