@@ -136,14 +136,15 @@ constexpr int workgroups_per_cu(Pass pass, int nh, int nc) { return pass != BOTH
 
 // NH: heads per KV group, rounded up to 1, 2, 4 or 8.
 // NC: key blocks per wavefront, at most, whose scores one launch holds in LDS.
+// WK: a promoted block's 16-bit K tile is asked for whole, not half by half (load16 says where that pays).
 // NR: the promoted blocks come from the order keys of rows of up to 64 NR key blocks, every workgroup asking for its own blocks
 // (a row or two per wavefront); 0: from the bitmap of a launch before.
-template <typename T, int NH, Pass PASS, int NR, int NC = 1>
+template <typename T, int NH, Pass PASS, int NR, int NC = 1, bool WK = false>
 __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_split_kernel(DecodeSplitArgs s) {
   const DecodeArgs& a = s.a;
   constexpr bool SELECT = NR > 0;
-  // Both halves of a 16-bit tile asked for at once: of V, of K
-  constexpr bool kWholeV = PASS == BOTH, kWholeK = PASS == BOTH && (SELECT ? NH > 2 && NC == 4 : NH <= 2);
+  constexpr bool kWholeV = PASS == BOTH;                       // both halves of a 16-bit V tile are asked for at once
+  static_assert(PASS == BOTH || !WK, "two launches have no registers for it");
   constexpr int kSlot = 4096 + 256;                            // codes and scales of a V block
   // per wavefront: half a 16-bit K tile; then two V blocks, which give way to its partial sums, and behind them its
   // maxima and sums
@@ -430,7 +431,7 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
       // The first half of a 16-bit K tile by LDS DMA, the second at the same time into registers, from where it takes the first one's
       // place, or behind it (see load16)
       v4i second[8];
-      if (kWholeK && M != 0) {
+      if (WK && M != 0) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the reads of the tile before are over
         issue_k16(j0 + i, 0, 8);
         const uint8_t* half1 = k16base + (size_t)(j0 + i) * kTile16 + kTile16 / 2 + 16 * lane;
@@ -438,12 +439,12 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
         for (int q = 0; q < 8; ++q) second[q] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(half1 + 1024 * q));
       }
       if (M != all) scores4(kt, i, M);
-      if (!kWholeK || M == 0) load_next(i + 1);
+      if (!WK || M == 0) load_next(i + 1);
       if (M != 0) {
         v4f acc[4];
         v8s qf[4];
         query16(qf);
-        if constexpr (kWholeK) {
+        if constexpr (WK) {
           vm_wait<0>();
           load_next(i + 1);
           scores16(qf, 0, 2, acc);
@@ -509,7 +510,7 @@ __global__ void __launch_bounds__(256, workgroups_per_cu(PASS, NH, NC)) decode_s
   // at most four blocks 24.2 / 24.9 us for 2 x 4096, 32/8, 25 %, 36.5 / 37.5 for 5 x 3296-6592, 64/8, 5 %; with eight blocks, or in long rows, the other
   // wavefronts use that time, 45.3 / 43.1 for 16 x 4096-8192, 32/8, 64.8 / 63.1 for 1 x 131072, 146.1 / 143.5 for the 8 x 16384-32768, 41.7 / 40.8 for
   // 5 x 11648-23296, 64/8, 0 %.  One or two heads leave little but the tile on its way in long rows, 109.3 / 116.2 for 11 x 12288, 16/8, 100 %, 106 / 109 for
-  // 3 x 13088-26176, 16/16 (without promoted blocks the code alone costs 47.3 / 45.6, 14 x 12800), and in short ones 61.5 / 58.9 for 6 x 3584-7168,
+  // 3 x 13088-26176, 16/16 (an instance of its own: without promoted blocks the code alone costs 47.3 / 45.6, 14 x 12800), and in short ones 61.5 / 58.9 for 6 x 3584-7168,
   // 16/16, 100 %, 34.8 / 33.9 for 7 x 3104-6208, 5 % (but 113 / 117 for 10 x 8192, 100 %).
   // In two launches the registers would leave a CU three workgroups instead of four (44.4 -> 47.7 us for 2 x 28672), and where three
   // are enough it gains nothing (1 x 32768).
@@ -939,8 +940,9 @@ void launch_decode_split(const DecodeSplitArgs& s, hipStream_t st) {
   }
 #define THRIFT_BOTH(T, NH, NC)                                                                            \
   do {                                                                                                    \
-    if (s.keys != nullptr) decode_split_kernel<T, NH, BOTH, kSelectBoth / 64, NC><<<grid, block, 0, st>>>(s);             \
-    else decode_split_kernel<T, NH, BOTH, 0, NC><<<grid, block, 0, st>>>(s);                              \
+    if (s.keys != nullptr) decode_split_kernel<T, NH, BOTH, kSelectBoth / 64, NC, (NH > 2 && NC == 4)><<<grid, block, 0, st>>>(s);        \
+    else if (a.bitmap != nullptr) decode_split_kernel<T, NH, BOTH, 0, NC, (NH <= 2)><<<grid, block, 0, st>>>(s);                          \
+    else decode_split_kernel<T, NH, BOTH, 0, NC, false><<<grid, block, 0, st>>>(s);                       \
   } while (0)
 #define THRIFT_SPLIT(T, NH)                                                                               \
   do {                                                                                                    \
